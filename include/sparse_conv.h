@@ -140,6 +140,14 @@ typedef struct {
                            then multiplies its rows of tile i (contiguous row ranges, one barrier per
                            tile); needs wsrc = 1 and at least one stored weight per row; with chunk_c > 0 at
                            most 4 positions per lane and 8 rows per wave.  0 = one tile per workgroup.
+                           3 (SC_F32, any layer shape; not for tables that store a column twice in one row or hold
+                           weights that are not finite or smaller than 2^-100) = the densified tile on the matrix
+                           cores, every fp32 value split into three bfloat16 terms and a product into the six
+                           largest products of terms, accumulated in fp32: no less precise than the other
+                           shapes (inputs below about 2^-100 in magnitude lose their last terms).  Its fields
+                           are DENSE's: tile_p, sub_batch, chunk_c (a multiple of 32), tile_d, waves_m,
+                           wg_per_cu, wg_threads 256 or 512 (0 = 512); split_n = 2..16 as for the chunked
+                           one-shot form, each workgroup with at least one chunk; all other fields 0
                            DENSE: 1 = the chunks of input channels are staged by `producers` waves of their
                            own into two LDS buffers, one chunk ahead of the multiplying waves (which run
                            over the steps of all chunks without draining their weights in flight);

@@ -321,6 +321,58 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     return SC_OK;
 }
 
+// The split form (SLAB with pipeline = 3): fill the fields left 0 and derive the geometry.
+static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out, MfmaGeom* mgeom)
+{
+    const sc_layer_t& L = p.L;
+    if (p.dtype != SC_F32 || !p.splittable || p.has_dup || p.n == 0 || has_epilogue(p)) return SC_ERR_UNSUPPORTED;
+    if (t.wsrc || t.ragged || t.pack || t.tile_q || t.buffers || t.producers || t.stage_rows) return SC_ERR_UNSUPPORTED;
+    if (t.wg_threads != 0 && t.wg_threads != 256 && t.wg_threads != 512) return SC_ERR_UNSUPPORTED;
+    const int KG = t.wg_threads == 256 ? 1 : 2;               // (eight waves by default: two per SIMD)
+    if (t.wg_per_cu == 0) t.wg_per_cu = 1;
+    if (t.wg_per_cu < 1 || t.wg_per_cu > 8) return SC_ERR_UNSUPPORTED;
+    if (t.tile_p < 0 || t.sub_batch < 0 || t.chunk_c < 0 || t.tile_d < 0 || t.waves_m < 0 || t.split_n < 0) return SC_ERR_UNSUPPORTED;
+    const int budget = kMaxLdsBytes / t.wg_per_cu;
+    const int KS = std::max(1, t.split_n);
+    const int DB = t.tile_d ? t.tile_d : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16));
+    const int WM = t.waves_m ? t.waves_m : (DB >= 64 ? 2 : 1);
+    int TP = t.tile_p, NS = t.sub_batch;
+    const bool fixed_tile = TP != 0 || NS != 0;
+    const int maxpos = (4 / WM) * 64;
+    if (!fixed_tile) {
+        if (p.P * p.Q <= maxpos) { TP = p.P; NS = std::max(1, std::min(16, maxpos / (p.P * p.Q))); }
+        else { TP = std::max(1, maxpos / p.Q); NS = 1; }
+    }
+    if (TP == 0) TP = p.P;
+    if (NS == 0) NS = 1;
+    MfmaGeom g{};
+    for (;;) {
+        bool ok = false;
+        if (t.chunk_c) ok = split_geometry(p, TP, NS, t.chunk_c, DB, WM, KG, KS, budget, &g);
+        else
+            for (int cc = (L.C + 31) / 32 * 32; cc >= 32 && !ok; cc -= 32) ok = split_geometry(p, TP, NS, cc, DB, WM, KG, KS, budget, &g);
+        if (ok) break;
+        if (fixed_tile) return SC_ERR_UNSUPPORTED;
+        if (NS > 1) NS /= 2;
+        else if (TP > 1) TP = (TP + 1) / 2;
+        else return SC_ERR_UNSUPPORTED;
+    }
+    sc_tuning_t r{};
+    r.variant = SC_VARIANT_SLAB;
+    r.pipeline = 3;
+    r.wg_threads = 256 * KG;
+    r.tile_p = g.TP;
+    r.sub_batch = g.NS;
+    r.chunk_c = g.CC;
+    r.tile_d = g.DB;
+    r.waves_m = g.WM;
+    r.wg_per_cu = t.wg_per_cu;
+    r.split_n = KS > 1 ? KS : 0;
+    *out = r;
+    *mgeom = g;
+    return SC_OK;
+}
+
 sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* out, SlabGeom* geom, MfmaGeom* mgeom)
 {
     sc_tuning_t t = in;
@@ -329,6 +381,10 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
     if (t.variant == SC_VARIANT_DENSE) {
         *geom = SlabGeom{};
         return resolve_dense(p, t, out, mgeom);
+    }
+    if (is_split(t)) {
+        *geom = SlabGeom{};
+        return resolve_split(p, t, out, mgeom);
     }
     *mgeom = MfmaGeom{};
     if (t.waves_m) return SC_ERR_UNSUPPORTED;
@@ -547,17 +603,18 @@ static sc_status_t hip_status(hipError_t e)
 // succeeded: on any error the plan keeps its previous tuning, geometry and tables untouched.
 static sc_status_t install_tuning(Plan* p, const sc_tuning_t& t, const SlabGeom& g, const MfmaGeom& mg, hipStream_t stream)
 {
-    if (t.variant == SC_VARIANT_DENSE && !p->d_wfrag) {
+    if ((t.variant == SC_VARIANT_DENSE || is_split(t)) && !p->d_wfrag) {
         // dense weights in MFMA operand order: built on first use, the same for every tile shape
+        // (fp32 plans: three bfloat16 terms per weight; such a plan never runs DENSE)
         hipError_t e;
         unsigned char* w = nullptr;
-        if ((e = hipMalloc((void**)&w, mfma_weight_bytes(*p))) != hipSuccess) return hip_status(e);
-        sc_status_t st = mfma_densify(*p, w, stream);
+        if ((e = hipMalloc((void**)&w, is_split(t) ? split_weight_bytes(*p) : mfma_weight_bytes(*p))) != hipSuccess) return hip_status(e);
+        sc_status_t st = is_split(t) ? split_densify(*p, w, stream) : mfma_densify(*p, w, stream);
         if (st == SC_OK && hipStreamSynchronize(stream) != hipSuccess) st = SC_ERR_HIP;
         if (st != SC_OK) { (void)hipFree(w); return st; }
         p->d_wfrag = w;
     }
-    if (t.variant != SC_VARIANT_SLAB) {
+    if (t.variant != SC_VARIANT_SLAB || is_split(t)) {
         p->tuning = t;
         p->geom = g;
         p->mg = mg;
@@ -670,6 +727,15 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
     for (int d = 0; d < p->L.D && !p->has_dup; ++d)
         for (int j = 1; j < p->h_len[d]; ++j)
             if ((p->h_col[(size_t)d * p->n + j] & 0x7fffffff) == (p->h_col[(size_t)d * p->n + j - 1] & 0x7fffffff)) { p->has_dup = true; break; }
+
+    // three bfloat16 terms hold a weight exactly unless it is not finite or so small that the last term
+    // would leave the normal range
+    if (p->dtype == SC_F32) {
+        const float* w = reinterpret_cast<const float*>(tab.val.data());
+        p->splittable = true;
+        for (size_t i = 0; i < cnt && p->splittable; ++i)
+            p->splittable = w[i] == 0.0f || (std::isfinite(w[i]) && std::fabs(w[i]) >= 0x1p-100f);
+    }
 
     std::vector<uint8_t> packed;
     const uint8_t* theta_src = tab.val.data();
@@ -890,7 +956,10 @@ sc_status_t sparse_conv_plan_info(const sparse_conv_plan_t* plan, sc_plan_info_t
     info->out_P = p->Po;
     info->out_Q = p->Qo;
     info->out_elem_bytes = p->epi.requant ? 1 : p->ey;
-    if (p->tuning.variant == SC_VARIANT_SLAB) {
+    if (is_split(p->tuning)) {
+        info->lds_bytes = p->mg.lds_bytes;
+        info->grid_size = p->last_N ? split_grid_size(p->mg, p->last_N) : 0;
+    } else if (p->tuning.variant == SC_VARIANT_SLAB) {
         info->lds_bytes = p->geom.lds_bytes;
         info->grid_size = p->last_N ? slab_grid_size(*p, p->geom, p->last_N) : 0;
     } else if (p->tuning.variant == SC_VARIANT_DENSE) {
@@ -1093,6 +1162,31 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
                     }
                 }
             }
+        }
+    }
+    // fp32 on the matrix cores: output-channel block x wave layout (a wave owns one or two blocks of 16
+    // channels) x tile x chunk, one or two workgroups per CU; layers with small planes also with the
+    // chunks dealt to several workgroups
+    if (p.dtype == SC_F32) {
+        const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}};
+        for (int thr : {512, 256}) for (const auto& lw : layouts) for (int cc : {0, 64, 128, 256}) for (int wpc : {1, 2}) {
+            if ((lw[0] > 32 && lw[0] >= 2 * p.L.D) || (cc && cc >= p.L.C)) continue;
+            auto pushk = [&](int tp, int ns) {
+                sc_tuning_t t{};
+                t.variant = SC_VARIANT_SLAB;
+                t.pipeline = 3;
+                t.wg_threads = thr;
+                t.tile_d = lw[0];
+                t.waves_m = lw[1];
+                t.chunk_c = cc;
+                t.wg_per_cu = wpc;
+                t.tile_p = tp;
+                t.sub_batch = ns;
+                push(t);
+                if (p.P * p.Q <= 256 && cc) for (int ks : {2, 4}) { t.split_n = ks; push(t); }
+            };
+            for (int tp : {1, 2, 4, 7, 8, 14, 16}) if (tp < p.P) pushk(tp, 0);
+            for (int ns : {1, 2, 4}) pushk(p.P, ns);
         }
     }
     const bool pw = is_pointwise(p.L);

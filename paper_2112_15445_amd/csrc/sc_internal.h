@@ -104,6 +104,7 @@ struct Plan {
     void* d_codebook = nullptr;     // [16] i8 or f16 centroids
     unsigned char* d_wfrag = nullptr;  // dense weights in MFMA operand order (DENSE variant), built on first use
     int32_t* d_len = nullptr;       // [D] stored entries of every row before unification (device copy of h_len)
+    bool splittable = false;        // fp32 weights that three bfloat16 terms hold exactly (SLAB with pipeline = 3)
     bool has_dup = false;           // some row stores a column twice (such a table cannot be densified exactly)
     sc_epilogue_t epi{};            // fused epilogue (all zero: none)
     float* d_requant = nullptr;     // [D] requantisation multipliers (epi.requant)
@@ -133,6 +134,7 @@ sc_status_t launch_gather(const Plan& p, const void* x, void* y, int N, void* ws
 
 // slab.hip
 sc_status_t launch_slab(const Plan& p, const void* x, void* y, int N, hipStream_t stream);
+sc_status_t launch_clear(void* y, int64_t words, hipStream_t stream);   // zeros, by a kernel (may be captured)
 int slab_grid_size(const Plan& p, const SlabGeom& g, int N);
 bool slab_rows_stageable(const Plan& p, const SlabGeom& g);   // tuning.stage_rows applies to this layer and tile
 sc_status_t expand_weights(const Plan& p, const int32_t* lam_slab, int2* wl32_out, hipStream_t stream);
@@ -155,5 +157,14 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
 inline bool has_epilogue(const Plan& p) { return p.epi.relu || p.epi.pool || p.epi.requant; }
 int mfma_grid_size(const Plan& p, const MfmaGeom& g, int N);
 sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_t stream);
+
+
+// split_mfma.hip: fp32 on the matrix cores, every operand split into three bfloat16 terms (SLAB, pipeline = 3)
+size_t split_weight_bytes(const Plan& p);
+sc_status_t split_densify(const Plan& p, unsigned char* out, hipStream_t stream);
+bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int lds_budget, MfmaGeom* out);
+int split_grid_size(const MfmaGeom& g, int N);
+sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream_t stream);
+inline bool is_split(const sc_tuning_t& t) { return t.variant == SC_VARIANT_SLAB && t.pipeline == 3; }
 
 }  // namespace sc

@@ -2085,9 +2085,17 @@ __global__ void __launch_bounds__(256) clear_kernel(uint32_t* __restrict__ dst, 
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) dst[i] = 0u;
 }
 
+sc_status_t launch_clear(void* y, int64_t words, hipStream_t stream)
+{
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>((words + 1023) / 1024, 4096)), dim3(256), 0, stream,
+                       static_cast<uint32_t*>(y), words);
+    return hipGetLastError() == hipSuccess ? SC_OK : SC_ERR_HIP;
+}
+
 sc_status_t launch_slab(const Plan& p, const void* x, void* y, int N, hipStream_t stream)
 {
     const SlabGeom& g = p.geom;
+    if (is_split(p.tuning)) return launch_split(p, x, y, N, stream);
     if (p.tuning.chunk_c > 0 && p.tuning.pipeline >= 1) {
         // direct-to-LDS copies: the caller's pointer must be aligned like the rows
         if (reinterpret_cast<uintptr_t>(x) % (uintptr_t)std::max(g.dmab, 1) != 0) return SC_ERR_UNSUPPORTED;
@@ -2138,9 +2146,8 @@ sc_status_t launch_slab(const Plan& p, const void* x, void* y, int N, hipStream_
             // captured in a graph)
             const int64_t words = ((int64_t)N * p.L.D * g.Pf * g.Qf * p.ey + 3) / 4;
             if (p.ey != 4) return SC_ERR_UNSUPPORTED;
-            hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>((words + 1023) / 1024, 4096)), dim3(256), 0, stream,
-                               static_cast<uint32_t*>(y), words);
-            if (hipGetLastError() != hipSuccess) return SC_ERR_HIP;
+            const sc_status_t st = launch_clear(y, words, stream);
+            if (st != SC_OK) return st;
         }
         switch (p.dtype) {
             case SC_F32: return launch_cc<SC_F32>(p, a, x, y, (int)gridc, stream);

@@ -1381,3 +1381,88 @@ def test_natural_layout_candidates_on_seeded_random_pointwise_layers():
             ran += 1
         plan.destroy()
     assert ran >= 150, ran
+
+
+def _split(plan, **kw):
+    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_SLAB, pipeline=3, **kw)
+
+
+@pytest.mark.parametrize("name,C,D,H,W,R,S,sh,sw,ph,pw,N,scale", [
+    ("odd3x3", 37, 45, 13, 11, 3, 3, 1, 1, 1, 1, 5, 1.0),
+    ("stride2", 64, 70, 14, 15, 3, 3, 2, 2, 1, 1, 3, 1.0),
+    ("pointwise7", 200, 33, 7, 7, 1, 1, 1, 1, 0, 0, 9, 1.0),
+    ("pointwise28", 96, 130, 28, 28, 1, 1, 1, 1, 0, 0, 2, 2.0 ** 60),
+    ("conv1d", 70, 20, 1, 61, 1, 3, 1, 1, 0, 0, 6, 2.0 ** -60),
+    ("wide_pad", 8, 17, 6, 9, 2, 3, 1, 2, 4, 3, 2, 1.0),
+    ("one_channel", 1, 3, 4, 4, 1, 1, 1, 1, 0, 0, 1, 1.0),
+])
+def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph, pw, N, scale):
+    """SLAB tunings with pipeline = 3: tails of channels, rows, columns and output channels, several chunks,
+    four and eight waves, several samples per workgroup, chunks dealt to several workgroups, large and
+    small magnitudes.  The six kept products are within 2^-24 of the exact one and the sum is rounded
+    2 K / 32 times, so a result is held to 4e-7 of the sum of the magnitudes' root mean square -- and to
+    no more error than the gather kernel's on the same table, times 1.2 for the draw."""
+    l = wl.Layer(name, C, D, H, W, R, S, sh, sw, ph, pw, N=N, sparsity=0.6, dtype="f32", seed=sum(map(ord, name)))
+    data = wl.prepare(l, ragged=True)
+    data["x"] = data["x"] * np.float32(scale)
+    ref = G.oracle_out(l, data).astype(np.float64)
+    nrm = np.sqrt(np.sum(ref * ref))
+    plan = G.make_plan(l, data)
+    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_GATHER, split_n=1)
+    gather = np.sqrt(np.sum((G.run_gpu(plan, data["x"]) - ref) ** 2)) / nrm
+    ran = 0
+    for threads in (256, 512):
+        for kw in ({}, {"tile_d": 16, "waves_m": 1}, {"tile_d": 32, "waves_m": 1, "tile_p": 1}, {"tile_d": 32, "waves_m": 2, "chunk_c": 32},
+                   {"tile_d": 64, "waves_m": 4, "tile_p": 2}, {"tile_d": 128, "waves_m": 4, "tile_p": 1, "wg_per_cu": 2},
+                   {"tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32}, {"tile_d": 32, "waves_m": 2, "tile_p": 1000, "sub_batch": 3},
+                   {"tile_d": 64, "waves_m": 4, "tile_p": 3, "chunk_c": 64}, {"tile_d": 32, "waves_m": 1, "tile_p": 4, "chunk_c": 32, "split_n": 2},
+                   {"tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 32, "split_n": 3}):
+            try:
+                _split(plan, wg_threads=threads, **kw)
+            except B.SparseConvError as e:
+                assert e.status == 4
+                continue
+            t = plan.get_tuning().as_dict()
+            print("case split", name, t, flush=True)
+            got = G.run_gpu(plan, data["x"])
+            G.check(l, got, ref.astype(np.float32), f"{name} {t}", tol=2e-6)
+            err = np.sqrt(np.sum((got - ref) ** 2)) / nrm
+            assert err <= max(4e-7 if C * R * S > 64 else 1.2e-7, 0.0) and err <= max(1.2 * gather, 6e-8), (name, t, err, gather)
+            ran += 1
+    assert ran >= 8, (name, ran)
+    plan.destroy()
+
+
+def test_fp32_split_form_is_refused_where_it_does_not_apply():
+    l = wl.Layer("splitno", 96, 12, 6, 6, N=2, sparsity=0.7, dtype="f32", seed=6)
+    data = wl.prepare(l)
+
+    def refused(plan, **kw):
+        before = plan.get_tuning().as_dict()
+        with pytest.raises(B.SparseConvError) as e:
+            _split(plan, **kw)
+        assert e.value.status == 4 and plan.get_tuning().as_dict() == before
+
+    plan = G.make_plan(l, data)
+    # (96 channels in chunks of 32: four shares would leave a workgroup without a chunk)
+    for kw in (dict(chunk_c=32, split_n=4), dict(chunk_c=33), dict(tile_d=48), dict(wg_threads=384), dict(wsrc=1), dict(pack=2),
+               dict(producers=2), dict(stage_rows=1), dict(ragged=1), dict(tile_d=32, waves_m=4)):
+        refused(plan, **kw)
+    plan.set_epilogue(relu=True)
+    refused(plan)
+    plan.destroy()
+    for bad in (np.inf, np.nan, 1e-35):                       # weights that three terms do not hold
+        va = data["values"].copy()
+        va[5] = bad
+        plan = B.Plan.create_csr(G.layer_desc(l), B.DTYPES["f32"], data["rowptr"], data["colidx"], va, None, None)
+        refused(plan)
+        plan.destroy()
+    ci = data["colidx"].copy()
+    ci[1] = ci[0]                                             # a column stored twice in one row
+    plan = B.Plan.create_csr(G.layer_desc(l), B.DTYPES["f32"], data["rowptr"], ci, data["values"], None, None)
+    refused(plan)
+    plan.destroy()
+    l16 = l.replace(dtype="f16")
+    plan = G.make_plan(l16, wl.prepare(l16))
+    refused(plan)
+    plan.destroy()
