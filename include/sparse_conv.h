@@ -147,14 +147,17 @@ typedef struct {
                            shapes (inputs below about 2^-100 in magnitude lose their last terms).  Its fields
                            are DENSE's: tile_p, sub_batch, chunk_c (a multiple of 32), tile_d, waves_m,
                            wg_per_cu, wg_threads 256 or 512 (0 = 512); split_n = 2..16 as for the chunked
-                           one-shot form, each workgroup with at least one chunk; all other fields 0
+                           one-shot form, each workgroup with at least one chunk; producers = 4: the chunks are
+                           staged by four more waves into two LDS buffers, one chunk ahead (wg_threads 512,
+                           split_n 0); all other fields 0
                            DENSE: 1 = the chunks of input channels are staged by `producers` waves of their
                            own into two LDS buffers, one chunk ahead of the multiplying waves (which run
                            over the steps of all chunks without draining their weights in flight);
                            chunk_c then defaults to two channel blocks.  Same results as with 0 for four
                            multiplying waves; with eight, the two groups split the steps of the whole
                            contraction instead of each chunk's (another fixed summation order) */
-    int32_t producers;  /* SLAB with pipeline = 1: waves of the workgroup that only copy tiles (1, 2 or 4);
+    int32_t producers;  /* SLAB with pipeline = 1: waves of the workgroup that only copy tiles (1, 2 or 4), with
+                           pipeline = 3: waves that only stage (0 or 4);
                            DENSE with pipeline = 1: staging waves behind the multiplying ones (1 .. 4, 0 = 2) */
     int32_t chunk_c;    /* SLAB: input channels per LDS buffer (0 = all of them); with pipeline = 0 for any
                            layer shape (wsrc = 1 or 3, at most 4 positions per lane and 8 rows per wave), with

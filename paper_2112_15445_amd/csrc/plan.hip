@@ -326,7 +326,9 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
 {
     const sc_layer_t& L = p.L;
     if (p.dtype != SC_F32 || !p.splittable || p.has_dup || p.n == 0 || has_epilogue(p)) return SC_ERR_UNSUPPORTED;
-    if (t.wsrc || t.ragged || t.pack || t.tile_q || t.buffers || t.producers || t.stage_rows) return SC_ERR_UNSUPPORTED;
+    if (t.wsrc || t.ragged || t.pack || t.tile_q || t.buffers || t.stage_rows) return SC_ERR_UNSUPPORTED;
+    if (t.producers != 0 && t.producers != 4) return SC_ERR_UNSUPPORTED;      // 4: staging waves of their own, two chunk buffers
+    const int PW = t.producers;
     if (t.wg_threads != 0 && t.wg_threads != 256 && t.wg_threads != 512) return SC_ERR_UNSUPPORTED;
     const int KG = t.wg_threads == 256 ? 1 : 2;               // (eight waves by default: two per SIMD)
     if (t.wg_per_cu == 0) t.wg_per_cu = 1;
@@ -348,9 +350,9 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     MfmaGeom g{};
     for (;;) {
         bool ok = false;
-        if (t.chunk_c) ok = split_geometry(p, TP, NS, t.chunk_c, DB, WM, KG, KS, budget, &g);
+        if (t.chunk_c) ok = split_geometry(p, TP, NS, t.chunk_c, DB, WM, KG, KS, PW, budget, &g);
         else
-            for (int cc = (L.C + 31) / 32 * 32; cc >= 32 && !ok; cc -= 32) ok = split_geometry(p, TP, NS, cc, DB, WM, KG, KS, budget, &g);
+            for (int cc = PW ? 64 : (L.C + 31) / 32 * 32; cc >= 32 && !ok; cc -= 32) ok = split_geometry(p, TP, NS, cc, DB, WM, KG, KS, PW, budget, &g);
         if (ok) break;
         if (fixed_tile) return SC_ERR_UNSUPPORTED;
         if (NS > 1) NS /= 2;
@@ -367,6 +369,7 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     r.tile_d = g.DB;
     r.waves_m = g.WM;
     r.wg_per_cu = t.wg_per_cu;
+    r.producers = PW;
     r.split_n = KS > 1 ? KS : 0;
     *out = r;
     *mgeom = g;
@@ -1184,6 +1187,8 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
                 t.sub_batch = ns;
                 push(t);
                 if (p.P * p.Q <= 256 && cc) for (int ks : {2, 4}) { t.split_n = ks; push(t); }
+                // pipelined: small chunks, staged one ahead by waves of their own
+                if (thr == 512 && wpc == 1 && (cc != 256 || is_pointwise(p.L))) { t.split_n = 0; t.producers = 4; t.chunk_c = cc ? cc : 32; push(t); }
             };
             for (int tp : {1, 2, 4, 7, 8, 14, 16}) if (tp < p.P) pushk(tp, 0);
             for (int ns : {1, 2, 4}) pushk(p.P, ns);

@@ -162,7 +162,7 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
 // split_mfma.hip: fp32 on the matrix cores, every operand split into three bfloat16 terms (SLAB, pipeline = 3)
 size_t split_weight_bytes(const Plan& p);
 sc_status_t split_densify(const Plan& p, unsigned char* out, hipStream_t stream);
-bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int lds_budget, MfmaGeom* out);
+bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int PW, int lds_budget, MfmaGeom* out);
 int split_grid_size(const MfmaGeom& g, int N);
 sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream_t stream);
 inline bool is_split(const sc_tuning_t& t) { return t.variant == SC_VARIANT_SLAB && t.pipeline == 3; }

@@ -28,6 +28,7 @@ namespace sc {
 struct SplitArgs {
     int C, D, N, H, W, P, Q, S, RS, s_h, s_w, pad_h, pad_w;
     int TP, NS, tiles_p, Hs, Ws, npos_s, npos, CC, nchunks, NCB, pitch, bufsz, DB, ndb, epv, TPQ;
+    int cbs_last;            // channel blocks of the last chunk
     int KS, cps;             // workgroups that share the chunks of a tile, chunks for each
     int npos1;               // staged positions of one sample (Hs * Ws)
     int flat;                // the staged rows of a sample are one contiguous run per channel
@@ -460,9 +461,260 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 }
 
 // ------------------------------------------------------------------------------------------------
+// The pipelined form (producers = 4): the chunks are staged by four waves of their own into two LDS
+// buffers, one chunk ahead of the eight multiplying waves, whose weights in flight never drain --
+// the one-shot form above spends as long between two multiplications (refilling the weights, waiting
+// for its staging, splitting) as in them on deep layers: 10 of 16.5 thousand clocks per chunk of the 1x1
+// 2048-512 layer on 7 x 7 planes.  Protocol of the DENSE variant's pipelined kernel: barrier k says "chunk
+// k is staged" and "chunk k - 1 has been multiplied"; it waits for LDS traffic only, so that weight loads
+// stay in flight across it.  Twelve waves leave 168 registers a wave: wave tiles of at most 8 blocks.
+// ------------------------------------------------------------------------------------------------
+__device__ __forceinline__ void split_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// One wave-uniform position in the sequence of steps (chunk, filter tap, channel block of the chunk).
+struct SplitCursor {
+    int ch, r, s, tap, cb, cbs;
+    __device__ __forceinline__ void advance(const SplitArgs& a)
+    {
+        if (++cb < cbs) return;
+        cb = 0;
+        ++tap;
+        if (++s == a.S) { s = 0; ++r; }
+        if (tap < a.RS) return;
+        tap = r = s = 0;
+        ++ch;
+        cbs = ch == a.nchunks - 1 ? a.cbs_last : a.CC >> 5;
+    }
+};
+
+template <int MW, int NW, int WM>
+__global__ void __launch_bounds__(768)
+split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsigned char* __restrict__ wfrag, const SplitArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    constexpr int NTC = 512, NTP = 256;                      // multiplying, staging threads
+    constexpr int PF = 2;                                    // steps of weights in flight
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave12 = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const int grid = gridDim.x;
+    const int wg = (grid & 7) == 0 ? (int)(blockIdx.x & 7) * (grid >> 3) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    int bt, db;
+    if (a.wmajor) { db = sdiv(wg, a.inv_ntiles); bt = wg - db * a.ntiles; }
+    else { bt = sdiv(wg, a.inv_ndb); db = wg - bt * a.ndb; }
+    const int bg = sdiv(bt, a.inv_tiles_p);
+    const int tpi = bt - bg * a.tiles_p;
+    const int b0 = bg * a.NS, p0 = tpi * a.TP;
+    const int row0 = p0 * a.s_h - a.pad_h;
+    const int plane = a.H * a.W, PQ = a.P * a.Q;
+    const int cgroups = a.CC >> 3;
+    const int buf = 3 * a.bufsz;
+
+    SplitRows sa;
+    sa.nsv = min(a.NS, a.N - b0);
+    sa.ilo = max(0, -row0);
+    sa.nrows = max(0, min(a.Hs, a.H - row0) - sa.ilo);
+    sa.rlo = row0 + sa.ilo;
+    sa.wcols = min(a.W, a.Ws - a.pad_w);
+
+    if (wave12 >= 8) {
+        // ------------------------------------------------------------------ staging waves
+        const int ptid = tid - NTC;
+        SplitStage st;
+        const int rows = a.flat ? 1 : sa.nrows;
+        st.run = a.flat ? sa.nrows * a.W : sa.wcols;
+        st.G = (st.run + a.epv - 1) >> (a.epv >> 1);
+        st.rowsG = rows * st.G;
+        st.per_cg = sa.nsv * st.rowsG;
+        st.nblocks = cgroups * st.per_cg;
+        st.inv_per_cg = __builtin_amdgcn_rcpf((float)max(st.per_cg, 1));
+        st.inv_rowsG = __builtin_amdgcn_rcpf((float)max(st.rowsG, 1));
+        st.inv_G = __builtin_amdgcn_rcpf((float)max(st.G, 1));
+        st.dst0 = sa.ilo * a.Ws + a.pad_w;
+        st.plane4 = (unsigned)plane * 4u;
+        st.sample4 = (unsigned)a.C * st.plane4;
+        st.row4 = (unsigned)a.W * 4u;
+        st.xs = reinterpret_cast<const char*>(x + (int64_t)b0 * a.C * plane + (int64_t)sa.rlo * a.W);
+        st.cleft = a.C;
+        st.whole = st.cleft >= a.CC;
+        const int per_round = NTP * (a.epv == 4 ? 1 : (a.epv == 2 ? 2 : 4));
+        float pre[2][32];
+        auto load_pre = [&](float (&v)[32], int v0) {
+            if (st.nblocks == 0) return;                     // (a tile that lies in the padding altogether)
+            asm volatile("" : "+v"(v0));                     // (addresses worked out again, not kept: registers)
+            if (a.epv == 4) load_round<4>(v, st, v0, NTP);
+            else if (a.epv == 2) load_round<2>(v, st, v0, NTP);
+            else load_round<1>(v, st, v0, NTP);
+        };
+        auto store_pre = [&](const float (&v)[32], unsigned char* to, int v0) {
+            asm volatile("" : "+v"(v0));
+            if (a.epv == 4) store_round<4>(v, st, to, v0, NTP, a);
+            else if (a.epv == 2) store_round<2>(v, st, to, v0, NTP, a);
+            else store_round<1>(v, st, to, v0, NTP, a);
+        };
+        // two rounds of a chunk are loaded a chunk ahead, the others in place
+        const bool two = st.nblocks > per_round;
+        load_pre(pre[0], ptid);
+        if (two) load_pre(pre[1], ptid + per_round);
+        for (int k = 0; k < a.nchunks; ++k) {
+            unsigned char* to = lds + (k & 1) * buf;
+            store_pre(pre[0], to, ptid);
+            if (two) store_pre(pre[1], to, ptid + per_round);
+            for (int v0 = ptid + 2 * per_round; v0 < st.nblocks; v0 += per_round) {
+                load_pre(pre[0], v0);
+                store_pre(pre[0], to, v0);
+            }
+            if (k + 1 < a.nchunks) {
+                st.xs += (int64_t)a.CC * st.plane4;
+                st.cleft -= a.CC;
+                st.whole = st.cleft >= a.CC;
+                load_pre(pre[0], ptid);
+                if (two) load_pre(pre[1], ptid + per_round);
+            }
+            split_barrier();                                 // barrier k
+        }
+        return;
+    }
+
+    const int kgrp = wave12 >> 2, wave = wave12 & 3;
+    const int wm = wave % WM, wn = wave / WM;
+    const int n16 = lane & 15, kg = lane >> 4;
+    const int mblk0 = db * (a.DB >> 4) + wm * MW;
+    const int wrow = a.RS * a.NCB * 3072;
+    const unsigned char* wbase = wfrag + (int64_t)mblk0 * wrow + lane * 16;
+
+    // the two groups of four waves take the even and the odd steps of the whole contraction
+    const int total = a.RS * a.NCB;
+    const int nsteps = (total - kgrp + 1) >> 1, last = nsteps - 1;
+    SplitCursor wc{0, 0, 0, 0, 0, a.nchunks == 1 ? a.cbs_last : a.CC >> 5}, xc_ = wc;
+    if (kgrp && nsteps > 0) { wc.advance(a); xc_.advance(a); }
+    int wk = 0, xk = 0, nbar = 0;
+    uint4w aq[PF][MW][3], bq[2][3];
+    auto fetch_w = [&](uint4w (&av)[MW][3]) {
+        const unsigned char* wu = wbase + (int64_t)(wc.tap * a.NCB + wc.ch * (a.CC >> 5) + wc.cb) * 3072;
+#pragma unroll
+        for (int m = 0; m < MW; ++m)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) av[m][t] = *reinterpret_cast<const uint4w*>(wu + m * wrow + t * 1024);
+        if (wk < last) { wc.advance(a); if (wk + 1 <= last) wc.advance(a); ++wk; }
+    };
+    if (nsteps > 0) {
+#pragma unroll
+        for (int u = 0; u < PF; ++u) fetch_w(aq[u]);
+    }
+    // the padding of both buffers is written once, behind the first weight requests
+    __builtin_amdgcn_sched_barrier(0);
+    split_pad(lds, tid, NTC, cgroups, sa, a);
+    if (a.nchunks > 1) split_pad(lds + buf, tid, NTC, cgroups, sa, a);
+
+    auto position = [&](int i, int& sm, int& tp, int& tq) {
+        const int f = (wn * NW + i) * 16 + n16;
+        sm = sdiv(f, a.inv_TPQ);
+        const int rem = f - mul24(sm, a.TPQ);
+        tp = sdiv(rem, a.inv_Q);
+        tq = rem - mul24(tp, a.Q);
+        return f < a.npos && b0 + sm < a.N && p0 + tp < a.P;
+    };
+    int bbase[NW];
+    float4v acc[MW][NW], accs[MW][NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        int sm, tp, tq;
+        const bool ok = position(i, sm, tp, tq);
+        const int pos = mul24(sm, a.npos1) + mul24(mul24(tp, a.s_h), a.Ws) + mul24(tq, a.s_w);
+        bbase[i] = (ok ? mul24(pos, a.pitch) : 0) + kg * 16;
+#pragma unroll
+        for (int m = 0; m < MW; ++m) acc[m][i] = accs[m][i] = float4v{0, 0, 0, 0};
+    }
+    auto fetch_x = [&](uint4w (&bv)[3], int i) {
+        if (i == 0) while (nbar <= xc_.ch) { split_barrier(); ++nbar; }      // the chunk of this step is staged
+        const int off = bbase[i] + (xc_.ch & 1) * buf + (xc_.r * a.Ws + xc_.s) * a.pitch + xc_.cb * 64;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) bv[t] = *reinterpret_cast<const uint4w*>(lds + off + t * a.bufsz);
+        if (i == NW - 1 && xk < last) { xc_.advance(a); xc_.advance(a); ++xk; }
+    };
+    auto mul = [&](float4v& c, const uint4w& av, const uint4w& bv) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, av), __builtin_bit_cast(bf8v, bv), c, 0, 0, 0);
+    };
+    auto multiply = [&](const uint4w (&av)[MW][3], const uint4w (&bv)[3], int i) {
+#pragma unroll
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[2]);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) mul(acc[m][i], av[m][0], bv[0]);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[0]);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[1]);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[1]);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[0]);
+    };
+    if (nsteps > 0) {
+        fetch_x(bq[0], 0);
+        __builtin_amdgcn_sched_barrier(0);
+        const int main_steps = nsteps / PF * PF;
+        for (int s0 = 0; s0 < main_steps; s0 += PF) {
+#pragma unroll
+            for (int u = 0; u < PF; ++u) {
+#pragma unroll
+                for (int i = 0; i < NW; ++i) {
+                    fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(aq[u], bq[(u * NW + i) & 1], i);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                fetch_w(aq[u]);
+            }
+        }
+        if (main_steps < nsteps) {
+#pragma unroll
+            for (int i = 0; i < NW; ++i) {
+                if (i + 1 < NW) fetch_x(bq[(i + 1) & 1], i + 1);
+                multiply(aq[0], bq[i & 1], i);
+            }
+        }
+    }
+    while (nbar < a.nchunks) { split_barrier(); ++nbar; }    // (a wave without steps in the last chunks)
+#pragma unroll
+    for (int m = 0; m < MW; ++m)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) acc[m][i] += accs[m][i];
+    // the second group hands its sums to the first (the staging waves have ended)
+    __syncthreads();
+    float4v* ex = reinterpret_cast<float4v*>(lds) + wave * (MW * NW * 64) + lane;
+    if (kgrp == 1) {
+#pragma unroll
+        for (int m = 0; m < MW; ++m)
+#pragma unroll
+            for (int i = 0; i < NW; ++i) ex[(m * NW + i) * 64] = acc[m][i];
+    }
+    __syncthreads();
+    if (kgrp == 1) return;
+#pragma unroll
+    for (int m = 0; m < MW; ++m)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
+    float* yb = y + (int64_t)b0 * a.D * PQ;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        int sm, tp, tq;
+        if (!position(i, sm, tp, tq)) continue;
+        const unsigned o = (unsigned)((sm * a.D + mblk0 * 16 + 4 * kg) * PQ) + (unsigned)(mul24(p0 + tp, a.Q) + tq);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((mblk0 + m) * 16 + 4 * kg + j < a.D) store_out(yb + (o + (unsigned)((16 * m + j) * PQ)), acc[m][i][j]);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // Geometry and launch.
 // ------------------------------------------------------------------------------------------------
-bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int lds_budget, MfmaGeom* out)
+bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int PW, int lds_budget, MfmaGeom* out)
 {
     const sc_layer_t& L = p.L;
     MfmaGeom g{};
@@ -478,6 +730,10 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     g.Ws = (int)Ws;
     g.npos_s = g.NS * g.Hs * g.Ws;
     g.npos = g.NS * g.TP * p.Q;
+    // (32-bit offsets inside the samples of a workgroup and inside a 16-row block of the weights)
+    if ((int64_t)g.NS * L.C * L.H * L.W >= (1ll << 29) || (int64_t)g.NS * L.D * p.P * p.Q >= (1ll << 29) ||
+        (int64_t)L.R * L.S * ((L.C + 31) / 32) >= (1 << 18))
+        return false;
     g.NCB = (L.C + 31) / 32;
     g.CC = std::min(CC, g.NCB * 32);
     g.nchunks = (g.NCB * 32 + g.CC - 1) / g.CC;
@@ -496,7 +752,11 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     // (each of them has at least one)
     if (KS < 1 || KS > 16 || (KS - 1) * ((g.nchunks + KS - 1) / KS) >= g.nchunks) return false;
     g.bufsz = g.npos_s * g.pitch;
-    int64_t lds = 3ll * g.bufsz;
+    if ((int64_t)(g.CC / 8) * g.npos_s >= (1 << 19)) return false;     // sdiv() range of the staging
+    // pipelined: two chunk buffers, eight multiplying waves, a wave tile of at most 8 blocks in 168 registers
+    if (PW && (PW != 4 || KG != 2 || KS != 1 || g.MW * g.NW > 8)) return false;
+    g.PW = PW;
+    int64_t lds = 3ll * g.bufsz * (PW && g.nchunks > 1 ? 2 : 1);
     if (KG == 2) lds = std::max<int64_t>(lds, (int64_t)g.MW * g.NW * 4096);
     if (lds > lds_budget || lds > kMaxLdsBytes) return false;
     g.lds_bytes = (int)lds;
@@ -509,7 +769,11 @@ int split_grid_size(const MfmaGeom& g, int N) { return ((N + g.NS - 1) / g.NS) *
 template <int MW, int NW, int WM, int KG>
 static sc_status_t launch_split_one(const Plan& p, const SplitArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
-    auto kernel = &split_conv_kernel<MW, NW, WM, KG>;
+    // KG = 3: the pipelined form (eight multiplying waves and four that stage)
+    auto kernel = [] {
+        if constexpr (KG == 3) return &split_pipe_kernel<MW, NW, WM>;
+        else return &split_conv_kernel<MW, NW, WM, KG>;
+    }();
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -529,7 +793,7 @@ static sc_status_t launch_split_nw(const Plan& p, const SplitArgs& a, const void
         case 1: return launch_split_one<MW, 1, WM, KG>(p, a, x, y, grid, stream);
         case 2: return launch_split_one<MW, 2, WM, KG>(p, a, x, y, grid, stream);
         case 4: return launch_split_one<MW, 4, WM, KG>(p, a, x, y, grid, stream);
-        case 7: return launch_split_one<MW, 7, WM, KG>(p, a, x, y, grid, stream);
+        case 7: if constexpr (MW == 1 || KG != 3) return launch_split_one<MW, 7, WM, KG>(p, a, x, y, grid, stream); break;
         case 8: if constexpr (MW == 1) return launch_split_one<MW, 8, WM, KG>(p, a, x, y, grid, stream); break;
     }
     return SC_ERR_UNSUPPORTED;
@@ -553,8 +817,19 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
 {
     const MfmaGeom& g = p.mg;
     if (!p.d_wfrag) return SC_ERR_UNSUPPORTED;
-    const int64_t grid = (int64_t)((N + g.NS - 1) / g.NS) * g.tiles_p * g.ndb * g.DL;
-    if (grid >= (1 << 19)) return SC_ERR_UNSUPPORTED;                       // fdiv19() range
+    // sdiv() range: a batch that needs more workgroups is run in slices
+    const int64_t per_group = (int64_t)g.tiles_p * g.ndb * g.DL, groups = ((1 << 19) - 1) / per_group;
+    if (groups < 1) return SC_ERR_UNSUPPORTED;
+    if ((N + g.NS - 1) / g.NS > groups) {
+        const int step = (int)groups * g.NS;
+        for (int n0 = 0; n0 < N; n0 += step) {
+            const sc_status_t st = launch_split(p, static_cast<const float*>(x) + (int64_t)n0 * p.L.C * p.L.H * p.L.W,
+                                                static_cast<float*>(y) + (int64_t)n0 * p.L.D * p.P * p.Q, std::min(step, N - n0), stream);
+            if (st != SC_OK) return st;
+        }
+        return SC_OK;
+    }
+    const int64_t grid = (int64_t)((N + g.NS - 1) / g.NS) * per_group;
     SplitArgs a{};
     a.C = p.L.C; a.D = p.L.D; a.N = N; a.H = p.L.H; a.W = p.L.W; a.P = p.P; a.Q = p.Q;
     a.S = p.L.S; a.RS = p.L.R * p.L.S; a.s_h = p.L.stride_h; a.s_w = p.L.stride_w; a.pad_h = p.L.pad_h; a.pad_w = p.L.pad_w;
@@ -563,6 +838,7 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
     a.KS = g.DL; a.cps = (g.nchunks + g.DL - 1) / g.DL; a.inv_KS = 1.0f / (float)g.DL;
     a.TPQ = g.TP * p.Q;
     a.npos1 = g.Hs * g.Ws;
+    a.cbs_last = g.NCB - (g.nchunks - 1) * (g.CC / 32);
     {
         // what an XCD reads into its L2: with the tile outermost all weights and an eighth of the input,
         // else its share of the weights and (of the chunks its workgroups take) of the input
@@ -585,13 +861,11 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
         const bool fits = p.L.W % e == 0 || (a.flat && pointwise && plane % e == 0 && (g.tiles_p == 1 || a.TPQ % e == 0));
         if (fits && reinterpret_cast<uintptr_t>(x) % (uintptr_t)(e * 4) == 0) { a.epv = e; break; }
     }
-    // (32-bit offsets inside the samples of a workgroup and inside a 16-row block of the weights)
-    if ((int64_t)a.RS * g.NCB >= (1 << 18) || (int64_t)g.NS * p.L.C * plane >= (1ll << 29) || (int64_t)g.NS * p.L.D * p.P * p.Q >= (1ll << 29)) return SC_ERR_UNSUPPORTED;
-    if ((int64_t)(g.CC / 8) * g.npos_s >= (1 << 19)) return SC_ERR_UNSUPPORTED;     // fdiv19() range of the staging
     if (g.DL > 1) {
         const sc_status_t st = launch_clear(y, (int64_t)N * p.L.D * p.P * p.Q, stream);
         if (st != SC_OK) return st;
     }
+    if (g.PW) return launch_split_kg<3>(p, a, x, y, (int)grid, stream);
     return g.KG == 2 ? launch_split_kg<2>(p, a, x, y, (int)grid, stream) : launch_split_kg<1>(p, a, x, y, (int)grid, stream);
 }
 

@@ -1416,7 +1416,11 @@ def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph,
                    {"tile_d": 64, "waves_m": 4, "tile_p": 2}, {"tile_d": 128, "waves_m": 4, "tile_p": 1, "wg_per_cu": 2},
                    {"tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32}, {"tile_d": 32, "waves_m": 2, "tile_p": 1000, "sub_batch": 3},
                    {"tile_d": 64, "waves_m": 4, "tile_p": 3, "chunk_c": 64}, {"tile_d": 32, "waves_m": 1, "tile_p": 4, "chunk_c": 32, "split_n": 2},
-                   {"tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 32, "split_n": 3}):
+                   {"tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 32, "split_n": 3},
+                   # pipelined: staging waves of their own (with eight multiplying waves only)
+                   {"producers": 4}, {"producers": 4, "tile_d": 32, "waves_m": 1, "tile_p": 1, "chunk_c": 32},
+                   {"producers": 4, "tile_d": 64, "waves_m": 4, "tile_p": 3, "chunk_c": 64}, {"producers": 4, "tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32},
+                   {"producers": 4, "tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 96}):
             try:
                 _split(plan, wg_threads=threads, **kw)
             except B.SparseConvError as e:
@@ -1466,3 +1470,4 @@ def test_fp32_split_form_is_refused_where_it_does_not_apply():
     plan = G.make_plan(l16, wl.prepare(l16))
     refused(plan)
     plan.destroy()
+
