@@ -149,7 +149,8 @@ typedef struct {
                            wg_per_cu, wg_threads 256 or 512 (0 = 512); split_n = 2..16 as for the chunked
                            one-shot form, each workgroup with at least one chunk; producers = 4: the chunks are
                            staged by four more waves into two LDS buffers, one chunk ahead (wg_threads 512,
-                           split_n 0); all other fields 0
+                           split_n 0); ragged may be 1 (the dense image never holds the fillers: same result);
+                           all other fields 0
                            DENSE: 1 = the chunks of input channels are staged by `producers` waves of their
                            own into two LDS buffers, one chunk ahead of the multiplying waves (which run
                            over the steps of all chunks without draining their weights in flight);
@@ -234,6 +235,9 @@ typedef struct {
  *   codebook[16]   centroids, i8 (SC_CB4_I8) or IEEE half bits (SC_CB4_F16); required for those, else NULL
  * Rows are padded to n = max row length with zero-valued entries that repeat the row's last column
  * (column 0 for an empty row); then a device pass stretches every column to its input offset.
+ * The new plan's launch shape is chosen by a rule on sizes: the matrix-core tile (DENSE, for SC_F32 the
+ * split form) when at least one weight in 32 is stored, no column twice, and the dense weights are at
+ * most 256 MB, else a gather kernel.
  * Errors: SC_ERR_NULL, SC_ERR_SHAPE, SC_ERR_CSR, SC_ERR_UNSUPPORTED, SC_ERR_RANGE, SC_ERR_OOM, SC_ERR_HIP.
  * On error *out is NULL. */
 sc_status_t sparse_conv_plan_create_csr(const sc_layer_t* layer, sc_dtype_t dtype,

@@ -286,9 +286,11 @@ class Plan:
     # -- execution (raw device pointers) --------------------------------------------------------
     def forward(self, x_ptr: int, y_ptr: int, N: int, ws_ptr: int = 0, ws_bytes: int = 0,
                 stream: int = 0):
-        _check(lib().sparse_conv_forward(self._h, ctypes.c_void_p(x_ptr), ctypes.c_void_p(y_ptr), N,
-                                         ctypes.c_void_p(ws_ptr), ws_bytes, ctypes.c_void_p(stream)),
-               "sparse_conv_forward")
+        # (plain integers: the declared argument types convert them.  Wrapping the four pointers took as
+        # long as the rest of the call, which on the smallest layers is longer than the kernel)
+        st = lib().sparse_conv_forward(self._h, x_ptr, y_ptr, N, ws_ptr, ws_bytes, stream)
+        if st:
+            raise SparseConvError(st, "sparse_conv_forward")
 
     def forward_static(self, x_ptr: int, y_ptr: int, N: int, stream: int = 0):
         _check(lib().sparse_conv_forward_static(self._h, ctypes.c_void_p(x_ptr), ctypes.c_void_p(y_ptr), N,

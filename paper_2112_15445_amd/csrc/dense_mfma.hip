@@ -29,6 +29,8 @@
 //     the multiplying waves).
 // Integer results are exact (bit-identical to the gather kernels); f16 results differ from them in
 // summation order only.
+#include <algorithm>
+
 #include "dense_mfma_kernel.h"
 
 namespace sc {
@@ -190,8 +192,19 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
     const MfmaGeom& g = p.mg;
     if (!p.d_wfrag) return SC_ERR_UNSUPPORTED;
     const int ndbg = (g.ndb + g.DL - 1) / g.DL;
-    const int64_t grid = (int64_t)((N + g.NS - 1) / g.NS) * g.tiles_p * ndbg;
-    if (grid >= (1 << 19)) return SC_ERR_UNSUPPORTED;                       // fdiv19() range
+    // fdiv19() range: a batch that needs more workgroups is run in slices
+    const int64_t per_group = (int64_t)g.tiles_p * ndbg, groups = ((1 << 19) - 1) / per_group;
+    if (groups < 1) return SC_ERR_UNSUPPORTED;
+    if ((N + g.NS - 1) / g.NS > groups) {
+        const int step = (int)groups * g.NS;
+        const int64_t xs = (int64_t)p.L.C * p.L.H * p.L.W * p.ex, ys = (int64_t)p.L.D * p.Po * p.Qo * (p.epi.requant ? 1 : p.ey);
+        for (int n0 = 0; n0 < N; n0 += step) {
+            const sc_status_t st = launch_mfma(p, static_cast<const char*>(x) + n0 * xs, static_cast<char*>(y) + n0 * ys, std::min(step, N - n0), stream);
+            if (st != SC_OK) return st;
+        }
+        return SC_OK;
+    }
+    const int64_t grid = (int64_t)((N + g.NS - 1) / g.NS) * per_group;
     if ((int64_t)g.NS * p.L.C * p.L.H * p.L.W >= (1ll << 31)) return SC_ERR_UNSUPPORTED;
     MfmaArgs a{};
     a.C = p.L.C; a.D = p.L.D; a.N = N; a.H = p.L.H; a.W = p.L.W; a.P = p.P; a.Q = p.Q;

@@ -326,7 +326,8 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
 {
     const sc_layer_t& L = p.L;
     if (p.dtype != SC_F32 || !p.splittable || p.has_dup || p.n == 0 || has_epilogue(p)) return SC_ERR_UNSUPPORTED;
-    if (t.wsrc || t.ragged || t.pack || t.tile_q || t.buffers || t.stage_rows) return SC_ERR_UNSUPPORTED;
+    if (t.wsrc || t.ragged < 0 || t.ragged > 1 || t.pack || t.tile_q || t.buffers || t.stage_rows) return SC_ERR_UNSUPPORTED;
+    // (the dense image never holds the fillers: ragged = 1 says so, the result is the same)
     if (t.producers != 0 && t.producers != 4) return SC_ERR_UNSUPPORTED;      // 4: staging waves of their own, two chunk buffers
     const int PW = t.producers;
     if (t.wg_threads != 0 && t.wg_threads != 256 && t.wg_threads != 512) return SC_ERR_UNSUPPORTED;
@@ -370,6 +371,7 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     r.waves_m = g.WM;
     r.wg_per_cu = t.wg_per_cu;
     r.producers = PW;
+    r.ragged = t.ragged;
     r.split_n = KS > 1 ? KS : 0;
     *out = r;
     *mgeom = g;
@@ -486,6 +488,57 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
     *out = t;
     *geom = SlabGeom{};
     return SC_OK;
+}
+
+// ------------------------------------------------------------------------------------------------
+// The launch shape of a plan that nobody has tuned.
+//
+// The matrix-core tiles (DENSE; for fp32 the split form) need the same time at any sparsity, and
+// untuned they beat the untuned gather kernels on every layer tried down to a few stored weights in a
+// hundred (f16 3x3 256-256 at 14 x 14, batch 32, 80 %: 261 us on the slab default, 20 here; fp32 1x1
+// 2048-512 at 7 x 7, 80 %: 217 and 41).  They are taken when at least one weight in 32 is stored (below
+// that the dense image is mostly zeros and the gather kernels' work shrinks with the table) and the
+// dense weights are at most 256 MB.  The tile is the one with the least estimated time of a batch of
+// 32: per workgroup the largest of its matrix instructions (22 clocks each with two waves on a SIMD,
+// 32 with one: measured), its weights and input through the vector L1 (64 bytes a clock) and its
+// operands from LDS (128 bytes a clock), plus a fixed 8000 clocks of start and drain.
+// ------------------------------------------------------------------------------------------------
+static bool default_dense_tuning(const Plan& p, sc_tuning_t* out, MfmaGeom* mgeom)
+{
+    const sc_layer_t& L = p.L;
+    const bool split = p.dtype == SC_F32;
+    const int64_t K = (int64_t)L.C * L.R * L.S;
+    if (p.n == 0 || p.has_dup || (split && !p.splittable) || (int64_t)p.n * 32 < K) return false;
+    if ((split ? split_weight_bytes(p) : mfma_weight_bytes(p)) > ((size_t)256 << 20)) return false;
+    const int CB = split ? 32 : mfma_chan_block(p.dtype), terms = split ? 3 : 1, products = split ? 6 : 1;
+    const int64_t steps = (int64_t)L.R * L.S * ((L.C + CB - 1) / CB);
+    double best = INFINITY;
+    const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}};
+    for (int thr : {256, 512}) for (const auto& lw : layouts) for (int wpc : {1, 2}) for (int tile = 0; tile < 10; ++tile) {
+        if (lw[0] > 32 && lw[0] >= 2 * L.D) continue;
+        static const int rows[] = {1, 2, 4, 7, 8, 14};
+        const int tp = tile < 6 ? rows[tile] : p.P, ns = tile < 6 ? 1 : 1 << (tile - 6);
+        if (tile < 6 && tp >= p.P) continue;
+        sc_tuning_t t{}, r{};
+        t.variant = split ? SC_VARIANT_SLAB : SC_VARIANT_DENSE;
+        t.pipeline = split ? 3 : 0;
+        t.wg_threads = thr; t.tile_d = lw[0]; t.waves_m = lw[1]; t.wg_per_cu = wpc; t.tile_p = tp; t.sub_batch = ns;
+        MfmaGeom g{};
+        if ((split ? resolve_split(p, t, &r, &g) : resolve_dense(p, t, &r, &g)) != SC_OK) continue;
+        // (what the launch would refuse)
+        if ((int64_t)g.NS * L.C * L.H * L.W >= (1ll << 29) || (int64_t)g.DB * g.npos >= (1 << 19) || g.npos_s >= (1 << 16) ||
+            (int64_t)g.tiles_p * g.ndb >= (1 << 19))
+            continue;
+        const double wgs = std::ceil(32.0 / g.NS) * g.tiles_p * g.ndb, per_cu = std::ceil(wgs / kNumCU);
+        const double resident = std::min(per_cu, (double)std::max(1, std::min(wpc, kMaxLdsBytes / std::max(g.lds_bytes, 1))));
+        const double clocks = g.KG * resident >= 2.0 ? 22.0 : 32.0;
+        const double mfma = (double)steps * g.MW * g.NW * products * clocks;
+        const double l1 = ((double)steps * 4 * g.MW * terms * 1024 + (double)g.npos_s * L.C * p.ex) / 64.0;
+        const double lds = (double)steps * 4 * g.NW * terms * 1024 / 128.0 + (double)g.npos_s * L.C * p.ex / 16.0;
+        const double time = 8000.0 * std::ceil(per_cu / resident) + 3000.0 * g.nchunks * per_cu / resident + per_cu * std::max(mfma, std::max(l1, lds));
+        if (time < best) { best = time; *out = r; *mgeom = g; }
+    }
+    return best < INFINITY;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -713,18 +766,6 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
     p->np = (p->n + 1) / 2 * 2;
     p->h_col = std::move(tab.col);
     p->h_len = std::move(tab.len);
-    // resolve the default tuning first: it is pure host arithmetic
-    // default launch shape before any autotune: the slab kernel with 16 waves per workgroup and
-    // weights by scalar loads where the layer allows it, otherwise whatever the heuristic resolves
-    sc_tuning_t t{};
-    SlabGeom g{};
-    MfmaGeom mg{};
-    sc_tuning_t want{};
-    want.wg_threads = 1024;
-    want.wsrc = is_codebook(p->dtype) ? 0 : 1;
-    sc_status_t st = resolve_tuning(*p, want, &t, &g, &mg);
-    if (st != SC_OK) st = resolve_tuning(*p, sc_tuning_t{}, &t, &g, &mg);
-    if (st != SC_OK) return st;
     // a column stored twice in one row: legal (the entries add up), but such a table has no exact
     // dense image in the weights' own width, so the DENSE variant is not offered for it
     for (int d = 0; d < p->L.D && !p->has_dup; ++d)
@@ -739,6 +780,22 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
         for (size_t i = 0; i < cnt && p->splittable; ++i)
             p->splittable = w[i] == 0.0f || (std::isfinite(w[i]) && std::fabs(w[i]) >= 0x1p-100f);
     }
+
+    // the default launch shape first: it is pure host arithmetic.  The matrix-core tile where it applies
+    // (default_dense_tuning), else the slab kernel with 16 waves per workgroup and
+    // weights by scalar loads where the layer allows it, otherwise whatever the heuristic resolves
+    sc_tuning_t t{};
+    SlabGeom g{};
+    MfmaGeom mg{};
+    sc_tuning_t want{};
+    want.wg_threads = 1024;
+    want.wsrc = is_codebook(p->dtype) ? 0 : 1;
+    sc_status_t st = resolve_tuning(*p, want, &t, &g, &mg);
+    if (st != SC_OK) st = resolve_tuning(*p, sc_tuning_t{}, &t, &g, &mg);
+    if (st != SC_OK) return st;
+    sc_tuning_t td{};
+    MfmaGeom mgd{};
+    const bool dense = default_dense_tuning(*p, &td, &mgd);
 
     std::vector<uint8_t> packed;
     const uint8_t* theta_src = tab.val.data();
@@ -789,6 +846,12 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
     if (hipStreamSynchronize(stream) != hipSuccess) return SC_ERR_HIP;
     p->path = SC_PATH_SPARSE;
     p->dispatch.choice = -1;
+    if (dense) {
+        st = install_tuning(p, td, SlabGeom{}, mgd, stream);
+        if (st == SC_OK) p->path = td.variant == SC_VARIANT_DENSE ? SC_PATH_DENSE : SC_PATH_SPARSE;
+        if (st != SC_ERR_OOM) return st;
+        (void)hipGetLastError();       // (no room for the dense weights: the sparse table alone)
+    }
     return install_tuning(p, t, g, mg, stream);
 }
 
@@ -1085,6 +1148,8 @@ sc_status_t sparse_conv_forward(const sparse_conv_plan_t* plan, const void* x_de
 static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
 {
     out->clear();
+    // fillers (zero weights that unify the row lengths) are more than 5 % of the table
+    const bool uneven = p.n > 0 && p.true_nnz * 100 < (int64_t)p.L.D * p.n * 95;
     auto push = [&](sc_tuning_t t) {
         sc_tuning_t r{};
         SlabGeom g{};
@@ -1178,6 +1243,7 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
                 sc_tuning_t t{};
                 t.variant = SC_VARIANT_SLAB;
                 t.pipeline = 3;
+                t.ragged = uneven ? 1 : 0;
                 t.wg_threads = thr;
                 t.tile_d = lw[0];
                 t.waves_m = lw[1];
@@ -1491,7 +1557,7 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
     }
     // A table whose rows differ in length carries fillers (zero weights that unify the rows): when
     // they are more than 5 % of it, every chunked shape is also tried with the fillers left out.
-    if (p.n > 0 && p.true_nnz * 100 < (int64_t)p.L.D * p.n * 95) {
+    if (uneven) {
         const size_t count = out->size();
         for (size_t k = 0; k < count; ++k) {
             sc_tuning_t t = (*out)[k];

@@ -1420,7 +1420,7 @@ def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph,
                    # pipelined: staging waves of their own (with eight multiplying waves only)
                    {"producers": 4}, {"producers": 4, "tile_d": 32, "waves_m": 1, "tile_p": 1, "chunk_c": 32},
                    {"producers": 4, "tile_d": 64, "waves_m": 4, "tile_p": 3, "chunk_c": 64}, {"producers": 4, "tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32},
-                   {"producers": 4, "tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 96}):
+                   {"producers": 4, "tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 96, "ragged": 1}):
             try:
                 _split(plan, wg_threads=threads, **kw)
             except B.SparseConvError as e:
@@ -1450,7 +1450,7 @@ def test_fp32_split_form_is_refused_where_it_does_not_apply():
     plan = G.make_plan(l, data)
     # (96 channels in chunks of 32: four shares would leave a workgroup without a chunk)
     for kw in (dict(chunk_c=32, split_n=4), dict(chunk_c=33), dict(tile_d=48), dict(wg_threads=384), dict(wsrc=1), dict(pack=2),
-               dict(producers=2), dict(stage_rows=1), dict(ragged=1), dict(tile_d=32, waves_m=4)):
+               dict(producers=2), dict(stage_rows=1), dict(ragged=2), dict(tile_d=32, waves_m=4)):
         refused(plan, **kw)
     plan.set_epilogue(relu=True)
     refused(plan)
@@ -1471,3 +1471,43 @@ def test_fp32_split_form_is_refused_where_it_does_not_apply():
     refused(plan)
     plan.destroy()
 
+
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("C,D,H,W,k,stride,pad,N", [(40, 24, 9, 9, 3, 1, 1, 3), (64, 48, 14, 14, 1, 1, 0, 2), (33, 70, 8, 5, 3, 2, 1, 5), (3, 16, 12, 12, 3, 1, 1, 1)])
+def test_default_launch_shape_of_a_new_plan(dtype, C, D, H, W, k, stride, pad, N):
+    """A plan nobody has tuned takes the matrix-core tile (fp32: the split form) when at least one weight in 32 is
+    stored and each column once, and a gather kernel otherwise; both give the oracle's result, also with the
+    fused epilogue's own default."""
+    for sparsity, dup in ((0.6, False), (0.995, False), (0.6, True)):
+        l = wl.Layer("default", C, D, H, W, k, k, stride, stride, pad, pad, N=N, sparsity=sparsity, dtype=dtype, seed=C + D)
+        data = wl.prepare(l, ragged=False)
+        if dup:
+            data["colidx"] = data["colidx"].copy()
+            data["colidx"][1] = data["colidx"][0]
+        plan = G.make_plan(l, data)
+        t = plan.get_tuning()
+        matrix = t.variant == B.SC_VARIANT_DENSE or (t.variant == B.SC_VARIANT_SLAB and t.pipeline == 3)
+        assert matrix == (l.n * 32 >= l.K and not dup), t.as_dict()
+        assert not matrix or (t.pipeline == 3) == (dtype == "f32")
+        print("case default", dtype, C, D, sparsity, dup, t.as_dict(), flush=True)
+        G.check(l, G.run_gpu(plan, data["x"]), G.oracle_out(l, data), f"default {t.as_dict()}")
+        plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "i8"])
+def test_matrix_core_tiles_run_a_batch_of_more_workgroups_than_one_launch_holds_in_slices(dtype):
+    """A launch decodes at most 2^19 - 1 workgroups; 2^19 + 3 samples of one workgroup each take two."""
+    n = 2 ** 19 + 3
+    l = wl.Layer("slices", 4, 3, 1, 2, 1, 1, 1, 1, 0, 0, N=n, sparsity=0.4, dtype=dtype, seed=12)
+    data = wl.prepare(l)
+    plan = G.make_plan(l, data)
+    if dtype == "f32":
+        _split(plan, tile_p=1, sub_batch=1)
+    else:
+        plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, tile_p=1, sub_batch=1)
+    print("case slices", dtype, plan.get_tuning().as_dict(), flush=True)
+    got = G.run_gpu(plan, data["x"])
+    pick = [0, 1, 2 ** 19 - 2, 2 ** 19 - 1, 2 ** 19, n - 1]
+    G.check(l, got[pick], G.oracle_out(l, data, samples=pick), f"slices {dtype}")
+    assert not np.any(got.view(np.uint8).reshape(n, -1).min(axis=1) == 0x7f)      # every sample was written
+    plan.destroy()
