@@ -222,6 +222,10 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
     a.CC = g.CC; a.nchunks = g.nchunks; a.NCB = g.NCB; a.pitch = g.pitch; a.DB = g.DB; a.ndb = g.ndb;
     a.epi = has_epilogue(p) ? 1 : 0; a.epi_relu = p.epi.relu; a.epi_pool = p.epi.pool; a.epi_pitch = g.epi_pitch;
     a.Po = p.Po; a.Qo = p.Qo; a.requant = p.epi.requant ? p.d_requant : nullptr;
+    // (without pooling; a group of four lanes must not straddle a sample, or the last row of the plane
+    // inside a tile)
+    a.epi_quads = (a.requant && !p.epi.pool && (p.P * p.Q) % 4 == 0 && (p.Q % 4 == 0 || g.tiles_p == 1) &&
+                   reinterpret_cast<uintptr_t>(y) % 4 == 0) ? 1 : 0;
     if ((int64_t)g.DB * g.NS * g.TP * p.Q >= (1 << 19)) return SC_ERR_UNSUPPORTED;
     // elements per staging load: the widest power of two (up to 16 bytes) that divides the row length
     // and the caller's pointer

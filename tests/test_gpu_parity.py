@@ -1511,3 +1511,40 @@ def test_matrix_core_tiles_run_a_batch_of_more_workgroups_than_one_launch_holds_
     G.check(l, got[pick], G.oracle_out(l, data, samples=pick), f"slices {dtype}")
     assert not np.any(got.view(np.uint8).reshape(n, -1).min(axis=1) == 0x7f)      # every sample was written
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["i8", "cb4"])
+@pytest.mark.parametrize("C,D,H,W,k,N,relu", [(5, 37, 6, 8, 3, 3, True), (64, 18, 2, 2, 3, 7, False), (70, 64, 4, 3, 1, 5, True), (9, 16, 5, 5, 3, 2, True)])
+def test_requantised_codes_stored_four_positions_at_a_time(dtype, C, D, H, W, k, N, relu):
+    """Planes of whole groups of four positions (the last shape is not one: byte stores), output channels that are
+    no multiple of 16 or 4, batches that end inside a workgroup, tiles of one row and of whole planes, and a y that
+    is not aligned to four bytes: bit-exact codes, nothing written past the end."""
+    import oracle
+    import torch
+    l = wl.Layer("quads", C, D, H, W, k, k, 1, 1, k // 2, k // 2, N=N, sparsity=0.5, dtype=dtype, seed=C + D)
+    data = wl.prepare(l)
+    acc = G.oracle_out(l, data)
+    rq = (np.linspace(40.0, 160.0, D) / max(1.0, float(np.abs(acc).max()))).astype(np.float32)
+    want = oracle.epilogue(acc, relu=relu, pool=0, requant_scale=rq)
+    plan = G.make_plan(l, data)
+    plan.set_epilogue(relu=relu, requant_scale=rq)
+    xd = G.to_device(data["x"])
+    ran = 0
+    for kw in ({}, {"tile_d": 16, "tile_p": 1}, {"tile_d": 32, "waves_m": 2, "tile_p": 1000, "sub_batch": 4}, {"tile_d": 64, "waves_m": 4, "tile_p": 2},
+               {"tile_d": 16, "tile_p": 1000, "split_n": 2}, {"wg_threads": 512, "tile_d": 32}, {"pipeline": 1, "tile_d": 32}):
+        try:
+            plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, **kw)
+        except B.SparseConvError as e:
+            assert e.status == 4
+            continue
+        for shift in (0, 1):
+            buf = torch.full((want.size + 16,), 0x55, dtype=torch.int8, device="cuda")
+            print("case quads", dtype, C, D, kw, shift, flush=True)
+            plan.forward(xd.data_ptr(), buf.data_ptr() + shift, N, 0, 0, torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            got = buf.cpu().numpy()
+            assert np.array_equal(got[shift:shift + want.size].reshape(want.shape), want), (dtype, kw, shift)
+            assert np.all(got[:shift] == 0x55) and np.all(got[shift + want.size:] == 0x55)
+            ran += 1
+    assert ran >= 8
+    plan.destroy()
