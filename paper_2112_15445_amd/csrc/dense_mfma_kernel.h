@@ -17,8 +17,9 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 typedef int int4v_ __attribute__((ext_vector_type(4)));
 typedef unsigned uint4w __attribute__((ext_vector_type(4)));
 
-// (Measured on this chip: the 16 x 16 block instructions used here sustain 1.3 PFLOP/s in fp16
-// with four waves per SIMD and 0.8 with one, the 32 x 32 ones 2.3 and 2.0.  The layers this
+// (Measured on this chip, loops with 16 independent accumulators: the 16 x 16 x 32 instructions used here
+// take 32 clocks with one wave per SIMD and 22 with two or more -- 1.25 and 1.85 PFLOP/s in fp16, 2.8 and
+// 4.0 POP/s in int8 -- and the 32 x 32 x 16 ones 42 and 40 clocks, 1.9 and 2.0 PFLOP/s.  The layers this
 // variant serves are too small for the wave tiles of 64 x 128 outputs that the 32 x 32 form needs
 // to be fed from LDS and L2 at that rate: built that way it was 10 - 40 % slower on every layer
 // tried, so the blocks stay 16 x 16.)
