@@ -142,7 +142,7 @@ typedef struct {
                            most 4 positions per lane and 8 rows per wave.  0 = one tile per workgroup.
                            3 (SC_F32, any layer shape; not for tables that store a column twice in one row or hold
                            weights that are not finite or smaller than 2^-100) = the densified tile on the matrix
-                           cores, every fp32 value split into three bfloat16 terms and a product into the six
+                           cores, every fp32 value split into three bfloat16 terms and a product into the eight
                            largest products of terms, accumulated in fp32: no less precise than the other
                            shapes (inputs below about 2^-100 in magnitude lose their last terms).  Its fields
                            are DENSE's: tile_p, sub_batch, chunk_c (a multiple of 32), tile_d, waves_m,

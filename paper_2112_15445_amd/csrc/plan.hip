@@ -510,7 +510,7 @@ static bool default_dense_tuning(const Plan& p, sc_tuning_t* out, MfmaGeom* mgeo
     const int64_t K = (int64_t)L.C * L.R * L.S;
     if (p.n == 0 || p.has_dup || (split && !p.splittable) || (int64_t)p.n * 32 < K) return false;
     if ((split ? split_weight_bytes(p) : mfma_weight_bytes(p)) > ((size_t)256 << 20)) return false;
-    const int CB = split ? 32 : mfma_chan_block(p.dtype), terms = split ? 3 : 1, products = split ? 6 : 1;
+    const int CB = split ? 32 : mfma_chan_block(p.dtype), terms = split ? 3 : 1, products = split ? 8 : 1;
     const int64_t steps = (int64_t)L.R * L.S * ((L.C + CB - 1) / CB);
     double best = INFINITY;
     const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}};

@@ -3,16 +3,19 @@
 //
 // An fp32 value is exactly x = hi + mid + lo with hi the upper 16 bits of x (truncated, so that no
 // finite x becomes an infinity), mid the rounded bfloat16 of x - hi and lo the rest, which fits a
-// bfloat16: 8 significant bits each.  A product is then the sum of nine exact products, of which
-// the six largest are kept (hi hi, hi mid, mid hi, mid mid, hi lo, lo hi); the other three are below
-// 2^-24 of it.  Each is one v_mfma_f32_16x16x32_bf16 over 32 input channels of one filter tap,
-// accumulated in fp32: hi hi in one set of accumulators, the five small ones in a second set (their
-// roundings are 2^-7 of the first set's), added once at the end.  The sum over a row is rounded
+// bfloat16: 8 significant bits each (the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16
+// artificial intelligence datatype for higher-precision computations", 2019).  With x in
+// [2^e, 2^(e+1)), |mid| is at most 2^(e-7) and |lo| at most 2^(e-16).  A product is then the sum of nine exact
+// products, of which eight are kept; the ninth, lo lo, is at most 2^-32 of it.  (Without mid lo and lo mid, which reach 2^-22 of it together, rows of
+// one and two stored weights came out less exact than from a fused multiply-add: largest error 2.4e-7 of
+// the product against 6.0e-8.)  Each is one v_mfma_f32_16x16x32_bf16 over 32 input channels of one filter tap,
+// accumulated in fp32: hi hi in one set of accumulators, the seven small ones in a second set (their
+// roundings are 2^-6 of the first set's), added once at the end.  The sum over a row is rounded
 // once per 32 channels of a tap instead of once per stored entry, which is why the result is
 // closer to the exact one than the gather kernels' (relative error against 64 bits 5e-8 .. 1.3e-7 where theirs is 0.9e-7 .. 3.7e-7).
-// Bound by the matrix pipes: 6 instructions per 16 x 16 x 32 block, at the 1.8 - 1.9 PFLOP/s that
+// Bound by the matrix pipes: 8 instructions per 16 x 16 x 32 block, at the 1.8 - 1.9 PFLOP/s that
 // the 16 x 16 x 32 bfloat16 instruction sustains with two waves per SIMD (1.24 with one, which is
-// why the workgroups that do not share a CU have eight waves) about 300 TFLOP/s of fp32 products,
+// why the workgroups that do not share a CU have eight waves) about 230 TFLOP/s of fp32 products,
 // against 154 of the fp32 matrix instructions and 78 of the vector units without packed math.
 //
 // Tile, staging, weight order and step order are those of the DENSE variant (dense_mfma.hip): a
@@ -51,6 +54,33 @@ __device__ __forceinline__ void split3x2(float x0, float x1, unsigned& hi, unsig
     mid = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){r0, r1}, bf2v));                   // to nearest
     const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xffff0000u);         // exact
     lo = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){l0, l1}, bf2v));                    // exact
+}
+
+// One block of positions times MW blocks of output channels: eight matrix instructions for each, the
+// smallest products first.
+template <int MW, int NW>
+__device__ __forceinline__ void split_multiply(float4v (&acc)[MW][NW], float4v (&accs)[MW][NW], const uint4w (&av)[MW][3],
+                                               const uint4w (&bv)[3], int i)
+{
+    auto mul = [&](float4v& c, const uint4w& a, const uint4w& b) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a), __builtin_bit_cast(bf8v, b), c, 0, 0, 0);
+    };
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[2]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(acc[m][i], av[m][0], bv[0]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[1]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[2]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[0]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[1]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[1]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[0]);
 }
 
 // floor(e / d) as fdiv19, one fused multiply-add (e < 2^19; inv within an ulp of 1 / d)
@@ -218,7 +248,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int NT = 256 * KG;
-    // steps of weights in flight: a step multiplies for 6 MW NW matrix instructions (16 clocks and
+    // steps of weights in flight: a step multiplies for 8 MW NW matrix instructions (16 clocks and
     // more each), L2 answers after several hundred clocks.  PF * NW is even (parity of the ring below).
     constexpr int PF = MW * NW >= 7 ? 2 : (MW * NW >= 2 ? 4 : 6);
     const int tid = threadIdx.x;
@@ -310,7 +340,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         return f < a.npos && b0 + sm < a.N && p0 + tp < a.P;
     };
     int bbase[NW];
-    float4v acc[MW][NW], accs[MW][NW];                       // hi hi; the five small products
+    float4v acc[MW][NW], accs[MW][NW];                       // hi hi; the seven small products
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
         int sm, tp, tq;
@@ -357,23 +387,6 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
                 xk += xk < last ? 1 : 0;
             }
         };
-        auto mul = [&](float4v& c, const uint4w& av, const uint4w& bv) {
-            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, av), __builtin_bit_cast(bf8v, bv), c, 0, 0, 0);
-        };
-        auto multiply = [&](const uint4w (&av)[MW][3], const uint4w (&bv)[3], int i) {
-#pragma unroll
-            for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[2]);
-#pragma unroll
-            for (int m = 0; m < MW; ++m) mul(acc[m][i], av[m][0], bv[0]);
-#pragma unroll
-            for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[0]);
-#pragma unroll
-            for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[1]);
-#pragma unroll
-            for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[1]);
-#pragma unroll
-            for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[0]);
-        };
         if (KG == 1 || ksteps > 0) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) fetch_w(aq[u]);
@@ -400,10 +413,10 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
                 for (int i = 0; i < NW; ++i) {
                     // the operands of the next position block (or of the next step's first) come from LDS
-                    // while this one's 6 MW matrix instructions run
+                    // while this one's 8 MW matrix instructions run
                     fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    multiply(aq[u], bq[(u * NW + i) & 1], i);
+                    split_multiply<MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 fetch_w(aq[u]);
@@ -415,7 +428,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
                 for (int i = 0; i < NW; ++i) {
                     fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
-                    multiply(aq[u], bq[(u * NW + i) & 1], i);
+                    split_multiply<MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                 }
             }
         }
@@ -634,23 +647,6 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         for (int t = 0; t < 3; ++t) bv[t] = *reinterpret_cast<const uint4w*>(lds + off + t * a.bufsz);
         if (i == NW - 1 && xk < last) { xc_.advance(a); xc_.advance(a); ++xk; }
     };
-    auto mul = [&](float4v& c, const uint4w& av, const uint4w& bv) {
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, av), __builtin_bit_cast(bf8v, bv), c, 0, 0, 0);
-    };
-    auto multiply = [&](const uint4w (&av)[MW][3], const uint4w (&bv)[3], int i) {
-#pragma unroll
-        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[2]);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) mul(acc[m][i], av[m][0], bv[0]);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[0]);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[1]);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[1]);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[0]);
-    };
     if (nsteps > 0) {
         fetch_x(bq[0], 0);
         __builtin_amdgcn_sched_barrier(0);
@@ -662,7 +658,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
                 for (int i = 0; i < NW; ++i) {
                     fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    multiply(aq[u], bq[(u * NW + i) & 1], i);
+                    split_multiply<MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 fetch_w(aq[u]);
@@ -672,7 +668,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
                 if (i + 1 < NW) fetch_x(bq[(i + 1) & 1], i + 1);
-                multiply(aq[0], bq[i & 1], i);
+                split_multiply<MW, NW>(acc, accs, aq[0], bq[i & 1], i);
             }
         }
     }

@@ -1399,7 +1399,7 @@ def _split(plan, **kw):
 def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph, pw, N, scale):
     """SLAB tunings with pipeline = 3: tails of channels, rows, columns and output channels, several chunks,
     four and eight waves, several samples per workgroup, chunks dealt to several workgroups, large and
-    small magnitudes.  The six kept products are within 2^-24 of the exact one and the sum is rounded
+    small magnitudes.  The eight kept products are within 2^-32 of the exact one and the sum is rounded
     2 K / 32 times, so a result is held to 4e-7 of the sum of the magnitudes' root mean square -- and to
     no more error than the gather kernel's on the same table, times 1.2 for the draw."""
     l = wl.Layer(name, C, D, H, W, R, S, sh, sw, ph, pw, N=N, sparsity=0.6, dtype="f32", seed=sum(map(ord, name)))
@@ -1434,6 +1434,47 @@ def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph,
             assert err <= max(4e-7 if C * R * S > 64 else 1.2e-7, 0.0) and err <= max(1.2 * gather, 6e-8), (name, t, err, gather)
             ran += 1
     assert ran >= 8, (name, ran)
+    plan.destroy()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4])
+def test_fp32_split_form_element_by_element_on_short_rows(n):
+    """Rows of one to four stored weights, where no averaging hides what a product lost: every output against
+    64 bits, one-shot and pipelined, over random significands and the ones whose dropped terms are largest
+    (upper 16 bits far below the value, the next ones just below a carry).  Of a product only lo lo is dropped, at
+    most 2^-32 of it (mid is at most 2^-7 of the value and lo 2^-16); the accumulators are rounded once each per
+    matrix instruction, hi hi to 2^-24 of the sum so far at most once per entry, the small terms to 2^-24 of a
+    2^-6 part, and the two are added with one rounding: n + 1/4 roundings of half a unit (2^-24) in all."""
+    C = n
+    l = wl.Layer("short", C, 64, 24, 24, 1, 1, 1, 1, 0, 0, N=6, sparsity=0.0, dtype="f32", seed=n)
+    rng = np.random.default_rng(n)
+    worst = np.array([0x3f80fe7f, 0x3f80ff80, 0x3f80ffff, 0x3f807f80, 0x3f80feff], np.uint32).view(np.float32)
+
+    def values(count):
+        v = rng.uniform(1, 2, count).astype(np.float32)
+        v[::3] = rng.choice(worst, v[::3].size)
+        return v * rng.choice(np.float32([-1, 1]), count) * np.float32(2.0) ** rng.integers(-3, 4, count).astype(np.float32)
+
+    w = values(l.D * n)
+    x = values(l.N * C * l.H * l.W).reshape(l.N, C, l.H, l.W)
+    plan = B.Plan.create_csr(G.layer_desc(l), B.DTYPES["f32"], np.arange(l.D + 1, dtype=np.int32) * n,
+                             np.tile(np.arange(n, dtype=np.int32), l.D), w, None, None)
+    w64, x64 = w.astype(np.float64).reshape(l.D, n), x.astype(np.float64)
+    ref = np.einsum("dc,bchw->bdhw", w64, x64)
+    mag = np.einsum("dc,bchw->bdhw", np.abs(w64), np.abs(x64))
+
+    def error():
+        return np.abs(G.run_gpu(plan, x).astype(np.float64) - ref) / mag
+
+    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_GATHER, split_n=1)
+    gather = error()
+    for kw in ({}, {"wg_threads": 256, "tile_d": 64, "waves_m": 2}, {"producers": 4}):
+        _split(plan, **kw)
+        print("case split short rows", n, plan.get_tuning().as_dict(), flush=True)
+        e = error()
+        assert e.max() <= (n + 0.25) * 2.0 ** -24, (n, kw, e.max(), gather.max())
+        rms, rms_g = np.sqrt((e * e).mean()), np.sqrt((gather * gather).mean())
+        assert rms <= 1.02 * rms_g, (n, kw, rms, rms_g)          # (2 %: the small terms' own roundings)
     plan.destroy()
 
 
