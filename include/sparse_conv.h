@@ -144,7 +144,9 @@ typedef struct {
                            weights that are not finite or smaller than 2^-100) = the densified tile on the matrix
                            cores, every fp32 value split into three bfloat16 terms and a product into the eight
                            largest products of terms, accumulated in fp32: no less precise than the other
-                           shapes (inputs below about 2^-100 in magnitude lose their last terms).  Its fields
+                           shapes.  (Inputs other than zero below 2^-110 / min(1, smallest weight) are beyond the
+                           terms: the workgroups that read one sum their outputs entry by entry from the sparse
+                           table, with the gather kernels' result and many times their cost.)  Its fields
                            are DENSE's: tile_p, sub_batch, chunk_c (a multiple of 32), tile_d, waves_m,
                            wg_per_cu, wg_threads 256 or 512 (0 = 512); split_n = 2..16 as for the chunked
                            one-shot form, each workgroup with at least one chunk; producers = 4: the chunks are
@@ -236,8 +238,8 @@ typedef struct {
  * Rows are padded to n = max row length with zero-valued entries that repeat the row's last column
  * (column 0 for an empty row); then a device pass stretches every column to its input offset.
  * The new plan's launch shape is chosen by a rule on sizes: the matrix-core tile (DENSE, for SC_F32 the
- * split form) when at least one weight in 32 is stored, no column twice, and the dense weights are at
- * most 256 MB, else a gather kernel.
+ * split form, and no weight but zero below 2^-50) when at least one weight in 32 is stored, no column
+ * twice, and the dense weights are at most 256 MB, else a gather kernel.
  * Errors: SC_ERR_NULL, SC_ERR_SHAPE, SC_ERR_CSR, SC_ERR_UNSUPPORTED, SC_ERR_RANGE, SC_ERR_OOM, SC_ERR_HIP.
  * On error *out is NULL. */
 sc_status_t sparse_conv_plan_create_csr(const sc_layer_t* layer, sc_dtype_t dtype,

@@ -18,11 +18,18 @@
 // why the workgroups that do not share a CU have eight waves) about 230 TFLOP/s of fp32 products,
 // against 154 of the fp32 matrix instructions and 78 of the vector units without packed math.
 //
+// The terms hold a value's 24 bits only down to 2^-110 (the last bit of lo is then the smallest bfloat16), and a
+// product's small terms need room above the smallest fp32.  The staging therefore notes whether a nonzero
+// input is below a bound that the host derives from the smallest weight (p.split_min: 2^-110, or more where some weight
+// is below 1), three vector instructions per pair; a workgroup that met one sums its outputs entry by entry
+// from the sparse table instead of storing the tile's (split_exact).  Ordinary activations never get there.
+//
 // Tile, staging, weight order and step order are those of the DENSE variant (dense_mfma.hip): a
 // workgroup owns DB output channels x a tile of positions; the input region of the tile is staged
 // channel-minor in LDS, here as three bfloat16 images, split on the way; weights are split and put
 // in operand order once per plan.
 #include <algorithm>
+#include <cstring>
 
 #include "dense_mfma_kernel.h"
 
@@ -37,6 +44,11 @@ struct SplitArgs {
     int flat;                // the staged rows of a sample are one contiguous run per channel
     int wmajor, ntiles;      // output-channel blocks outermost; (sample group, row tile) pairs
     float inv_ntiles, inv_KS, inv_ndb, inv_tiles_p, inv_HsWs, inv_Ws, inv_TPQ, inv_Q;
+    unsigned tiny;           // 2 bits(m) - 1 of the smallest magnitude m that the terms serve
+    int flags;               // LDS offset of the staging waves' notes, 2 bytes each
+    int n;                   // the sparse table, for split_exact
+    const float* theta;
+    const int32_t *col, *len;
 };
 
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
@@ -209,10 +221,13 @@ __device__ __forceinline__ void load_round(float (&pre)[32], const SplitStage& s
     }
 }
 
+// Returns the smallest 2 |bits| - 1 of the lane's values (a zero's is the largest): below a.tiny if the terms
+// do not serve one of them.
 template <int EPV>
-__device__ __forceinline__ void store_round(const float (&pre)[32], const SplitStage& st, unsigned char* lds, int v0, int NT, const SplitArgs& a)
+__device__ __forceinline__ unsigned store_round(const float (&pre)[32], const SplitStage& st, unsigned char* lds, int v0, int NT, const SplitArgs& a)
 {
     constexpr int VB = 4 / EPV;
+    unsigned least = ~0u;
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
         int cg, sm, ii, g;
@@ -230,6 +245,7 @@ __device__ __forceinline__ void store_round(const float (&pre)[32], const SplitS
                     if (cg * 8 + 2 * q >= st.cleft) v0 = 0.0f;
                     if (cg * 8 + 2 * q + 1 >= st.cleft) v1 = 0.0f;
                 }
+                least = min(least, min((__float_as_uint(v0) << 1) - 1u, (__float_as_uint(v1) << 1) - 1u));
                 unsigned t0, t1, t2;
                 split3x2(v0, v1, t0, t1, t2);
                 w0[q] = t0; w1[q] = t1; w2[q] = t2;
@@ -239,6 +255,35 @@ __device__ __forceinline__ void store_round(const float (&pre)[32], const SplitS
             *reinterpret_cast<uint4w*>(dst + e * a.pitch + 2 * a.bufsz) = w2;
             __builtin_amdgcn_sched_barrier(0);                 // (one column's terms at a time: registers)
         }
+    }
+    return least;
+}
+
+// The outputs of a workgroup entry by entry, in the order of the gather kernels: where some staged input is too
+// small for the terms.  Input channels [c_lo, c_hi); `add`: other workgroups have the other channels.
+__device__ __forceinline__ void split_exact(const float* __restrict__ x, float* __restrict__ y, const SplitArgs& a, int tid, int NT,
+                                            int db, int b0, int p0, int c_lo, int c_hi, bool add)
+{
+    const int rows = min(a.DB, a.D - db * a.DB);
+#pragma unroll 1
+    for (int e = tid; e < rows * a.npos; e += NT) {
+        const int dd = e / a.npos, f = e - dd * a.npos;
+        const int sm = f / a.TPQ, rem = f - sm * a.TPQ, tp = rem / a.Q, tq = rem - tp * a.Q;
+        if (b0 + sm >= a.N || p0 + tp >= a.P) continue;
+        const int d = db * a.DB + dd, i0 = (p0 + tp) * a.s_h - a.pad_h, w0 = tq * a.s_w - a.pad_w;
+        const float* xb = x + (int64_t)(b0 + sm) * a.C * a.H * a.W;
+        float sum = 0.0f;
+#pragma unroll 1
+        for (int j = 0; j < a.len[d]; ++j) {
+            const int64_t at = (int64_t)d * a.n + j;
+            const int k = a.col[at] & 0x7fffffff, c = k / a.RS, tap = k - c * a.RS, r = tap / a.S;
+            const int i = i0 + r, w = w0 + tap - r * a.S;
+            if (c >= c_lo && c < c_hi && i >= 0 && i < a.H && w >= 0 && w < a.W)
+                sum = __builtin_fmaf(a.theta[at], xb[((int64_t)c * a.H + i) * a.W + w], sum);
+        }
+        float* yp = y + ((int64_t)(b0 + sm) * a.D + d) * a.P * a.Q + (p0 + tp) * a.Q + tq;
+        if (add) add_out(yp, sum);
+        else store_out(yp, sum);
     }
 }
 
@@ -317,11 +362,14 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         else if (a.epv == 2) load_round<2>(pre, st, v0, NT);
         else load_round<1>(pre, st, v0, NT);
     };
+    bool tiny = false;                                       // (wave-uniform) some input is too small for the terms
     auto store_pre = [&](int v0) {
         asm volatile("" : "+v"(v0));
-        if (a.epv == 4) store_round<4>(pre, st, lds, v0, NT, a);
-        else if (a.epv == 2) store_round<2>(pre, st, lds, v0, NT, a);
-        else store_round<1>(pre, st, lds, v0, NT, a);
+        unsigned least;
+        if (a.epv == 4) least = store_round<4>(pre, st, lds, v0, NT, a);
+        else if (a.epv == 2) least = store_round<2>(pre, st, lds, v0, NT, a);
+        else least = store_round<1>(pre, st, lds, v0, NT, a);
+        tiny |= __ballot(least < a.tiny) != 0;
     };
     const int per_round = NT * (a.epv == 4 ? 1 : (a.epv == 2 ? 2 : 4));
     st.xs = reinterpret_cast<const char*>(x + ((int64_t)b0 * a.C + ch_lo * a.CC) * plane + (int64_t)sa.rlo * a.W);
@@ -397,6 +445,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
             load_pre(v0);
             store_pre(v0);
         }
+        if (lane == 0) reinterpret_cast<unsigned short*>(lds + a.flags)[wave8] = tiny ? 1 : 0;
         __syncthreads();
         if (ch + 1 < ch_hi) {
             st.xs += (int64_t)a.CC * st.plane4;
@@ -432,6 +481,13 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
                 }
             }
         }
+    }
+    unsigned noted = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * KG; ++k) noted |= reinterpret_cast<const unsigned*>(lds + a.flags)[k];
+    if (__builtin_amdgcn_readfirstlane(noted)) {             // (the same words for every wave)
+        split_exact(x, y, a, tid, NT, db, b0, p0, ch_lo * a.CC, ch_hi * a.CC, a.KS > 1);
+        return;
     }
 #pragma unroll
     for (int m = 0; m < MW; ++m)
@@ -560,11 +616,14 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
             else if (a.epv == 2) load_round<2>(v, st, v0, NTP);
             else load_round<1>(v, st, v0, NTP);
         };
+        bool tiny = false;                                   // (wave-uniform) some input is too small for the terms
         auto store_pre = [&](const float (&v)[32], unsigned char* to, int v0) {
             asm volatile("" : "+v"(v0));
-            if (a.epv == 4) store_round<4>(v, st, to, v0, NTP, a);
-            else if (a.epv == 2) store_round<2>(v, st, to, v0, NTP, a);
-            else store_round<1>(v, st, to, v0, NTP, a);
+            unsigned least;
+            if (a.epv == 4) least = store_round<4>(v, st, to, v0, NTP, a);
+            else if (a.epv == 2) least = store_round<2>(v, st, to, v0, NTP, a);
+            else least = store_round<1>(v, st, to, v0, NTP, a);
+            tiny |= __ballot(least < a.tiny) != 0;
         };
         // two rounds of a chunk are loaded a chunk ahead, the others in place
         const bool two = st.nblocks > per_round;
@@ -585,6 +644,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
                 load_pre(pre[0], ptid);
                 if (two) load_pre(pre[1], ptid + per_round);
             }
+            if (lane == 0) reinterpret_cast<unsigned short*>(lds + a.flags)[wave12 - 8] = tiny ? 1 : 0;
             split_barrier();                                 // barrier k
         }
         return;
@@ -673,6 +733,11 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         }
     }
     while (nbar < a.nchunks) { split_barrier(); ++nbar; }    // (a wave without steps in the last chunks)
+    const unsigned* note = reinterpret_cast<const unsigned*>(lds + a.flags);
+    if (__builtin_amdgcn_readfirstlane(note[0] | note[1])) { // (the same words for every wave)
+        split_exact(x, y, a, tid, NTC, db, b0, p0, 0, a.C, false);
+        return;
+    }
 #pragma unroll
     for (int m = 0; m < MW; ++m)
 #pragma unroll
@@ -710,6 +775,16 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 // ------------------------------------------------------------------------------------------------
 // Geometry and launch.
 // ------------------------------------------------------------------------------------------------
+static unsigned float_bits(float f)
+{
+    unsigned u;
+    std::memcpy(&u, &f, 4);
+    return u;
+}
+
+// LDS offset of the staging waves' notes: behind the chunk buffers
+static int64_t split_flags(const MfmaGeom& g) { return 3ll * g.bufsz * (g.PW && g.nchunks > 1 ? 2 : 1); }
+
 bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int PW, int lds_budget, MfmaGeom* out)
 {
     const sc_layer_t& L = p.L;
@@ -752,7 +827,8 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     // pipelined: two chunk buffers, eight multiplying waves, a wave tile of at most 8 blocks in 168 registers
     if (PW && (PW != 4 || KG != 2 || KS != 1 || g.MW * g.NW > 8)) return false;
     g.PW = PW;
-    int64_t lds = 3ll * g.bufsz * (PW && g.nchunks > 1 ? 2 : 1);
+    // (and 16 bytes of notes of the staging waves behind the chunk buffers)
+    int64_t lds = split_flags(g) + 16;
     if (KG == 2) lds = std::max<int64_t>(lds, (int64_t)g.MW * g.NW * 4096);
     if (lds > lds_budget || lds > kMaxLdsBytes) return false;
     g.lds_bytes = (int)lds;
@@ -834,6 +910,9 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
     a.KS = g.DL; a.cps = (g.nchunks + g.DL - 1) / g.DL; a.inv_KS = 1.0f / (float)g.DL;
     a.TPQ = g.TP * p.Q;
     a.npos1 = g.Hs * g.Ws;
+    a.tiny = 2u * float_bits(p.split_min) - 1u;
+    a.flags = (int)split_flags(g);
+    a.n = p.n; a.theta = static_cast<const float*>(p.d_theta); a.col = p.d_col; a.len = p.d_len;
     a.cbs_last = g.NCB - (g.nchunks - 1) * (g.CC / 32);
     {
         // what an XCD reads into its L2: with the tile outermost all weights and an eighth of the input,

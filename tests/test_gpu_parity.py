@@ -1478,6 +1478,56 @@ def test_fp32_split_form_element_by_element_on_short_rows(n):
     plan.destroy()
 
 
+@pytest.mark.parametrize("C,D,H,W,k,stride,pad,N", [(70, 20, 9, 11, 3, 2, 1, 3), (64, 33, 7, 7, 1, 1, 0, 5), (40, 70, 12, 8, 3, 1, 1, 2)])
+@pytest.mark.parametrize("xe,we", [(-112, 0), (-122, 0), (-140, 0), (-60, -64), (-90, -30)])
+def test_fp32_split_form_sums_inputs_that_the_terms_do_not_hold_entry_by_entry(C, D, H, W, k, stride, pad, N, xe, we):
+    """Inputs so small that bfloat16 has no room for their last terms, or their products none in fp32: in every
+    workgroup (the gather kernel's sums, bit for bit), in one value of one sample only, and in the channels of one
+    of the workgroups that share a tile.  A sum of n products rounded n times is within n 2^-24 of the sum of the
+    magnitudes, n 2^-150 where it is denormal; the tile that holds the values rounds less often."""
+    l = wl.Layer("tiny", C, D, H, W, k, k, stride, stride, pad, pad, N=N, sparsity=0.6, dtype="f32", seed=C)
+    data = wl.prepare(l)
+    data["values"] = data["values"] * np.float32(2.0 ** we)
+    plan = G.make_plan(l, data)
+    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_GATHER, split_n=1)
+    one = np.where(data["x"] == 0, np.float32(1), data["x"])
+    everywhere = one * np.float32(2.0 ** xe)
+    single, shared = one.copy(), one.copy()
+    single[1, C // 2, H // 2, W // 2] = 2.0 ** xe
+    shared[:, :4] *= np.float32(2.0 ** xe)
+    gather = G.run_gpu(plan, everywhere)
+
+    def dense64(x, values):
+        w = np.zeros((D, C * k * k))
+        w[np.repeat(np.arange(D), np.diff(data["rowptr"])), data["colidx"]] = values
+        xp = np.pad(x.astype(np.float64), ((0, 0), (0, 0), (pad, pad), (pad, pad)))
+        cols = np.stack([xp[:, :, r:r + (l.P - 1) * stride + 1:stride, c:c + (l.Q - 1) * stride + 1:stride] for r in range(k) for c in range(k)], 2)
+        return np.einsum("dk,bkpq->bdpq", w, cols.reshape(N, C * k * k, l.P, l.Q))
+
+    v = data["values"].astype(np.float64)
+    for kw in ({}, {"wg_threads": 256, "tile_d": 64, "waves_m": 4, "tile_p": 3}, {"tile_d": 32, "waves_m": 1, "tile_p": 2, "chunk_c": 32, "split_n": 2},
+               {"producers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2, "chunk_c": 32}, {"tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32}):
+        _split(plan, **kw)
+        for what, x in (("everywhere", everywhere), ("single", single), ("shared", shared)):
+            print("case split tiny", C, D, xe, we, kw, what, flush=True)
+            got = G.run_gpu(plan, x)
+            if what == "everywhere" and "split_n" not in kw:
+                assert np.array_equal(got, gather), (kw, what)
+            mag = dense64(np.abs(x), np.abs(v))
+            excess = np.abs(got.astype(np.float64) - dense64(x, v)) - l.n * (2.0 ** -24 * mag + 2.0 ** -150)
+            assert excess.max() <= 0, (kw, what, np.unravel_index(excess.argmax(), excess.shape))
+    plan.destroy()
+    # small weights: a new plan does not start on the split form, and takes it when it is asked for
+    assert we > -50 or not _starts_split(l, data)
+
+
+def _starts_split(l, data):
+    plan = G.make_plan(l, data)
+    t = plan.get_tuning()
+    plan.destroy()
+    return t.variant == B.SC_VARIANT_SLAB and t.pipeline == 3
+
+
 def test_fp32_split_form_is_refused_where_it_does_not_apply():
     l = wl.Layer("splitno", 96, 12, 6, 6, N=2, sparsity=0.7, dtype="f32", seed=6)
     data = wl.prepare(l)
