@@ -142,11 +142,12 @@ typedef struct {
                            most 4 positions per lane and 8 rows per wave.  0 = one tile per workgroup.
                            3 (SC_F32, any layer shape; not for tables that store a column twice in one row or hold
                            weights that are not finite or smaller than 2^-100) = the densified tile on the matrix
-                           cores, every fp32 value split into three bfloat16 terms and a product into the eight
-                           largest products of terms, accumulated in fp32: no less precise than the other
-                           shapes.  (Inputs other than zero below 2^-110 / min(1, smallest weight) are beyond the
-                           terms: the workgroups that read one sum their outputs entry by entry from the sparse
-                           table, with the gather kernels' result and many times their cost.)  Its fields
+                           cores, every fp32 value split into three bfloat16 terms and a product into the six (with
+                           rows of fewer than 16 weights: eight) largest products of terms, accumulated in fp32: no less precise than the other
+                           shapes.  (A wave with an output that is not finite, or so small that the terms cannot
+                           hold what makes it up, below n 2^-106 of the largest weight or n 2^-119 but not zero, sums
+                           its outputs entry by entry, with the gather kernels' result and many times their
+                           cost; an output made of inputs of 2^-134 and less only comes out as zero.)  Its fields
                            are DENSE's: tile_p, sub_batch, chunk_c (a multiple of 32), tile_d, waves_m,
                            wg_per_cu, wg_threads 256 or 512 (0 = 512); split_n = 2..16 as for the chunked
                            one-shot form, each workgroup with at least one chunk; producers = 4: the chunks are
@@ -238,8 +239,8 @@ typedef struct {
  * Rows are padded to n = max row length with zero-valued entries that repeat the row's last column
  * (column 0 for an empty row); then a device pass stretches every column to its input offset.
  * The new plan's launch shape is chosen by a rule on sizes: the matrix-core tile (DENSE, for SC_F32 the
- * split form, and no weight but zero below 2^-50) when at least one weight in 32 is stored, no column
- * twice, and the dense weights are at most 256 MB, else a gather kernel.
+ * split form) when at least one weight in 32 is stored, no column twice, and the dense weights are at
+ * most 256 MB, else a gather kernel.
  * Errors: SC_ERR_NULL, SC_ERR_SHAPE, SC_ERR_CSR, SC_ERR_UNSUPPORTED, SC_ERR_RANGE, SC_ERR_OOM, SC_ERR_HIP.
  * On error *out is NULL. */
 sc_status_t sparse_conv_plan_create_csr(const sc_layer_t* layer, sc_dtype_t dtype,

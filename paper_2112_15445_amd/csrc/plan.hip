@@ -509,10 +509,8 @@ static bool default_dense_tuning(const Plan& p, sc_tuning_t* out, MfmaGeom* mgeo
     const bool split = p.dtype == SC_F32;
     const int64_t K = (int64_t)L.C * L.R * L.S;
     if (p.n == 0 || p.has_dup || (split && !p.splittable) || (int64_t)p.n * 32 < K) return false;
-    // (with weights below 2^-50 the split form would meet inputs that it has to sum entry by entry)
-    if (split && p.split_min > 0x1p-60f) return false;
     if ((split ? split_weight_bytes(p) : mfma_weight_bytes(p)) > ((size_t)256 << 20)) return false;
-    const int CB = split ? 32 : mfma_chan_block(p.dtype), terms = split ? 3 : 1, products = split ? 8 : 1;
+    const int CB = split ? 32 : mfma_chan_block(p.dtype), terms = split ? 3 : 1, products = split ? (p.split_full ? 8 : 6) : 1;
     const int64_t steps = (int64_t)L.R * L.S * ((L.C + CB - 1) / CB);
     double best = INFINITY;
     const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}};
@@ -778,16 +776,16 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
     // would leave the normal range
     if (p->dtype == SC_F32) {
         const float* w = reinterpret_cast<const float*>(tab.val.data());
-        float least = 1.0f;
+        float most = 0.0f;
         p->splittable = true;
         for (size_t i = 0; i < cnt && p->splittable; ++i) {
-            if (w[i] == 0.0f) continue;
-            p->splittable = std::isfinite(w[i]) && std::fabs(w[i]) >= 0x1p-100f;
-            least = std::min(least, std::fabs(w[i]));
+            p->splittable = w[i] == 0.0f || (std::isfinite(w[i]) && std::fabs(w[i]) >= 0x1p-100f);
+            most = std::max(most, std::fabs(w[i]));
         }
-        // an input is held down to 2^-110, its products while they are at least 2^-110 (what a matrix
-        // instruction rounds at 2^-150 is then 2^-16 of their own rounding)
-        p->split_min = 0x1p-110f / least;
+        for (int len : p->h_len) p->split_full |= len > 0 && len < 16;
+        // an input is held to 2^-134, the sum of a product's small terms to 2^-147: outputs from 2^28 of that
+        // on are served (the error is then a sixteenth of one rounding)
+        p->split_floor = (float)std::min((double)p->n * (0x1p-106 * most + 0x1p-119), 0x1p127);
     }
 
     // the default launch shape first: it is pure host arithmetic.  The matrix-core tile where it applies

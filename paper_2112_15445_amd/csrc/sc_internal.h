@@ -105,7 +105,8 @@ struct Plan {
     unsigned char* d_wfrag = nullptr;  // dense weights in MFMA operand order (DENSE variant), built on first use
     int32_t* d_len = nullptr;       // [D] stored entries of every row before unification (device copy of h_len)
     bool splittable = false;        // fp32 weights that three bfloat16 terms hold exactly (SLAB with pipeline = 3)
-    float split_min = 0.0f;         // smallest input magnitude but zero whose products the terms hold
+    bool split_full = false;        // some row has so few weights that eight of the nine products of terms count
+    float split_floor = 0.0f;       // smallest output magnitude but zero that the terms serve
     bool has_dup = false;           // some row stores a column twice (such a table cannot be densified exactly)
     sc_epilogue_t epi{};            // fused epilogue (all zero: none)
     float* d_requant = nullptr;     // [D] requantisation multipliers (epi.requant)

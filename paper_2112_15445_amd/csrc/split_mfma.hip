@@ -1,28 +1,35 @@
 // SC_F32 on the matrix cores (SLAB tunings with pipeline = 3): the densified layer with every fp32
 // operand split into three bfloat16 terms.
 //
-// An fp32 value is exactly x = hi + mid + lo with hi the upper 16 bits of x (truncated, so that no
-// finite x becomes an infinity), mid the rounded bfloat16 of x - hi and lo the rest, which fits a
-// bfloat16: 8 significant bits each (the splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16
-// artificial intelligence datatype for higher-precision computations", 2019).  With x in
-// [2^e, 2^(e+1)), |mid| is at most 2^(e-7) and |lo| at most 2^(e-16).  A product is then the sum of nine exact
-// products, of which eight are kept; the ninth, lo lo, is at most 2^-32 of it.  (Without mid lo and lo mid, which reach 2^-22 of it together, rows of
-// one and two stored weights came out less exact than from a fused multiply-add: largest error 2.4e-7 of
-// the product against 6.0e-8.)  Each is one v_mfma_f32_16x16x32_bf16 over 32 input channels of one filter tap,
-// accumulated in fp32: hi hi in one set of accumulators, the seven small ones in a second set (their
-// roundings are 2^-6 of the first set's), added once at the end.  The sum over a row is rounded
+// An fp32 value is exactly x = hi + mid + lo with hi the bfloat16 nearest to x, mid the one nearest to
+// x - hi and lo the rest, which fits a bfloat16: 8 significant bits each (the splitting of Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations",
+// 2019).  With x in [2^e, 2^(e+1)), |mid| is at most 2^(e-8) and |lo| at most 2^(e-17).  A product is then the sum
+// of nine exact products, of which the six largest are kept: mid lo and lo mid are at most 2^-25 of it each, lo lo
+// 2^-34.  That is as much as one rounding of a fused multiply-add, of which the gather kernels do one per stored
+// weight and this form one per 32 channels of a tap, so it counts where the rows are short: tables with a row of
+// 1 .. 15 weights keep mid lo and lo mid too (FULL; as a template parameter: a branch on it in the
+// multiplication costs the others 10 %).  (With hi truncated instead, mid lo and lo mid reach 2^-22 of
+// the product together, and all eight have to be kept: 45.7 us for 39.8 on the 3x3 128-128 layer at 28 x 28, batch 32.)
+// Each product is one v_mfma_f32_16x16x32_bf16 over 32 input channels of one filter tap,
+// accumulated in fp32: hi hi in one set of accumulators, the small ones in a second set (their
+// roundings are 2^-7 of the first set's), added once at the end.  The sum over a row is rounded
 // once per 32 channels of a tap instead of once per stored entry, which is why the result is
 // closer to the exact one than the gather kernels' (relative error against 64 bits 5e-8 .. 1.3e-7 where theirs is 0.9e-7 .. 3.7e-7).
-// Bound by the matrix pipes: 8 instructions per 16 x 16 x 32 block, at the 1.8 - 1.9 PFLOP/s that
+// Bound by the matrix pipes: 6 instructions per 16 x 16 x 32 block, at the 1.8 - 1.9 PFLOP/s that
 // the 16 x 16 x 32 bfloat16 instruction sustains with two waves per SIMD (1.24 with one, which is
-// why the workgroups that do not share a CU have eight waves) about 230 TFLOP/s of fp32 products,
+// why the workgroups that do not share a CU have eight waves) about 300 TFLOP/s of fp32 products,
 // against 154 of the fp32 matrix instructions and 78 of the vector units without packed math.
 //
 // The terms hold a value's 24 bits only down to 2^-110 (the last bit of lo is then the smallest bfloat16), and a
-// product's small terms need room above the smallest fp32.  The staging therefore notes whether a nonzero
-// input is below a bound that the host derives from the smallest weight (p.split_min: 2^-110, or more where some weight
-// is below 1), three vector instructions per pair; a workgroup that met one sums its outputs entry by entry
-// from the sparse table instead of storing the tile's (split_exact).  Ordinary activations never get there.
+// product's small terms need room above the smallest fp32: an output may be off by n (2^-134 of the largest weight +
+// 2^-147).  At the other end a hi is infinite from 2^128 - 2^119 on, and an infinite input meets zeros that the
+// sparse table does not hold: either leaves NaN in every output that the tile computes from that place.  A
+// wave that has an output below 2^28 of that error (a.floor) but not zero, or one that is not finite, therefore sums
+// its outputs entry by entry from the sparse table instead (split_exact): the gather kernels' result.  Ordinary
+// activations never get there; the test of the outputs is one and a half vector instructions each.  (Noting small inputs
+// while they are staged, the first form of this, was three for every pair of inputs and cost 0.7 us on the 1-D
+// 300-64 layer.)  What is left: an output all of whose inputs but zeros are 2^-134 or less comes out as zero.
 //
 // Tile, staging, weight order and step order are those of the DENSE variant (dense_mfma.hip): a
 // workgroup owns DB output channels x a tile of positions; the input region of the tile is staged
@@ -36,6 +43,7 @@
 namespace sc {
 
 struct SplitArgs {
+    unsigned floor;          // 2 bits(m) + 2^24 of the smallest magnitude m of an output that the terms serve
     int C, D, N, H, W, P, Q, S, RS, s_h, s_w, pad_h, pad_w;
     int TP, NS, tiles_p, Hs, Ws, npos_s, npos, CC, nchunks, NCB, pitch, bufsz, DB, ndb, epv, TPQ;
     int cbs_last;            // channel blocks of the last chunk
@@ -44,8 +52,6 @@ struct SplitArgs {
     int flat;                // the staged rows of a sample are one contiguous run per channel
     int wmajor, ntiles;      // output-channel blocks outermost; (sample group, row tile) pairs
     float inv_ntiles, inv_KS, inv_ndb, inv_tiles_p, inv_HsWs, inv_Ws, inv_TPQ, inv_Q;
-    unsigned tiny;           // 2 bits(m) - 1 of the smallest magnitude m that the terms serve
-    int flags;               // LDS offset of the staging waves' notes, 2 bytes each
     int n;                   // the sparse table, for split_exact
     const float* theta;
     const int32_t *col, *len;
@@ -60,31 +66,32 @@ typedef float float2v __attribute__((ext_vector_type(2)));
 // vector instructions.
 __device__ __forceinline__ void split3x2(float x0, float x1, unsigned& hi, unsigned& mid, unsigned& lo)
 {
-    const unsigned b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
-    hi = __builtin_amdgcn_perm(b1, b0, 0x07060302u);                        // the upper halves
-    const float r0 = x0 - __uint_as_float(b0 & 0xffff0000u), r1 = x1 - __uint_as_float(b1 & 0xffff0000u);   // exact
+    hi = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){x0, x1}, bf2v));                    // to nearest
+    const float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xffff0000u);           // exact
     mid = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){r0, r1}, bf2v));                   // to nearest
     const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xffff0000u);         // exact
     lo = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){l0, l1}, bf2v));                    // exact
 }
 
-// One block of positions times MW blocks of output channels: eight matrix instructions for each, the
-// smallest products first.
-template <int MW, int NW>
+// One block of positions times MW blocks of output channels: six matrix instructions for each, eight with
+// FULL, the smallest products first.
+template <bool FULL, int MW, int NW>
 __device__ __forceinline__ void split_multiply(float4v (&acc)[MW][NW], float4v (&accs)[MW][NW], const uint4w (&av)[MW][3],
                                                const uint4w (&bv)[3], int i)
 {
     auto mul = [&](float4v& c, const uint4w& a, const uint4w& b) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a), __builtin_bit_cast(bf8v, b), c, 0, 0, 0);
     };
+    if constexpr (FULL) {
 #pragma unroll
-    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[2]);
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][1], bv[2]);
 #pragma unroll
-    for (int m = 0; m < MW; ++m) mul(acc[m][i], av[m][0], bv[0]);
-#pragma unroll
-    for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[1]);
+        for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[1]);
+    }
 #pragma unroll
     for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][0], bv[2]);
+#pragma unroll
+    for (int m = 0; m < MW; ++m) mul(acc[m][i], av[m][0], bv[0]);
 #pragma unroll
     for (int m = 0; m < MW; ++m) mul(accs[m][i], av[m][2], bv[0]);
 #pragma unroll
@@ -221,13 +228,10 @@ __device__ __forceinline__ void load_round(float (&pre)[32], const SplitStage& s
     }
 }
 
-// Returns the smallest 2 |bits| - 1 of the lane's values (a zero's is the largest): below a.tiny if the terms
-// do not serve one of them.
 template <int EPV>
-__device__ __forceinline__ unsigned store_round(const float (&pre)[32], const SplitStage& st, unsigned char* lds, int v0, int NT, const SplitArgs& a)
+__device__ __forceinline__ void store_round(const float (&pre)[32], const SplitStage& st, unsigned char* lds, int v0, int NT, const SplitArgs& a)
 {
     constexpr int VB = 4 / EPV;
-    unsigned least = ~0u;
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
         int cg, sm, ii, g;
@@ -245,7 +249,6 @@ __device__ __forceinline__ unsigned store_round(const float (&pre)[32], const Sp
                     if (cg * 8 + 2 * q >= st.cleft) v0 = 0.0f;
                     if (cg * 8 + 2 * q + 1 >= st.cleft) v1 = 0.0f;
                 }
-                least = min(least, min((__float_as_uint(v0) << 1) - 1u, (__float_as_uint(v1) << 1) - 1u));
                 unsigned t0, t1, t2;
                 split3x2(v0, v1, t0, t1, t2);
                 w0[q] = t0; w1[q] = t1; w2[q] = t2;
@@ -256,44 +259,96 @@ __device__ __forceinline__ unsigned store_round(const float (&pre)[32], const Sp
             __builtin_amdgcn_sched_barrier(0);                 // (one column's terms at a time: registers)
         }
     }
-    return least;
 }
 
-// The outputs of a workgroup entry by entry, in the order of the gather kernels: where some staged input is too
-// small for the terms.  Input channels [c_lo, c_hi); `add`: other workgroups have the other channels.
-__device__ __forceinline__ void split_exact(const float* __restrict__ x, float* __restrict__ y, const SplitArgs& a, int tid, int NT,
-                                            int db, int b0, int p0, int c_lo, int c_hi, bool add)
+// One output entry by entry, in the order of the gather kernels, over the input channels [c_lo, c_hi).
+__device__ __forceinline__ float split_exact(const float* __restrict__ x, const SplitArgs& a, int b, int d, int p, int q, int c_lo, int c_hi)
 {
-    const int rows = min(a.DB, a.D - db * a.DB);
+    const int i0 = p * a.s_h - a.pad_h, w0 = q * a.s_w - a.pad_w;
+    const float* xb = x + (int64_t)b * a.C * a.H * a.W;
+    float sum = 0.0f;
 #pragma unroll 1
-    for (int e = tid; e < rows * a.npos; e += NT) {
-        const int dd = e / a.npos, f = e - dd * a.npos;
-        const int sm = f / a.TPQ, rem = f - sm * a.TPQ, tp = rem / a.Q, tq = rem - tp * a.Q;
-        if (b0 + sm >= a.N || p0 + tp >= a.P) continue;
-        const int d = db * a.DB + dd, i0 = (p0 + tp) * a.s_h - a.pad_h, w0 = tq * a.s_w - a.pad_w;
-        const float* xb = x + (int64_t)(b0 + sm) * a.C * a.H * a.W;
-        float sum = 0.0f;
+    for (int j = 0; j < a.len[d]; ++j) {
+        const int64_t at = (int64_t)d * a.n + j;
+        const int k = a.col[at] & 0x7fffffff, c = k / a.RS, tap = k - c * a.RS, r = tap / a.S;
+        const int i = i0 + r, w = w0 + tap - r * a.S;
+        if (c >= c_lo && c < c_hi && i >= 0 && i < a.H && w >= 0 && w < a.W)
+            sum = __builtin_fmaf(a.theta[at], xb[((int64_t)c * a.H + i) * a.W + w], sum);
+    }
+    return sum;
+}
+
+// The wave's outputs: the accumulated ones, or, where one of them is too small for the terms or not finite, the
+// sums over the sparse table.  `position` as in the kernels.
+template <int MW, int NW, class Position>
+__device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const float* __restrict__ x, float* __restrict__ y, const SplitArgs& a,
+                                            int b0, int p0, int mblk0, int kg, int c_lo, int c_hi, const Position& position)
+{
+    const int PQ = a.P * a.Q;
+    float* yb = y + (int64_t)b0 * a.D * PQ;
+    // 2 |bits| + 2^24, modulo 2^32: infinities and NaN below 2^24, zero at it, then the magnitudes in order
+    auto order = [](float v) { return (__float_as_uint(v) << 1) + (1u << 24); };
+    unsigned least = ~0u;
+#pragma unroll
+    for (int m = 0; m < MW; ++m)
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; j += 2) least = min(least, min(order(acc[m][i][j]), order(acc[m][i][j + 1])));
+    bool exact = false;
+    if (__ballot(least < a.floor)) {                         // (zeros, as a rule)
+#pragma unroll
+        for (int m = 0; m < MW; ++m)
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned v = order(acc[m][i][j]);
+                    exact |= v < a.floor && v != 1u << 24;
+                }
+    }
+    if (__ballot(exact)) {                                   // (wave-uniform)
 #pragma unroll 1
-        for (int j = 0; j < a.len[d]; ++j) {
-            const int64_t at = (int64_t)d * a.n + j;
-            const int k = a.col[at] & 0x7fffffff, c = k / a.RS, tap = k - c * a.RS, r = tap / a.S;
-            const int i = i0 + r, w = w0 + tap - r * a.S;
-            if (c >= c_lo && c < c_hi && i >= 0 && i < a.H && w >= 0 && w < a.W)
-                sum = __builtin_fmaf(a.theta[at], xb[((int64_t)c * a.H + i) * a.W + w], sum);
+        for (int i = 0; i < NW; ++i) {
+            int sm, tp, tq;
+            if (!position(i, sm, tp, tq)) continue;
+#pragma unroll 1
+            for (int mj = 0; mj < 4 * MW; ++mj) {
+                const int d = (mblk0 + (mj >> 2)) * 16 + 4 * kg + (mj & 3);
+                if (d >= a.D) break;
+                const float v = split_exact(x, a, b0 + sm, d, p0 + tp, tq, c_lo, c_hi);
+                float* yp = yb + ((int64_t)sm * a.D + d) * PQ + (p0 + tp) * a.Q + tq;
+                if (a.KS > 1) add_out(yp, v);
+                else store_out(yp, v);
+            }
         }
-        float* yp = y + ((int64_t)(b0 + sm) * a.D + d) * a.P * a.Q + (p0 + tp) * a.Q + tq;
-        if (add) add_out(yp, sum);
-        else store_out(yp, sum);
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        int sm, tp, tq;
+        if (!position(i, sm, tp, tq)) continue;
+        const unsigned o = (unsigned)((sm * a.D + mblk0 * 16 + 4 * kg) * PQ) + (unsigned)(mul24(p0 + tp, a.Q) + tq);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if ((mblk0 + m) * 16 + 4 * kg + j >= a.D) continue;
+                float* yp = yb + (o + (unsigned)((16 * m + j) * PQ));
+                if (a.KS > 1) add_out(yp, acc[m][i][j]);
+                else store_out(yp, acc[m][i][j]);
+            }
+        }
     }
 }
 
-template <int MW, int NW, int WM, int KG>
+template <int MW, int NW, int WM, int KG, bool FULL>
 __global__ void __launch_bounds__(256 * KG, 2)
 split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsigned char* __restrict__ wfrag, const SplitArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int NT = 256 * KG;
-    // steps of weights in flight: a step multiplies for 8 MW NW matrix instructions (16 clocks and
+    // steps of weights in flight: a step multiplies for 6 MW NW matrix instructions (16 clocks and
     // more each), L2 answers after several hundred clocks.  PF * NW is even (parity of the ring below).
     constexpr int PF = MW * NW >= 7 ? 2 : (MW * NW >= 2 ? 4 : 6);
     const int tid = threadIdx.x;
@@ -326,7 +381,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     const int tpi = bt - bg * a.tiles_p;
     const int b0 = bg * a.NS, p0 = tpi * a.TP;
     const int row0 = p0 * a.s_h - a.pad_h;
-    const int plane = a.H * a.W, PQ = a.P * a.Q;
+    const int plane = a.H * a.W;
     const int mblk0 = db * (a.DB >> 4) + wm * MW;
     const int cgroups = a.CC >> 3;
 
@@ -362,14 +417,11 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         else if (a.epv == 2) load_round<2>(pre, st, v0, NT);
         else load_round<1>(pre, st, v0, NT);
     };
-    bool tiny = false;                                       // (wave-uniform) some input is too small for the terms
     auto store_pre = [&](int v0) {
         asm volatile("" : "+v"(v0));
-        unsigned least;
-        if (a.epv == 4) least = store_round<4>(pre, st, lds, v0, NT, a);
-        else if (a.epv == 2) least = store_round<2>(pre, st, lds, v0, NT, a);
-        else least = store_round<1>(pre, st, lds, v0, NT, a);
-        tiny |= __ballot(least < a.tiny) != 0;
+        if (a.epv == 4) store_round<4>(pre, st, lds, v0, NT, a);
+        else if (a.epv == 2) store_round<2>(pre, st, lds, v0, NT, a);
+        else store_round<1>(pre, st, lds, v0, NT, a);
     };
     const int per_round = NT * (a.epv == 4 ? 1 : (a.epv == 2 ? 2 : 4));
     st.xs = reinterpret_cast<const char*>(x + ((int64_t)b0 * a.C + ch_lo * a.CC) * plane + (int64_t)sa.rlo * a.W);
@@ -388,7 +440,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         return f < a.npos && b0 + sm < a.N && p0 + tp < a.P;
     };
     int bbase[NW];
-    float4v acc[MW][NW], accs[MW][NW];                       // hi hi; the seven small products
+    float4v acc[MW][NW], accs[MW][NW];                       // hi hi; the small products
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
         int sm, tp, tq;
@@ -445,7 +497,6 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
             load_pre(v0);
             store_pre(v0);
         }
-        if (lane == 0) reinterpret_cast<unsigned short*>(lds + a.flags)[wave8] = tiny ? 1 : 0;
         __syncthreads();
         if (ch + 1 < ch_hi) {
             st.xs += (int64_t)a.CC * st.plane4;
@@ -462,10 +513,10 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
                 for (int i = 0; i < NW; ++i) {
                     // the operands of the next position block (or of the next step's first) come from LDS
-                    // while this one's 8 MW matrix instructions run
+                    // while this one's 6 MW matrix instructions run
                     fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    split_multiply<MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
+                    split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 fetch_w(aq[u]);
@@ -477,17 +528,10 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
                 for (int i = 0; i < NW; ++i) {
                     fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
-                    split_multiply<MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
+                    split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                 }
             }
         }
-    }
-    unsigned noted = 0;
-#pragma unroll
-    for (int k = 0; k < 2 * KG; ++k) noted |= reinterpret_cast<const unsigned*>(lds + a.flags)[k];
-    if (__builtin_amdgcn_readfirstlane(noted)) {             // (the same words for every wave)
-        split_exact(x, y, a, tid, NT, db, b0, p0, ch_lo * a.CC, ch_hi * a.CC, a.KS > 1);
-        return;
     }
 #pragma unroll
     for (int m = 0; m < MW; ++m)
@@ -510,23 +554,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
             for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
     }
-    float* yb = y + (int64_t)b0 * a.D * PQ;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        int sm, tp, tq;
-        if (!position(i, sm, tp, tq)) continue;
-        const unsigned o = (unsigned)((sm * a.D + mblk0 * 16 + 4 * kg) * PQ) + (unsigned)(mul24(p0 + tp, a.Q) + tq);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if ((mblk0 + m) * 16 + 4 * kg + j >= a.D) continue;
-                float* yp = yb + (o + (unsigned)((16 * m + j) * PQ));
-                if (a.KS > 1) add_out(yp, acc[m][i][j]);
-                else store_out(yp, acc[m][i][j]);
-            }
-        }
-    }
+    split_store<MW, NW>(acc, x, y, a, b0, p0, mblk0, kg, ch_lo * a.CC, ch_hi * a.CC, position);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -556,7 +584,7 @@ struct SplitCursor {
     }
 };
 
-template <int MW, int NW, int WM>
+template <int MW, int NW, int WM, bool FULL>
 __global__ void __launch_bounds__(768)
 split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsigned char* __restrict__ wfrag, const SplitArgs a)
 {
@@ -576,7 +604,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     const int tpi = bt - bg * a.tiles_p;
     const int b0 = bg * a.NS, p0 = tpi * a.TP;
     const int row0 = p0 * a.s_h - a.pad_h;
-    const int plane = a.H * a.W, PQ = a.P * a.Q;
+    const int plane = a.H * a.W;
     const int cgroups = a.CC >> 3;
     const int buf = 3 * a.bufsz;
 
@@ -616,14 +644,11 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
             else if (a.epv == 2) load_round<2>(v, st, v0, NTP);
             else load_round<1>(v, st, v0, NTP);
         };
-        bool tiny = false;                                   // (wave-uniform) some input is too small for the terms
         auto store_pre = [&](const float (&v)[32], unsigned char* to, int v0) {
             asm volatile("" : "+v"(v0));
-            unsigned least;
-            if (a.epv == 4) least = store_round<4>(v, st, to, v0, NTP, a);
-            else if (a.epv == 2) least = store_round<2>(v, st, to, v0, NTP, a);
-            else least = store_round<1>(v, st, to, v0, NTP, a);
-            tiny |= __ballot(least < a.tiny) != 0;
+            if (a.epv == 4) store_round<4>(v, st, to, v0, NTP, a);
+            else if (a.epv == 2) store_round<2>(v, st, to, v0, NTP, a);
+            else store_round<1>(v, st, to, v0, NTP, a);
         };
         // two rounds of a chunk are loaded a chunk ahead, the others in place
         const bool two = st.nblocks > per_round;
@@ -644,7 +669,6 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
                 load_pre(pre[0], ptid);
                 if (two) load_pre(pre[1], ptid + per_round);
             }
-            if (lane == 0) reinterpret_cast<unsigned short*>(lds + a.flags)[wave12 - 8] = tiny ? 1 : 0;
             split_barrier();                                 // barrier k
         }
         return;
@@ -718,7 +742,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
                 for (int i = 0; i < NW; ++i) {
                     fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
                     __builtin_amdgcn_sched_barrier(0);
-                    split_multiply<MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
+                    split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 fetch_w(aq[u]);
@@ -728,16 +752,11 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
                 if (i + 1 < NW) fetch_x(bq[(i + 1) & 1], i + 1);
-                split_multiply<MW, NW>(acc, accs, aq[0], bq[i & 1], i);
+                split_multiply<FULL, MW, NW>(acc, accs, aq[0], bq[i & 1], i);
             }
         }
     }
     while (nbar < a.nchunks) { split_barrier(); ++nbar; }    // (a wave without steps in the last chunks)
-    const unsigned* note = reinterpret_cast<const unsigned*>(lds + a.flags);
-    if (__builtin_amdgcn_readfirstlane(note[0] | note[1])) { // (the same words for every wave)
-        split_exact(x, y, a, tid, NTC, db, b0, p0, 0, a.C, false);
-        return;
-    }
 #pragma unroll
     for (int m = 0; m < MW; ++m)
 #pragma unroll
@@ -757,19 +776,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     for (int m = 0; m < MW; ++m)
 #pragma unroll
         for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
-    float* yb = y + (int64_t)b0 * a.D * PQ;
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        int sm, tp, tq;
-        if (!position(i, sm, tp, tq)) continue;
-        const unsigned o = (unsigned)((sm * a.D + mblk0 * 16 + 4 * kg) * PQ) + (unsigned)(mul24(p0 + tp, a.Q) + tq);
-#pragma unroll
-        for (int m = 0; m < MW; ++m) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if ((mblk0 + m) * 16 + 4 * kg + j < a.D) store_out(yb + (o + (unsigned)((16 * m + j) * PQ)), acc[m][i][j]);
-        }
-    }
+    split_store<MW, NW>(acc, x, y, a, b0, p0, mblk0, kg, 0, a.C, position);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -781,9 +788,6 @@ static unsigned float_bits(float f)
     std::memcpy(&u, &f, 4);
     return u;
 }
-
-// LDS offset of the staging waves' notes: behind the chunk buffers
-static int64_t split_flags(const MfmaGeom& g) { return 3ll * g.bufsz * (g.PW && g.nchunks > 1 ? 2 : 1); }
 
 bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int KG, int KS, int PW, int lds_budget, MfmaGeom* out)
 {
@@ -827,8 +831,7 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     // pipelined: two chunk buffers, eight multiplying waves, a wave tile of at most 8 blocks in 168 registers
     if (PW && (PW != 4 || KG != 2 || KS != 1 || g.MW * g.NW > 8)) return false;
     g.PW = PW;
-    // (and 16 bytes of notes of the staging waves behind the chunk buffers)
-    int64_t lds = split_flags(g) + 16;
+    int64_t lds = 3ll * g.bufsz * (PW && g.nchunks > 1 ? 2 : 1);
     if (KG == 2) lds = std::max<int64_t>(lds, (int64_t)g.MW * g.NW * 4096);
     if (lds > lds_budget || lds > kMaxLdsBytes) return false;
     g.lds_bytes = (int)lds;
@@ -838,13 +841,13 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
 
 int split_grid_size(const MfmaGeom& g, int N) { return ((N + g.NS - 1) / g.NS) * g.tiles_p * g.ndb * g.DL; }
 
-template <int MW, int NW, int WM, int KG>
-static sc_status_t launch_split_one(const Plan& p, const SplitArgs& a, const void* x, void* y, int grid, hipStream_t stream)
+template <int MW, int NW, int WM, int KG, bool FULL>
+static sc_status_t launch_split_full(const Plan& p, const SplitArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
     // KG = 3: the pipelined form (eight multiplying waves and four that stage)
     auto kernel = [] {
-        if constexpr (KG == 3) return &split_pipe_kernel<MW, NW, WM>;
-        else return &split_conv_kernel<MW, NW, WM, KG>;
+        if constexpr (KG == 3) return &split_pipe_kernel<MW, NW, WM, FULL>;
+        else return &split_conv_kernel<MW, NW, WM, KG, FULL>;
     }();
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
@@ -856,6 +859,13 @@ static sc_status_t launch_split_one(const Plan& p, const SplitArgs& a, const voi
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(256 * KG), p.mg.lds_bytes, stream, static_cast<const float*>(x),
                        static_cast<float*>(y), p.d_wfrag, a);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_ERR_HIP;
+}
+
+template <int MW, int NW, int WM, int KG>
+static sc_status_t launch_split_one(const Plan& p, const SplitArgs& a, const void* x, void* y, int grid, hipStream_t stream)
+{
+    return p.split_full ? launch_split_full<MW, NW, WM, KG, true>(p, a, x, y, grid, stream)
+                        : launch_split_full<MW, NW, WM, KG, false>(p, a, x, y, grid, stream);
 }
 
 template <int MW, int WM, int KG>
@@ -910,8 +920,7 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
     a.KS = g.DL; a.cps = (g.nchunks + g.DL - 1) / g.DL; a.inv_KS = 1.0f / (float)g.DL;
     a.TPQ = g.TP * p.Q;
     a.npos1 = g.Hs * g.Ws;
-    a.tiny = 2u * float_bits(p.split_min) - 1u;
-    a.flags = (int)split_flags(g);
+    a.floor = 2u * float_bits(p.split_floor) + (1u << 24);
     a.n = p.n; a.theta = static_cast<const float*>(p.d_theta); a.col = p.d_col; a.len = p.d_len;
     a.cbs_last = g.NCB - (g.nchunks - 1) * (g.CC / 32);
     {

@@ -1399,7 +1399,7 @@ def _split(plan, **kw):
 def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph, pw, N, scale):
     """SLAB tunings with pipeline = 3: tails of channels, rows, columns and output channels, several chunks,
     four and eight waves, several samples per workgroup, chunks dealt to several workgroups, large and
-    small magnitudes.  The eight kept products are within 2^-32 of the exact one and the sum is rounded
+    small magnitudes.  The six kept products are within 2^-24 of the exact one and the sum is rounded
     2 K / 32 times, so a result is held to 4e-7 of the sum of the magnitudes' root mean square -- and to
     no more error than the gather kernel's on the same table, times 1.2 for the draw."""
     l = wl.Layer(name, C, D, H, W, R, S, sh, sw, ph, pw, N=N, sparsity=0.6, dtype="f32", seed=sum(map(ord, name)))
@@ -1437,18 +1437,19 @@ def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph,
     plan.destroy()
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 4])
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 15, 16, 40])
 def test_fp32_split_form_element_by_element_on_short_rows(n):
-    """Rows of one to four stored weights, where no averaging hides what a product lost: every output against
-    64 bits, one-shot and pipelined, over random significands and the ones whose dropped terms are largest
-    (upper 16 bits far below the value, the next ones just below a carry).  Of a product only lo lo is dropped, at
-    most 2^-32 of it (mid is at most 2^-7 of the value and lo 2^-16); the accumulators are rounded once each per
-    matrix instruction, hi hi to 2^-24 of the sum so far at most once per entry, the small terms to 2^-24 of a
-    2^-6 part, and the two are added with one rounding: n + 1/4 roundings of half a unit (2^-24) in all."""
+    """Rows of few stored weights, where no averaging hides what a product lost: every output against
+    64 bits, one-shot and pipelined, over random significands and the ones whose mid lo is largest.  Up to 15 weights a
+    row only lo lo is dropped, at most 2^-34 of a product (mid is at most 2^-8 of the value and lo 2^-17), from
+    16 on mid lo and lo mid, 2^-24 of it together.  The accumulators are rounded once each per matrix
+    instruction, hi hi to 2^-24 of the sum so far, the small terms to 2^-24 of a 2^-7 part, and the two are added
+    with one rounding: for one weight 1 + 1/8 roundings of half a unit (2^-24) in all, for n the n + 1/8 that a sum of n
+    products may have, and no more than 4 of them where the products are summed inside the instruction."""
     C = n
     l = wl.Layer("short", C, 64, 24, 24, 1, 1, 1, 1, 0, 0, N=6, sparsity=0.0, dtype="f32", seed=n)
     rng = np.random.default_rng(n)
-    worst = np.array([0x3f80fe7f, 0x3f80ff80, 0x3f80ffff, 0x3f807f80, 0x3f80feff], np.uint32).view(np.float32)
+    worst = np.array([0x3f807fc0, 0x3f808040, 0x3f807ec0, 0x3f817fc0, 0x3f80feff], np.uint32).view(np.float32)
 
     def values(count):
         v = rng.uniform(1, 2, count).astype(np.float32)
@@ -1472,19 +1473,21 @@ def test_fp32_split_form_element_by_element_on_short_rows(n):
         _split(plan, **kw)
         print("case split short rows", n, plan.get_tuning().as_dict(), flush=True)
         e = error()
-        assert e.max() <= (n + 0.25) * 2.0 ** -24, (n, kw, e.max(), gather.max())
+        print("   largest", e.max(), "gather", gather.max(), flush=True)
+        assert e.max() <= min(n + 0.125, 4.0) * 2.0 ** -24, (n, kw, e.max(), gather.max())
         rms, rms_g = np.sqrt((e * e).mean()), np.sqrt((gather * gather).mean())
         assert rms <= 1.02 * rms_g, (n, kw, rms, rms_g)          # (2 %: the small terms' own roundings)
     plan.destroy()
 
 
 @pytest.mark.parametrize("C,D,H,W,k,stride,pad,N", [(70, 20, 9, 11, 3, 2, 1, 3), (64, 33, 7, 7, 1, 1, 0, 5), (40, 70, 12, 8, 3, 1, 1, 2)])
-@pytest.mark.parametrize("xe,we", [(-112, 0), (-122, 0), (-140, 0), (-60, -64), (-90, -30)])
-def test_fp32_split_form_sums_inputs_that_the_terms_do_not_hold_entry_by_entry(C, D, H, W, k, stride, pad, N, xe, we):
-    """Inputs so small that bfloat16 has no room for their last terms, or their products none in fp32: in every
-    workgroup (the gather kernel's sums, bit for bit), in one value of one sample only, and in the channels of one
-    of the workgroups that share a tile.  A sum of n products rounded n times is within n 2^-24 of the sum of the
-    magnitudes, n 2^-150 where it is denormal; the tile that holds the values rounds less often."""
+@pytest.mark.parametrize("xe,we", [(-112, 0), (-122, 0), (-140, 0), (-60, -64), (-90, -30), (-120, 60)])
+def test_fp32_split_form_sums_outputs_that_the_terms_do_not_serve_entry_by_entry(C, D, H, W, k, stride, pad, N, xe, we):
+    """Inputs so small that bfloat16 has no room for their last terms, or their products none in fp32: everywhere
+    (the gather kernel's sums, bit for bit; zero from inputs of 2^-134 and less), in one value of one sample only, and
+    in a few channels.  A sum of n products rounded n times is within n 2^-24 of the sum of the magnitudes, n
+    2^-150 where it is denormal; the tile that holds the values rounds less often and is off by 2^-28 of the smallest
+    output it keeps, n (2^-134 of the largest weight + 2^-147)."""
     l = wl.Layer("tiny", C, D, H, W, k, k, stride, stride, pad, pad, N=N, sparsity=0.6, dtype="f32", seed=C)
     data = wl.prepare(l)
     data["values"] = data["values"] * np.float32(2.0 ** we)
@@ -1512,20 +1515,39 @@ def test_fp32_split_form_sums_inputs_that_the_terms_do_not_hold_entry_by_entry(C
             print("case split tiny", C, D, xe, we, kw, what, flush=True)
             got = G.run_gpu(plan, x)
             if what == "everywhere" and "split_n" not in kw:
-                assert np.array_equal(got, gather), (kw, what)
+                assert np.array_equal(got, gather) or xe < -134 and not np.any(got), (kw, what)
             mag = dense64(np.abs(x), np.abs(v))
-            excess = np.abs(got.astype(np.float64) - dense64(x, v)) - l.n * (2.0 ** -24 * mag + 2.0 ** -150)
+            excess = np.abs(got.astype(np.float64) - dense64(x, v)) - l.n * (2.0 ** -24 * mag + 2.0 ** -134 * np.abs(v).max() + 2.0 ** -147)
             assert excess.max() <= 0, (kw, what, np.unravel_index(excess.argmax(), excess.shape))
     plan.destroy()
-    # small weights: a new plan does not start on the split form, and takes it when it is asked for
-    assert we > -50 or not _starts_split(l, data)
 
 
-def _starts_split(l, data):
-    plan = G.make_plan(l, data)
-    t = plan.get_tuning()
-    plan.destroy()
-    return t.variant == B.SC_VARIANT_SLAB and t.pipeline == 3
+@pytest.mark.parametrize("bad", [3.4e38, -np.inf, np.nan])
+def test_fp32_split_form_on_inputs_whose_first_term_is_infinite(bad):
+    """Inputs that round to an infinite bfloat16, infinities and NaN in one place: the gather kernel's result
+    where an output reads that place (the table has no fillers), the usual one elsewhere in the tile, and
+    weights that round to an infinite bfloat16 beside zeros and ordinary inputs."""
+    l = wl.Layer("huge", 48, 40, 9, 9, 3, 3, 1, 1, 1, 1, N=3, sparsity=0.7, dtype="f32", seed=3)
+    data = wl.prepare(l)
+    data["values"] = data["values"] * np.float32(1e-3)
+    x = data["x"].copy()
+    x[1, 7, 4, 5] = bad
+    x[2] = 0
+    huge = data["values"].copy()
+    huge[::50] = np.float32(3.4e38)
+    for values, inp in ((data["values"], x), (huge, np.nan_to_num(x, nan=0, neginf=0) * np.float32(1e-30))):
+        plan = B.Plan.create_csr(G.layer_desc(l), B.DTYPES["f32"], data["rowptr"], data["colidx"], values, None, None)
+        plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_GATHER, split_n=1)
+        want = G.run_gpu(plan, inp)
+        for kw in ({}, {"producers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2}, {"wg_threads": 256, "chunk_c": 32, "tile_p": 3}):
+            _split(plan, **kw)
+            print("case split huge", bad, kw, flush=True)
+            got = G.run_gpu(plan, inp)
+            fin = np.isfinite(want)
+            assert np.array_equal(got[~fin], want[~fin], equal_nan=True), kw
+            assert np.abs(got[fin].astype(np.float64) - want[fin]).max() <= 1e-5 * np.abs(want[fin]).max(), kw
+            assert not np.any(got[2]) and np.array_equal(np.isfinite(got), fin), kw
+        plan.destroy()
 
 
 def test_fp32_split_form_is_refused_where_it_does_not_apply():
