@@ -239,8 +239,12 @@ typedef struct {
  * Rows are padded to n = max row length with zero-valued entries that repeat the row's last column
  * (column 0 for an empty row); then a device pass stretches every column to its input offset.
  * The new plan's launch shape is chosen by a rule on sizes: the matrix-core tile (DENSE, for SC_F32 the
- * split form) when at least one weight in 32 is stored, no column twice, and the dense weights are at
- * most 256 MB, else a gather kernel.
+ * split form) for larger layers that are not very sparse (D >= 32; n >= 32; D n of at least 32768 for SC_F32, 8192
+ * with a codebook, else 16384; at least one weight in 12, with 8-bit activations and codebooks 24, in the unified rows; where
+ * the slab kernel does not fit also n >= 128 and one weight in 16; with twice these entries and n >= 128 one weight
+ * in 32 is enough; no column twice), else a gather kernel.  A plan
+ * on the matrix-core tile also holds its dense weights on the device: 1, 2 or (SC_F32) 6 bytes for each of
+ * the D C R S, rounded up to whole blocks, at most 256 MB by this rule.
  * Errors: SC_ERR_NULL, SC_ERR_SHAPE, SC_ERR_CSR, SC_ERR_UNSUPPORTED, SC_ERR_RANGE, SC_ERR_OOM, SC_ERR_HIP.
  * On error *out is NULL. */
 sc_status_t sparse_conv_plan_create_csr(const sc_layer_t* layer, sc_dtype_t dtype,

@@ -493,24 +493,40 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
 // ------------------------------------------------------------------------------------------------
 // The launch shape of a plan that nobody has tuned.
 //
-// The matrix-core tiles (DENSE; for fp32 the split form) need the same time at any sparsity, and
-// untuned they beat the untuned gather kernels on every layer tried down to a few stored weights in a
-// hundred (f16 3x3 256-256 at 14 x 14, batch 32, 80 %: 261 us on the slab default, 20 here; fp32 1x1
-// 2048-512 at 7 x 7, 80 %: 217 and 41).  They are taken when at least one weight in 32 is stored (below
-// that the dense image is mostly zeros and the gather kernels' work shrinks with the table) and the
-// dense weights are at most 256 MB.  The tile is the one with the least estimated time of a batch of
+// The matrix-core tiles (DENSE; for fp32 the split form) need the same time at any sparsity, while the
+// gather kernels' time grows with the entries of the unified table (fillers included: they are multiplied), D n,
+// and has little to do with K = C R S.  The tile is taken where it is faster at any batch, as measured on 7700 seeded
+// layers (1x1 to 7x7 and 1-D, 8 .. 2048 channels, planes of 2 .. 112, batches of 1 .. 128, 30 .. 96.5 %), both
+// sides untuned (profiles/default_launch_shape_of_untuned_plans.md):
+//   against the slab kernel   at least 32 output channels and 32 entries a row, a table of at least 32768 (fp32),
+//                             16384 (fp16, int8) or 8192 (codebook) entries, and at least 1 weight in 12
+//                             (fp32, fp16) or 24 (int8, codebook) stored, input channels counted in whole blocks: 1.0 - 400
+//                             times as fast, one layer in 150 slower (0.5 - 0.95); of the fp32 layers below these lines half lose
+//                             up to 5 times (1x1 64-256 at 56 x 56, batch 32, 90 %: 45 us for 26)
+//   against GATHER            (the slab does not fit, or there is an epilogue) also 128 entries a row and 1
+//                             weight in 16: GATHER spreads a single image over more workgroups
+//   large tables              of twice as many entries, 128 or more a row: from 1 weight in 32 on, against either
+//                             (1.1 - 9 times as fast; one layer in 60 slower, 0.79)
+// and the dense weights are at most 256 MB.  The tile is the one with the least estimated time of a batch of
 // 32: per workgroup the largest of its matrix instructions (22 clocks each with two waves on a SIMD,
 // 32 with one: measured), its weights and input through the vector L1 (64 bytes a clock) and its
 // operands from LDS (128 bytes a clock), plus a fixed 8000 clocks of start and drain.
 // ------------------------------------------------------------------------------------------------
-static bool default_dense_tuning(const Plan& p, sc_tuning_t* out, MfmaGeom* mgeom)
+static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t* out, MfmaGeom* mgeom)
 {
     const sc_layer_t& L = p.L;
     const bool split = p.dtype == SC_F32;
-    const int64_t K = (int64_t)L.C * L.R * L.S;
-    if (p.n == 0 || p.has_dup || (split && !p.splittable) || (int64_t)p.n * 32 < K) return false;
+    const int CB = split ? 32 : mfma_chan_block(p.dtype);
+    const int64_t K = (int64_t)((L.C + CB - 1) / CB * CB) * L.R * L.S, n = p.n;      // (the tile's: whole blocks of channels)
+    if (p.has_dup || (split && !p.splittable)) return false;
+    const int64_t entries = split ? 32768 : (is_codebook(p.dtype) ? 8192 : 16384);
+    if (L.D < 32 || n < 32 || L.D * n < entries || n * 32 < K) return false;
+    if (n < 128 || L.D * n < 2 * entries) {
+        if (n * (split || p.dtype == SC_F16 ? 12 : 24) < K) return false;
+        if (gather_variant == SC_VARIANT_GATHER && (n < 128 || n * 16 < K)) return false;
+    }
     if ((split ? split_weight_bytes(p) : mfma_weight_bytes(p)) > ((size_t)256 << 20)) return false;
-    const int CB = split ? 32 : mfma_chan_block(p.dtype), terms = split ? 3 : 1, products = split ? (p.split_full ? 8 : 6) : 1;
+    const int terms = split ? 3 : 1, products = split ? (p.split_full ? 8 : 6) : 1;
     const int64_t steps = (int64_t)L.R * L.S * ((L.C + CB - 1) / CB);
     double best = INFINITY;
     const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}};
@@ -802,7 +818,7 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
     if (st != SC_OK) return st;
     sc_tuning_t td{};
     MfmaGeom mgd{};
-    const bool dense = default_dense_tuning(*p, &td, &mgd);
+    const bool dense = default_dense_tuning(*p, t.variant, &td, &mgd);
 
     std::vector<uint8_t> packed;
     const uint8_t* theta_src = tab.val.data();

@@ -1586,12 +1586,21 @@ def test_fp32_split_form_is_refused_where_it_does_not_apply():
 
 
 @pytest.mark.parametrize("dtype", DT)
-@pytest.mark.parametrize("C,D,H,W,k,stride,pad,N", [(40, 24, 9, 9, 3, 1, 1, 3), (64, 48, 14, 14, 1, 1, 0, 2), (33, 70, 8, 5, 3, 2, 1, 5), (3, 16, 12, 12, 3, 1, 1, 1)])
-def test_default_launch_shape_of_a_new_plan(dtype, C, D, H, W, k, stride, pad, N):
-    """A plan nobody has tuned takes the matrix-core tile (fp32: the split form) when at least one weight in 32 is
-    stored and each column once, and a gather kernel otherwise; both give the oracle's result, also with the
-    fused epilogue's own default."""
-    for sparsity, dup in ((0.6, False), (0.995, False), (0.6, True)):
+@pytest.mark.parametrize("C,D,H,W,k,stride,pad,N,sparsity", [
+    (40, 24, 9, 9, 3, 1, 1, 3, 0.6),          # few output channels
+    (64, 130, 10, 10, 3, 1, 1, 2, 0.5),       # matrix-core tile for every type
+    (64, 130, 10, 10, 3, 1, 1, 2, 0.92),      # one weight in 12.5: not for fp32 and fp16
+    (64, 130, 10, 10, 3, 1, 1, 2, 0.96),      # one weight in 25
+    (384, 520, 3, 4, 3, 1, 1, 2, 0.96),       # the same in a large table
+    (100, 200, 7, 7, 1, 1, 0, 5, 0.5),        # 10000 entries: for the codebook types only
+    (33, 70, 8, 5, 3, 2, 1, 5, 0.9),          # rows of 30
+    (3, 16, 12, 12, 3, 1, 1, 1, 0.5),
+    (64, 48, 260, 260, 3, 1, 1, 1, 0.8)])     # rows of 115; the slab of such a plane does not fit for every type
+def test_default_launch_shape_of_a_new_plan(dtype, C, D, H, W, k, stride, pad, N, sparsity):
+    """A plan nobody has tuned takes the matrix-core tile (fp32: the split form) where its table is large and dense
+    enough for the type and each column is stored once, and a gather kernel otherwise; both give the oracle's
+    result."""
+    for dup in (False, True):
         l = wl.Layer("default", C, D, H, W, k, k, stride, stride, pad, pad, N=N, sparsity=sparsity, dtype=dtype, seed=C + D)
         data = wl.prepare(l, ragged=False)
         if dup:
@@ -1600,10 +1609,23 @@ def test_default_launch_shape_of_a_new_plan(dtype, C, D, H, W, k, stride, pad, N
         plan = G.make_plan(l, data)
         t = plan.get_tuning()
         matrix = t.variant == B.SC_VARIANT_DENSE or (t.variant == B.SC_VARIANT_SLAB and t.pipeline == 3)
-        assert matrix == (l.n * 32 >= l.K and not dup), t.as_dict()
+        entries, per = {"f32": (32768, 12), "f16": (16384, 12), "i8": (16384, 24)}.get(dtype, (8192, 24))
+        block = 64 if dtype in ("i8", "cb4") else 32
+        K = (C + block - 1) // block * block * k * k
+        takes = D >= 32 and l.n >= 32 and D * l.n >= entries and l.n * 32 >= K and not dup
+        large = l.n >= 128 and D * l.n >= 2 * entries
+        takes = takes and (large or l.n * per >= K)
+        got = G.run_gpu(plan, data["x"])
+        try:
+            plan.set_tuning(B.sc_tuning_t(), wg_threads=1024, wsrc=0 if dtype in ("cb4", "cb4h") else 1)
+        except B.SparseConvError:
+            plan.set_tuning(B.sc_tuning_t())
+        if plan.get_tuning().variant == B.SC_VARIANT_GATHER:     # the slab does not fit
+            takes = takes and (large or l.n >= 128 and l.n * 16 >= K)
+        assert matrix == takes, (t.as_dict(), l.n, K)
         assert not matrix or (t.pipeline == 3) == (dtype == "f32")
         print("case default", dtype, C, D, sparsity, dup, t.as_dict(), flush=True)
-        G.check(l, G.run_gpu(plan, data["x"]), G.oracle_out(l, data), f"default {t.as_dict()}")
+        G.check(l, got, G.oracle_out(l, data), f"default {t.as_dict()}")
         plan.destroy()
 
 
