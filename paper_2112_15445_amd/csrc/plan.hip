@@ -1083,7 +1083,10 @@ sc_status_t sparse_conv_plan_set_tuning(sparse_conv_plan_t* plan, const sc_tunin
     sc_status_t st = resolve_tuning(*p, *tuning, &t, &g, &mg);
     if (st != SC_OK) return st;
     st = install_tuning(p, t, g, mg, (hipStream_t)stream);
-    if (st == SC_OK) p->path = t.variant == SC_VARIANT_DENSE ? SC_PATH_DENSE : SC_PATH_SPARSE;
+    if (st == SC_OK) {
+        p->path = t.variant == SC_VARIANT_DENSE ? SC_PATH_DENSE : SC_PATH_SPARSE;
+        p->untuned = false;
+    }
     return st;
 }
 
@@ -1109,14 +1112,23 @@ sc_status_t sparse_conv_plan_set_epilogue(sparse_conv_plan_t* plan, const sc_epi
     p->Po = ep->pool ? p->P / 2 : p->P;
     p->Qo = ep->pool ? p->Q / 2 : p->Q;
     // the installed launch shape may not carry an epilogue (SLAB) or not this one (DENSE with an odd
-    // tile under pooling): re-resolve it, falling back to the GATHER default
+    // tile under pooling): re-resolve it, falling back to the tile that the default rule takes under this
+    // epilogue if nobody has chosen a shape, and to the GATHER default
+    const bool untuned = p->untuned;
     sc_status_t st = sparse_conv_plan_set_tuning(plan, &p->tuning, stream);
+    sc_tuning_t td{};
+    MfmaGeom mgd{};
+    if (st == SC_ERR_UNSUPPORTED && untuned && default_dense_tuning(*p, SC_VARIANT_GATHER, &td, &mgd)) {
+        st = sparse_conv_plan_set_tuning(plan, &td, stream);
+        if (st == SC_ERR_OOM) { (void)hipGetLastError(); st = SC_ERR_UNSUPPORTED; }
+    }
     if (st == SC_ERR_UNSUPPORTED) {
         sc_tuning_t g{};
         g.variant = SC_VARIANT_GATHER;
         g.split_n = 1;
         st = sparse_conv_plan_set_tuning(plan, &g, stream);
     }
+    p->untuned = untuned;
     if (st != SC_OK) {
         p->epi = old_epi; p->d_requant = old_rq; p->Po = old_Po; p->Qo = old_Qo;
         if (d_rq) (void)hipFree(d_rq);

@@ -107,6 +107,7 @@ struct Plan {
     bool splittable = false;        // fp32 weights that three bfloat16 terms hold exactly (SLAB with pipeline = 3)
     bool split_full = false;        // some row has so few weights that eight of the nine products of terms count
     float split_floor = 0.0f;       // smallest output magnitude but zero that the terms serve
+    bool untuned = true;            // nobody has chosen a launch shape yet
     bool has_dup = false;           // some row stores a column twice (such a table cannot be densified exactly)
     sc_epilogue_t epi{};            // fused epilogue (all zero: none)
     float* d_requant = nullptr;     // [D] requantisation multipliers (epi.requant)

@@ -1629,6 +1629,45 @@ def test_default_launch_shape_of_a_new_plan(dtype, C, D, H, W, k, stride, pad, N
         plan.destroy()
 
 
+@pytest.mark.parametrize("dtype,relu,pool,requant", [("f16", True, 2, False), ("i8", True, 2, True), ("cb4", False, 2, False), ("f16", True, 0, False), ("f32", True, 2, False)])
+@pytest.mark.parametrize("P", [7, 21, 28])
+def test_epilogue_on_a_plan_that_nobody_tuned(dtype, relu, pool, requant, P):
+    """Large tables (the default is the matrix-core tile) under each epilogue: the plan keeps a matrix-core tile,
+    another one where pooling rules its own out, and gives the oracle's result; fp32 goes to GATHER.  A shape that
+    was set by hand and is ruled out goes to GATHER."""
+    import oracle
+    import torch
+    l = wl.Layer("untuned", 96, 160, P, P, N=3, sparsity=0.75, dtype=dtype, seed=P)
+    data = wl.prepare(l)
+    acc = G.oracle_out(l, data)
+    rq = (np.linspace(40.0, 160.0, l.D) / max(1.0, float(np.abs(acc).max()))).astype(np.float32) if requant else None
+    want = oracle.epilogue(acc, relu=relu, pool=pool, requant_scale=rq)
+    xd = G.to_device(data["x"])
+    for by_hand in (False, True):
+        plan = G.make_plan(l, data)
+        matrix = plan.get_tuning().variant == B.SC_VARIANT_DENSE
+        assert matrix == (dtype != "f32")
+        if by_hand:
+            if dtype == "f32":
+                plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_SLAB, wsrc=1)
+            else:
+                plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, tile_p=3)
+        plan.set_epilogue(relu=relu, pool=pool, requant_scale=rq)
+        t = plan.get_tuning()
+        print("case untuned epilogue", dtype, relu, pool, requant, P, by_hand, t.as_dict(), flush=True)
+        assert t.variant == (B.SC_VARIANT_DENSE if matrix and not (by_hand and pool) else B.SC_VARIANT_GATHER)
+        y = torch.empty(want.shape, dtype=torch.int8 if requant else B.torch_out_dtype(plan.dtype), device="cuda")
+        ws = torch.empty(max(plan.workspace_size(l.N), 16), dtype=torch.uint8, device="cuda")
+        plan.forward(xd.data_ptr(), y.data_ptr(), l.N, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = G.to_host(y)
+        if requant:
+            assert np.array_equal(got, want)
+        else:
+            G.check(l, got, want, f"untuned epilogue {t.as_dict()}")
+        plan.destroy()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "i8"])
 def test_matrix_core_tiles_run_a_batch_of_more_workgroups_than_one_launch_holds_in_slices(dtype):
     """A launch decodes at most 2^19 - 1 workgroups; 2^19 + 3 samples of one workgroup each take two."""
