@@ -165,6 +165,9 @@ def make_layer(C, D, H, W, R, S, stride=(1, 1), pad=(0, 0)) -> sc_layer_t:
     return sc_layer_t(C, D, H, W, R, S, stride[0], stride[1], pad[0], pad[1])
 
 
+_ADDRESS = (int, type(None))
+
+
 class Plan:
     """Owner of one sparse_conv_plan_t.  Same calls as the C ABI, same names."""
 
@@ -286,8 +289,11 @@ class Plan:
     # -- execution (raw device pointers) --------------------------------------------------------
     def forward(self, x_ptr: int, y_ptr: int, N: int, ws_ptr: int = 0, ws_bytes: int = 0,
                 stream: int = 0):
-        # (plain integers: the declared argument types convert them.  Wrapping the four pointers took as
-        # long as the rest of the call, which on the smallest layers is longer than the kernel)
+        # (plain integers: the declared argument types convert them, which is quicker than four pointer
+        # objects -- but they would also take the address of a bytes or str object)
+        if not (isinstance(x_ptr, _ADDRESS) and isinstance(y_ptr, _ADDRESS) and isinstance(ws_ptr, _ADDRESS) and
+                isinstance(stream, _ADDRESS)):
+            raise TypeError("device pointers and the stream are integers (or None)")
         st = lib().sparse_conv_forward(self._h, x_ptr, y_ptr, N, ws_ptr, ws_bytes, stream)
         if st:
             raise SparseConvError(st, "sparse_conv_forward")

@@ -146,3 +146,18 @@ def test_pow2_quantiser_helper_matches_the_oracle_bit_for_bit():
     assert L.sparse_conv_quantize_pow2(p(one), 1, 8, 0.0, p(out), ctypes.byref(fb)) == 4
     bad = np.array([np.inf], np.float32)
     assert L.sparse_conv_quantize_pow2(p(bad), 1, 8, 1.0, p(out), ctypes.byref(fb)) == 5
+
+
+@pytest.mark.parametrize("bad", [b"0123456789abcdef", "text", 1.5, np.zeros(4, np.float32), ctypes.c_int64(0)])
+@pytest.mark.parametrize("where", ["x_ptr", "y_ptr", "ws_ptr", "stream"])
+def test_forward_takes_integers_for_its_pointers(bad, where):
+    """Anything else is a TypeError before the library is called (bytes and str would pass as their address)."""
+    plan = B.Plan(0, B.make_layer(1, 1, 4, 4, 1, 1, (1, 1), (0, 0)), B.SC_F32)
+    args = {"x_ptr": 0, "y_ptr": 0, "N": 1, "ws_ptr": 0, "stream": 0}
+    with pytest.raises(B.SparseConvError):                   # (the null plan is refused by the library)
+        plan.forward(**args)
+    with pytest.raises(B.SparseConvError):
+        plan.forward(**{**args, where: None})
+    args[where] = bad
+    with pytest.raises(TypeError):
+        plan.forward(**args)
