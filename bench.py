@@ -233,7 +233,7 @@ def run_layer(l, steps, warmup, autotune, torch, G, B, wl, with_dense=True, tuni
         "hbm_frac": alg_bytes / (ev_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "tuning": inf.tuning.as_dict(), "lds_bytes": inf.lds_bytes, "ring": len(xs),
         "ring_bytes": ring_bytes, "dispatch": dispatch,
-        "path": dispatch["choice"] if dispatch else ("dense" if inf.tuning.variant == B.SC_VARIANT_DENSE else "sparse"),
+        "path": dispatch["choice"] if dispatch else ("dense" if _densified(inf.tuning.as_dict()) else "sparse"),
     }
     if ev_ms < 0.010:
         # launch-limited: back-to-back launches from the host cannot keep up with kernels this short
@@ -406,10 +406,19 @@ def main():
         sys.exit(1)
 
 
+def _densified(t):
+    """The launch shape multiplies the dense image on the matrix cores (fp32: the split form)."""
+    return t.get("variant") == 3 or (t.get("variant") == 2 and t.get("pipeline") == 3)
+
+
 def short_shape(t):
     """One-line name of a launch shape."""
     if t.get("variant") == 1:
         return f"gather sb{t.get('sub_batch', 0)} split{t.get('split_n', 1)}"
+    if _densified(t) and t["variant"] == 2:
+        return (f"mfma bf16x3 tp{t.get('tile_p', 0)} ns{t.get('sub_batch', 1)} cc{t.get('chunk_c', 0)} td{t.get('tile_d', 0)} "
+                f"wm{t.get('waves_m', 0)} wpc{t.get('wg_per_cu', 1)} thr{t.get('wg_threads')}"
+                + (f" np{t['producers']}" if t.get("producers") else "") + (f" ks{t['split_n']}" if t.get("split_n") else ""))
     if t.get("variant") == 3:
         return (f"mfma tp{t.get('tile_p', 0)} ns{t.get('sub_batch', 1)} cc{t.get('chunk_c', 0)} td{t.get('tile_d', 0)} "
                 f"wm{t.get('waves_m', 0)} wpc{t.get('wg_per_cu', 1)}" + (f" thr{t['wg_threads']}" if t.get("wg_threads", 256) > 256 else "")
@@ -501,7 +510,8 @@ def report_table(rows):
             out.append(f"# {r['layer']} ({r['dtype']}): {r['ms_events']*1e3:.2f} us between events, "
                        f"{r['graph_ms']*1e3:.2f} us per launch inside a captured HIP graph (launch-limited)")
     # rows that run on the matrix cores: their bound is "mfma" -- dense flops (the tile multiplies every
-    # weight, stored or not) against 2.5 PFLOP/s (fp16) / 5.0 POP/s (int8)
+    # weight, stored or not) against 2.5 PFLOP/s (fp16) / 5.0 POP/s (int8); fp32: six bf16 products each (eight with
+    # rows of fewer than 16 weights) against 2.5 PFLOP/s
     from paper_2112_15445_amd import workloads as _wl
     layers = {(l.name, l.dtype): l for c in _wl.CONFIGS for l in _wl.CONFIGS[c]()}
 
@@ -511,6 +521,8 @@ def report_table(rows):
             return None
         flops = 2.0 * l.N * l.D * l.P * l.Q * l.C * l.R * l.S
         peak = 5.0e15 if r["dtype"] in ("i8", "cb4") else 2.5e15
+        if r["dtype"] == "f32":
+            flops *= 6 if r["n"] >= 16 else 8
         return flops / (r["ms_events"] * 1e-3) / peak
     out.append("cfg layer                      dtype    n  choice   timed_us  alg_GB/s hbm_frac useful_TF mfma_frac | gather_us   mfma_us lib_us(warm) | "
                "torch_cold torch_warm | parity | launch shape of the choice")

@@ -378,7 +378,8 @@ sc_status_t sparse_conv_plan_set_epilogue(sparse_conv_plan_t* plan, const sc_epi
 /* Which implementation sparse_conv_forward runs for a plan. */
 enum {
     SC_PATH_SPARSE = 0,   /* the gather kernels (SC_VARIANT_GATHER / SC_VARIANT_SLAB) */
-    SC_PATH_DENSE = 1,    /* the library's densified tile on the matrix cores (SC_VARIANT_DENSE) */
+    SC_PATH_DENSE = 1,    /* the library's densified tile on the matrix cores (SC_VARIANT_DENSE; SC_F32: SLAB
+                             with pipeline = 3) */
     SC_PATH_LIBRARY = 2   /* the dense library's convolution (MIOpen, looked up at run time) */
 };
 
@@ -396,8 +397,8 @@ typedef struct {
 
 /* Per-layer dispatch: steps 3 and 4 of the paper's "Main scheme" -- compare the layer's time in the
  * sparse kernel with the dense convolution's, then configure the network layer by layer.  Tunes the
- * gather kernels and (16- / 8-bit activations) the densified MFMA tile like
- * sparse_conv_plan_autotune, each over the cold ring, sets up the dense library's convolution of
+ * gather kernels and the densified MFMA tile like sparse_conv_plan_autotune, each over the cold
+ * ring, sets up the dense library's convolution of
  * the same layer from the plan's weights (fp32 / fp16 layers, when a MIOpen is in the process or
  * can be loaded; NCHW buffers, whatever layout changes the library makes are inside its time) and
  * times it on the caller's buffers, records all three in *out and installs the fastest (the

@@ -665,6 +665,9 @@ static void free_device(Plan* p)
     p->d_codebook = nullptr;
 }
 
+// the shapes that multiply the dense image on the matrix cores: DENSE, for SC_F32 the split form
+static bool is_densified(const sc_tuning_t& t) { return t.variant == SC_VARIANT_DENSE || is_split(t); }
+
 static sc_status_t hip_status(hipError_t e)
 {
     if (e == hipSuccess) return SC_OK;
@@ -675,7 +678,7 @@ static sc_status_t hip_status(hipError_t e)
 // succeeded: on any error the plan keeps its previous tuning, geometry and tables untouched.
 static sc_status_t install_tuning(Plan* p, const sc_tuning_t& t, const SlabGeom& g, const MfmaGeom& mg, hipStream_t stream)
 {
-    if ((t.variant == SC_VARIANT_DENSE || is_split(t)) && !p->d_wfrag) {
+    if (is_densified(t) && !p->d_wfrag) {
         // dense weights in MFMA operand order: built on first use, the same for every tile shape
         // (fp32 plans: three bfloat16 terms per weight; such a plan never runs DENSE)
         hipError_t e;
@@ -871,7 +874,7 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
     p->dispatch.choice = -1;
     if (dense) {
         st = install_tuning(p, td, SlabGeom{}, mgd, stream);
-        if (st == SC_OK) p->path = td.variant == SC_VARIANT_DENSE ? SC_PATH_DENSE : SC_PATH_SPARSE;
+        if (st == SC_OK) p->path = SC_PATH_DENSE;
         if (st != SC_ERR_OOM) return st;
         (void)hipGetLastError();       // (no room for the dense weights: the sparse table alone)
     }
@@ -1084,7 +1087,7 @@ sc_status_t sparse_conv_plan_set_tuning(sparse_conv_plan_t* plan, const sc_tunin
     if (st != SC_OK) return st;
     st = install_tuning(p, t, g, mg, (hipStream_t)stream);
     if (st == SC_OK) {
-        p->path = t.variant == SC_VARIANT_DENSE ? SC_PATH_DENSE : SC_PATH_SPARSE;
+        p->path = is_densified(t) ? SC_PATH_DENSE : SC_PATH_SPARSE;
         p->untuned = false;
     }
     return st;
@@ -1644,7 +1647,7 @@ sc_status_t sparse_conv_autotune_workspace_size(const sparse_conv_plan_t* plan, 
 }
 
 // The launch-shape search over the candidates whose kind is in `kinds` (bit 0: the gather kernels,
-// SC_VARIANT_GATHER and SC_VARIANT_SLAB; bit 1: the densified tile, SC_VARIANT_DENSE).  Installs
+// SC_VARIANT_GATHER and SC_VARIANT_SLAB; bit 1: the densified tile, SC_VARIANT_DENSE or the split form).  Installs
 // the winner; *best_ms receives its time per launch in the second (cold) round.
 static sc_status_t autotune_impl(sparse_conv_plan_t* plan, const void* x_dev, void* y_dev, int32_t N, void* workspace_dev,
                                  size_t workspace_bytes, void* stream, int kinds, float* best_ms)
@@ -1656,7 +1659,7 @@ static sc_status_t autotune_impl(sparse_conv_plan_t* plan, const void* x_dev, vo
     std::vector<sc_tuning_t> cands;
     build_candidates(*p, &cands);
     cands.erase(std::remove_if(cands.begin(), cands.end(), [&](const sc_tuning_t& c) {
-                    return !(kinds & (c.variant == SC_VARIANT_DENSE ? 2 : 1));
+                    return !(kinds & (is_densified(c) ? 2 : 1));
                 }), cands.end());
     if (cands.empty()) return SC_ERR_UNSUPPORTED;
     const size_t gather_ws = gather_workspace_bytes(*p, N);
@@ -1832,7 +1835,7 @@ sc_status_t sparse_conv_plan_dispatch(sparse_conv_plan_t* plan, const void* x_de
     sc_status_t st = autotune_impl(plan, x_dev, y_dev, N, workspace_dev, workspace_bytes, stream, 1, &r.sparse_ms);
     if (st != SC_OK) return st;
     r.sparse_tuning = p->tuning;
-    // leg 2: the densified tile on the matrix cores, tuned (16- and 8-bit activations)
+    // leg 2: the densified tile on the matrix cores, tuned
     st = autotune_impl(plan, x_dev, y_dev, N, workspace_dev, workspace_bytes, stream, 2, &r.dense_ms);
     if (st == SC_OK) r.dense_tuning = p->tuning;
     else if (st == SC_ERR_UNSUPPORTED) r.dense_ms = -1.0f;

@@ -912,8 +912,11 @@ def test_per_layer_dispatch_records_three_contenders_and_forward_honours_the_cho
     st = torch.cuda.current_stream().cuda_stream
     rec = plan.dispatch(xd.data_ptr(), y.data_ptr(), l.N, ws.data_ptr(), ws.numel(), st)
     print("dispatch", dtype, rec.as_dict(), flush=True)
-    assert rec.sparse_ms > 0
-    assert (rec.dense_ms > 0) == (dtype != "f32")
+    assert rec.sparse_ms > 0 and rec.dense_ms > 0
+    # (the two contenders are what their names say: for fp32 the densified tile is the split form)
+    assert rec.sparse_tuning.variant != B.SC_VARIANT_DENSE and not _is_split(rec.sparse_tuning)
+    assert rec.dense_tuning.variant == B.SC_VARIANT_DENSE or _is_split(rec.dense_tuning)
+    assert _is_split(rec.dense_tuning) == (dtype == "f32")
     if dtype == "i8":
         assert rec.library_ms < 0                            # the dense library is used for floating point only
     times = {B.SC_PATH_SPARSE: rec.sparse_ms}
@@ -1381,6 +1384,10 @@ def test_natural_layout_candidates_on_seeded_random_pointwise_layers():
             ran += 1
         plan.destroy()
     assert ran >= 150, ran
+
+
+def _is_split(t):
+    return t.variant == B.SC_VARIANT_SLAB and t.pipeline == 3
 
 
 def _split(plan, **kw):
