@@ -337,6 +337,9 @@ sc_status_t sparse_conv_forward_static(const sparse_conv_plan_t* plan, const voi
  *                   the caller's buffers.
  * Candidates that these pointers rule out (see sparse_conv_forward) are skipped, so the installed
  * shape is valid for buffers aligned like x_dev and y_dev.
+ * Shapes on the dense weights (DENSE, SLAB with pipeline = 3) are left out when there is no device
+ * memory for those; the dense weights that the search itself made are freed unless such a shape wins.
+ * The search tries up to a few thousand shapes and takes seconds (see sparse_conv_plan_num_candidates).
  * On any error the tuning the plan had on entry is installed again before the call returns.
  * On layers with fewer tiles than compute units the winner can be a shape that sums the partial
  * results of several workgroups with atomic adds (SLAB with split_n > 1, see sc_tuning_t): an SC_F32

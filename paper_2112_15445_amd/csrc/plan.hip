@@ -1665,6 +1665,7 @@ static sc_status_t autotune_impl(sparse_conv_plan_t* plan, const void* x_dev, vo
     const size_t gather_ws = gather_workspace_bytes(*p, N);
     if (workspace_bytes < gather_ws || (gather_ws && !workspace_dev)) return SC_ERR_WORKSPACE;
     const sc_tuning_t entry = p->tuning;          // re-installed if the search fails
+    const bool had_dense = p->d_wfrag != nullptr; // (else the dense weights are given back if no shape on them wins)
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return SC_ERR_HIP;
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return SC_ERR_HIP; }
@@ -1684,6 +1685,8 @@ static sc_status_t autotune_impl(sparse_conv_plan_t* plan, const void* x_dev, vo
     for (size_t i = 0; i < cands.size() && st == SC_OK; ++i) {
         st = sparse_conv_plan_set_tuning(plan, &cands[i], stream);
         if (st == SC_ERR_UNSUPPORTED) { st = SC_OK; continue; }
+        // (no room for the dense weights: the shapes on them are no candidates)
+        if (st == SC_ERR_OOM && is_densified(cands[i]) && !p->d_wfrag) { (void)hipGetLastError(); st = SC_OK; continue; }
         if (st != SC_OK) break;
         // one warm-up launch, then enough repeats for a stable mean
         st = sparse_conv_forward(plan, x_dev, y_dev, N, workspace_dev, workspace_bytes, stream);
@@ -1807,8 +1810,13 @@ static sc_status_t autotune_impl(sparse_conv_plan_t* plan, const void* x_dev, vo
         // leave the plan as it was found
         (void)hipStreamSynchronize(s);
         (void)sparse_conv_plan_set_tuning(plan, &entry, stream);
-        return st;
     }
+    if (!had_dense && p->d_wfrag && !is_densified(p->tuning)) {
+        (void)hipStreamSynchronize(s);
+        (void)hipFree(p->d_wfrag);
+        p->d_wfrag = nullptr;
+    }
+    if (st != SC_OK) return st;
     p->last_N = N;
     if (best_ms) *best_ms = best;
     return SC_OK;

@@ -1557,6 +1557,29 @@ def test_fp32_split_form_on_inputs_whose_first_term_is_infinite(bad):
         plan.destroy()
 
 
+def test_autotune_gives_the_dense_weights_back_when_a_gather_kernel_wins():
+    """A very sparse fp32 layer: the search tries the split form, for which it makes 32 MB of dense weights, installs
+    a gather kernel and leaves none of them behind; a shape on the dense weights works afterwards."""
+    import torch
+    l = wl.Layer("verysparse", 2304, 2304, 5, 5, 1, 1, 1, 1, 0, 0, N=1, sparsity=0.998, dtype="f32", seed=7)
+    data = wl.prepare(l)
+    plan = G.make_plan(l, data)
+    xd = G.to_device(data["x"])
+    y = torch.empty((l.N, l.D, l.P, l.Q), device="cuda")
+    ws = torch.empty(plan.autotune_workspace_size(l.N), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    plan.autotune(xd.data_ptr(), y.data_ptr(), l.N, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    after = torch.cuda.mem_get_info()[0]
+    assert not _is_split(plan.get_tuning()), plan.get_tuning().as_dict()
+    assert before - after < 16 << 20, (before, after)
+    G.check(l, G.run_gpu(plan, data["x"]), G.oracle_out(l, data), "after the search")
+    _split(plan)
+    G.check(l, G.run_gpu(plan, data["x"]), G.oracle_out(l, data), "split form after the search")
+    plan.destroy()
+
+
 def test_fp32_split_form_is_refused_where_it_does_not_apply():
     l = wl.Layer("splitno", 96, 12, 6, 6, N=2, sparsity=0.7, dtype="f32", seed=6)
     data = wl.prepare(l)
