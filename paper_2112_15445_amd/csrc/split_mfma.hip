@@ -15,7 +15,7 @@
 // accumulated in fp32: hi hi in one set of accumulators, the small ones in a second set (their
 // roundings are 2^-7 of the first set's), added once at the end.  The sum over a row is rounded
 // once per 32 channels of a tap instead of once per stored entry, which is why the result is
-// closer to the exact one than the gather kernels' (relative error against 64 bits 5e-8 .. 1.3e-7 where theirs is 0.9e-7 .. 3.7e-7).
+// closer to the exact one than the gather kernels' (relative error against 64 bits 5e-8 .. 1e-7 where theirs is 0.9e-7 .. 3.7e-7).
 // Bound by the matrix pipes: 6 instructions per 16 x 16 x 32 block, at the 1.8 - 1.9 PFLOP/s that
 // the 16 x 16 x 32 bfloat16 instruction sustains with two waves per SIMD (1.24 with one, which is
 // why the workgroups that do not share a CU have eight waves) about 300 TFLOP/s of fp32 products,
@@ -694,7 +694,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         for (int m = 0; m < MW; ++m)
 #pragma unroll
             for (int t = 0; t < 3; ++t) av[m][t] = *reinterpret_cast<const uint4w*>(wu + m * wrow + t * 1024);
-        if (wk < last) { wc.advance(a); if (wk + 1 <= last) wc.advance(a); ++wk; }
+        if (wk < last) { wc.advance(a); wc.advance(a); ++wk; }
     };
     if (nsteps > 0) {
 #pragma unroll
@@ -812,7 +812,8 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     g.NCB = (L.C + 31) / 32;
     g.CC = std::min(CC, g.NCB * 32);
     g.nchunks = (g.NCB * 32 + g.CC - 1) / g.CC;
-    g.pitch = g.CC * 2 + 16;                      // odd in units of 16 bytes: conflict-free operand reads
+    g.pitch = g.CC * 2 + 16;                      // odd in units of 16 bytes (the counters still show bank conflicts, 6 clocks for
+                                                  // each LDS instruction; 32, 48 or 80 instead of 16 take the same time)
     g.DB = DB;
     g.ndb = (L.D + DB - 1) / DB;
     g.WM = WM;
