@@ -145,7 +145,7 @@ typedef struct {
                            cores, every fp32 value split into three bfloat16 terms and a product into the six (with
                            rows of fewer than 16 weights: eight) largest products of terms, accumulated in fp32: no less precise than the other
                            shapes.  (A wave with an output that is not finite, or so small that the terms cannot
-                           hold what makes it up, below n 2^-106 of the largest weight or n 2^-119 but not zero, sums
+                           hold what makes it up, below n 2^-105 of the largest weight or n 2^-119 but not zero, sums
                            its outputs entry by entry, with the gather kernels' result and many times their
                            cost; an output made of inputs of 2^-134 and less only comes out as zero.)  Its fields
                            are DENSE's: tile_p, sub_batch, chunk_c (a multiple of 32), tile_d, waves_m,

@@ -802,9 +802,9 @@ static sc_status_t finish_create(Plan* p, HostTable& tab, const float* scales, c
             most = std::max(most, std::fabs(w[i]));
         }
         for (int len : p->h_len) p->split_full |= len > 0 && len < 16;
-        // an input is held to 2^-134, the sum of a product's small terms to 2^-147: outputs from 2^28 of that
+        // an input is held to 2^-133, the sum of a product's small terms to 2^-147: outputs from 2^28 of that
         // on are served (the error is then a sixteenth of one rounding)
-        p->split_floor = (float)std::min((double)p->n * (0x1p-106 * most + 0x1p-119), 0x1p127);
+        p->split_floor = (float)std::min((double)p->n * (0x1p-105 * most + 0x1p-119), 0x1p127);
     }
 
     // the default launch shape first: it is pure host arithmetic.  The matrix-core tile where it applies

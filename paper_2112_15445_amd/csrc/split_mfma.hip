@@ -22,7 +22,7 @@
 // against 154 of the fp32 matrix instructions and 78 of the vector units without packed math.
 //
 // The terms hold a value's 24 bits only down to 2^-110 (the last bit of lo is then the smallest bfloat16), and a
-// product's small terms need room above the smallest fp32: an output may be off by n (2^-134 of the largest weight +
+// product's small terms need room above the smallest fp32: an output may be off by n (2^-133 of the largest weight +
 // 2^-147).  At the other end a hi is infinite from 2^128 - 2^119 on, and an infinite input meets zeros that the
 // sparse table does not hold: either leaves NaN in every output that the tile computes from that place.  A
 // wave that has an output below 2^28 of that error (a.floor) but not zero, or one that is not finite, therefore sums
@@ -70,7 +70,7 @@ __device__ __forceinline__ void split3x2(float x0, float x1, unsigned& hi, unsig
     const float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xffff0000u);           // exact
     mid = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){r0, r1}, bf2v));                   // to nearest
     const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xffff0000u);         // exact
-    lo = __builtin_bit_cast(unsigned, __builtin_convertvector((float2v){l0, l1}, bf2v));                    // exact
+    lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);                      // exact: the upper halves
 }
 
 // One block of positions times MW blocks of output channels: six matrix instructions for each, eight with

@@ -1498,7 +1498,7 @@ def test_fp32_split_form_sums_outputs_that_the_terms_do_not_serve_entry_by_entry
     (the gather kernel's sums, bit for bit; zero from inputs of 2^-134 and less), in one value of one sample only, and
     in a few channels.  A sum of n products rounded n times is within n 2^-24 of the sum of the magnitudes, n
     2^-150 where it is denormal; the tile that holds the values rounds less often and is off by 2^-28 of the smallest
-    output it keeps, n (2^-134 of the largest weight + 2^-147)."""
+    output it keeps, n (2^-133 of the largest weight + 2^-147)."""
     l = wl.Layer("tiny", C, D, H, W, k, k, stride, stride, pad, pad, N=N, sparsity=0.6, dtype="f32", seed=C)
     data = wl.prepare(l)
     data["values"] = data["values"] * np.float32(2.0 ** we)
@@ -1528,7 +1528,7 @@ def test_fp32_split_form_sums_outputs_that_the_terms_do_not_serve_entry_by_entry
             if what == "everywhere" and "split_n" not in kw:
                 assert np.array_equal(got, gather) or xe < -134 and not np.any(got), (kw, what)
             mag = dense64(np.abs(x), np.abs(v))
-            excess = np.abs(got.astype(np.float64) - dense64(x, v)) - l.n * (2.0 ** -24 * mag + 2.0 ** -134 * np.abs(v).max() + 2.0 ** -147)
+            excess = np.abs(got.astype(np.float64) - dense64(x, v)) - l.n * (2.0 ** -24 * mag + 2.0 ** -133 * np.abs(v).max() + 2.0 ** -147)
             assert excess.max() <= 0, (kw, what, np.unravel_index(excess.argmax(), excess.shape))
     plan.destroy()
 
