@@ -279,8 +279,9 @@ __device__ __forceinline__ float split_exact(const float* __restrict__ x, const 
 }
 
 // The wave's outputs: the accumulated ones, or, where one of them is too small for the terms or not finite, the
-// sums over the sparse table.  `position` as in the kernels.
-template <int MW, int NW, class Position>
+// sums over the sparse table.  SHARED: other workgroups may have other chunks of the tile.  `position` as in the
+// kernels.
+template <bool SHARED, int MW, int NW, class Position>
 __device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const float* __restrict__ x, float* __restrict__ y, const SplitArgs& a,
                                             int b0, int p0, int mblk0, int kg, int c_lo, int c_hi, const Position& position)
 {
@@ -318,7 +319,7 @@ __device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const 
                 if (d >= a.D) break;
                 const float v = split_exact(x, a, b0 + sm, d, p0 + tp, tq, c_lo, c_hi);
                 float* yp = yb + ((int64_t)sm * a.D + d) * PQ + (p0 + tp) * a.Q + tq;
-                if (a.KS > 1) add_out(yp, v);
+                if (SHARED && a.KS > 1) add_out(yp, v);
                 else store_out(yp, v);
             }
         }
@@ -335,7 +336,7 @@ __device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const 
             for (int j = 0; j < 4; ++j) {
                 if ((mblk0 + m) * 16 + 4 * kg + j >= a.D) continue;
                 float* yp = yb + (o + (unsigned)((16 * m + j) * PQ));
-                if (a.KS > 1) add_out(yp, acc[m][i][j]);
+                if (SHARED && a.KS > 1) add_out(yp, acc[m][i][j]);
                 else store_out(yp, acc[m][i][j]);
             }
         }
@@ -554,7 +555,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
             for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
     }
-    split_store<MW, NW>(acc, x, y, a, b0, p0, mblk0, kg, ch_lo * a.CC, ch_hi * a.CC, position);
+    split_store<true, MW, NW>(acc, x, y, a, b0, p0, mblk0, kg, ch_lo * a.CC, ch_hi * a.CC, position);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -776,7 +777,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     for (int m = 0; m < MW; ++m)
 #pragma unroll
         for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
-    split_store<MW, NW>(acc, x, y, a, b0, p0, mblk0, kg, 0, a.C, position);
+    split_store<false, MW, NW>(acc, x, y, a, b0, p0, mblk0, kg, 0, a.C, position);
 }
 
 // ------------------------------------------------------------------------------------------------
