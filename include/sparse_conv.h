@@ -191,10 +191,15 @@ typedef struct {
                            LDS word (128 bits; 32 bits for i8) holds the same element of each, so every
                            offset is a whole word on any layer shape -- one LDS read per stored weight
                            feeds that many samples; at most 8 / word-size positions per lane */
-    int32_t waves_m;    /* DENSE: how many of the workgroup's four waves lie along the output channels
+    int32_t waves_m;    /* DENSE: how many of a group's waves (four, but see buffers) lie along the output channels
                            (1, 2 or 4; the others along the positions).  A wave then owns tile_d / waves_m
                            output channels (16, 32 or 64) and up to 128 positions.  0 = heuristic */
-    int32_t buffers;    /* SLAB with pipeline = 1 and chunk_c > 0: LDS chunk buffers.  0 (or 2) = two, the
+    int32_t buffers;    /* DENSE, one-shot form (pipeline, split_n and stage_rows 0): 1, 2, 4 or 8 groups of waves split
+                           the steps of the contraction (filter tap x channel block) among them and meet through
+                           LDS (a fixed summation order); waves_m waves of a group lie along the output channels, the
+                           others along the positions, so that waves_m x buffers must divide the 4 or 8 waves.
+                           0 = one group of four waves, two of eight.
+                           SLAB with pipeline = 1 and chunk_c > 0: LDS chunk buffers.  0 (or 2) = two, the
                            producer waves share the copy of every chunk; 3 .. 5 = producers + 1 buffers
                            (producers is set to match when 0): every producer wave copies whole chunks by
                            itself, so that as many chunks as there are producers are in flight while one

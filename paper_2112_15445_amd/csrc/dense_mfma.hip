@@ -23,10 +23,10 @@
 //     with one coalesced 1 KB load from global memory (L2-resident, shared by all workgroups);
 //   * every wave keeps MW x NW blocks of 16 x 16 accumulators in registers; several workgroups per
 //     CU overlap the staging of one with the multiplication of another;
-//   * two kernels share this tile and the epilogue: the one-shot form (a chunk of input channels
-//     is staged by all waves, then multiplied; four waves, or eight that split the steps) and the
+//   * two kernels share this tile: the one-shot form (dense_tile_kernel.h: a chunk of input channels is staged by
+//     all waves, then multiplied; four or eight waves, in up to eight groups that split the steps) and the
 //     pipelined form (waves of their own stage the chunks into two LDS buffers, one chunk ahead of
-//     the multiplying waves).
+//     the multiplying waves); pointwise layers have more (dense_mfma_kernel.h).
 // Integer results are exact (bit-identical to the gather kernels); f16 results differ from them in
 // summation order only.
 #include <algorithm>
@@ -109,7 +109,7 @@ sc_status_t mfma_densify(const Plan& p, unsigned char* out, hipStream_t stream)
 // ------------------------------------------------------------------------------------------------
 // Geometry of one (plan, tuning) pair, derived on the host.
 // ------------------------------------------------------------------------------------------------
-bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int lds_budget, MfmaGeom* out, int KG, int PW, int nat, int DL)
+bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int lds_budget, MfmaGeom* out, int waves, int KG, int PW, int nat, int DL)
 {
     const sc_layer_t& L = p.L;
     MfmaGeom g{};
@@ -130,21 +130,24 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
     g.nat = nat;
     g.DB = DB;
     g.ndb = (L.D + DB - 1) / DB;
-    // the four waves: WM along the output channels (MW 16-row blocks each), 4 / WM along the
-    // positions (NW 16-column blocks each, at most 8)
+    // the waves: KG groups that split the contraction; of a group WM along the output channels (MW 16-channel
+    // blocks each), the others along the positions (NW blocks of 16 each, at most 8)
     if (WM != 1 && WM != 2 && WM != 4) return false;
     g.WM = WM;
     if (DB % (16 * WM)) return false;
     g.MW = DB / (16 * WM);
     if (g.MW != 1 && g.MW != 2 && g.MW != 4) return false;
-    const int WN = 4 / WM;
+    const bool one_shot = !PW && !nat && DL == 1;
+    if ((waves != 4 && waves != 8) || (KG != 1 && KG != 2 && KG != 4 && KG != 8) || waves % (WM * KG)) return false;
+    if (!one_shot && waves != 4 * KG) return false;
+    g.waves = waves;
+    g.KG = KG;
+    const int WN = g.WN = waves / (WM * KG);
     const int NB = (g.npos + 15) / 16;
     const int nw = (NB + WN - 1) / WN;
     if (nw > 8) return false;
-    g.NW = nw <= 1 ? 1 : (nw <= 2 ? 2 : (nw <= 4 ? 4 : 8));
-    if (g.NW == 8 && g.MW == 4) return false;     // 32 accumulator blocks per wave: not instantiated
-    if (KG != 1 && KG != 2) return false;
-    g.KG = KG;
+    g.NW = nw <= 1 ? 1 : (nw <= 2 ? 2 : (nw <= 4 ? 4 : (nw <= 7 && one_shot ? 7 : 8)));
+    if (g.NW >= 7 && g.MW == 4) return false;     // more than 16 accumulator blocks per wave: not instantiated
     if (PW < 0 || PW > 4) return false;
     g.PW = PW;
     if (nat) {
@@ -166,7 +169,26 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
     int64_t lds = (int64_t)g.bufsz * (PW > 0 && g.nchunks > 1 ? 2 : 1);
     // pooling windows must not straddle tiles
     if (has_epilogue(p) && p.epi.pool && g.TP < p.P && (g.TP & 1)) return false;
-    if ((has_epilogue(p) && p.epi.pool) || KG == 2) {
+    const bool pooled = has_epilogue(p) && p.epi.pool;
+    if (one_shot) {
+        // the groups hand on their accumulators (two: the second one's; more: all of them), pooling lays them out by
+        // output channel, rows a multiple of 16 bytes
+        if (KG > 1) lds = std::max<int64_t>(lds, (int64_t)(KG == 2 ? waves / 2 : waves) * g.MW * g.NW * 1024);
+        g.epi_pitch = WN * g.NW * 16 + 4;
+        if (pooled) lds = std::max<int64_t>(lds, (int64_t)g.DB * g.epi_pitch * 4);
+        // the runs that are staged: input rows, or all rows of a tile where they carry no padding columns
+        g.flat = g.Ws == L.W && L.pad_w == 0 ? 1 : 0;
+        g.minrun = std::max(0, std::min(L.W, g.Ws - L.pad_w));
+        if (g.flat) {
+            int least = 0;
+            for (int t = 0; t < g.tiles_p; ++t) {
+                const int row0 = t * g.TP * L.stride_h - L.pad_h;
+                const int rows = std::min(g.Hs, L.H - row0) - std::max(0, -row0);
+                if (rows > 0) least = least ? std::min(least, rows) : rows;
+            }
+            g.minrun = (int)std::min<int64_t>((int64_t)least * L.W, 1 << 20);
+        }
+    } else if (pooled || KG == 2) {
         // the accumulators are exchanged through LDS (between the two step groups, or for pooling)
         g.epi_pitch = (4 / g.WM) * g.NW * 16 + 1;
         lds = std::max<int64_t>(lds, (int64_t)g.DB * g.epi_pitch * 4);
@@ -239,6 +261,31 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
     if (g.nat && (int64_t)g.CC * g.NS * g.TP * p.Q >= (1 << 19)) return SC_ERR_UNSUPPORTED;     // fdiv19() range of the copy
     // (the direct-to-LDS copies of the pipelined natural-layout form move 16-byte words)
     if (g.nat && g.PW && reinterpret_cast<uintptr_t>(x) % 16 != 0) return SC_ERR_UNSUPPORTED;
+    if (!g.nat && !g.PW && g.DL == 1) {
+        a.lwm = __builtin_ctz(g.WM); a.lwn = __builtin_ctz(g.WN); a.lkg = __builtin_ctz(g.KG); a.KG = g.KG;
+        a.flat = g.flat;
+        a.zero = p.L.pad_h || p.L.pad_w ? (int)(((int64_t)g.npos_s * g.pitch + 15) / 16) : 0;
+        // Columns per staging load, 8, 4, 2 or 1: the least estimated time of a chunk, rounds of NT blocks times a
+        // block's instructions (its loads and address, then for each column the permutations and the LDS write).
+        const int cv = 16 / p.ex, nt = g.waves * 64;
+        const int64_t run = g.flat ? (int64_t)g.Hs * p.L.W : std::min(p.L.W, g.Ws - p.L.pad_w), rows = g.flat ? 1 : g.Hs;
+        int64_t best = 0;
+        for (int l = 3; l >= 0; --l) {
+            const int e = 1 << l;
+            if (e > 1 && e > g.minrun) continue;
+            const int64_t blocks = (int64_t)(g.CC / cv) * g.NS * rows * ((run + e - 1) / e);
+            const int64_t cost = ((blocks + nt - 1) / nt) * (cv + 24 + e * (p.ex == 2 ? 8 : 12));
+            if (l == 3 || best == 0 || cost < best) { best = cost; a.lepv = l; }
+        }
+        a.ntiles = ((N + g.NS - 1) / g.NS) * g.tiles_p;
+        a.inv_ntiles = 1.0f / (float)a.ntiles;
+        // Order of the workgroups: by tile, but where the weights outgrow the 4 MB L2 of an XCD by block of output
+        // channels, if an XCD then reads less in all (its share of the weights and of the input against all weights and an
+        // eighth of the input).  4b/16b 3x3 512-512 at 4 x 4, batch 64, 4.7 MB of weights: 12.9 us so, 14.0 by tile; below
+        // 2.4 MB level (int8) or 4 % slower (f16 3x3 256-256 at 14 x 14, 1.2 MB: 15.9 for 15.3).
+        const double w = (double)mfma_weight_bytes(p), xin = (double)N * p.L.C * p.L.H * p.L.W * p.ex;
+        a.wmajor = w > 3.0 * (1 << 20) && w / std::min(8.0, (double)g.ndb) + xin * std::min(1.0, g.ndb / 8.0) < w + xin / 8.0 ? 1 : 0;
+    }
     a.inv_ndb = 1.0f / (float)g.ndb; a.inv_tiles_p = 1.0f / (float)g.tiles_p;
     a.inv_HsWs = 1.0f / (float)(g.Hs * g.Ws); a.inv_Ws = 1.0f / (float)g.Ws;
     a.inv_TPQ = 1.0f / (float)(g.TP * p.Q); a.inv_Q = 1.0f / (float)p.Q;

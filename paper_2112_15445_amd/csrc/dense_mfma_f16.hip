@@ -1,9 +1,9 @@
 // DENSE variant, 16-bit activations (SC_F16, SC_CB4_F16): v_mfma_f32_16x16x32_f16 instantiations.
-#include "dense_mfma_kernel.h"
+#include "dense_tile_kernel.h"
 
 namespace sc {
 sc_status_t launch_mfma_f16(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
-    return launch_mfma_typed<SC_F16, 0>(p, a, x, y, grid, stream);
+    return launch_tile_typed<SC_F16>(p, a, x, y, grid, stream);
 }
 }  // namespace sc

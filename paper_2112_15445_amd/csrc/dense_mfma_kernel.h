@@ -37,6 +37,11 @@ struct MfmaArgs {
     int TPQ;                 // natural layout: positions of one sample in the tile (TP * Q)
     int DL, ndbg;            // one-shot form: output-channel blocks per workgroup, groups of them (ndb / DL, rounded up)
     float inv_ndbg;
+    // one-shot form on the transposed tile: workgroup order (see mfma_block), log2 of the waves along the output
+    // channels and the positions and of the groups that split the contraction, log2 of the columns per staging
+    // load, 16-byte words of the tile image to clear, staged rows of a sample are one run per channel
+    int wmajor, ntiles, lwm, lwn, lkg, KG, lepv, zero, flat;
+    float inv_ntiles;
     float inv_spc, inv_ccb, inv_cbs_last, inv_S;
     float inv_ndb, inv_tiles_p, inv_HsWs, inv_Ws, inv_TPQ, inv_Q;
     // fused epilogue (epi = 0: none): ReLU, 2 x 2 max-pooling, requantisation multipliers (or NULL),
@@ -60,6 +65,23 @@ sc_status_t launch_mfma_dl_i8(const Plan& p, const MfmaArgs& a, const void* x, v
 // floor(e / d) for 0 <= e < 2^19 given inv = 1.0f / d (exact: the half-integer bias keeps the
 // product at least 1/(2d) away from every integer, well above the two float roundings)
 __device__ inline int fdiv19(int e, float inv) { return (int)(((float)e + 0.5f) * inv); }
+
+// Workgroup -> (tile of positions bt, block of output channels db of ndb).  Workgroups are dealt round-robin to
+// the 8 XCDs: they are renumbered so that each XCD gets a contiguous run.  Within it either the blocks of one tile
+// are neighbours (they find the tile in the L2 that their siblings loaded), or, where the weights outweigh the
+// input (a.wmajor), the tiles of one block: an XCD then streams its share of the weights and not all of them.
+__device__ __forceinline__ void mfma_block(const MfmaArgs& a, int ndb, float inv_ndb, int& bt, int& db)
+{
+    const int q = gridDim.x >> 3, r = gridDim.x & 7, xcd = blockIdx.x & 7;
+    const int wg = xcd * q + min(xcd, r) + (int)(blockIdx.x >> 3);
+    if (a.wmajor) {
+        db = fdiv19(wg, a.inv_ntiles);
+        bt = wg - db * a.ntiles;
+    } else {
+        bt = fdiv19(wg, inv_ndb);
+        db = wg - bt * ndb;
+    }
+}
 
 // ------------------------------------------------------------------------------------------------
 // Staging of one chunk of CC input channels of the tile, transposed on the way: global memory is

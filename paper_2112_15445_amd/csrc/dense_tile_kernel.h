@@ -1,0 +1,623 @@
+// The one-shot kernel of the DENSE variant: the tile is staged transposed, a chunk of input channels at a
+// time, by all waves, and multiplied by all of them.  See dense_mfma.hip for the formulation.
+//
+// What bounds the layers that it serves is not the matrix pipe (21 clocks per 16 x 16 x 32 instruction) but what
+// happens around it, so the kernel is laid out for short phases:
+//   * the loads of the first chunk are requested before anything else is worked out; weights, LDS zeroing, the
+//     lanes' positions and the table of steps are prepared while they are on their way;
+//   * staging moves whole registers: blocks of 8 (16) channels x up to 8 columns, transposed by byte
+//     permutations, and four neighbouring lanes take four channel groups of the same columns, so that their
+//     16-byte LDS writes fall into different banks (with the column groups on neighbouring lanes the writes
+//     were up to 8-way conflicts);
+//   * weights come through the vector L1, which was measured at 40 - 45 bytes a clock and CU whatever the number
+//     of loads in flight: what a workgroup reads of them is what counts.  The eight waves may therefore
+//     split the contraction up to eight ways (KG) over one tile of outputs instead of fetching the
+//     same weights for several tiles; their sums meet in LDS;
+//   * the operands are exchanged (positions are the rows of the matrix instruction, channels its columns), so
+//     that a lane holds four neighbouring positions of one channel and stores them as one word.
+// Measured per pass, before (staging by whole rows of blocks, one or two groups, 2-byte stores) and after: f16 3x3
+// 64-64 at 56 x 56, batch 32 19.5 -> 15.7 us; f16 3x3 256-256 at 14 x 14, batch 32 19.0 -> 15.0; 4b/16b 3x3 512-512 at
+// 4 x 4, batch 64 19.8 -> 13.2; the 13 int8 layers of VGG-16, batch 64 170 -> 133.
+#pragma once
+
+#include "dense_mfma_kernel.h"
+
+namespace sc {
+
+// ------------------------------------------------------------------------------------------------
+// Staging.  One block = CV channels x EPV columns of one run (an input row; or, where the staged rows carry no
+// padding columns, all of them).  A run that is no multiple of EPV ends in a block that starts EPV before its end: the
+// columns that two blocks share are written twice with the same values.  The loads therefore have any
+// alignment that an element has.  A round is one load of 32 registers per thread; two rounds are in flight.
+// ------------------------------------------------------------------------------------------------
+struct TileStage {
+    const char* xs;              // first staged element of sample 0, channel 0 of the chunk
+    unsigned sample_b, plane_b, row_b;   // bytes per sample, channel and input row
+    int nblocks, rowsG, per_cg4, G, run, cleft, dst0;
+    int npos1, Ws;
+    bool whole;                  // every channel of the chunk's groups exists in the layer
+    float inv_per_cg4, inv_rowsG, inv_G;
+};
+
+__device__ __forceinline__ int tdiv(int e, float inv) { return (int)__builtin_fmaf((float)e, inv, 0.5f * inv); }   // as fdiv19
+
+template <typename X> constexpr int kTileCV = 16 / (int)sizeof(X);
+template <typename X, int EPV> constexpr int kTileWPE = EPV * (int)sizeof(X) >= 4 ? EPV * (int)sizeof(X) / 4 : 1;
+template <typename X, int EPV> constexpr int kTileVB = 32 / (kTileCV<X> * kTileWPE<X, EPV>);    // blocks per thread and round
+
+// block v: channel group, sample, row, first column (false: past the end, then block v mod 4)
+template <int EPV>
+__device__ __forceinline__ bool tile_block(const TileStage& st, int v, int& cg, int& sm, int& ii, int& col)
+{
+    const bool live = v < st.nblocks;
+    int r = live ? v >> 2 : 0;
+    const int cg4 = tdiv(r, st.inv_per_cg4);
+    cg = cg4 * 4 + (v & 3);
+    r -= cg4 * st.per_cg4;
+    sm = 0;
+    if (st.rowsG != st.per_cg4) { sm = tdiv(r, st.inv_rowsG); r -= sm * st.rowsG; }
+    ii = 0;
+    if (st.rowsG != st.G) { ii = tdiv(r, st.inv_G); r -= ii * st.G; }
+    col = min(r * EPV, st.run - EPV);
+    return live;
+}
+
+template <typename X, int EPV>
+__device__ __forceinline__ void tile_load(unsigned (&pre)[32], const TileStage& st, int v0, int NT)
+{
+    constexpr int CV = kTileCV<X>, W = kTileWPE<X, EPV>, VB = kTileVB<X, EPV>, B = EPV * (int)sizeof(X);
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+        int cg, sm, ii, col;
+        tile_block<EPV>(st, v0 + u * NT, cg, sm, ii, col);
+        const unsigned off = (unsigned)sm * st.sample_b + (unsigned)ii * st.row_b + (unsigned)col * (unsigned)sizeof(X);
+        unsigned o = off + (unsigned)(cg * CV) * st.plane_b;
+#pragma unroll
+        for (int j = 0; j < CV; ++j) {
+            // (channels past the layer's last: the block's place in channel 0, zeroed when it is stored)
+            const char* src = st.xs + (st.whole || cg * CV + j < st.cleft ? o : off);
+            // (of any alignment: one load each all the same)
+            if constexpr (B >= 4) {
+                unsigned e[W];
+                __builtin_memcpy(e, src, B);
+#pragma unroll
+                for (int w = 0; w < W; ++w) pre[(u * CV + j) * W + w] = e[w];
+            } else if constexpr (B == 2) {
+                unsigned short e;
+                __builtin_memcpy(&e, src, 2);
+                pre[u * CV + j] = e;
+            } else {
+                pre[u * CV + j] = *reinterpret_cast<const unsigned char*>(src);
+            }
+            o += st.plane_b;
+        }
+    }
+}
+
+template <typename X, int EPV>
+__device__ __forceinline__ void tile_store(unsigned (&pre)[32], const TileStage& st, unsigned char* lds, int pitch, int v0, int NT)
+{
+    constexpr int CV = kTileCV<X>, W = kTileWPE<X, EPV>, VB = kTileVB<X, EPV>;
+    constexpr int EPW = 4 / (int)sizeof(X);                  // columns per register
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
+        int cg, sm, ii, col;
+        if (!tile_block<EPV>(st, v0 + u * NT, cg, sm, ii, col)) continue;
+        unsigned char* dst = lds + (sm * st.npos1 + st.dst0 + ii * st.Ws + col) * pitch + cg * 16;
+        if (!st.whole) {
+#pragma unroll
+            for (int j = 0; j < CV; ++j)
+                if (cg * CV + j >= st.cleft) {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) pre[(u * CV + j) * W + w] = 0u;
+                }
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if constexpr (sizeof(X) == 2) {
+#pragma unroll
+                for (int e = 0; e < (EPV < EPW ? EPV : EPW); ++e) {
+                    uint4w o;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        o[q] = __builtin_amdgcn_perm(pre[(u * CV + 2 * q + 1) * W + w], pre[(u * CV + 2 * q) * W + w], e ? 0x07060302u : 0x05040100u);
+                    *reinterpret_cast<uint4w*>(dst + (w * EPW + e) * pitch) = o;
+                }
+            } else {
+                // 4 x 4 bytes of 4 channels at a time: pairs of channels first, then pairs of pairs
+                uint4w o[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const unsigned c0 = pre[(u * CV + 4 * q) * W + w], c1 = pre[(u * CV + 4 * q + 1) * W + w];
+                    const unsigned c2 = pre[(u * CV + 4 * q + 2) * W + w], c3 = pre[(u * CV + 4 * q + 3) * W + w];
+                    const unsigned a0 = __builtin_amdgcn_perm(c1, c0, 0x05010400u), b0 = __builtin_amdgcn_perm(c3, c2, 0x05010400u);
+                    o[0][q] = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
+                    o[1][q] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+                    if constexpr (EPV >= 4) {
+                        const unsigned a1 = __builtin_amdgcn_perm(c1, c0, 0x07030602u), b1 = __builtin_amdgcn_perm(c3, c2, 0x07030602u);
+                        o[2][q] = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
+                        o[3][q] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < (EPV < 4 ? EPV : 4); ++e) *reinterpret_cast<uint4w*>(dst + (w * 4 + e) * pitch) = o[e];
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Stores of four neighbouring positions of one output channel (of any alignment that an element has).  Not with the
+// non-temporal hint: a wave's store covers 32 bytes (f16) of each of 16 channels, and the hint keeps L2 from joining
+// the neighbouring blocks to whole lines (f16 1x1 128-512 at 28 x 28, batch 32: 28.4 us with it, 18.8 without).
+// ------------------------------------------------------------------------------------------------
+template <typename A> __device__ __forceinline__ A tile_max(A p, A q)
+{
+    if constexpr (std::is_same<A, float>::value) return __builtin_fmaxf(p, q);
+    else return p > q ? p : q;
+}
+
+__device__ __forceinline__ int8_t tile_code(int v, float rq)
+{
+    const float q = rintf(__int2float_rn(v) * rq);
+    return (int8_t)(int)fminf(fmaxf(q, -127.0f), 127.0f);
+}
+
+template <sc_dtype_t DT, typename Acc>
+__device__ __forceinline__ void tile_put4(typename Types<DT>::Y* __restrict__ y, int64_t off, Acc v, bool relu, bool codes, float rq, int count)
+{
+    if (relu) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const typename Types<DT>::A e = v[j];
+            v[j] = tile_max(e, typename Types<DT>::A(0));
+        }
+    }
+    if constexpr (kIntActs<DT>) {
+        if (codes) {
+            int8_t* yc = reinterpret_cast<int8_t*>(y) + off;
+            if (count >= 4) {
+                const unsigned w = (unsigned)(uint8_t)tile_code(v[0], rq) | (unsigned)(uint8_t)tile_code(v[1], rq) << 8 |
+                                   (unsigned)(uint8_t)tile_code(v[2], rq) << 16 | (unsigned)(uint8_t)tile_code(v[3], rq) << 24;
+                typedef unsigned __attribute__((aligned(1))) U;
+                *reinterpret_cast<U*>(yc) = w;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    if (j < count) yc[j] = tile_code(v[j], rq);
+            }
+            return;
+        }
+        if (count >= 4) {
+            typedef int4v_ __attribute__((aligned(4))) U;
+            *reinterpret_cast<U*>(y + off) = v;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j < count) store_out(y + off + j, v[j]);
+        }
+    } else {
+        if (count >= 4) {
+            typedef unsigned V2 __attribute__((ext_vector_type(2)));
+            typedef V2 __attribute__((aligned(2))) U;
+            V2 w;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                w[j] = (unsigned)__half_as_ushort(narrow<DT>(v[2 * j])) | (unsigned)__half_as_ushort(narrow<DT>(v[2 * j + 1])) << 16;
+            *reinterpret_cast<U*>(y + off) = w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (j < count) store_out(y + off + j, narrow<DT>(v[j]));
+        }
+    }
+}
+
+template <sc_dtype_t DT, int MW, int NW>
+__global__ void __launch_bounds__(512, 2)
+mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>::Y* __restrict__ y,
+                 const uint4w* __restrict__ wfrag, const MfmaArgs a)
+{
+    using X = typename Types<DT>::X;
+    using A = typename Types<DT>::A;
+    using Acc = typename std::conditional<kIntActs<DT>, int4v_, float4v>::type;
+    constexpr int CB = kChanBlock<DT>, CV = kChanVec<DT>;
+    constexpr int PF = MW >= 2 ? 4 : 8;                      // steps of weights in flight
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+
+    const int NT = blockDim.x;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kg = lane >> 4;
+
+    int bt, db;
+    mfma_block(a, a.ndb, a.inv_ndb, bt, db);
+    const int bg = fdiv19(bt, a.inv_tiles_p);
+    const int tpi = bt - bg * a.tiles_p;
+    const int b0 = bg * a.NS, p0 = tpi * a.TP;
+    const int row0 = p0 * a.s_h - a.pad_h;
+    const int PQ = a.P * a.Q;
+
+    // ---------------------------------------------------------------- the loads of the first chunk
+    TileStage st;
+    {
+        const int nsv = min(a.NS, a.N - b0);                 // samples inside the batch
+        const int ilo = max(0, -row0);                       // staged rows inside the input: [ilo, ilo + nrows)
+        const int nrows = max(0, min(a.Hs, a.H - row0) - ilo);
+        const int rows = a.flat ? min(nrows, 1) : nrows;
+        st.run = a.flat ? nrows * a.W : max(0, min(a.W, a.Ws - a.pad_w));
+        st.G = (st.run + (1 << a.lepv) - 1) >> a.lepv;
+        st.rowsG = rows * st.G;
+        st.per_cg4 = nsv * st.rowsG;
+        st.nblocks = (a.CC / CV) * st.per_cg4;
+        st.inv_per_cg4 = __builtin_amdgcn_rcpf((float)max(st.per_cg4, 1));
+        st.inv_rowsG = __builtin_amdgcn_rcpf((float)max(st.rowsG, 1));
+        st.inv_G = __builtin_amdgcn_rcpf((float)max(st.G, 1));
+        st.dst0 = ilo * a.Ws + a.pad_w;
+        st.npos1 = a.Hs * a.Ws;
+        st.Ws = a.Ws;
+        st.plane_b = (unsigned)(a.H * a.W) * (unsigned)sizeof(X);
+        st.sample_b = (unsigned)a.C * st.plane_b;
+        st.row_b = (unsigned)a.W * (unsigned)sizeof(X);
+        st.xs = reinterpret_cast<const char*>(x) + (int64_t)b0 * st.sample_b + (int64_t)(row0 + ilo) * st.row_b;
+        st.cleft = a.C;
+        st.whole = st.cleft >= a.CC;
+    }
+    constexpr int PR = MW * NW >= 16 && MW == 4 ? 1 : 2;     // rounds of a chunk that are loaded a chunk ahead
+    unsigned pre[2][32];
+    // (opaque block index: a block's addresses are worked out again for every chunk, not kept in registers)
+    auto load_pre = [&](unsigned (&r)[32], int v0) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(v0));
+        switch (a.lepv) {
+            case 3: tile_load<X, 8>(r, st, v0, NT); break;
+            case 2: tile_load<X, 4>(r, st, v0, NT); break;
+            case 1: tile_load<X, 2>(r, st, v0, NT); break;
+            default: tile_load<X, 1>(r, st, v0, NT); break;
+        }
+    };
+    auto store_pre = [&](unsigned (&r)[32], int v0) __attribute__((always_inline)) {
+        asm volatile("" : "+v"(v0));
+        switch (a.lepv) {
+            case 3: tile_store<X, 8>(r, st, lds, a.pitch, v0, NT); break;
+            case 2: tile_store<X, 4>(r, st, lds, a.pitch, v0, NT); break;
+            case 1: tile_store<X, 2>(r, st, lds, a.pitch, v0, NT); break;
+            default: tile_store<X, 1>(r, st, lds, a.pitch, v0, NT); break;
+        }
+    };
+    const int per_round = NT * (a.lepv == 3 ? kTileVB<X, 8> : a.lepv == 2 ? kTileVB<X, 4> : a.lepv == 1 ? kTileVB<X, 2> : kTileVB<X, 1>);
+    const bool two = PR == 2 && st.nblocks > per_round;
+    // (nblocks = 0: a tile that lies in the padding altogether)
+    if (st.nblocks) load_pre(pre[0], tid);
+    if (two) load_pre(pre[1], tid + per_round);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---------------------------------------------------------------- roles of the waves
+    const int wm = wave & ((1 << a.lwm) - 1), wn = (wave >> a.lwm) & ((1 << a.lwn) - 1), kgrp = wave >> (a.lwm + a.lwn);
+    const int KG = a.KG;
+    const int mblk0 = db * (a.DB >> 4) + wm * MW;
+    const int64_t wrow = (int64_t)(a.RS * a.NCB) << 10;      // bytes per 16-row block of the weights
+    const unsigned char* wrows = reinterpret_cast<const unsigned char*>(wfrag) + mblk0 * wrow;
+
+    // Steps of a chunk: filter tap, then channel block of the chunk; this wave takes kgrp, kgrp + KG, ...
+    // Up to 64 of them are tabulated one per lane (LDS offset of the tile operands, offset of the weights) and
+    // read back with v_readlane; steps past the last repeat it (operands are requested without a test).
+    int xtab, wtab;
+    auto table = [&](int s0, int n, int cbs, int gcb0) {
+        const int s = kgrp + KG * (s0 + min(lane, n - 1));
+        const int tap = tdiv(s, cbs == a.CC / CB ? a.inv_ccb : a.inv_cbs_last);
+        const int cb = s - tap * cbs;
+        const int r = tdiv(tap, a.inv_S);
+        const int sx = tap - r * a.S;
+        xtab = (r * a.Ws + sx) * a.pitch + cb * 64;
+        wtab = tap * a.NCB + gcb0 + cb;
+    };
+    uint4w aq[PF][MW], bq[4];
+    auto fetch_w = [&](uint4w (&av)[MW], int s) __attribute__((always_inline)) {
+        const unsigned char* ws = wrows + ((int64_t)__builtin_amdgcn_readlane(wtab, min(s, 63)) << 10);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(ws + m * wrow + (unsigned)lane * 16u);
+    };
+    // steps of this wave in a chunk of cbs channel blocks
+    auto steps_of = [&](int cbs) { const int all = a.RS * cbs; return all > kgrp ? (all - kgrp + KG - 1) >> a.lkg : 0; };
+    auto start_w = [&](int s0, int n, int cbs, int gcb0) __attribute__((always_inline)) {
+        table(s0, min(64, n - s0), cbs, gcb0);
+#pragma unroll
+        for (int u = 0; u < PF; ++u) fetch_w(aq[u], u);
+    };
+    int cbs = min(a.CC, a.NCB * CB) / CB;
+    int nsteps = steps_of(cbs);
+    if (nsteps > 0) start_w(0, nsteps, cbs, 0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---------------------------------------------------------------- padding: the whole image is cleared once
+    if (a.zero) {
+        for (int i = tid; i < a.zero; i += NT) *reinterpret_cast<uint4w*>(lds + i * 16) = uint4w{0u, 0u, 0u, 0u};
+        lds_barrier();                                       // (the loads stay in flight)
+    }
+
+    // positions of this lane's NW column blocks in the tile image (with its k group)
+    int bbase[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+        const int f = (wn * NW + i) * 16 + n16;
+        const int sm = tdiv(f, a.inv_TPQ);
+        const int rem = f - sm * a.TPQ;
+        const int tp = tdiv(rem, a.inv_Q);
+        const int tq = rem - tp * a.Q;
+        const bool ok = f < a.npos;
+        bbase[i] = (ok ? ((sm * a.Hs + tp * a.s_h) * a.Ws + tq * a.s_w) * a.pitch : 0) + kg * 16;
+    }
+    Acc acc[MW][NW];
+#pragma unroll
+    for (int m = 0; m < MW; ++m)
+#pragma unroll
+        for (int i = 0; i < NW; ++i) acc[m][i] = Acc{0, 0, 0, 0};
+
+    for (int ch = 0; ch < a.nchunks; ++ch) {
+        if (ch > 0) lds_barrier();                           // the previous chunk has been multiplied
+        if (st.nblocks) store_pre(pre[0], tid);
+        if (two) {
+            store_pre(pre[1], tid + per_round);
+            for (int v0 = tid + 2 * per_round; v0 - tid < st.nblocks; v0 += 2 * per_round) {
+                const bool more = v0 - tid + per_round < st.nblocks;
+                load_pre(pre[0], v0);
+                if (more) load_pre(pre[1], v0 + per_round);
+                store_pre(pre[0], v0);
+                if (more) store_pre(pre[1], v0 + per_round);
+            }
+        } else if constexpr (PR == 1) {
+            for (int v0 = tid + per_round; v0 - tid < st.nblocks; v0 += per_round) {
+                load_pre(pre[0], v0);
+                store_pre(pre[0], v0);
+            }
+        }
+        lds_barrier();
+        if (ch + 1 < a.nchunks) {
+            st.xs += (int64_t)a.CC * st.plane_b;
+            st.cleft -= a.CC;
+            st.whole = st.cleft >= a.CC;
+            if (st.nblocks) load_pre(pre[0], tid);
+            if (two) load_pre(pre[1], tid + per_round);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // ------------------------------------------------------------ multiply
+        const int gcb0 = ch * (a.CC / CB);
+        for (int s0 = 0; s0 < nsteps; s0 += 64) {
+            const int n = min(64, nsteps - s0);
+            if (s0 > 0) start_w(s0, nsteps, cbs, gcb0);
+            // operands of the tile: block b of the sequence (step, position block) goes to slot b mod 4, requested three
+            // blocks ahead of its use
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                bq[b] = *reinterpret_cast<const uint4w*>(lds + bbase[b % NW] + __builtin_amdgcn_readlane(xtab, b / NW));
+            auto step = [&](int k, int u, bool refill) __attribute__((always_inline)) {
+                constexpr int AH = (NW + 2) / NW;            // steps that the requests reach ahead
+                int toff[AH + 1];
+#pragma unroll
+                for (int q = 0; q <= AH; ++q) toff[q] = __builtin_amdgcn_readlane(xtab, min(k + q, 63));
+#pragma unroll
+                for (int i = 0; i < NW; ++i) {
+                    bq[(u * NW + i + 3) & 3] = *reinterpret_cast<const uint4w*>(lds + bbase[(i + 3) % NW] + toff[(i + 3) / NW]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    const uint4w bv = bq[(u * NW + i) & 3];
+#pragma unroll
+                    for (int m = 0; m < MW; ++m) {
+                        if constexpr (kIntActs<DT>)
+                            acc[m][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(int4v_, bv), __builtin_bit_cast(int4v_, aq[u][m]), acc[m][i], 0, 0, 0);
+                        else
+                            acc[m][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8v, bv), __builtin_bit_cast(half8v, aq[u][m]), acc[m][i], 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (refill) fetch_w(aq[u], k + PF);
+            };
+            const int main_steps = n / PF * PF;
+            for (int k = 0; k < main_steps; k += PF) {
+#pragma unroll
+                for (int u = 0; u < PF; ++u) step(k + u, u, true);
+            }
+#pragma unroll
+            for (int u = 0; u < PF - 1; ++u)
+                if (main_steps + u < n) step(main_steps + u, u, false);
+        }
+        if (ch + 1 < a.nchunks) {
+            cbs = min(a.CC, a.NCB * CB - (ch + 1) * a.CC) / CB;
+            nsteps = steps_of(cbs);
+            if (nsteps > 0) start_w(0, nsteps, cbs, gcb0 + a.CC / CB);
+        }
+    }
+
+    // ---------------------------------------------------------------- the outputs: a lane holds the positions 4 kg .. 4 kg + 3 of a
+    // block for channel n16 of the row block
+    const int nvalid = (a.NS == 1 ? min(a.TP, a.P - p0) : a.P) * a.Q;      // positions of a sample that exist
+    auto multiplier = [&](int m) { return kIntActs<DT> && a.requant ? a.requant[min((mblk0 + m) * 16 + n16, a.D - 1)] : 0.0f; };
+    auto put = [&](int m, int i, const Acc& v, float rq) __attribute__((always_inline)) {
+        const int d = (mblk0 + m) * 16 + n16;
+        const int f = (wn * NW + i) * 16 + 4 * kg;
+        if (d >= a.D) return;
+        if (a.NS == 1) {
+            const int count = min(nvalid - f, 4);
+            if (count > 0) tile_put4<DT>(y, ((int64_t)b0 * a.D + d) * PQ + p0 * a.Q + f, v, a.epi_relu, a.requant, rq, count);
+        } else {
+            // whole planes of several samples: a group of four that reaches into the next sample is stored one by one
+            const int sm = tdiv(f, a.inv_TPQ), rem = f - sm * a.TPQ;
+            if (rem + 4 <= a.TPQ) {
+                if (f < a.npos && b0 + sm < a.N) tile_put4<DT>(y, ((int64_t)(b0 + sm) * a.D + d) * PQ + rem, v, a.epi_relu, a.requant, rq, 4);
+                return;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int smj = tdiv(f + j, a.inv_TPQ), remj = f + j - smj * a.TPQ;
+                if (f + j < a.npos && b0 + smj < a.N)
+                    tile_put4<DT>(y, ((int64_t)(b0 + smj) * a.D + d) * PQ + remj, Acc{v[j], v[j], v[j], v[j]}, a.epi_relu, a.requant, rq, 1);
+            }
+        }
+    };
+    const int waves1 = 1 << (a.lwm + a.lwn);                 // waves of one group
+    const int w1 = wave & (waves1 - 1);
+    if (KG == 2) {
+        // the second group hands its sums to the first, a lane's own 16 bytes per block
+        lds_barrier();
+        Acc* ex = reinterpret_cast<Acc*>(lds) + w1 * (MW * NW * 64) + lane;
+        if (kgrp == 1) {
+#pragma unroll
+            for (int m = 0; m < MW; ++m)
+#pragma unroll
+                for (int i = 0; i < NW; ++i) ex[(m * NW + i) * 64] = acc[m][i];
+        }
+        lds_barrier();
+        if (kgrp == 0) {
+#pragma unroll
+            for (int m = 0; m < MW; ++m)
+#pragma unroll
+                for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
+        }
+    }
+    if (KG > 2) {
+        // all groups put their sums into LDS; block b of the wave tile is added up (in the order of the groups) and
+        // stored by group b mod KG
+        lds_barrier();
+        Acc* ex = reinterpret_cast<Acc*>(lds) + lane;
+#pragma unroll
+        for (int m = 0; m < MW; ++m)
+#pragma unroll
+            for (int i = 0; i < NW; ++i) ex[((kgrp * waves1 + w1) * (MW * NW) + m * NW + i) * 64] = acc[m][i];
+        lds_barrier();
+        constexpr int BPW = (MW * NW + 3) / 4;               // blocks per wave, at most
+#pragma unroll
+        for (int t = 0; t < BPW; ++t) {
+            const int b = kgrp + t * KG;
+            if (b < MW * NW) {
+                Acc s = ex[(w1 * (MW * NW) + b) * 64];
+                for (int g = 1; g < KG; ++g) s += ex[((g * waves1 + w1) * (MW * NW) + b) * 64];
+                acc[t / NW][t % NW] = s;
+            }
+        }
+        if (!a.epi_pool) {
+#pragma unroll
+            for (int t = 0; t < BPW; ++t) {
+                const int b = kgrp + t * KG;
+                if (b < MW * NW) put(b / NW, b % NW, acc[t / NW][t % NW], multiplier(b / NW));
+            }
+            return;
+        }
+    } else if (!a.epi_pool) {
+        if (kgrp > 0) return;
+#pragma unroll
+        for (int m = 0; m < MW; ++m) {
+            const float rq = multiplier(m);
+#pragma unroll
+            for (int i = 0; i < NW; ++i) put(m, i, acc[m][i], rq);
+        }
+        return;
+    }
+
+    // ---------------------------------------------------------------- fused epilogue with pooling: the sums as
+    // [output channel][tile position] in LDS, then every thread finishes elements of y -- the maximum over
+    // its 2 x 2 window, ReLU, and the store as the layer's type or, requantised, as an 8-bit code
+    lds_barrier();
+    A* ex = reinterpret_cast<A*>(lds);
+    auto give = [&](int m, int i, const Acc& v) {
+        *reinterpret_cast<Acc*>(ex + ((wm * MW + m) * 16 + n16) * a.epi_pitch + (wn * NW + i) * 16 + 4 * kg) = v;
+    };
+    if (KG > 2) {
+        constexpr int BPW = (MW * NW + 3) / 4;
+#pragma unroll
+        for (int t = 0; t < BPW; ++t) {
+            const int b = kgrp + t * KG;
+            if (b < MW * NW) give(b / NW, b % NW, acc[t / NW][t % NW]);
+        }
+    } else if (kgrp == 0) {
+#pragma unroll
+        for (int m = 0; m < MW; ++m)
+#pragma unroll
+            for (int i = 0; i < NW; ++i) give(m, i, acc[m][i]);
+    }
+    lds_barrier();
+    // One element = V neighbouring outputs of a row (4 where the rows allow it).  A thread keeps to one element of the
+    // tile (decoded once) and walks over the output channels; the threads lie as (channel group,
+    // element) with the elements a power of two wide, so that small tiles still use every thread.
+    auto pool = [&](auto vtag) {
+        constexpr int V = decltype(vtag)::value;
+        const int TPo = a.TP / 2, Qe = a.Qo / V;             // output rows of y per tile (TP is even, or the whole plane); elements per row
+        const int per_s = TPo * Qe, per_d = a.NS * per_s;
+        const float inv_per_s = __builtin_amdgcn_rcpf((float)max(per_s, 1)), inv_Qe = __builtin_amdgcn_rcpf((float)Qe);
+        const int prow0 = p0 / 2;
+        int pw2 = 1;
+        while (pw2 < per_d && pw2 < NT) pw2 <<= 1;
+        const int dgroups = NT / pw2;
+        const int o_first = tid & (pw2 - 1), dg = tid / pw2;
+        for (int o = o_first; o < per_d; o += pw2) {
+            const int sm = tdiv(o, inv_per_s);
+            const int r2 = o - sm * per_s;
+            const int tpo = tdiv(r2, inv_Qe);
+            const int tqo = (r2 - tpo * Qe) * V;
+            if (b0 + sm >= a.N || prow0 + tpo >= a.Po) continue;
+            const A* src = ex + sm * a.TPQ + (tpo * 2) * a.Q + tqo * 2;
+            const int64_t off0 = (((int64_t)(b0 + sm) * a.D) * a.Po + prow0 + tpo) * a.Qo + tqo;
+            const int64_t dstride = (int64_t)a.Po * a.Qo;
+            const int dend = min(a.DB, a.D - db * a.DB);
+            for (int dl = dg; dl < dend; dl += dgroups) {
+                const int d = db * a.DB + dl;
+                const A* sp = src + dl * a.epi_pitch;
+                const float rq = kIntActs<DT> && a.requant ? a.requant[d] : 0.0f;
+                if constexpr (V == 4) {
+                    const Acc u0 = *reinterpret_cast<const Acc*>(sp), u1 = *reinterpret_cast<const Acc*>(sp + 4);
+                    const Acc w0 = *reinterpret_cast<const Acc*>(sp + a.Q), w1_ = *reinterpret_cast<const Acc*>(sp + a.Q + 4);
+                    auto most = [](A p, A q, A r, A s) { return tile_max(tile_max(p, q), tile_max(r, s)); };
+                    const Acc v = {most(u0[0], u0[1], w0[0], w0[1]), most(u0[2], u0[3], w0[2], w0[3]),
+                                   most(u1[0], u1[1], w1_[0], w1_[1]), most(u1[2], u1[3], w1_[2], w1_[3])};
+                    tile_put4<DT>(y, off0 + d * dstride, v, a.epi_relu, a.requant, rq, 4);
+                } else {
+                    const A v = tile_max(tile_max(sp[0], sp[1]), tile_max(sp[a.Q], sp[a.Q + 1]));
+                    tile_put4<DT>(y, off0 + d * dstride, Acc{v, v, v, v}, a.epi_relu, a.requant, rq, 1);
+                }
+            }
+        }
+    };
+    // (four outputs read 8 neighbouring sums of two rows, as 16-byte words)
+    if (a.Qo % 4 == 0 && a.Q % 4 == 0) pool(std::integral_constant<int, 4>{});
+    else pool(std::integral_constant<int, 1>{});
+}
+
+template <sc_dtype_t DT, int MW, int NW>
+static sc_status_t launch_tile_one(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream)
+{
+    using X = typename Types<DT>::X;
+    using Y = typename Types<DT>::Y;
+    auto kernel = &mfma_tile_kernel<DT, MW, NW>;
+    static std::once_flag once;
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(once, [&] {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
+    });
+    if (attr_err != hipSuccess) return SC_ERR_HIP;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(p.mg.waves * 64), p.mg.lds_bytes, stream, static_cast<const X*>(x),
+                       static_cast<Y*>(y), reinterpret_cast<const uint4w*>(p.d_wfrag), a);
+    return hipGetLastError() == hipSuccess ? SC_OK : SC_ERR_HIP;
+}
+
+template <sc_dtype_t DT>
+static sc_status_t launch_tile_typed(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream)
+{
+    switch (p.mg.MW * 10 + p.mg.NW) {
+        case 11: return launch_tile_one<DT, 1, 1>(p, a, x, y, grid, stream);
+        case 12: return launch_tile_one<DT, 1, 2>(p, a, x, y, grid, stream);
+        case 14: return launch_tile_one<DT, 1, 4>(p, a, x, y, grid, stream);
+        case 17: return launch_tile_one<DT, 1, 7>(p, a, x, y, grid, stream);
+        case 18: return launch_tile_one<DT, 1, 8>(p, a, x, y, grid, stream);
+        case 21: return launch_tile_one<DT, 2, 1>(p, a, x, y, grid, stream);
+        case 22: return launch_tile_one<DT, 2, 2>(p, a, x, y, grid, stream);
+        case 24: return launch_tile_one<DT, 2, 4>(p, a, x, y, grid, stream);
+        case 27: return launch_tile_one<DT, 2, 7>(p, a, x, y, grid, stream);
+        case 28: return launch_tile_one<DT, 2, 8>(p, a, x, y, grid, stream);
+        case 41: return launch_tile_one<DT, 4, 1>(p, a, x, y, grid, stream);
+        case 42: return launch_tile_one<DT, 4, 2>(p, a, x, y, grid, stream);
+        case 44: return launch_tile_one<DT, 4, 4>(p, a, x, y, grid, stream);
+    }
+    return SC_ERR_UNSUPPORTED;
+}
+
+}  // namespace sc

@@ -8,6 +8,8 @@
 #include <cstring>
 #include <new>
 #include <numeric>
+#include <string>
+#include <unordered_set>
 
 #include "sc_internal.h"
 
@@ -252,7 +254,7 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     if (t.wg_per_cu == 0) t.wg_per_cu = 2;
     if (t.wg_per_cu < 1 || t.wg_per_cu > 8) return SC_ERR_UNSUPPORTED;
     if (t.tile_p < 0 || t.sub_batch < 0 || t.chunk_c < 0 || t.tile_d < 0) return SC_ERR_UNSUPPORTED;
-    if (t.wsrc || t.ragged || t.pack || t.tile_q || t.buffers) return SC_ERR_UNSUPPORTED;
+    if (t.wsrc || t.ragged || t.pack || t.tile_q) return SC_ERR_UNSUPPORTED;
     // split_n = 2 .. 16: the workgroup walks over that many blocks of tile_d output channels, the tile resident in LDS
     if (t.split_n < 0 || t.split_n > 16) return SC_ERR_UNSUPPORTED;
     const int DL = std::max(1, t.split_n);
@@ -268,7 +270,11 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     const int CB = mfma_chan_block(p.dtype);
     // 256 threads: four waves; 512: two groups of four that split the steps of the contraction
     if (t.wg_threads != 0 && t.wg_threads != 256 && t.wg_threads != 512) return SC_ERR_UNSUPPORTED;
-    const int KG = t.wg_threads == 512 ? 2 : 1;
+    const int waves = t.wg_threads == 512 ? 8 : 4;
+    // buffers = 1, 2, 4 or 8: that many groups of waves split the contraction (one-shot form on the transposed tile)
+    if (t.buffers != 0 && t.buffers != 1 && t.buffers != 2 && t.buffers != 4 && t.buffers != 8) return SC_ERR_UNSUPPORTED;
+    if (t.buffers && (t.pipeline || nat || DL > 1)) return SC_ERR_UNSUPPORTED;
+    const int KG = t.buffers ? t.buffers : waves / 4;
     if (t.waves_m != 0 && t.waves_m != 1 && t.waves_m != 2 && t.waves_m != 4) return SC_ERR_UNSUPPORTED;
     int DB = t.tile_d;
     if (DB == 0) DB = L.D > 64 ? 128 : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16));
@@ -279,7 +285,8 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     if (WM == 0) WM = DB >= 128 ? 4 : (DB >= 64 ? 2 : 1);
     if (DB % (16 * WM) || DB / (16 * WM) < 1 || DB / (16 * WM) > 4) return SC_ERR_UNSUPPORTED;
     const int MWv = DB / (16 * WM);
-    const int maxpos = (4 / WM) * (MWv == 4 ? 4 : 8) * 16;    // positions the four waves can hold
+    if (waves % (WM * KG)) return SC_ERR_UNSUPPORTED;
+    const int maxpos = (waves / (WM * KG)) * (MWv == 4 ? 4 : 8) * 16;    // positions the waves of a group can hold
     int TP = t.tile_p, NS = t.sub_batch;
     const bool fixed_tile = TP != 0 || NS != 0;
     if (TP == 0 && NS == 0) {
@@ -291,11 +298,11 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     MfmaGeom g{};
     for (;;) {
         bool ok = false;
-        if (t.chunk_c) ok = mfma_geometry(p, TP, NS, t.chunk_c, DB, WM, budget, &g, KG, PW, nat, DL);
+        if (t.chunk_c) ok = mfma_geometry(p, TP, NS, t.chunk_c, DB, WM, budget, &g, waves, KG, PW, nat, DL);
         else
             // (one-shot: the largest chunk that fits; pipelined: small chunks are the point -- two blocks)
             for (int cc = PW ? std::min(2 * CB, (L.C + CB - 1) / CB * CB) : (L.C + CB - 1) / CB * CB; cc >= CB && !ok; cc -= CB)
-                ok = mfma_geometry(p, TP, NS, cc, DB, WM, budget, &g, KG, PW, nat, DL);
+                ok = mfma_geometry(p, TP, NS, cc, DB, WM, budget, &g, waves, KG, PW, nat, DL);
         if (ok) break;
         if (fixed_tile) return SC_ERR_UNSUPPORTED;
         // heuristic tile too large for LDS or for the waves: fewer samples, then fewer rows
@@ -305,7 +312,8 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     }
     sc_tuning_t r{};
     r.variant = SC_VARIANT_DENSE;
-    r.wg_threads = 256 * KG;
+    r.wg_threads = 64 * waves;
+    r.buffers = KG == waves / 4 ? 0 : KG;
     r.tile_p = g.TP;
     r.sub_batch = g.NS;
     r.chunk_c = g.CC;
@@ -529,16 +537,17 @@ static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t*
     const int terms = split ? 3 : 1, products = split ? (p.split_full ? 8 : 6) : 1;
     const int64_t steps = (int64_t)L.R * L.S * ((L.C + CB - 1) / CB);
     double best = INFINITY;
-    const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}};
-    for (int thr : {256, 512}) for (const auto& lw : layouts) for (int wpc : {1, 2}) for (int tile = 0; tile < 10; ++tile) {
+    const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}, {64, 1}};
+    for (int thr : {256, 512}) for (int kg : {0, 4, 8}) for (const auto& lw : layouts) for (int wpc : {1, 2}) for (int tile = 0; tile < 10; ++tile) {
         if (lw[0] > 32 && lw[0] >= 2 * L.D) continue;
+        if ((split && kg) || (lw[0] == 64 && lw[1] == 1 && !kg)) continue;
         static const int rows[] = {1, 2, 4, 7, 8, 14};
         const int tp = tile < 6 ? rows[tile] : p.P, ns = tile < 6 ? 1 : 1 << (tile - 6);
         if (tile < 6 && tp >= p.P) continue;
         sc_tuning_t t{}, r{};
         t.variant = split ? SC_VARIANT_SLAB : SC_VARIANT_DENSE;
         t.pipeline = split ? 3 : 0;
-        t.wg_threads = thr; t.tile_d = lw[0]; t.waves_m = lw[1]; t.wg_per_cu = wpc; t.tile_p = tp; t.sub_batch = ns;
+        t.wg_threads = thr; t.tile_d = lw[0]; t.waves_m = lw[1]; t.wg_per_cu = wpc; t.tile_p = tp; t.sub_batch = ns; t.buffers = kg;
         MfmaGeom g{};
         if ((split ? resolve_split(p, t, &r, &g) : resolve_dense(p, t, &r, &g)) != SC_OK) continue;
         // (what the launch would refuse)
@@ -547,10 +556,12 @@ static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t*
             continue;
         const double wgs = std::ceil(32.0 / g.NS) * g.tiles_p * g.ndb, per_cu = std::ceil(wgs / kNumCU);
         const double resident = std::min(per_cu, (double)std::max(1, std::min(wpc, kMaxLdsBytes / std::max(g.lds_bytes, 1))));
-        const double clocks = g.KG * resident >= 2.0 ? 22.0 : 32.0;
-        const double mfma = (double)steps * g.MW * g.NW * products * clocks;
-        const double l1 = ((double)steps * 4 * g.MW * terms * 1024 + (double)g.npos_s * L.C * p.ex) / 64.0;
-        const double lds = (double)steps * 4 * g.NW * terms * 1024 / 128.0 + (double)g.npos_s * L.C * p.ex / 16.0;
+        const double clocks = thr / 256 * resident >= 2.0 ? 22.0 : 32.0;
+        const double group = split ? 4.0 : (double)(g.waves / g.KG);      // waves that share a step
+        const double mfma = (double)steps * g.MW * g.NW * group / 4.0 * products * clocks;
+        const double l1 = ((double)steps * group * g.MW * terms * 1024 + (double)g.npos_s * L.C * p.ex) / 64.0;
+        const double lds = (double)steps * group * g.NW * terms * 1024 / 128.0 + (double)g.npos_s * L.C * p.ex / 16.0 +
+                           (g.KG > 1 && !split ? 16.0 * (g.KG == 2 ? group : g.waves) * g.MW * g.NW : 0.0);
         const double time = 8000.0 * std::ceil(per_cu / resident) + 3000.0 * g.nchunks * per_cu / resident + per_cu * std::max(mfma, std::max(l1, lds));
         if (time < best) { best = time; *out = r; *mgeom = g; }
     }
@@ -1188,13 +1199,16 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
     out->clear();
     // fillers (zero weights that unify the row lengths) are more than 5 % of the table
     const bool uneven = p.n > 0 && p.true_nnz * 100 < (int64_t)p.L.D * p.n * 95;
+    std::unordered_set<std::string> seen;
     auto push = [&](sc_tuning_t t) {
         sc_tuning_t r{};
         SlabGeom g{};
         MfmaGeom mg{};
         if (resolve_tuning(p, t, &r, &g, &mg) != SC_OK) return;
-        for (const sc_tuning_t& o : *out)
-            if (std::memcmp(&o, &r, sizeof(r)) == 0) return;
+        // (the tiles on the matrix cores: wg_per_cu only bounds the chunk, shapes that differ in nothing else are one)
+        sc_tuning_t c = r;
+        if (is_densified(r)) c.wg_per_cu = 0;
+        if (!seen.emplace(reinterpret_cast<const char*>(&c), sizeof(c)).second) return;
         out->push_back(r);
     };
     for (int ns : {1, 4, 16, 64}) {
@@ -1209,6 +1223,17 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
     // the densified tile on the matrix cores (16- and 8-bit activations): output-channel block x
     // tile of positions (rows of one sample, or whole planes of several) x workgroups per CU
     if (p.dtype != SC_F32 && !p.has_dup && p.n > 0) {
+        // one-shot form, the contraction split otherwise than by the default (one group of four waves, two of eight):
+        // the same tiles with as many groups as there are waves for, and with blocks of 16 output channels
+        for (int db : {16, 32, 64, 128}) for (int wm : {1, 2, 4}) for (int wpc : {1, 2}) for (int thr : {256, 512}) for (int kg : {1, 2, 4, 8}) {
+            if (db % (16 * wm) || db / (16 * wm) > 4 || (db > 32 && db >= 2 * p.L.D) || thr / 64 % (wm * kg) || kg == thr / 256 || (db == 16 && kg < 4)) continue;
+            auto base = [&]() { sc_tuning_t t{}; t.variant = SC_VARIANT_DENSE; t.tile_d = db; t.waves_m = wm; t.wg_per_cu = wpc; t.wg_threads = thr; t.buffers = kg; return t; };
+            for (int tp : {1, 2, 4, 7, 8, 14, 16}) {
+                if (tp >= p.P) continue;
+                sc_tuning_t t = base(); t.tile_p = tp; push(t);
+            }
+            for (int ns : {1, 2, 4, 8, 16}) { sc_tuning_t t = base(); t.tile_p = p.P; t.sub_batch = ns; push(t); }
+        }
         for (int db : {32, 64, 128}) for (int wm : {1, 2, 4}) for (int wpc : {1, 2, 3}) {
             if (db % (16 * wm) || db / (16 * wm) > 4 || (db > 32 && db >= 2 * p.L.D)) continue;
             for (int thr : {256, 512}) {

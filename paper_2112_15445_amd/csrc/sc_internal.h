@@ -68,7 +68,10 @@ struct MfmaGeom {
     int pitch;             // bytes per staged position
     int DB, ndb;           // output channels per workgroup, blocks of them
     int WM, MW, NW;        // waves along the output channels; 16-row / 16-column blocks per wave
-    int KG;                // groups of four waves that split the steps of the contraction (1 or 2)
+    int KG;                // groups of waves that split the steps of the contraction (1 or 2; the one-shot form also 4 or 8)
+    int waves, WN;         // multiplying waves of the workgroup; those along the positions, waves / (WM KG)
+    int minrun;            // one-shot form: the shortest run of input elements that a tile stages at once (0: none)
+    int flat;              // the staged rows of a sample are one contiguous run per channel
     int PW;                // pipelined form: waves that stage the chunks (0 = the one-shot form)
     int bufsz;             // bytes of one chunk buffer
     int nat;               // 1 = pointwise layer staged in its natural layout ([channel][position])
@@ -156,7 +159,7 @@ void library_conv_destroy(LibraryConv* c);
 int mfma_chan_block(sc_dtype_t dt);
 size_t mfma_weight_bytes(const Plan& p);
 sc_status_t mfma_densify(const Plan& p, unsigned char* out, hipStream_t stream);
-bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int lds_budget, MfmaGeom* out, int KG = 1, int PW = 0, int nat = 0, int DL = 1);
+bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int lds_budget, MfmaGeom* out, int waves = 4, int KG = 1, int PW = 0, int nat = 0, int DL = 1);
 inline bool has_epilogue(const Plan& p) { return p.epi.relu || p.epi.pool || p.epi.requant; }
 int mfma_grid_size(const Plan& p, const MfmaGeom& g, int N);
 sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_t stream);

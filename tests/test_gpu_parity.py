@@ -1785,3 +1785,90 @@ def test_requantised_codes_stored_four_positions_at_a_time(dtype, C, D, H, W, k,
             ran += 1
     assert ran >= 8
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8", "cb4", "cb4h"])
+@pytest.mark.parametrize("name,C,D,H,W,R,S,sh,sw,ph,pw,N", [
+    ("odd_runs", 70, 37, 9, 13, 3, 3, 1, 1, 1, 1, 3),            # rows of 13: loads that end before a run's end
+    ("short_runs", 130, 20, 5, 3, 3, 3, 1, 1, 1, 1, 7),          # runs shorter than the widest load; groups of four over samples
+    ("flat", 147, 50, 1, 23, 1, 3, 1, 1, 0, 0, 5),               # rows without padding columns, 21 positions a sample
+    ("flat7", 40, 130, 7, 7, 1, 1, 1, 1, 0, 0, 6),
+    ("strided", 33, 16, 11, 10, 3, 3, 2, 2, 1, 1, 4),
+    ("padding_tiles", 16, 33, 3, 4, 1, 1, 1, 1, 4, 4, 2),        # tiles that lie in the padding altogether
+    ("one_step", 8, 64, 6, 6, 1, 1, 1, 1, 0, 0, 2)])             # fewer steps than groups that split them
+def test_dense_contraction_split_among_the_waves(name, C, D, H, W, R, S, sh, sw, ph, pw, N, dtype):
+    """tuning.buffers on the one-shot matrix-core tile: 1, 2, 4 or 8 groups of waves split the contraction and meet in
+    LDS, with every layout of four and eight waves, tiles of rows and whole planes of several samples, one and
+    several chunks, and inputs that start at any element; other values are refused."""
+    import torch
+    l = wl.Layer(name, C, D, H, W, R, S, sh, sw, ph, pw, N=N, sparsity=0.6, dtype=dtype, seed=901)
+    data = wl.prepare(l)
+    ref = G.oracle_out(l, data)
+    plan = G.make_plan(l, data)
+    ran = set()
+    for threads in (256, 512):
+        for kg in (1, 2, 4, 8):
+            for wm, td in ((1, 16), (1, 64), (2, 32), (2, 128), (4, 64)):
+                for extra in ({"tile_p": 2}, {"tile_p": 1000, "sub_batch": 3}, {"tile_p": 1, "chunk_c": 64}):
+                    try:
+                        plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, wg_threads=threads, waves_m=wm, tile_d=td, buffers=kg, **extra)
+                    except B.SparseConvError as e:
+                        assert e.status == 4
+                        continue
+                    t = plan.get_tuning()
+                    assert t.buffers == (0 if kg == threads // 256 else kg)
+                    print("case split", name, dtype, t.as_dict(), flush=True)
+                    G.check(l, G.run_gpu(plan, data["x"]), ref, f"{name} split {threads} {kg} {wm} {td} {extra}")
+                    ran.add(kg)
+    assert ran == {1, 2, 4, 8}, ran
+    # x that is aligned to its elements only
+    xd = G.to_device(np.ascontiguousarray(data["x"]))
+    raw = torch.empty(xd.numel() + 1, dtype=xd.dtype, device="cuda")
+    raw[1:].copy_(xd.reshape(-1))
+    y = torch.empty((N, D, plan.info().P, plan.info().Q), dtype=B.torch_out_dtype(plan.dtype), device="cuda")
+    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, wg_threads=512, waves_m=1, tile_d=32, tile_p=1)
+    plan.forward(raw[1:].data_ptr(), y.data_ptr(), N, 0, 0, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    G.check(l, G.to_host(y), ref, f"{name} shifted x")
+    for bad in ({"buffers": 3}, {"buffers": 16}, {"buffers": 4, "waves_m": 4}, {"buffers": 2, "pipeline": 1}, {"buffers": 2, "split_n": 2, "tile_d": 16}):
+        with pytest.raises(B.SparseConvError) as e:
+            plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, **{"wg_threads": 512, **bad})
+        assert e.value.status == 4
+    plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("C,D,H,W,N", [(70, 40, 8, 16, 3), (64, 24, 6, 8, 5), (40, 33, 4, 4, 7), (33, 18, 5, 7, 4)])
+def test_dense_epilogue_with_the_contraction_split(C, D, H, W, N, dtype):
+    """The fused epilogue behind 1, 2, 4 and 8 groups of waves: pooled rows of whole groups of four outputs and odd
+    ones, tiles of rows and planes of several samples, requantised codes (bit-exact) and fp16."""
+    import oracle
+    l = wl.Layer("episplit", C, D, H, W, 3, 3, 1, 1, 1, 1, N=N, sparsity=0.6, dtype=dtype, seed=902)
+    data = wl.prepare(l)
+    acc = oracle.sparse_conv(data["x"], data["rowptr"], data["colidx"], data["values"], l.R, l.S, (1, 1), (1, 1),
+                             codebook=data["codebook"], out_dtype=np.int32 if dtype == "i8" else np.float32)
+    plan = G.make_plan(l, data)
+    rq = (100.0 / max(1.0, float(np.abs(acc).max())) * (0.5 + np.random.default_rng(3).random(D))).astype(np.float32) if dtype == "i8" else None
+    for relu, pool, requant in ((1, 2, 1), (1, 0, 1), (1, 2, 0), (0, 2, 0), (1, 0, 0)):
+        if requant and dtype != "i8":
+            continue
+        plan.set_epilogue(relu=relu, pool=pool, requant_scale=rq if requant else None)
+        out_dt = np.int8 if requant else G.NP_OUT[dtype]
+        ref = oracle.epilogue(acc, relu=bool(relu), pool=pool, requant_scale=rq if requant else None, out_dtype=None if requant else G.NP_OUT[dtype])
+        ran = set()
+        for threads, kg, wm, td in ((256, 1, 2, 32), (256, 4, 1, 32), (512, 1, 2, 64), (512, 2, 2, 64), (512, 4, 1, 16), (512, 4, 2, 32), (512, 8, 1, 32)):
+            for extra in ({"tile_p": 2}, {"tile_p": 4}, {"tile_p": 1000, "sub_batch": 2}):
+                try:
+                    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, wg_threads=threads, waves_m=wm, tile_d=td, buffers=kg, **extra)
+                except B.SparseConvError as e:
+                    assert e.status == 4
+                    continue
+                print("case episplit", dtype, (relu, pool, requant), plan.get_tuning().as_dict(), flush=True)
+                got = _run_epi(plan, l, data["x"], out_dt)
+                if dtype == "i8":
+                    assert np.array_equal(got, ref), (relu, pool, requant, threads, kg, extra, np.count_nonzero(got != ref))
+                else:
+                    G.check(l, got, ref, f"episplit {(relu, pool)} {threads} {kg} {extra}")
+                ran.add(kg)
+        assert ran == {1, 2, 4, 8}, ran
+    plan.destroy()
