@@ -6,18 +6,21 @@
 //   * the loads of the first chunk are requested before anything else is worked out; weights, LDS zeroing, the
 //     lanes' positions and the table of steps are prepared while they are on their way;
 //   * staging moves whole registers: blocks of 8 (16) channels x up to 8 columns, transposed by byte
-//     permutations, and four neighbouring lanes take four channel groups of the same columns, so that their
-//     16-byte LDS writes fall into different banks (with the column groups on neighbouring lanes the writes
-//     were up to 8-way conflicts);
+//     permutations; of 16 neighbouring lanes, four take neighbouring blocks of one channel group and the next fours the next
+//     channel groups.  The address unit joins only neighbouring lanes to lines, so that a load wants as many of them
+//     along a row as it can get, while a 16-byte LDS write of 16 lanes falls into different banks with four channel
+//     groups beside each other (all 16 lanes along a row: up to 8-way conflicts; four channel groups on every four lanes, the
+//     first arrangement here: a quarter of a line for each lane group);
 //   * weights come through the vector L1, which was measured at 40 - 45 bytes a clock and CU whatever the number
 //     of loads in flight: what a workgroup reads of them is what counts.  The eight waves may therefore
 //     split the contraction up to eight ways (KG) over one tile of outputs instead of fetching the
 //     same weights for several tiles; their sums meet in LDS;
 //   * the operands are exchanged (positions are the rows of the matrix instruction, channels its columns), so
 //     that a lane holds four neighbouring positions of one channel and stores them as one word.
-// Measured per pass, before (staging by whole rows of blocks, one or two groups, 2-byte stores) and after: f16 3x3
-// 64-64 at 56 x 56, batch 32 19.5 -> 15.7 us; f16 3x3 256-256 at 14 x 14, batch 32 19.0 -> 15.0; 4b/16b 3x3 512-512 at
-// 4 x 4, batch 64 19.8 -> 13.2; the 13 int8 layers of VGG-16, batch 64 170 -> 133.
+// Measured per pass: before this kernel (staging by whole rows of blocks, one or two groups, 2-byte stores), with four channel
+// groups on every four lanes, and with the 4 x 4 lanes (eight blocks of a row x 2 channel groups is level, 15.7 / 14.2 / 12.2 / 126):
+// f16 3x3 64-64 at 56 x 56, batch 32 19.4, 15.7, 15.2 us; f16 3x3 256-256 at 14 x 14, batch 32 19.0, 15.0, 14.1; 4b/16b 3x3
+// 512-512 at 4 x 4, batch 64 19.7, 13.2, 11.3 - 11.8; the 13 int8 layers of VGG-16, batch 64 170, 133, 126 - 128.
 #pragma once
 
 #include "dense_mfma_kernel.h"
@@ -33,10 +36,10 @@ namespace sc {
 struct TileStage {
     const char* xs;              // first staged element of sample 0, channel 0 of the chunk
     unsigned sample_b, plane_b, row_b;   // bytes per sample, channel and input row
-    int nblocks, rowsG, per_cg4, G, run, cleft, dst0;
+    int nblocks, rowsG, per_cg, quads, G, run, cleft, dst0;      // blocks (dead ones of the last quad of a channel group too)
     int npos1, Ws;
     bool whole;                  // every channel of the chunk's groups exists in the layer
-    float inv_per_cg4, inv_rowsG, inv_G;
+    float inv_quads, inv_rowsG, inv_G;
 };
 
 __device__ __forceinline__ int tdiv(int e, float inv) { return (int)__builtin_fmaf((float)e, inv, 0.5f * inv); }   // as fdiv19
@@ -45,17 +48,17 @@ template <typename X> constexpr int kTileCV = 16 / (int)sizeof(X);
 template <typename X, int EPV> constexpr int kTileWPE = EPV * (int)sizeof(X) >= 4 ? EPV * (int)sizeof(X) / 4 : 1;
 template <typename X, int EPV> constexpr int kTileVB = 32 / (kTileCV<X> * kTileWPE<X, EPV>);    // blocks per thread and round
 
-// block v: channel group, sample, row, first column (false: past the end, then block v mod 4)
+// block v: channel group, sample, row, first column (false: none, then a block of the first channel groups)
 template <int EPV>
 __device__ __forceinline__ bool tile_block(const TileStage& st, int v, int& cg, int& sm, int& ii, int& col)
 {
-    const bool live = v < st.nblocks;
-    int r = live ? v >> 2 : 0;
-    const int cg4 = tdiv(r, st.inv_per_cg4);
-    cg = cg4 * 4 + (v & 3);
-    r -= cg4 * st.per_cg4;
+    int cg4 = tdiv(v >> 4, st.inv_quads);
+    int r = ((v >> 4) - cg4 * st.quads) * 4 + (v & 3);
+    const bool live = v < st.nblocks && r < st.per_cg;
+    if (!live) cg4 = r = 0;
+    cg = cg4 * 4 + (v >> 2 & 3);
     sm = 0;
-    if (st.rowsG != st.per_cg4) { sm = tdiv(r, st.inv_rowsG); r -= sm * st.rowsG; }
+    if (st.rowsG != st.per_cg) { sm = tdiv(r, st.inv_rowsG); r -= sm * st.rowsG; }
     ii = 0;
     if (st.rowsG != st.G) { ii = tdiv(r, st.inv_G); r -= ii * st.G; }
     col = min(r * EPV, st.run - EPV);
@@ -249,9 +252,10 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         st.run = a.flat ? nrows * a.W : max(0, min(a.W, a.Ws - a.pad_w));
         st.G = (st.run + (1 << a.lepv) - 1) >> a.lepv;
         st.rowsG = rows * st.G;
-        st.per_cg4 = nsv * st.rowsG;
-        st.nblocks = (a.CC / CV) * st.per_cg4;
-        st.inv_per_cg4 = __builtin_amdgcn_rcpf((float)max(st.per_cg4, 1));
+        st.per_cg = nsv * st.rowsG;
+        st.quads = (st.per_cg + 3) >> 2;
+        st.nblocks = (a.CC / CV) * st.quads * 4;
+        st.inv_quads = __builtin_amdgcn_rcpf((float)max(st.quads, 1));
         st.inv_rowsG = __builtin_amdgcn_rcpf((float)max(st.rowsG, 1));
         st.inv_G = __builtin_amdgcn_rcpf((float)max(st.G, 1));
         st.dst0 = ilo * a.Ws + a.pad_w;

@@ -1872,3 +1872,28 @@ def test_dense_epilogue_with_the_contraction_split(C, D, H, W, N, dtype):
                 ran.add(kg)
         assert ran == {1, 2, 4, 8}, ran
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("W", [1, 2, 3, 7, 8, 9, 16, 17, 25, 33, 40])
+def test_dense_staging_deals_blocks_by_fours(W, dtype):
+    """The blocks of a channel group are dealt to the lanes four at a time: 1 .. 5 and more of them in a tile, whole and
+    shared last blocks, one and several samples, rows that carry padding and rows staged as one run, a last channel group that is not whole."""
+    for C, H, pad, N in ((40, 1, 0, 3), (150, 3, 1, 2), (64, 2, 1, 5)):
+        l = wl.Layer("quads", C, 24, H, W, 1 if H == 1 else 3, 1 if W < 3 and not pad else 3, 1, 1, pad if H > 1 else 0, pad, N=N, sparsity=0.5, dtype=dtype, seed=910 + W)
+        data = wl.prepare(l)
+        ref = G.oracle_out(l, data)
+        plan = G.make_plan(l, data)
+        ran = 0
+        for threads in (256, 512):
+            for extra in ({"tile_p": 1}, {"tile_p": 1000, "sub_batch": 2}, {"tile_p": 1000, "sub_batch": 4, "chunk_c": 64}):
+                try:
+                    plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, wg_threads=threads, waves_m=1, tile_d=32, **extra)
+                except B.SparseConvError as e:
+                    assert e.status == 4
+                    continue
+                print("case quads", dtype, C, H, W, plan.get_tuning().as_dict(), flush=True)
+                G.check(l, G.run_gpu(plan, data["x"]), ref, f"quads {C} {H} {W} {threads} {extra}")
+                ran += 1
+        assert ran >= 2
+        plan.destroy()
