@@ -281,7 +281,7 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
         a.inv_ntiles = 1.0f / (float)a.ntiles;
         // Order of the workgroups: by tile, but where the weights outgrow the 4 MB L2 of an XCD by block of output
         // channels, if an XCD then reads less in all (its share of the weights and of the input against all weights and an
-        // eighth of the input).  4b/16b 3x3 512-512 at 4 x 4, batch 64, 4.7 MB of weights: 12.9 us so, 14.0 by tile; below
+        // eighth of the input).  4b/16b 3x3 512-512 at 4 x 4, batch 64, 4.7 MB of weights: 12.9 us so, 14.0 by tile (both with an earlier order of the staging, 11.3 now); below
         // 2.4 MB level (int8) or 4 % slower (f16 3x3 256-256 at 14 x 14, 1.2 MB: 15.9 for 15.3).
         const double w = (double)mfma_weight_bytes(p), xin = (double)N * p.L.C * p.L.H * p.L.W * p.ex;
         a.wmajor = w > 3.0 * (1 << 20) && w / std::min(8.0, (double)g.ndb) + xin * std::min(1.0, g.ndb / 8.0) < w + xin / 8.0 ? 1 : 0;
