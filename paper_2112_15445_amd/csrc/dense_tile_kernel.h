@@ -17,10 +17,10 @@
 //     same weights for several tiles; their sums meet in LDS;
 //   * the operands are exchanged (positions are the rows of the matrix instruction, channels its columns), so
 //     that a lane holds four neighbouring positions of one channel and stores them as one word.
-// Measured per pass: before this kernel (staging by whole rows of blocks, one or two groups, 2-byte stores), with four channel
-// groups on every four lanes, and with the 4 x 4 lanes (eight blocks of a row x 2 channel groups is level, 15.7 / 14.2 / 12.2 / 126):
-// f16 3x3 64-64 at 56 x 56, batch 32 19.4, 15.7, 15.2 us; f16 3x3 256-256 at 14 x 14, batch 32 19.0, 15.0, 14.1; 4b/16b 3x3
-// 512-512 at 4 x 4, batch 64 19.7, 13.2, 11.3 - 11.8; the 13 int8 layers of VGG-16, batch 64 170, 133, 126 - 128.
+// Measured per pass: before this kernel (staging by whole rows of blocks, one or two groups, 2-byte stores), and in turn on one card with
+// four channel groups on every four lanes and with the 4 x 4 lanes: f16 3x3 64-64 at 56 x 56, batch 32 19.4, 15.7, 15.5 us;
+// f16 3x3 256-256 at 14 x 14, batch 32 19.0, 15.0, 14.5; 4b/16b 3x3 512-512 at 4 x 4, batch 64 19.7, 13.2, 11.4 - 12.2; the
+// 13 int8 layers of VGG-16, batch 64 170, 132, 123 - 126.
 #pragma once
 
 #include "dense_mfma_kernel.h"
