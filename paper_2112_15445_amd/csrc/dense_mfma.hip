@@ -130,6 +130,9 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
     g.nat = nat;
     g.DB = DB;
     g.ndb = (L.D + DB - 1) / DB;
+    // (a layer of one block has nothing to walk over: the plain one-shot form, in everything that follows)
+    if (DL < 1 || DL > 16) return false;
+    g.DL = DL = std::min(DL, g.ndb);
     // the waves: KG groups that split the contraction; of a group WM along the output channels (MW 16-channel
     // blocks each), the others along the positions (NW blocks of 16 each, at most 8)
     if (WM != 1 && WM != 2 && WM != 4) return false;
@@ -194,8 +197,6 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
         lds = std::max<int64_t>(lds, (int64_t)g.DB * g.epi_pitch * 4);
     }
     // several output-channel blocks per workgroup: the tile stays in LDS, so one chunk, no exchange through LDS
-    if (DL < 1 || DL > 16) return false;
-    g.DL = std::min(DL, g.ndb);
     if (g.DL > 1 && (g.nchunks != 1 || KG != 1 || PW || (has_epilogue(p) && p.epi.pool))) return false;
     if (lds > lds_budget || lds > kMaxLdsBytes) return false;
     g.lds_bytes = (int)((lds + 15) / 16 * 16);

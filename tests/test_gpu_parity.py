@@ -1897,3 +1897,37 @@ def test_dense_staging_deals_blocks_by_fours(W, dtype):
                 ran += 1
         assert ran >= 2
         plan.destroy()
+
+
+@pytest.mark.parametrize("pool", [0, 2])
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("D,tile_d,threads,split_n", [(37, 64, 256, 2), (16, 16, 256, 16), (37, 64, 512, 2), (130, 128, 256, 16)])
+def test_dense_blocks_per_workgroup_more_than_the_layer_has(D, tile_d, threads, split_n, dtype, pool):
+    """tuning.split_n beyond the blocks of output channels of the layer is cut to them, and to the plain one-shot form where
+    there is one: the tile that runs is the one that the plan reports, so that installing the report again changes nothing."""
+    import oracle
+    l = wl.Layer("dlclamp", 40, D, 8, 16, 3, 3, 1, 1, 1, 1, N=3, sparsity=0.6, dtype=dtype, seed=920)
+    data = wl.prepare(l)
+    plan = G.make_plan(l, data)
+    plan.set_epilogue(relu=False, pool=pool)
+    shape = dict(variant=B.SC_VARIANT_DENSE, tile_d=tile_d, waves_m=2 if tile_d == 128 else 1, wg_threads=threads, split_n=split_n, tile_p=2)
+    if pool and D > tile_d:                                  # (several blocks on one tile do not pool)
+        with pytest.raises(B.SparseConvError) as e:
+            plan.set_tuning(B.sc_tuning_t(), **shape)
+        assert e.value.status == 4
+        plan.destroy()
+        return
+    ref = oracle.epilogue(oracle.sparse_conv(data["x"], data["rowptr"], data["colidx"], data["values"], l.R, l.S, (1, 1), (1, 1),
+                                             out_dtype=np.int32 if dtype == "i8" else np.float32), relu=False, pool=pool, out_dtype=G.NP_OUT[dtype])
+    plan.set_tuning(B.sc_tuning_t(), **shape)
+    first, lds = plan.get_tuning(), plan.info().lds_bytes
+    blocks = -(-D // tile_d)
+    assert first.split_n == (min(split_n, blocks) if blocks > 1 else 0)
+    plan.set_tuning(first)
+    assert plan.get_tuning().as_dict() == first.as_dict() and plan.info().lds_bytes == lds
+    for k in range(2):
+        if k:
+            plan.set_tuning(B.sc_tuning_t(), **shape)
+        print("case dlclamp", D, dtype, pool, plan.get_tuning().as_dict(), plan.info().lds_bytes, flush=True)
+        G.check(l, _run_epi(plan, l, data["x"], G.NP_OUT[dtype]), ref, f"dlclamp {D} {pool} {k}")
+    plan.destroy()
