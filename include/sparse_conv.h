@@ -101,9 +101,10 @@ enum {
  * Fields that do not apply to a variant are ignored.  All-zero = SC_VARIANT_AUTO. */
 typedef struct {
     int32_t variant;    /* SC_VARIANT_* */
-    int32_t wg_threads; /* workgroup size: 64..1024, multiple of 64.  DENSE: 256 (0 = that) or 512 -- with 512 two
-                           groups of four waves own the same outputs and take the even and the odd steps
-                           of the contraction (filter tap x channel block), meeting through LDS at the end */
+    int32_t wg_threads; /* workgroup size: 64..1024, multiple of 64.  DENSE: 256 (0 = that, but 512 with buffers = 8) or
+                           512 -- with 512 (and buffers = 0) two groups of four waves own the same outputs and take the
+                           even and the odd steps of the contraction (filter tap x channel block), meeting through
+                           LDS at the end */
     int32_t sub_batch;  /* GATHER: output positions per thread that share each (theta, lambda) read
                            from LDS (the role of sb_S), 1, 2, 4 or 8.  SLAB with pipeline = 0 and
                            chunk_c > 0: samples per workgroup (0 / 1 = one; 2..4 for tiles of at most
@@ -193,8 +194,9 @@ typedef struct {
                            feeds that many samples; at most 8 / word-size positions per lane */
     int32_t waves_m;    /* DENSE: how many of a group's waves (four, but see buffers) lie along the output channels
                            (1, 2 or 4; the others along the positions).  A wave then owns tile_d / waves_m
-                           output channels (16, 32 or 64) and up to 128 positions.  0 = heuristic */
-    int32_t buffers;    /* DENSE, one-shot form (pipeline, split_n and stage_rows 0): 1, 2, 4 or 8 groups of waves split
+                           output channels (16, 32 or 64) and up to 128 positions.  0 = heuristic, at most the waves
+                           of a group */
+    int32_t buffers;    /* DENSE, one-shot form (pipeline and stage_rows 0, split_n at most 1): 1, 2, 4 or 8 groups of waves split
                            the steps of the contraction (filter tap x channel block) among them and meet through
                            LDS (a fixed summation order); waves_m waves of a group lie along the output channels, the
                            others along the positions, so that waves_m x buffers must divide the 4 or 8 waves.

@@ -270,19 +270,24 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     const int CB = mfma_chan_block(p.dtype);
     // 256 threads: four waves; 512: two groups of four that split the steps of the contraction
     if (t.wg_threads != 0 && t.wg_threads != 256 && t.wg_threads != 512) return SC_ERR_UNSUPPORTED;
-    const int waves = t.wg_threads == 512 ? 8 : 4;
+    // (by default four waves; eight groups of waves need eight)
+    const int waves = t.wg_threads == 512 || (t.wg_threads == 0 && t.buffers == 8) ? 8 : 4;
     // buffers = 1, 2, 4 or 8: that many groups of waves split the contraction (one-shot form on the transposed tile)
     if (t.buffers != 0 && t.buffers != 1 && t.buffers != 2 && t.buffers != 4 && t.buffers != 8) return SC_ERR_UNSUPPORTED;
     if (t.buffers && (t.pipeline || nat || DL > 1)) return SC_ERR_UNSUPPORTED;
     const int KG = t.buffers ? t.buffers : waves / 4;
     if (t.waves_m != 0 && t.waves_m != 1 && t.waves_m != 2 && t.waves_m != 4) return SC_ERR_UNSUPPORTED;
+    // (more groups leave fewer waves to a group: the default tile is what those can own, 64 channels a wave, or 32
+    // where a wave of 64, which holds 64 positions, could not take one row of outputs)
+    const int group = waves / KG;
+    if (group < 1) return SC_ERR_UNSUPPORTED;
     int DB = t.tile_d;
-    if (DB == 0) DB = L.D > 64 ? 128 : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16));
+    if (DB == 0) DB = std::min(L.D > 64 ? 128 : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16)), (p.Q > 64 ? 32 : 64) * group);
     // waves along the output channels: by default as many as still leave every wave 32 channels
     // (two 16-row blocks), so that the weights, which every wave fetches for itself from L2, are
     // fetched by few waves each
     int WM = t.waves_m;
-    if (WM == 0) WM = DB >= 128 ? 4 : (DB >= 64 ? 2 : 1);
+    if (WM == 0) WM = std::min(DB >= 128 ? 4 : (DB >= 64 ? 2 : 1), group);
     if (DB % (16 * WM) || DB / (16 * WM) < 1 || DB / (16 * WM) > 4) return SC_ERR_UNSUPPORTED;
     const int MWv = DB / (16 * WM);
     if (waves % (WM * KG)) return SC_ERR_UNSUPPORTED;

@@ -1931,3 +1931,29 @@ def test_dense_blocks_per_workgroup_more_than_the_layer_has(D, tile_d, threads, 
         print("case dlclamp", D, dtype, pool, plan.get_tuning().as_dict(), plan.info().lds_bytes, flush=True)
         G.check(l, _run_epi(plan, l, data["x"], G.NP_OUT[dtype]), ref, f"dlclamp {D} {pool} {k}")
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("D,W", [(20, 9), (37, 9), (100, 9), (300, 9), (37, 80), (100, 80), (100, 128)])
+def test_dense_defaults_beside_the_contraction_split(D, W, dtype):
+    """tuning.buffers with every other field left to the heuristics: waves_m, tile_d and wg_threads follow the waves that the groups
+    leave, and only more groups than waves are refused."""
+    l = wl.Layer("splitdef", 70, D, 5, W, 3, 3, 1, 1, 1, 1, N=2, sparsity=0.6, dtype=dtype, seed=930)
+    data = wl.prepare(l)
+    ref = G.oracle_out(l, data)
+    plan = G.make_plan(l, data)
+    for threads in (0, 256, 512):
+        for kg in (0, 1, 2, 4, 8):
+            shape = dict(variant=B.SC_VARIANT_DENSE, wg_threads=threads, buffers=kg)
+            if (threads, kg) == (256, 8):
+                with pytest.raises(B.SparseConvError) as e:
+                    plan.set_tuning(B.sc_tuning_t(), **shape)
+                assert e.value.status == 4
+                continue
+            plan.set_tuning(B.sc_tuning_t(), **shape)
+            t = plan.get_tuning()
+            waves = 8 if threads == 512 or kg == 8 else 4
+            assert t.wg_threads == 64 * waves and t.buffers == (0 if kg == waves // 4 else kg)
+            print("case splitdef", D, W, dtype, t.as_dict(), flush=True)
+            G.check(l, G.run_gpu(plan, data["x"]), ref, f"splitdef {D} {W} {threads} {kg}")
+    plan.destroy()
