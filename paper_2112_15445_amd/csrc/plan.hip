@@ -251,7 +251,8 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
 {
     const sc_layer_t& L = p.L;
     if (p.dtype == SC_F32 || p.has_dup || p.n == 0) return SC_ERR_UNSUPPORTED;
-    if (t.wg_per_cu == 0) t.wg_per_cu = 2;
+    // (eight waves that split the contraction four ways and more hand on up to 128 KB of sums through LDS)
+    if (t.wg_per_cu == 0) t.wg_per_cu = t.buffers == 8 || (t.buffers == 4 && t.wg_threads == 512) ? 1 : 2;
     if (t.wg_per_cu < 1 || t.wg_per_cu > 8) return SC_ERR_UNSUPPORTED;
     if (t.tile_p < 0 || t.sub_batch < 0 || t.chunk_c < 0 || t.tile_d < 0) return SC_ERR_UNSUPPORTED;
     if (t.wsrc || t.ragged || t.pack || t.tile_q) return SC_ERR_UNSUPPORTED;
@@ -278,11 +279,11 @@ static sc_status_t resolve_dense(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     const int KG = t.buffers ? t.buffers : waves / 4;
     if (t.waves_m != 0 && t.waves_m != 1 && t.waves_m != 2 && t.waves_m != 4) return SC_ERR_UNSUPPORTED;
     // (more groups leave fewer waves to a group: the default tile is what those can own, 64 channels a wave, or 32
-    // where a wave of 64, which holds 64 positions, could not take one row of outputs)
+    // where a wave of 64, which holds 64 positions, could not take the least tile: a row of outputs, two under pooling)
     const int group = waves / KG;
     if (group < 1) return SC_ERR_UNSUPPORTED;
     int DB = t.tile_d;
-    if (DB == 0) DB = std::min(L.D > 64 ? 128 : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16)), (p.Q > 64 ? 32 : 64) * group);
+    if (DB == 0) DB = std::min(L.D > 64 ? 128 : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16)), (p.Q * (p.epi.pool ? 2 : 1) > 64 ? 32 : 64) * group);
     // waves along the output channels: by default as many as still leave every wave 32 channels
     // (two 16-row blocks), so that the weights, which every wave fetches for itself from L2, are
     // fetched by few waves each
