@@ -70,17 +70,17 @@ __device__ inline int fdiv19(int e, float inv) { return (int)(((float)e + 0.5f) 
 // the 8 XCDs: they are renumbered so that each XCD gets a contiguous run.  Within it either the blocks of one tile
 // are neighbours (they find the tile in the L2 that their siblings loaded), or, where the weights outweigh the
 // input (a.wmajor), the tiles of one block: an XCD then streams its share of the weights and not all of them.
-__device__ __forceinline__ void mfma_block(const MfmaArgs& a, int ndb, float inv_ndb, int& bt, int& db)
+// Both indices are chosen by value and made wave-uniform: written through references in two branches they went
+// through scratch memory, a store and a load before the first address could be formed, and everything derived from them
+// was vector arithmetic (all 26 tile kernels: 12 bytes of scratch and 15 - 18 vector registers more).
+struct MfmaBlock { int bt, db; };
+__device__ __forceinline__ MfmaBlock mfma_block(const MfmaArgs& a)
 {
     const int q = gridDim.x >> 3, r = gridDim.x & 7, xcd = blockIdx.x & 7;
     const int wg = xcd * q + min(xcd, r) + (int)(blockIdx.x >> 3);
-    if (a.wmajor) {
-        db = fdiv19(wg, a.inv_ntiles);
-        bt = wg - db * a.ntiles;
-    } else {
-        bt = fdiv19(wg, inv_ndb);
-        db = wg - bt * ndb;
-    }
+    const int inner = a.wmajor ? a.ntiles : a.ndb;
+    const int hi = __builtin_amdgcn_readfirstlane(fdiv19(wg, a.wmajor ? a.inv_ntiles : a.inv_ndb)), lo = wg - hi * inner;
+    return {a.wmajor ? lo : hi, a.wmajor ? hi : lo};
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -65,6 +65,18 @@ __device__ __forceinline__ bool tile_block(const TileStage& st, int v, int& cg, 
     return live;
 }
 
+// Address of a staging load, whole in the lane's registers.  Left to itself the compiler takes the scalar base and the 32-bit
+// offset apart (global_load v, v, s[]), and loads in that form that are not aligned to their width are slower than
+// those from a 64-bit lane address, 16.4 us for 13.6 (4-bit 1x1 1633-18 at 15 x 14, batch 58, rows of 210 bytes),
+// 10.7 for 9.2 (f16 3x3 33-93 at 13 x 13, batch 20, tuned for two rows a tile); aligned ones are level.
+using TileSrc = const __attribute__((address_space(1))) char*;
+__device__ __forceinline__ TileSrc tile_src(const char* base, unsigned off)
+{
+    uint64_t ad = reinterpret_cast<uint64_t>(base) + off;
+    asm("" : "+v"(ad));
+    return reinterpret_cast<TileSrc>(ad);
+}
+
 template <typename X, int EPV>
 __device__ __forceinline__ void tile_load(unsigned (&pre)[32], const TileStage& st, int v0, int NT)
 {
@@ -78,19 +90,19 @@ __device__ __forceinline__ void tile_load(unsigned (&pre)[32], const TileStage& 
 #pragma unroll
         for (int j = 0; j < CV; ++j) {
             // (channels past the layer's last: the block's place in channel 0, zeroed when it is stored)
-            const char* src = st.xs + (st.whole || cg * CV + j < st.cleft ? o : off);
+            const TileSrc src = tile_src(st.xs, st.whole || cg * CV + j < st.cleft ? o : off);
             // (of any alignment: one load each all the same)
             if constexpr (B >= 4) {
                 unsigned e[W];
-                __builtin_memcpy(e, src, B);
+                __builtin_memcpy(e, (const void*)src, B);
 #pragma unroll
                 for (int w = 0; w < W; ++w) pre[(u * CV + j) * W + w] = e[w];
             } else if constexpr (B == 2) {
                 unsigned short e;
-                __builtin_memcpy(&e, src, 2);
+                __builtin_memcpy(&e, (const void*)src, 2);
                 pre[u * CV + j] = e;
             } else {
-                pre[u * CV + j] = *reinterpret_cast<const unsigned char*>(src);
+                pre[u * CV + j] = *reinterpret_cast<const __attribute__((address_space(1))) unsigned char*>(src);
             }
             o += st.plane_b;
         }
@@ -234,9 +246,9 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, kg = lane >> 4;
 
-    int bt, db;
-    mfma_block(a, a.ndb, a.inv_ndb, bt, db);
-    const int bg = fdiv19(bt, a.inv_tiles_p);
+    const MfmaBlock block = mfma_block(a);
+    const int bt = block.bt, db = block.db;
+    const int bg = __builtin_amdgcn_readfirstlane(fdiv19(bt, a.inv_tiles_p));
     const int tpi = bt - bg * a.tiles_p;
     const int b0 = bg * a.NS, p0 = tpi * a.TP;
     const int row0 = p0 * a.s_h - a.pad_h;
