@@ -521,10 +521,16 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
 //                             weight in 16: GATHER spreads a single image over more workgroups
 //   large tables              of twice as many entries, 128 or more a row: from 1 weight in 32 on, against either
 //                             (1.1 - 9 times as fast; one layer in 60 slower, 0.79)
+// (the fp16, int8 and codebook lines with the one-shot kernel of that time; the present one takes 0.69 of its time in the
+// mean over 742 such layers of another draw, with the tile that is chosen now, and 1.03 - 1.23 of it on 22 of them)
 // and the dense weights are at most 256 MB.  The tile is the one with the least estimated time of a batch of
 // 32: per workgroup the largest of its matrix instructions (22 clocks each with two waves on a SIMD,
 // 32 with one: measured), its weights and input through the vector L1 (64 bytes a clock) and its
-// operands from LDS (128 bytes a clock), plus a fixed 8000 clocks of start and drain.
+// operands from LDS (128 bytes a clock), plus a fixed 8000 clocks of start and drain.  (The vector L1 was measured at 40 - 45 on
+// the one-shot kernel; with 45 here the chosen tiles are no faster.)
+// Four and eight groups of waves (tuning.buffers) are taken only where they are no slower at a batch of 128 either: they pay
+// with small tiles, which stage the halo of the input again and again, and a batch of 32 may be too few workgroups for that to
+// show (int8 3x3 283-68 stride 2 at 20 x 17, batch 128: 52 us so, 31.8 with one group).
 // ------------------------------------------------------------------------------------------------
 static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t* out, MfmaGeom* mgeom)
 {
@@ -542,7 +548,7 @@ static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t*
     if ((split ? split_weight_bytes(p) : mfma_weight_bytes(p)) > ((size_t)256 << 20)) return false;
     const int terms = split ? 3 : 1, products = split ? (p.split_full ? 8 : 6) : 1;
     const int64_t steps = (int64_t)L.R * L.S * ((L.C + CB - 1) / CB);
-    double best = INFINITY;
+    struct Choice { double time = INFINITY, time128 = INFINITY; sc_tuning_t tuning{}; MfmaGeom geom{}; } best[2];      // tuning.buffers 0; 4 or 8
     const int layouts[][2] = {{32, 1}, {32, 2}, {64, 2}, {64, 4}, {128, 4}, {128, 2}, {64, 1}};
     for (int thr : {256, 512}) for (int kg : {0, 4, 8}) for (const auto& lw : layouts) for (int wpc : {1, 2}) for (int tile = 0; tile < 10; ++tile) {
         if (lw[0] > 32 && lw[0] >= 2 * L.D) continue;
@@ -560,18 +566,29 @@ static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t*
         if ((int64_t)g.NS * L.C * L.H * L.W >= (1ll << 29) || (int64_t)g.DB * g.npos >= (1 << 19) || g.npos_s >= (1 << 16) ||
             (int64_t)g.tiles_p * g.ndb >= (1 << 19))
             continue;
-        const double wgs = std::ceil(32.0 / g.NS) * g.tiles_p * g.ndb, per_cu = std::ceil(wgs / kNumCU);
-        const double resident = std::min(per_cu, (double)std::max(1, std::min(wpc, kMaxLdsBytes / std::max(g.lds_bytes, 1))));
-        const double clocks = thr / 256 * resident >= 2.0 ? 22.0 : 32.0;
-        const double group = split ? 4.0 : (double)(g.waves / g.KG);      // waves that share a step
-        const double mfma = (double)steps * g.MW * g.NW * group / 4.0 * products * clocks;
-        const double l1 = ((double)steps * group * g.MW * terms * 1024 + (double)g.npos_s * L.C * p.ex) / 64.0;
-        const double lds = (double)steps * group * g.NW * terms * 1024 / 128.0 + (double)g.npos_s * L.C * p.ex / 16.0 +
-                           (g.KG > 1 && !split ? 16.0 * (g.KG == 2 ? group : g.waves) * g.MW * g.NW : 0.0);
-        const double time = 8000.0 * std::ceil(per_cu / resident) + 3000.0 * g.nchunks * per_cu / resident + per_cu * std::max(mfma, std::max(l1, lds));
-        if (time < best) { best = time; *out = r; *mgeom = g; }
+        // clocks of a batch of N.  (Workgroups that share a CU: by LDS, and on the one-shot kernel by its registers, two waves
+        // per SIMD.)
+        auto estimate = [&](double N) {
+            const double wgs = std::ceil(N / g.NS) * g.tiles_p * g.ndb, per_cu = std::ceil(wgs / kNumCU);
+            const int room = kMaxLdsBytes / std::max(g.lds_bytes, 1);
+            const double resident = std::min(per_cu, (double)std::max(1, split ? std::min(wpc, room) : std::min(8 / g.waves, room)));
+            const double clocks = thr / 256 * resident >= 2.0 ? 22.0 : 32.0;
+            const double group = split ? 4.0 : (double)(g.waves / g.KG);      // waves that share a step
+            const double mfma = (double)steps * g.MW * g.NW * group / 4.0 * products * clocks;
+            const double l1 = ((double)steps * group * g.MW * terms * 1024 + (double)g.npos_s * L.C * p.ex) / 64.0;
+            const double lds = (double)steps * group * g.NW * terms * 1024 / 128.0 + (double)g.npos_s * L.C * p.ex / 16.0 +
+                               (g.KG > 1 && !split ? 16.0 * (g.KG == 2 ? group : g.waves) * g.MW * g.NW : 0.0);
+            return 8000.0 * std::ceil(per_cu / resident) + 3000.0 * g.nchunks * per_cu / resident + per_cu * std::max(mfma, std::max(l1, lds));
+        };
+        Choice& c = best[kg != 0];
+        const double time = estimate(32.0);
+        if (time < c.time) c = Choice{time, estimate(128.0), r, g};
     }
-    return best < INFINITY;
+    const Choice& c = best[1].time < best[0].time && best[1].time128 <= best[0].time128 ? best[1] : best[0];
+    if (!(c.time < INFINITY)) return false;
+    *out = c.tuning;
+    *mgeom = c.geom;
+    return true;
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -1957,3 +1957,21 @@ def test_dense_defaults_beside_the_contraction_split(D, W, dtype):
             print("case splitdef", D, W, dtype, t.as_dict(), flush=True)
             G.check(l, G.run_gpu(plan, data["x"]), ref, f"splitdef {D} {W} {threads} {kg}")
     plan.destroy()
+
+
+@pytest.mark.parametrize("name,C,D,H,W,stride,dtype,sparsity,split", [
+    ("halo", 283, 68, 20, 17, 2, "i8", 0.7, False),           # tiles of two rows: five staged rows for two of outputs
+    ("halo", 80, 383, 6, 6, 1, "cb4h", 0.6, False),
+    ("deep", 256, 256, 14, 14, 1, "f16", 0.8, True),
+    ("deep", 512, 512, 4, 4, 1, "cb4h", 0.9, True)])
+def test_default_tile_splits_the_contraction_only_where_large_batches_agree(name, C, D, H, W, stride, dtype, sparsity, split):
+    """The tile of a plan that nobody has tuned: four and eight groups of waves (small tiles that stage their halo again
+    and again) only where they are no slower at a batch of 128 than the best tile without."""
+    l = wl.Layer(name, C, D, H, W, 3, 3, stride, stride, 1, 1, N=2, sparsity=sparsity, dtype=dtype, seed=940)
+    data = wl.prepare(l)
+    plan = G.make_plan(l, data)
+    t = plan.get_tuning()
+    print("case default split", t.as_dict(), flush=True)
+    assert t.variant == B.SC_VARIANT_DENSE and (t.buffers >= 4) == split
+    G.check(l, G.run_gpu(plan, data["x"]), G.oracle_out(l, data), f"{name} default")
+    plan.destroy()
