@@ -280,7 +280,12 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         st.cleft = a.C;
         st.whole = st.cleft >= a.CC;
     }
-    constexpr int PR = MW * NW >= 16 && MW == 4 ? 1 : 2;     // rounds of a chunk that are loaded a chunk ahead
+    // Rounds of a chunk that are loaded a chunk ahead.  One for the smallest wave tiles: 32 registers fewer leave room
+    // for three waves per SIMD (132 - 157 registers, but 4 x 1 blocks; 167 - 195 with two rounds), which is what layers with many
+    // short workgroups need to overlap them (fp16 3x3 80-383 at 6 x 6, batch 128, 15.9 us so far, 14.2 and less so; 4-bit 3x3
+    // 48-32 at 17 x 17, batch 128, 15.6 and 14.6), and half the code, 42 - 51 KB for 75 - 83.  Other layers are level (0.99 in the
+    // mean over 104).  A bound of 128 registers for a fourth wave spills, and more than doubles the time.
+    constexpr int PR = (MW * NW >= 16 && MW == 4) || MW * NW <= 4 ? 1 : 2;
     unsigned pre[2][32];
     // (opaque block index: a block's addresses are worked out again for every chunk, not kept in registers)
     auto load_pre = [&](unsigned (&r)[32], int v0) __attribute__((always_inline)) {

@@ -521,8 +521,8 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
 //                             weight in 16: GATHER spreads a single image over more workgroups
 //   large tables              of twice as many entries, 128 or more a row: from 1 weight in 32 on, against either
 //                             (1.1 - 9 times as fast; one layer in 60 slower, 0.79)
-// (the fp16, int8 and codebook lines with the one-shot kernel of that time; the present one takes 0.69 of its time in the
-// mean over 742 such layers of another draw, with the tile that is chosen now, and 1.03 - 1.23 of it on 22 of them)
+// (the fp16, int8 and codebook lines with the one-shot kernel of that time; the present one takes 0.68 of its time in the
+// mean over 742 such layers of another draw, with the tile that is chosen now, and 1.03 - 1.22 of it on 16 of them)
 // and the dense weights are at most 256 MB.  The tile is the one with the least estimated time of a batch of
 // 32: per workgroup the largest of its matrix instructions (22 clocks each with two waves on a SIMD,
 // 32 with one: measured), its weights and input through the vector L1 (64 bytes a clock) and its
@@ -530,7 +530,7 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
 // the one-shot kernel; with 45 here the chosen tiles are no faster.)
 // Four and eight groups of waves (tuning.buffers) are taken only where they are no slower at a batch of 128 either: they pay
 // with small tiles, which stage the halo of the input again and again, and a batch of 32 may be too few workgroups for that to
-// show (int8 3x3 283-68 stride 2 at 20 x 17, batch 128: 52 us so, 31.8 with one group).
+// show (int8 3x3 283-68 stride 2 at 20 x 17, batch 128: 52 us so, 31 with one group).
 // ------------------------------------------------------------------------------------------------
 static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t* out, MfmaGeom* mgeom)
 {
@@ -566,12 +566,12 @@ static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t*
         if ((int64_t)g.NS * L.C * L.H * L.W >= (1ll << 29) || (int64_t)g.DB * g.npos >= (1 << 19) || g.npos_s >= (1 << 16) ||
             (int64_t)g.tiles_p * g.ndb >= (1 << 19))
             continue;
-        // clocks of a batch of N.  (Workgroups that share a CU: by LDS, and on the one-shot kernel by its registers, two waves
-        // per SIMD.)
+        // clocks of a batch of N.  (Workgroups that share a CU: by LDS, and on the one-shot kernel by its registers, three waves
+        // per SIMD with the smallest wave tiles, else two.)
         auto estimate = [&](double N) {
             const double wgs = std::ceil(N / g.NS) * g.tiles_p * g.ndb, per_cu = std::ceil(wgs / kNumCU);
             const int room = kMaxLdsBytes / std::max(g.lds_bytes, 1);
-            const double resident = std::min(per_cu, (double)std::max(1, split ? std::min(wpc, room) : std::min(8 / g.waves, room)));
+            const double resident = std::min(per_cu, (double)std::max(1, split ? std::min(wpc, room) : std::min((g.MW < 4 && g.MW * g.NW <= 4 ? 12 : 8) / g.waves, room)));
             const double clocks = thr / 256 * resident >= 2.0 ? 22.0 : 32.0;
             const double group = split ? 4.0 : (double)(g.waves / g.KG);      // waves that share a step
             const double mfma = (double)steps * g.MW * g.NW * group / 4.0 * products * clocks;

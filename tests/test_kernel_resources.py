@@ -1,4 +1,5 @@
 """Host-only checks of what the compiler made of the kernels, read from the code-object metadata in the built library."""
+import re
 import struct
 
 import pytest
@@ -39,11 +40,30 @@ def _kernels(elf):
             o = d + (desc + 3) // 4 * 4
 
 
+def _tile_kernels():
+    """{(type, blocks along the channels, along the positions): metadata} of the one-shot matrix-core kernels."""
+    with open(B.LIB_PATH, "rb") as f:
+        data = f.read()
+    out = {}
+    for elf in _code_objects(data):
+        for k in _kernels(elf):
+            m = re.search(r"mfma_tile_kernelIL\w*?10sc_dtype_t(\d)ELi(\d)ELi(\d)E", k[".name"])
+            if m:
+                out[tuple(map(int, m.groups()))] = k
+    assert len(out) >= 26
+    return out
+
+
 def test_tile_kernels_use_no_scratch_memory():
     """The one-shot matrix-core kernels: no private segment.  (A workgroup index kept in memory costs every launch a
     store and a load before its first address, about 0.8 us.)"""
-    with open(B.LIB_PATH, "rb") as f:
-        data = f.read()
-    tile = [k for elf in _code_objects(data) for k in _kernels(elf) if "mfma_tile_kernel" in k[".name"]]
-    assert len(tile) >= 26
+    tile = _tile_kernels().values()
     assert {k[".name"]: k[".private_segment_fixed_size"] for k in tile if k[".private_segment_fixed_size"]} == {}
+
+
+def test_small_tile_kernels_leave_room_for_three_waves():
+    """Wave tiles of up to four blocks: at most 168 of a SIMD's 512 registers a wave, so that three waves share it
+    (what default_dense_tuning counts on); the larger ones two."""
+    for (dtype, mw, nw), k in _tile_kernels().items():
+        small = mw < 4 and mw * nw <= 4
+        assert k[".vgpr_count"] + k.get(".agpr_count", 0) <= (168 if small else 256), (dtype, mw, nw)
