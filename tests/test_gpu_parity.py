@@ -1975,3 +1975,31 @@ def test_default_tile_splits_the_contraction_only_where_large_batches_agree(name
     assert t.variant == B.SC_VARIANT_DENSE and (t.buffers >= 4) == split
     G.check(l, G.run_gpu(plan, data["x"]), G.oracle_out(l, data), f"{name} default")
     plan.destroy()
+
+
+@pytest.mark.parametrize("name,C,D,HW,N,sparsity,dtype", [
+    ("s56_conv3x3", 64, 64, 56, 32, 0.8, "f16"), ("s14_conv3x3", 256, 256, 14, 32, 0.8, "f16"), ("s7_conv3x3", 512, 512, 7, 32, 0.9, "f16"),
+    ("vgg_4", 512, 512, 4, 64, 0.9, "cb4h"), ("vgg_4", 512, 512, 4, 64, 0.9, "i8"), ("vgg_16", 128, 128, 16, 64, 0.9, "i8")])
+def test_contraction_split_on_whole_layers(name, C, D, HW, N, sparsity, dtype):
+    """Four and eight groups of waves on layers of the workloads at full batch: hundreds of steps a wave, tables of more than
+    one register, several chunks, the order of the workgroups by output channels (512 x 512)."""
+    l = wl.Layer(name, C, D, HW, HW, 3, 3, 1, 1, 1, 1, N=N, sparsity=sparsity, dtype=dtype, seed=950)
+    data = wl.prepare(l)
+    plan = G.make_plan(l, data)
+    x_dev = G.to_device(np.ascontiguousarray(data["x"]))
+    ran = []
+    for shape in (dict(), dict(wg_threads=512, tile_d=128, waves_m=2, tile_p=4, buffers=4), dict(wg_threads=512, tile_d=64, waves_m=1, tile_p=2, buffers=8),
+                  dict(wg_threads=512, tile_d=64, waves_m=1, tile_p=1, chunk_c=128, buffers=8), dict(wg_threads=256, tile_d=32, waves_m=1, tile_p=2, buffers=4),
+                  dict(wg_threads=512, tile_d=32, waves_m=1, tile_p=1000, sub_batch=2, chunk_c=256, buffers=4)):
+        try:
+            plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, **shape)
+        except B.SparseConvError as e:
+            assert e.status == 4                             # (whole planes of more positions than the waves hold)
+            continue
+        t = plan.get_tuning()
+        print("case whole layer", name, dtype, t.as_dict(), flush=True)
+        res = G.full_batch_parity(l, data, plan, x_dev=x_dev)
+        assert res["ok"], (shape, res)
+        ran.append(t.buffers)
+    assert 8 in ran and 4 in ran
+    plan.destroy()
