@@ -1,6 +1,7 @@
-// Kernel of the DENSE variant (the densified tile on the matrix cores) and its typed launcher;
-// included by dense_mfma.hip (host side) and by the two translation units that instantiate it for
-// 16-bit and 8-bit activations.  See dense_mfma.hip for the formulation.
+// Kernels of the DENSE variant (the densified tile on the matrix cores) and their typed launcher: pointwise layers in
+// their natural layout, several blocks of output channels per workgroup, the pipelined form; what they share with the
+// one-shot kernel on the transposed tile (dense_tile_kernel.h).  Included by dense_mfma.hip (host side) and by the
+// translation units that instantiate them for 16-bit and 8-bit activations.  See dense_mfma.hip for the formulation.
 #pragma once
 
 #include <mutex>
@@ -405,8 +406,8 @@ __device__ __forceinline__ void mfma_finish(Acc (&acc)[MW][NW], const MfmaArgs& 
             // 8-bit codes, rows of y in whole groups of four: the four lanes of four neighbouring positions
             // transpose their 4 channels x 4 positions of codes (two exchanges across lanes, two byte
             // permutations), so that each stores the four positions of one channel as one word: a quarter of
-            // the store instructions, which bound the layers with few input channels (the 13 int8 layers of
-            // VGG-16, batch 64: 179 us with byte stores, 169 so)
+            // the store instructions, which bound the layers with few input channels (measured on the 13 int8 layers of
+            // VGG-16, batch 64, when these stores served their one-shot kernel: 179 us with byte stores, 169 so)
             const int q = n16 & 3;
             const unsigned sel1 = (q & 1) ? 0x03070105u : 0x06020400u, sel2 = (q & 2) ? 0x03020706u : 0x05040100u;
 #pragma unroll
@@ -471,11 +472,13 @@ __device__ __forceinline__ void mfma_finish(Acc (&acc)[MW][NW], const MfmaArgs& 
 // steps of the contraction; their accumulators meet through LDS at the end (a fixed order: the
 // result does not depend on timing).  Two waves then share a SIMD, which is what the matrix
 // instructions need to issue back to back, at no more traffic: every operand is still fetched once.
-template <sc_dtype_t DT, int MW, int NW, int WM, int KG, bool NAT>
+// The one-shot form on the natural layout (tuning.stage_rows = 1); the transposed tile has dense_tile_kernel.h.
+template <sc_dtype_t DT, int MW, int NW, int WM, int KG>
 __global__ void __launch_bounds__(256 * KG)
 mfma_conv_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>::Y* __restrict__ y,
                  const uint4w* __restrict__ wfrag, const MfmaArgs a)
 {
+    constexpr bool NAT = true;
 #define SC_DL_DECODE const int bt = fdiv19(wg, a.inv_ndb); const int db = wg - bt * a.ndb;
 #define SC_DL_MBLK0 const int mblk0 = db * (a.DB >> 4) + wm * MW;            /* first 16-row block of this wave */
 #define SC_DL_BEGIN
@@ -749,6 +752,8 @@ mfma_pipe_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     mfma_finish<DT, MW, NW, WM, KG>(acc, a, lds, y, tid, kgrp, wm, wn, kg, n16, mblk0, yoff, b0, p0, db, PQ);
 }
 
+// MODE: 1 = pipelined, 2 = natural layout, 3 = both; 4, 5 = several blocks of output channels per workgroup on the transposed
+// tile and on the natural layout
 template <sc_dtype_t DT, int MW, int NW, int WM, int KG, int MODE>
 static sc_status_t launch_mfma_kg(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
@@ -757,7 +762,10 @@ static sc_status_t launch_mfma_kg(const Plan& p, const MfmaArgs& a, const void* 
     auto kernel = [] {
         if constexpr (MODE == 1 || MODE == 3) return &mfma_pipe_kernel<DT, MW, NW, WM, KG, MODE == 3>;
         else if constexpr (MODE == 4 || MODE == 5) return &mfma_conv_dl_kernel<DT, MW, NW, WM, KG, MODE == 5>;
-        else return &mfma_conv_kernel<DT, MW, NW, WM, KG, MODE == 2>;
+        else {
+            static_assert(MODE == 2, "the one-shot form on the transposed tile is mfma_tile_kernel");
+            return &mfma_conv_kernel<DT, MW, NW, WM, KG>;
+        }
     }();
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
