@@ -26,7 +26,8 @@
 //   * two kernels share this tile: the one-shot form (dense_tile_kernel.h: a chunk of input channels is staged by
 //     all waves, then multiplied; four or eight waves, in up to eight groups that split the steps) and the
 //     pipelined form (waves of their own stage the chunks into two LDS buffers, one chunk ahead of
-//     the multiplying waves); pointwise layers have more (dense_mfma_kernel.h).
+//     the multiplying waves); pointwise layers can be staged in their natural layout, and a workgroup can walk
+//     over several blocks of output channels (dense_mfma_kernel.h).
 // Integer results are exact (bit-identical to the gather kernels); f16 results differ from them in
 // summation order only.
 #include <algorithm>
@@ -280,10 +281,11 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
         }
         a.ntiles = ((N + g.NS - 1) / g.NS) * g.tiles_p;
         a.inv_ntiles = 1.0f / (float)a.ntiles;
-        // Order of the workgroups: by tile, but where the weights outgrow the 4 MB L2 of an XCD by block of output
-        // channels, if an XCD then reads less in all (its share of the weights and of the input against all weights and an
-        // eighth of the input).  4b/16b 3x3 512-512 at 4 x 4, batch 64, 4.7 MB of weights: 12.9 us so, 14.0 by tile (both with an earlier order of the staging, 11.3 now); below
-        // 2.4 MB level (int8) or 4 % slower (f16 3x3 256-256 at 14 x 14, 1.2 MB: 15.9 for 15.3).
+        // Order of the workgroups: by tile, but by block of output channels where the weights are more than 3 MB -- three
+        // quarters of the 4 MB L2 of an XCD, which the input shares -- if an XCD then reads less in all (its share of the weights
+        // and of the input against all weights and an eighth of the input).  3x3 layers with either order forced, fp16 and int8:
+        // 512 and 768 output channels at 4 x 4, batch 64 are level up to 3.4 MB of weights (0.99 - 1.01 of the time by tile), 0.95 - 0.98 at
+        // 3.9 MB, 0.92 - 0.94 at 4.5, 0.85 at 6.8; at 7 x 7, batch 32 and 14 x 14, batch 16 level at all of them (0.97 - 1.01).
         const double w = (double)mfma_weight_bytes(p), xin = (double)N * p.L.C * p.L.H * p.L.W * p.ex;
         a.wmajor = w > 3.0 * (1 << 20) && w / std::min(8.0, (double)g.ndb) + xin * std::min(1.0, g.ndb / 8.0) < w + xin / 8.0 ? 1 : 0;
     }

@@ -1,26 +1,28 @@
 // The one-shot kernel of the DENSE variant: the tile is staged transposed, a chunk of input channels at a
 // time, by all waves, and multiplied by all of them.  See dense_mfma.hip for the formulation.
 //
-// What bounds the layers that it serves is not the matrix pipe (21 clocks per 16 x 16 x 32 instruction) but what
+// What bounds the layers that it serves is not the matrix pipe (22 clocks per 16 x 16 x 32 instruction) but what
 // happens around it, so the kernel is laid out for short phases:
 //   * the loads of the first chunk are requested before anything else is worked out; weights, LDS zeroing, the
 //     lanes' positions and the table of steps are prepared while they are on their way;
 //   * staging moves whole registers: blocks of 8 (16) channels x up to 8 columns, transposed by byte
 //     permutations; of 16 neighbouring lanes, four take neighbouring blocks of one channel group and the next fours the next
 //     channel groups.  The address unit joins only neighbouring lanes to lines, so that a load wants as many of them
-//     along a row as it can get, while a 16-byte LDS write of 16 lanes falls into different banks with four channel
-//     groups beside each other (all 16 lanes along a row: up to 8-way conflicts; four channel groups on every four lanes, the
-//     first arrangement here: a quarter of a line for each lane group);
-//   * weights come through the vector L1, which was measured at 40 - 45 bytes a clock and CU whatever the number
-//     of loads in flight: what a workgroup reads of them is what counts.  The eight waves may therefore
+//     along a row as it can get, while the 16-byte LDS writes of 16 lanes want different 16-byte banks: with four
+//     channel groups beside each other they have them for blocks of 4 columns, and pairs share one for 8 and 2 columns and
+//     mostly for 1 (all 16 lanes along a row of 8-column blocks would share two; four channel groups on every four lanes, the
+//     first arrangement here, read a quarter of a line for each lane group);
+//   * weights come through the vector L1, which gives a CU 39 bytes a clock with four waves and 45 with eight, from four
+//     loads in flight on and whatever the region (loads of 1 KB a wave alone, regions of 16 KB to 4 MB: 82 and 94 - 98 GB/s a
+//     CU at 2.1 GHz): what a workgroup reads of them is what counts.  The eight waves may therefore
 //     split the contraction up to eight ways (KG) over one tile of outputs instead of fetching the
 //     same weights for several tiles; their sums meet in LDS;
 //   * the operands are exchanged (positions are the rows of the matrix instruction, channels its columns), so
 //     that a lane holds four neighbouring positions of one channel and stores them as one word.
-// Measured per pass: before this kernel (staging by whole rows of blocks, one or two groups, 2-byte stores), and in turn on one card with
-// four channel groups on every four lanes and with the 4 x 4 lanes: f16 3x3 64-64 at 56 x 56, batch 32 19.4, 15.7, 15.5 us;
-// f16 3x3 256-256 at 14 x 14, batch 32 19.0, 15.0, 14.5; 4b/16b 3x3 512-512 at 4 x 4, batch 64 19.7, 13.2, 11.4 - 12.2; the
-// 13 int8 layers of VGG-16, batch 64 170, 132, 123 - 126.
+// Measured per pass: the kernel before (staging by whole rows of blocks, one or two groups, 2-byte stores), this one with four channel
+// groups on every four lanes, with the 4 x 4 lanes, and now (workgroup decode by value, see mfma_block; one round ahead on the smallest
+// wave tiles): f16 3x3 64-64 at 56 x 56, batch 32 19.4, 15.7, 15.5, 15.3 us; f16 3x3 256-256 at 14 x 14, batch 32 19.0, 15.0, 14.4, 13.9;
+// 4b/16b 3x3 512-512 at 4 x 4, batch 64 19.7, 13.2, 12.2, 11.9; the 13 int8 layers of VGG-16, batch 64 170, 132, 126, 123.
 #pragma once
 
 #include "dense_mfma_kernel.h"
@@ -282,8 +284,8 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     }
     // Rounds of a chunk that are loaded a chunk ahead.  One for the smallest wave tiles: 32 registers fewer leave room
     // for three waves per SIMD (132 - 157 registers, but 4 x 1 blocks; 167 - 195 with two rounds), which is what layers with many
-    // short workgroups need to overlap them (fp16 3x3 80-383 at 6 x 6, batch 128, 15.9 us so far, 14.2 and less so; 4-bit 3x3
-    // 48-32 at 17 x 17, batch 128, 15.6 and 14.6), and half the code, 42 - 51 KB for 75 - 83.  Other layers are level (0.99 in the
+    // short workgroups need to overlap them (4b/16b 3x3 80-383 at 6 x 6, batch 128, 15.8 us with two rounds, 12.4 with one; 4-bit 3x3
+    // 48-32 at 17 x 17, batch 128, 15.7 and 14.6), and half the code, 42 - 51 KB for 75 - 83.  Other layers are level (0.99 in the
     // mean over 104).  A bound of 128 registers for a fourth wave spills, and more than doubles the time.
     constexpr int PR = (MW * NW >= 16 && MW == 4) || MW * NW <= 4 ? 1 : 2;
     unsigned pre[2][32];

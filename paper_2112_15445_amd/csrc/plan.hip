@@ -526,8 +526,8 @@ sc_status_t resolve_tuning(const Plan& p, const sc_tuning_t& in, sc_tuning_t* ou
 // and the dense weights are at most 256 MB.  The tile is the one with the least estimated time of a batch of
 // 32: per workgroup the largest of its matrix instructions (22 clocks each with two waves on a SIMD,
 // 32 with one: measured), its weights and input through the vector L1 (64 bytes a clock) and its
-// operands from LDS (128 bytes a clock), plus a fixed 8000 clocks of start and drain.  (The vector L1 was measured at 40 - 45 on
-// the one-shot kernel; with 45 here the chosen tiles are no faster.)
+// operands from LDS (128 bytes a clock), plus a fixed 8000 clocks of start and drain.  (Loads of 1 KB a wave alone reach
+// 39 - 45; with 45 here the chosen tiles are no faster.)
 // Four and eight groups of waves (tuning.buffers) are taken only where they are no slower at a batch of 128 either: they pay
 // with small tiles, which stage the halo of the input again and again, and a batch of 32 may be too few workgroups for that to
 // show (int8 3x3 283-68 stride 2 at 20 x 17, batch 128: 52 us so, 31 with one group).
