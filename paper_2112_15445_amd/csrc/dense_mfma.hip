@@ -211,6 +211,66 @@ int mfma_grid_size(const Plan& p, const MfmaGeom& g, int N)
     return ((N + g.NS - 1) / g.NS) * g.tiles_p * ((g.ndb + g.DL - 1) / g.DL);
 }
 
+// One-shot kernel on the transposed tile: log2 of the columns per staging load, 8, 4, 2 or 1 of them: the least estimated time of a
+// chunk, rounds of NT blocks times a block's instructions (its loads and address, then for each column the permutations and
+// the LDS write).
+static int tile_load_columns(const Plan& p)
+{
+    const MfmaGeom& g = p.mg;
+    const int cv = 16 / p.ex, nt = g.waves * 64;
+    const int64_t run = g.flat ? (int64_t)g.Hs * p.L.W : std::min(p.L.W, g.Ws - p.L.pad_w), rows = g.flat ? 1 : g.Hs;
+    int64_t best = 0;
+    int lepv = 0;
+    for (int l = 3; l >= 0; --l) {
+        const int e = 1 << l;
+        if (e > 1 && e > g.minrun) continue;
+        const int64_t blocks = (int64_t)(g.CC / cv) * g.NS * rows * ((run + e - 1) / e);
+        const int64_t cost = ((blocks + nt - 1) / nt) * (cv + 24 + e * (p.ex == 2 ? 8 : 12));
+        if (l == 3 || best == 0 || cost < best) { best = cost; lepv = l; }
+    }
+    return lepv;
+}
+
+// Arguments of the one-shot kernel on the transposed tile, for one launch of `grid` workgroups.
+static TileArgs tile_launch_args(const Plan& p, int N, int grid)
+{
+    const MfmaGeom& g = p.mg;
+    TileArgs a{};
+    a.gq = grid >> 3; a.gr = grid & 7;
+    a.tiles_p = g.tiles_p; a.inv_tiles_p = 1.0f / (float)g.tiles_p;
+    a.NS = g.NS; a.N = N; a.TP = g.TP; a.s_h = p.L.stride_h; a.s_w = p.L.stride_w; a.pad_h = p.L.pad_h; a.pad_w = p.L.pad_w;
+    a.H = p.L.H; a.Hs = g.Hs; a.W = p.L.W; a.Ws = g.Ws; a.npos1 = g.Hs * g.Ws; a.CC = g.CC; a.C = p.L.C;
+    a.wcols = std::max(0, std::min(p.L.W, g.Ws - p.L.pad_w));
+    a.plane_b = (unsigned)(p.L.H * p.L.W) * (unsigned)p.ex;
+    a.sample_b = (unsigned)p.L.C * a.plane_b;
+    a.pitch = g.pitch;
+    a.inv_npos1 = 1.0f / (float)a.npos1; a.inv_Ws = 1.0f / (float)g.Ws;
+    if (p.L.pad_h || p.L.pad_w) {
+        int across = 0;
+        while ((1 << across) < g.npos_s && (1 << across) < g.waves * 64) ++across;
+        a.zero = g.npos_s | across << 16;
+    }
+    const int ccb = g.CC / mfma_chan_block(p.dtype);
+    a.DB = g.DB; a.RS = p.L.R * p.L.S; a.NCB = g.NCB; a.nchunks = g.nchunks; a.S = p.L.S;
+    a.inv_ccb = 1.0f / (float)ccb; a.inv_cbs_last = 1.0f / (float)(g.NCB - (g.nchunks - 1) * ccb); a.inv_S = 1.0f / (float)p.L.S;
+    a.TPQ = g.TP * p.Q; a.Q = p.Q; a.npos = g.npos; a.inv_TPQ = 1.0f / (float)a.TPQ; a.inv_Q = 1.0f / (float)p.Q;
+    a.P = p.P; a.D = p.L.D; a.epi_pitch = g.epi_pitch; a.Po = p.Po; a.Qo = p.Qo;
+    // (the weights hold more than D floats: 64 bytes and more for each of the D channels)
+    a.requant = p.epi.requant ? p.d_requant : reinterpret_cast<const float*>(p.d_wfrag);
+    // Order of the workgroups: by tile, but by block of output channels where the weights are more than 3 MB -- three
+    // quarters of the 4 MB L2 of an XCD, which the input shares -- if an XCD then reads less in all (its share of the weights
+    // and of the input against all weights and an eighth of the input).  3x3 layers with either order forced, fp16 and int8:
+    // 512 and 768 output channels at 4 x 4, batch 64 are level up to 3.4 MB of weights (0.99 - 1.01 of the time by tile), 0.95 - 0.98 at
+    // 3.9 MB, 0.92 - 0.94 at 4.5, 0.85 at 6.8; at 7 x 7, batch 32 and 14 x 14, batch 16 level at all of them (0.97 - 1.01).
+    const double w = (double)mfma_weight_bytes(p), xin = (double)N * p.L.C * p.L.H * p.L.W * p.ex;
+    const bool wmajor = w > 3.0 * (1 << 20) && w / std::min(8.0, (double)g.ndb) + xin * std::min(1.0, g.ndb / 8.0) < w + xin / 8.0;
+    a.inner = wmajor ? ((N + g.NS - 1) / g.NS) * g.tiles_p : g.ndb;
+    a.inv_inner = 1.0f / (float)a.inner;
+    a.bits = (wmajor ? 1 : 0) | (g.flat ? 2 : 0) | (p.epi.relu ? 4 : 0) | (p.epi.pool ? 8 : 0) | __builtin_ctz(g.WM) << 6 |
+             __builtin_ctz(g.WN) << 8 | __builtin_ctz(g.KG) << 10 | g.waves << 12 | (p.epi.requant ? 1 << 16 : 0);
+    return a;
+}
+
 sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_t stream)
 {
     const MfmaGeom& g = p.mg;
@@ -230,6 +290,13 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
     }
     const int64_t grid = (int64_t)((N + g.NS - 1) / g.NS) * per_group;
     if ((int64_t)g.NS * p.L.C * p.L.H * p.L.W >= (1ll << 31)) return SC_ERR_UNSUPPORTED;
+    if ((int64_t)g.DB * g.NS * g.TP * p.Q >= (1 << 19) || g.npos_s >= (1 << 19)) return SC_ERR_UNSUPPORTED;
+    if (!g.nat && !g.PW && g.DL == 1) {
+        using Launch = sc_status_t (*)(const Plan&, const TileArgs&, const void*, void*, int, hipStream_t);
+        static const Launch halves[4] = {launch_tile_f16_1, launch_tile_f16_2, launch_tile_f16_4, launch_tile_f16_8};
+        static const Launch bytes[4] = {launch_tile_i8_1, launch_tile_i8_2, launch_tile_i8_4, launch_tile_i8_8};
+        return (p.ex == 1 ? bytes : halves)[tile_load_columns(p)](p, tile_launch_args(p, N, (int)grid), x, y, (int)grid, stream);
+    }
     MfmaArgs a{};
     a.C = p.L.C; a.D = p.L.D; a.N = N; a.H = p.L.H; a.W = p.L.W; a.P = p.P; a.Q = p.Q;
     a.S = p.L.S; a.RS = p.L.R * p.L.S; a.s_h = p.L.stride_h; a.s_w = p.L.stride_w; a.pad_h = p.L.pad_h; a.pad_w = p.L.pad_w;
@@ -250,7 +317,6 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
     // inside a tile)
     a.epi_quads = (a.requant && !p.epi.pool && (p.P * p.Q) % 4 == 0 && (p.Q % 4 == 0 || g.tiles_p == 1) &&
                    reinterpret_cast<uintptr_t>(y) % 4 == 0) ? 1 : 0;
-    if ((int64_t)g.DB * g.NS * g.TP * p.Q >= (1 << 19)) return SC_ERR_UNSUPPORTED;
     // elements per staging load: the widest power of two (up to 16 bytes) that divides the row length
     // and the caller's pointer
     a.epv = 1;
@@ -263,48 +329,21 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
     if (g.nat && (int64_t)g.CC * g.NS * g.TP * p.Q >= (1 << 19)) return SC_ERR_UNSUPPORTED;     // fdiv19() range of the copy
     // (the direct-to-LDS copies of the pipelined natural-layout form move 16-byte words)
     if (g.nat && g.PW && reinterpret_cast<uintptr_t>(x) % 16 != 0) return SC_ERR_UNSUPPORTED;
-    if (!g.nat && !g.PW && g.DL == 1) {
-        a.lwm = __builtin_ctz(g.WM); a.lwn = __builtin_ctz(g.WN); a.lkg = __builtin_ctz(g.KG); a.KG = g.KG;
-        a.flat = g.flat;
-        a.zero = p.L.pad_h || p.L.pad_w ? (int)(((int64_t)g.npos_s * g.pitch + 15) / 16) : 0;
-        // Columns per staging load, 8, 4, 2 or 1: the least estimated time of a chunk, rounds of NT blocks times a
-        // block's instructions (its loads and address, then for each column the permutations and the LDS write).
-        const int cv = 16 / p.ex, nt = g.waves * 64;
-        const int64_t run = g.flat ? (int64_t)g.Hs * p.L.W : std::min(p.L.W, g.Ws - p.L.pad_w), rows = g.flat ? 1 : g.Hs;
-        int64_t best = 0;
-        for (int l = 3; l >= 0; --l) {
-            const int e = 1 << l;
-            if (e > 1 && e > g.minrun) continue;
-            const int64_t blocks = (int64_t)(g.CC / cv) * g.NS * rows * ((run + e - 1) / e);
-            const int64_t cost = ((blocks + nt - 1) / nt) * (cv + 24 + e * (p.ex == 2 ? 8 : 12));
-            if (l == 3 || best == 0 || cost < best) { best = cost; a.lepv = l; }
-        }
-        a.ntiles = ((N + g.NS - 1) / g.NS) * g.tiles_p;
-        a.inv_ntiles = 1.0f / (float)a.ntiles;
-        // Order of the workgroups: by tile, but by block of output channels where the weights are more than 3 MB -- three
-        // quarters of the 4 MB L2 of an XCD, which the input shares -- if an XCD then reads less in all (its share of the weights
-        // and of the input against all weights and an eighth of the input).  3x3 layers with either order forced, fp16 and int8:
-        // 512 and 768 output channels at 4 x 4, batch 64 are level up to 3.4 MB of weights (0.99 - 1.01 of the time by tile), 0.95 - 0.98 at
-        // 3.9 MB, 0.92 - 0.94 at 4.5, 0.85 at 6.8; at 7 x 7, batch 32 and 14 x 14, batch 16 level at all of them (0.97 - 1.01).
-        const double w = (double)mfma_weight_bytes(p), xin = (double)N * p.L.C * p.L.H * p.L.W * p.ex;
-        a.wmajor = w > 3.0 * (1 << 20) && w / std::min(8.0, (double)g.ndb) + xin * std::min(1.0, g.ndb / 8.0) < w + xin / 8.0 ? 1 : 0;
-    }
     a.inv_ndb = 1.0f / (float)g.ndb; a.inv_tiles_p = 1.0f / (float)g.tiles_p;
     a.inv_HsWs = 1.0f / (float)(g.Hs * g.Ws); a.inv_Ws = 1.0f / (float)g.Ws;
     a.inv_TPQ = 1.0f / (float)(g.TP * p.Q); a.inv_Q = 1.0f / (float)p.Q;
-    if (g.npos_s >= (1 << 19)) return SC_ERR_UNSUPPORTED;
     switch (p.dtype) {
         // (the codebook variants were decoded when the weights were densified: same arithmetic)
         case SC_F16:
         case SC_CB4_F16:
             if (g.DL > 1) return launch_mfma_dl_f16(p, a, x, y, (int)grid, stream);
             return g.nat ? (g.PW ? launch_mfma_pipe_nat_f16(p, a, x, y, (int)grid, stream) : launch_mfma_nat_f16(p, a, x, y, (int)grid, stream))
-                         : (g.PW ? launch_mfma_pipe_f16(p, a, x, y, (int)grid, stream) : launch_mfma_f16(p, a, x, y, (int)grid, stream));
+                         : (g.PW ? launch_mfma_pipe_f16(p, a, x, y, (int)grid, stream) : SC_ERR_UNSUPPORTED);
         case SC_I8:
         case SC_CB4_I8:
             if (g.DL > 1) return launch_mfma_dl_i8(p, a, x, y, (int)grid, stream);
             return g.nat ? (g.PW ? launch_mfma_pipe_nat_i8(p, a, x, y, (int)grid, stream) : launch_mfma_nat_i8(p, a, x, y, (int)grid, stream))
-                         : (g.PW ? launch_mfma_pipe_i8(p, a, x, y, (int)grid, stream) : launch_mfma_i8(p, a, x, y, (int)grid, stream));
+                         : (g.PW ? launch_mfma_pipe_i8(p, a, x, y, (int)grid, stream) : SC_ERR_UNSUPPORTED);
         default: return SC_ERR_UNSUPPORTED;
     }
 }

@@ -17,6 +17,7 @@ typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef int int4v_ __attribute__((ext_vector_type(4)));
 typedef unsigned uint4w __attribute__((ext_vector_type(4)));
+typedef int int16w_ __attribute__((ext_vector_type(16), aligned(4)));
 
 // (Measured on this chip, loops with 16 independent accumulators: the 16 x 16 x 32 instructions used here
 // take 32 clocks with one wave per SIMD and 22 with two or more -- 1.25 and 1.85 PFLOP/s in fp16, 2.8 and
@@ -38,11 +39,6 @@ struct MfmaArgs {
     int TPQ;                 // natural layout: positions of one sample in the tile (TP * Q)
     int DL, ndbg;            // one-shot form: output-channel blocks per workgroup, groups of them (ndb / DL, rounded up)
     float inv_ndbg;
-    // one-shot form on the transposed tile: workgroup order (see mfma_block), log2 of the waves along the output
-    // channels and the positions and of the groups that split the contraction, log2 of the columns per staging
-    // load, 16-byte words of the tile image to clear, staged rows of a sample are one run per channel
-    int wmajor, ntiles, lwm, lwn, lkg, KG, lepv, zero, flat;
-    float inv_ntiles;
     float inv_spc, inv_ccb, inv_cbs_last, inv_S;
     float inv_ndb, inv_tiles_p, inv_HsWs, inv_Ws, inv_TPQ, inv_Q;
     // fused epilogue (epi = 0: none): ReLU, 2 x 2 max-pooling, requantisation multipliers (or NULL),
@@ -52,8 +48,44 @@ struct MfmaArgs {
     int epi_quads;           // requantised rows of y are whole groups of four positions, y aligned to them
 };
 
-sc_status_t launch_mfma_f16(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
-sc_status_t launch_mfma_i8(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+// What a launch of the one-shot kernel on the transposed tile is made of.  A kernel reads its arguments through the scalar cache, 64 bytes a miss and about 450 clocks each
+// time that it waits; read where they are first used they cost it six such waits before its first load and eight more before
+// its first multiplication, 3 of the 9 us of an int8 VGG-16 layer.  They are therefore few, derived on the host as far as they
+// can be, and all read at once when the kernel starts (tile_args).
+struct TileArgs {
+    // workgroup order (see tile_block): workgroups / 8 and what is left, inner extent; samples and rows of tiles
+    int gq, gr, inner;
+    float inv_inner, inv_tiles_p;
+    int tiles_p, NS, N, TP, s_h, pad_h;
+    // staging: input rows, staged rows, columns of a row and those that are staged, input elements per row, staged positions of a
+    // sample and of a row, the first one of an input row, bytes per plane and sample, channels of a chunk and of the layer
+    int H, Hs, W, wcols, Ws, npos1, pad_w, CC, C;
+    unsigned plane_b, sample_b;
+    int pitch;                   // bytes per staged position
+    int zero;                    // with padding: staged positions of the workgroup, log2 of the threads across them from bit 16 on
+    // multiplication: 16-row blocks of a workgroup, taps, channel blocks of the layer and of the last chunk
+    int DB, RS, NCB, nchunks;
+    float inv_ccb, inv_cbs_last, inv_S;
+    int S, TPQ, Q, npos, s_w;
+    float inv_TPQ, inv_Q, inv_npos1, inv_Ws;
+    // outputs
+    int P, D, epi_pitch, Po, Qo;
+    // bit 0: by block of output channels, 1: staged rows of a sample are one run per channel, 2: ReLU, 3: pooling;
+    // 6-7 log2 of the waves along the output channels, 8-9 along the positions, 10-11 of the groups that split the
+    // contraction; 12-15 waves; 16 requantisation
+    int bits;
+    const float* requant;        // multipliers (without requantisation: any D floats)
+};
+
+// (by the columns per staging load)
+sc_status_t launch_tile_f16_1(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_f16_2(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_f16_4(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_f16_8(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_i8_1(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_i8_2(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_i8_4(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_i8_8(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_mfma_pipe_f16(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_mfma_pipe_i8(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_mfma_nat_f16(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
@@ -66,23 +98,6 @@ sc_status_t launch_mfma_dl_i8(const Plan& p, const MfmaArgs& a, const void* x, v
 // floor(e / d) for 0 <= e < 2^19 given inv = 1.0f / d (exact: the half-integer bias keeps the
 // product at least 1/(2d) away from every integer, well above the two float roundings)
 __device__ inline int fdiv19(int e, float inv) { return (int)(((float)e + 0.5f) * inv); }
-
-// Workgroup -> (tile of positions bt, block of output channels db of ndb).  Workgroups are dealt round-robin to
-// the 8 XCDs: they are renumbered so that each XCD gets a contiguous run.  Within it either the blocks of one tile
-// are neighbours (they find the tile in the L2 that their siblings loaded), or, where the weights outweigh the
-// input (a.wmajor), the tiles of one block: an XCD then streams its share of the weights and not all of them.
-// Both indices are chosen by value and made wave-uniform: written through references in two branches they went
-// through scratch memory, a store and a load before the first address could be formed, and everything derived from them
-// was vector arithmetic (all 26 tile kernels: 12 bytes of scratch and 15 - 18 vector registers more).
-struct MfmaBlock { int bt, db; };
-__device__ __forceinline__ MfmaBlock mfma_block(const MfmaArgs& a)
-{
-    const int q = gridDim.x >> 3, r = gridDim.x & 7, xcd = blockIdx.x & 7;
-    const int wg = xcd * q + min(xcd, r) + (int)(blockIdx.x >> 3);
-    const int inner = a.wmajor ? a.ntiles : a.ndb;
-    const int hi = __builtin_amdgcn_readfirstlane(fdiv19(wg, a.wmajor ? a.inv_ntiles : a.inv_ndb)), lo = wg - hi * inner;
-    return {a.wmajor ? lo : hi, a.wmajor ? hi : lo};
-}
 
 // ------------------------------------------------------------------------------------------------
 // Staging of one chunk of CC input channels of the tile, transposed on the way: global memory is

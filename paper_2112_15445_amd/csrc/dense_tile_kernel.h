@@ -19,10 +19,11 @@
 //     same weights for several tiles; their sums meet in LDS;
 //   * the operands are exchanged (positions are the rows of the matrix instruction, channels its columns), so
 //     that a lane holds four neighbouring positions of one channel and stores them as one word.
-// Measured per pass: the kernel before (staging by whole rows of blocks, one or two groups, 2-byte stores), this one with four channel
-// groups on every four lanes, with the 4 x 4 lanes, and now (workgroup decode by value, see mfma_block; one round ahead on the smallest
-// wave tiles): f16 3x3 64-64 at 56 x 56, batch 32 19.4, 15.7, 15.5, 15.3 us; f16 3x3 256-256 at 14 x 14, batch 32 19.0, 15.0, 14.4, 13.9;
-// 4b/16b 3x3 512-512 at 4 x 4, batch 64 19.7, 13.2, 12.2, 11.9; the 13 int8 layers of VGG-16, batch 64 170, 132, 126, 123.
+//   * a launch reads its arguments at once (TileArgs), staging is instantiated by the columns of a load, and the first chunk is staged
+//     ahead of the loop over the chunks, so that the compiler knows how many loads are in flight and waits for the input only, not for the weights behind it.
+// Measured per pass, before and after the last of these: f16 3x3 64-64 at 56 x 56, batch 32 14.9, 14.5 us; f16 3x3 256-256 at 14 x 14,
+// batch 32 13.6, 13.0; 4b/16b 3x3 512-512 at 4 x 4, batch 64 11.9, 10.9; the 13 int8 layers of VGG-16, batch 64 121, 111 (a layer launched alone again and
+// again 9.3, 7.5 in the mean: in the stack about 1.5 us of each launch are the first pass through its code).
 #pragma once
 
 #include "dense_mfma_kernel.h"
@@ -50,21 +51,25 @@ template <typename X> constexpr int kTileCV = 16 / (int)sizeof(X);
 template <typename X, int EPV> constexpr int kTileWPE = EPV * (int)sizeof(X) >= 4 ? EPV * (int)sizeof(X) / 4 : 1;
 template <typename X, int EPV> constexpr int kTileVB = 32 / (kTileCV<X> * kTileWPE<X, EPV>);    // blocks per thread and round
 
-// block v: channel group, sample, row, first column (false: none, then a block of the first channel groups)
-template <int EPV>
-__device__ __forceinline__ bool tile_block(const TileStage& st, int v, int& cg, int& sm, int& ii, int& col)
+// Where a block is read from (bytes from st.xs in the first channel group's first channel, and its channel) and written to
+// (bytes into the LDS image; -1: no such block, then the first block of the first channel groups is read).  The same for
+// every chunk.
+struct TileSlot { unsigned off; int cg, dst; };
+
+template <typename X, int EPV>
+__device__ __forceinline__ TileSlot tile_slot(const TileStage& st, int pitch, int v)
 {
     int cg4 = tdiv(v >> 4, st.inv_quads);
     int r = ((v >> 4) - cg4 * st.quads) * 4 + (v & 3);
     const bool live = v < st.nblocks && r < st.per_cg;
     if (!live) cg4 = r = 0;
-    cg = cg4 * 4 + (v >> 2 & 3);
-    sm = 0;
+    const int cg = cg4 * 4 + (v >> 2 & 3);
+    int sm = 0, ii = 0;
     if (st.rowsG != st.per_cg) { sm = tdiv(r, st.inv_rowsG); r -= sm * st.rowsG; }
-    ii = 0;
     if (st.rowsG != st.G) { ii = tdiv(r, st.inv_G); r -= ii * st.G; }
-    col = min(r * EPV, st.run - EPV);
-    return live;
+    const int col = min(r * EPV, st.run - EPV);
+    return {(unsigned)sm * st.sample_b + (unsigned)ii * st.row_b + (unsigned)col * (unsigned)sizeof(X), cg,
+            live ? (sm * st.npos1 + st.dst0 + ii * st.Ws + col) * pitch + cg * 16 : -1};
 }
 
 // Address of a staging load, whole in the lane's registers.  Left to itself the compiler takes the scalar base and the 32-bit
@@ -80,20 +85,17 @@ __device__ __forceinline__ TileSrc tile_src(const char* base, unsigned off)
 }
 
 template <typename X, int EPV>
-__device__ __forceinline__ void tile_load(unsigned (&pre)[32], const TileStage& st, int v0, int NT)
+__device__ __forceinline__ void tile_load(unsigned (&pre)[32], const TileStage& st, const TileSlot (&slot)[kTileVB<X, EPV>])
 {
     constexpr int CV = kTileCV<X>, W = kTileWPE<X, EPV>, VB = kTileVB<X, EPV>, B = EPV * (int)sizeof(X);
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
-        int cg, sm, ii, col;
-        tile_block<EPV>(st, v0 + u * NT, cg, sm, ii, col);
-        const unsigned off = (unsigned)sm * st.sample_b + (unsigned)ii * st.row_b + (unsigned)col * (unsigned)sizeof(X);
-        unsigned o = off + (unsigned)(cg * CV) * st.plane_b;
-#pragma unroll
-        for (int j = 0; j < CV; ++j) {
-            // (channels past the layer's last: the block's place in channel 0, zeroed when it is stored)
-            const TileSrc src = tile_src(st.xs, st.whole || cg * CV + j < st.cleft ? o : off);
-            // (of any alignment: one load each all the same)
+        unsigned off = slot[u].off;
+        int cg = slot[u].cg;
+        // (opaque: the addresses of a block are worked out again for every chunk, not kept in registers)
+        asm volatile("" : "+v"(off), "+v"(cg));
+        // (of any alignment: one load each all the same)
+        auto load = [&](int j, TileSrc src) __attribute__((always_inline)) {
             if constexpr (B >= 4) {
                 unsigned e[W];
                 __builtin_memcpy(e, (const void*)src, B);
@@ -106,21 +108,41 @@ __device__ __forceinline__ void tile_load(unsigned (&pre)[32], const TileStage& 
             } else {
                 pre[u * CV + j] = *reinterpret_cast<const __attribute__((address_space(1))) unsigned char*>(src);
             }
-            o += st.plane_b;
+        };
+        if (st.whole) {
+            // (one 64-bit addition from channel to channel)
+            TileSrc src = tile_src(st.xs, off + (unsigned)(cg * CV) * st.plane_b);
+#pragma unroll
+            for (int j = 0; j < CV; ++j) {
+                load(j, src);
+                src += st.plane_b;
+                asm("" : "+v"(src));
+                __builtin_amdgcn_sched_barrier(0);           // (one address at a time: registers)
+            }
+        } else {
+            unsigned o = off + (unsigned)(cg * CV) * st.plane_b;
+#pragma unroll
+            for (int j = 0; j < CV; ++j) {
+                // (channels past the layer's last: the block's place in channel 0, zeroed when it is stored)
+                load(j, tile_src(st.xs, cg * CV + j < st.cleft ? o : off));
+                o += st.plane_b;
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 }
 
 template <typename X, int EPV>
-__device__ __forceinline__ void tile_store(unsigned (&pre)[32], const TileStage& st, unsigned char* lds, int pitch, int v0, int NT)
+__device__ __forceinline__ void tile_store(unsigned (&pre)[32], const TileStage& st, unsigned char* lds, int pitch, const TileSlot (&slot)[kTileVB<X, EPV>])
 {
     constexpr int CV = kTileCV<X>, W = kTileWPE<X, EPV>, VB = kTileVB<X, EPV>;
     constexpr int EPW = 4 / (int)sizeof(X);                  // columns per register
 #pragma unroll
     for (int u = 0; u < VB; ++u) {
-        int cg, sm, ii, col;
-        if (!tile_block<EPV>(st, v0 + u * NT, cg, sm, ii, col)) continue;
-        unsigned char* dst = lds + (sm * st.npos1 + st.dst0 + ii * st.Ws + col) * pitch + cg * 16;
+        if (slot[u].dst < 0) continue;
+        int cg = slot[u].cg, to = slot[u].dst;
+        asm volatile("" : "+v"(cg), "+v"(to));
+        unsigned char* dst = lds + to;
         if (!st.whole) {
 #pragma unroll
             for (int j = 0; j < CV; ++j)
@@ -230,10 +252,46 @@ __device__ __forceinline__ void tile_put4(typename Types<DT>::Y* __restrict__ y,
     }
 }
 
-template <sc_dtype_t DT, int MW, int NW>
+// The arguments in scalar registers, requested together (see TileArgs).  Opaque to the compiler, which would read them again from
+// memory at each use.
+__device__ __forceinline__ TileArgs tile_args(const TileArgs& args)
+{
+    static_assert(sizeof(TileArgs) == 3 * sizeof(int16w_));
+    const int16w_* from = reinterpret_cast<const int16w_*>(&args);
+    int16w_ v0 = from[0], v1 = from[1], v2 = from[2];
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2));
+    int words[48];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        words[i] = v0[i];
+        words[16 + i] = v1[i];
+        words[32 + i] = v2[i];
+    }
+    TileArgs a;
+    __builtin_memcpy(&a, words, sizeof(a));
+    return a;
+}
+
+// Workgroup -> (tile of positions bt, block of output channels db of ndb).  Workgroups are dealt round-robin to
+// the 8 XCDs: they are renumbered so that each XCD gets a contiguous run.  Within it either the blocks of one tile
+// are neighbours (they find the tile in the L2 that their siblings loaded), or, where the weights outweigh the
+// input (bit 0), the tiles of one block: an XCD then streams its share of the weights and not all of them.
+// Both indices are chosen by value and made wave-uniform: written through references in two branches they went
+// through scratch memory, a store and a load before the first address could be formed, and everything derived from them
+// was vector arithmetic (all 26 tile kernels: 12 bytes of scratch and 15 - 18 vector registers more).
+struct TileBlock { int bt, db; };
+__device__ __forceinline__ TileBlock tile_block(const TileArgs& a)
+{
+    const int xcd = blockIdx.x & 7;
+    const int wg = xcd * a.gq + min(xcd, a.gr) + (int)(blockIdx.x >> 3);
+    const int hi = __builtin_amdgcn_readfirstlane(fdiv19(wg, a.inv_inner)), lo = wg - hi * a.inner;
+    return {a.bits & 1 ? lo : hi, a.bits & 1 ? hi : lo};
+}
+
+template <sc_dtype_t DT, int MW, int NW, int LEPV>
 __global__ void __launch_bounds__(512, 2)
 mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>::Y* __restrict__ y,
-                 const uint4w* __restrict__ wfrag, const MfmaArgs a)
+                 const uint4w* __restrict__ wfrag, const TileArgs args)
 {
     using X = typename Types<DT>::X;
     using A = typename Types<DT>::A;
@@ -242,83 +300,93 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     constexpr int PF = MW >= 2 ? 4 : 8;                      // steps of weights in flight
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-    const int NT = blockDim.x;
+    const TileArgs a = tile_args(args);
+    constexpr int lepv = LEPV;                               // log2 of the columns per staging load
+    const int lwm = a.bits >> 6 & 3, lwn = a.bits >> 8 & 3, lkg = a.bits >> 10 & 3;
+    const int NT = (a.bits >> 12 & 15) * 64;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, kg = lane >> 4;
 
-    const MfmaBlock block = mfma_block(a);
+    const TileBlock block = tile_block(a);
     const int bt = block.bt, db = block.db;
     const int bg = __builtin_amdgcn_readfirstlane(fdiv19(bt, a.inv_tiles_p));
     const int tpi = bt - bg * a.tiles_p;
     const int b0 = bg * a.NS, p0 = tpi * a.TP;
     const int row0 = p0 * a.s_h - a.pad_h;
-    const int PQ = a.P * a.Q;
 
     // ---------------------------------------------------------------- the loads of the first chunk
     TileStage st;
+    const int nsv = min(a.NS, a.N - b0);                     // samples inside the batch
+    const int ilo = max(0, -row0);                           // staged rows inside the input: [ilo, ilo + nrows)
+    const int nrows = max(0, min(a.Hs, a.H - row0) - ilo);
     {
-        const int nsv = min(a.NS, a.N - b0);                 // samples inside the batch
-        const int ilo = max(0, -row0);                       // staged rows inside the input: [ilo, ilo + nrows)
-        const int nrows = max(0, min(a.Hs, a.H - row0) - ilo);
-        const int rows = a.flat ? min(nrows, 1) : nrows;
-        st.run = a.flat ? nrows * a.W : max(0, min(a.W, a.Ws - a.pad_w));
-        st.G = (st.run + (1 << a.lepv) - 1) >> a.lepv;
+        const bool flat = a.bits & 2;
+        const int rows = flat ? min(nrows, 1) : nrows;
+        st.run = flat ? nrows * a.W : a.wcols;
+        st.G = (st.run + (1 << lepv) - 1) >> lepv;
         st.rowsG = rows * st.G;
         st.per_cg = nsv * st.rowsG;
         st.quads = (st.per_cg + 3) >> 2;
-        st.nblocks = (a.CC / CV) * st.quads * 4;
+        st.nblocks = (int)((unsigned)a.CC / CV) * st.quads * 4;
         st.inv_quads = __builtin_amdgcn_rcpf((float)max(st.quads, 1));
         st.inv_rowsG = __builtin_amdgcn_rcpf((float)max(st.rowsG, 1));
         st.inv_G = __builtin_amdgcn_rcpf((float)max(st.G, 1));
         st.dst0 = ilo * a.Ws + a.pad_w;
-        st.npos1 = a.Hs * a.Ws;
+        st.npos1 = a.npos1;
         st.Ws = a.Ws;
-        st.plane_b = (unsigned)(a.H * a.W) * (unsigned)sizeof(X);
-        st.sample_b = (unsigned)a.C * st.plane_b;
+        st.plane_b = a.plane_b;
+        st.sample_b = a.sample_b;
         st.row_b = (unsigned)a.W * (unsigned)sizeof(X);
         st.xs = reinterpret_cast<const char*>(x) + (int64_t)b0 * st.sample_b + (int64_t)(row0 + ilo) * st.row_b;
         st.cleft = a.C;
         st.whole = st.cleft >= a.CC;
     }
     // Rounds of a chunk that are loaded a chunk ahead.  One for the smallest wave tiles: 32 registers fewer leave room
-    // for three waves per SIMD (132 - 157 registers, but 4 x 1 blocks; 167 - 195 with two rounds), which is what layers with many
-    // short workgroups need to overlap them (4b/16b 3x3 80-383 at 6 x 6, batch 128, 15.8 us with two rounds, 12.4 with one; 4-bit 3x3
-    // 48-32 at 17 x 17, batch 128, 15.7 and 14.6), and half the code, 42 - 51 KB for 75 - 83.  Other layers are level (0.99 in the
-    // mean over 104).  A bound of 128 registers for a fourth wave spills, and more than doubles the time.
+    // for three or four waves per SIMD (109 - 139 registers; 168 are three), which is what layers with many
+    // short workgroups need to overlap them (4b/16b 3x3 80-383 at 6 x 6, batch 128, 15.8 us with two rounds and two waves, 12.4 with one
+    // and three; 4-bit 3x3 48-32 at 17 x 17, batch 128, 15.7 and 14.6).  Other layers are level (0.99 in the mean over 104).
     constexpr int PR = (MW * NW >= 16 && MW == 4) || MW * NW <= 4 ? 1 : 2;
-    unsigned pre[2][32];
-    // (opaque block index: a block's addresses are worked out again for every chunk, not kept in registers)
-    auto load_pre = [&](unsigned (&r)[32], int v0) __attribute__((always_inline)) {
-        asm volatile("" : "+v"(v0));
-        switch (a.lepv) {
-            case 3: tile_load<X, 8>(r, st, v0, NT); break;
-            case 2: tile_load<X, 4>(r, st, v0, NT); break;
-            case 1: tile_load<X, 2>(r, st, v0, NT); break;
-            default: tile_load<X, 1>(r, st, v0, NT); break;
-        }
+    constexpr int EPV = 1 << LEPV, VB = kTileVB<X, EPV>;
+    unsigned pre[PR][32];
+    TileSlot slots[PR][VB];
+    const int per_round = NT * VB;
+    auto locate = [&](TileSlot (&t)[VB], int v0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < VB; ++u) t[u] = tile_slot<X, EPV>(st, a.pitch, v0 + u * NT);
     };
-    auto store_pre = [&](unsigned (&r)[32], int v0) __attribute__((always_inline)) {
-        asm volatile("" : "+v"(v0));
-        switch (a.lepv) {
-            case 3: tile_store<X, 8>(r, st, lds, a.pitch, v0, NT); break;
-            case 2: tile_store<X, 4>(r, st, lds, a.pitch, v0, NT); break;
-            case 1: tile_store<X, 2>(r, st, lds, a.pitch, v0, NT); break;
-            default: tile_store<X, 1>(r, st, lds, a.pitch, v0, NT); break;
-        }
-    };
-    const int per_round = NT * (a.lepv == 3 ? kTileVB<X, 8> : a.lepv == 2 ? kTileVB<X, 4> : a.lepv == 1 ? kTileVB<X, 2> : kTileVB<X, 1>);
+    auto load_pre = [&](int r) __attribute__((always_inline)) { tile_load<X, EPV>(pre[r], st, slots[r]); };
+    auto store_pre = [&](int r) __attribute__((always_inline)) { tile_store<X, EPV>(pre[r], st, lds, a.pitch, slots[r]); };
     const bool two = PR == 2 && st.nblocks > per_round;
     // (nblocks = 0: a tile that lies in the padding altogether)
-    if (st.nblocks) load_pre(pre[0], tid);
-    if (two) load_pre(pre[1], tid + per_round);
+    if (st.nblocks) {
+        locate(slots[0], tid);
+        load_pre(0);
+    }
+    if constexpr (PR == 2) {
+        if (two) {
+            locate(slots[1], tid + per_round);
+            load_pre(1);
+        }
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     // ---------------------------------------------------------------- roles of the waves
-    const int wm = wave & ((1 << a.lwm) - 1), wn = (wave >> a.lwm) & ((1 << a.lwn) - 1), kgrp = wave >> (a.lwm + a.lwn);
-    const int KG = a.KG;
+    const int wm = wave & ((1 << lwm) - 1), wn = (wave >> lwm) & ((1 << lwn) - 1), kgrp = wave >> (lwm + lwn);
+    const int KG = 1 << lkg;
     const int mblk0 = db * (a.DB >> 4) + wm * MW;
+    // requantisation multipliers of this lane's channels (n16 of each row block), requested with the input: read where they are
+    // used they cost a pooled layer a trip to memory for every channel that a thread finishes
+    float rqs[MW];
+#pragma unroll
+    for (int m = 0; m < MW; ++m) rqs[m] = 0.0f;
+    if constexpr (kIntActs<DT>) {
+        // (through a global pointer: a load that might be from LDS would have to be waited for with everything else)
+        const auto* from = (const __attribute__((address_space(1))) float*)a.requant;
+#pragma unroll
+        for (int m = 0; m < MW; ++m) rqs[m] = from[min((mblk0 + m) * 16 + n16, a.D - 1)];
+    }
     const int64_t wrow = (int64_t)(a.RS * a.NCB) << 10;      // bytes per 16-row block of the weights
     const unsigned char* wrows = reinterpret_cast<const unsigned char*>(wfrag) + mblk0 * wrow;
 
@@ -327,8 +395,8 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     // read back with v_readlane; steps past the last repeat it (operands are requested without a test).
     int xtab, wtab;
     auto table = [&](int s0, int n, int cbs, int gcb0) {
-        const int s = kgrp + KG * (s0 + min(lane, n - 1));
-        const int tap = tdiv(s, cbs == a.CC / CB ? a.inv_ccb : a.inv_cbs_last);
+        const int s = min(kgrp + KG * (s0 + min(lane, max(n, 1) - 1)), a.RS * cbs - 1);
+        const int tap = tdiv(s, cbs == (int)((unsigned)a.CC / CB) ? a.inv_ccb : a.inv_cbs_last);
         const int cb = s - tap * cbs;
         const int r = tdiv(tap, a.inv_S);
         const int sx = tap - r * a.S;
@@ -342,7 +410,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(ws + m * wrow + (unsigned)lane * 16u);
     };
     // steps of this wave in a chunk of cbs channel blocks
-    auto steps_of = [&](int cbs) { const int all = a.RS * cbs; return all > kgrp ? (all - kgrp + KG - 1) >> a.lkg : 0; };
+    auto steps_of = [&](int cbs) { const int all = a.RS * cbs; return all > kgrp ? (all - kgrp + KG - 1) >> lkg : 0; };
     auto start_w = [&](int s0, int n, int cbs, int gcb0) __attribute__((always_inline)) {
         table(s0, min(64, n - s0), cbs, gcb0);
 #pragma unroll
@@ -350,13 +418,26 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     };
     int cbs = min(a.CC, a.NCB * CB) / CB;
     int nsteps = steps_of(cbs);
-    if (nsteps > 0) start_w(0, nsteps, cbs, 0);
+    // (A wave without steps requests weights all the same, here and below: behind loads that only some waves issue
+    // the compiler no longer knows how many are in flight, and waits for the weights before it stages the input.)
+    start_w(0, nsteps, cbs, 0);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---------------------------------------------------------------- padding: the whole image is cleared once
+    // ---------------------------------------------------------------- padding: zeros, once for all chunks.  Only the positions that the
+    // input does not reach, so that it and the staging need not wait for each other: threads lie as (group of 16-byte words, position).
+    // (Clearing the whole image took a 512-thread workgroup 1.5 us of its first 3 at 75 KB.)
     if (a.zero) {
-        for (int i = tid; i < a.zero; i += NT) *reinterpret_cast<uint4w*>(lds + i * 16) = uint4w{0u, 0u, 0u, 0u};
-        lds_barrier();                                       // (the loads stay in flight)
+        const int words = (int)((unsigned)a.CC / CV), pw = a.zero >> 16, groups = NT >> pw;      // (positions, rounded up to 2^pw <= NT)
+        const int first = tid >> pw;
+        for (int pos = tid & ((1 << pw) - 1); pos < (a.zero & 0xffff); pos += 1 << pw) {
+            const int sm = tdiv(pos, a.inv_npos1);
+            const int rem = pos - sm * a.npos1;
+            const int i = tdiv(rem, a.inv_Ws);
+            const int w = rem - i * a.Ws;
+            const bool inside = sm < nsv && (unsigned)(i - ilo) < (unsigned)nrows && (unsigned)(w - a.pad_w) < (unsigned)a.wcols;
+            if (!inside)
+                for (int cg = first; cg < words; cg += groups) *reinterpret_cast<uint4w*>(lds + pos * a.pitch + cg * 16) = uint4w{0u, 0u, 0u, 0u};
+        }
     }
 
     // positions of this lane's NW column blocks in the tile image (with its k group)
@@ -369,7 +450,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         const int tp = tdiv(rem, a.inv_Q);
         const int tq = rem - tp * a.Q;
         const bool ok = f < a.npos;
-        bbase[i] = (ok ? ((sm * a.Hs + tp * a.s_h) * a.Ws + tq * a.s_w) * a.pitch : 0) + kg * 16;
+        bbase[i] = (ok ? (sm * a.npos1 + tp * a.s_h * a.Ws + tq * a.s_w) * a.pitch : 0) + kg * 16;
     }
     Acc acc[MW][NW];
 #pragma unroll
@@ -377,35 +458,45 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
 #pragma unroll
         for (int i = 0; i < NW; ++i) acc[m][i] = Acc{0, 0, 0, 0};
 
-    for (int ch = 0; ch < a.nchunks; ++ch) {
-        if (ch > 0) lds_barrier();                           // the previous chunk has been multiplied
-        if (st.nblocks) store_pre(pre[0], tid);
-        if (two) {
-            store_pre(pre[1], tid + per_round);
-            for (int v0 = tid + 2 * per_round; v0 - tid < st.nblocks; v0 += 2 * per_round) {
-                const bool more = v0 - tid + per_round < st.nblocks;
-                load_pre(pre[0], v0);
-                if (more) load_pre(pre[1], v0 + per_round);
-                store_pre(pre[0], v0);
-                if (more) store_pre(pre[1], v0 + per_round);
+    // the rest of a chunk, once its first rounds have been loaded
+    auto stage = [&]() __attribute__((always_inline)) {
+        if (st.nblocks) store_pre(0);
+        if constexpr (PR == 2) {
+            if (two) store_pre(1);
+        }
+        for (int v0 = tid + PR * per_round; v0 - tid < st.nblocks; v0 += PR * per_round) {
+            TileSlot t[PR][VB];
+            const bool more = PR == 2 && v0 - tid + per_round < st.nblocks;
+            locate(t[0], v0);
+            tile_load<X, EPV>(pre[0], st, t[0]);
+            if constexpr (PR == 2) {
+                if (more) {
+                    locate(t[1], v0 + per_round);
+                    tile_load<X, EPV>(pre[1], st, t[1]);
+                }
             }
-        } else if constexpr (PR == 1) {
-            for (int v0 = tid + per_round; v0 - tid < st.nblocks; v0 += per_round) {
-                load_pre(pre[0], v0);
-                store_pre(pre[0], v0);
+            tile_store<X, EPV>(pre[0], st, lds, a.pitch, t[0]);
+            if constexpr (PR == 2) {
+                if (more) tile_store<X, EPV>(pre[1], st, lds, a.pitch, t[1]);
             }
         }
-        lds_barrier();
+    };
+    // (the first chunk ahead of the loop, so that the compiler knows there which loads are in flight)
+    stage();
+    lds_barrier();
+    for (int ch = 0;; ++ch) {
         if (ch + 1 < a.nchunks) {
             st.xs += (int64_t)a.CC * st.plane_b;
             st.cleft -= a.CC;
             st.whole = st.cleft >= a.CC;
-            if (st.nblocks) load_pre(pre[0], tid);
-            if (two) load_pre(pre[1], tid + per_round);
+            if (st.nblocks) load_pre(0);
+            if constexpr (PR == 2) {
+                if (two) load_pre(1);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         // ------------------------------------------------------------ multiply
-        const int gcb0 = ch * (a.CC / CB);
+        const int gcb0 = ch * (int)((unsigned)a.CC / CB);
         for (int s0 = 0; s0 < nsteps; s0 += 64) {
             const int n = min(64, nsteps - s0);
             if (s0 > 0) start_w(s0, nsteps, cbs, gcb0);
@@ -444,40 +535,49 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
             for (int u = 0; u < PF - 1; ++u)
                 if (main_steps + u < n) step(main_steps + u, u, false);
         }
-        if (ch + 1 < a.nchunks) {
-            cbs = min(a.CC, a.NCB * CB - (ch + 1) * a.CC) / CB;
-            nsteps = steps_of(cbs);
-            if (nsteps > 0) start_w(0, nsteps, cbs, gcb0 + a.CC / CB);
-        }
+        if (ch + 1 >= a.nchunks) break;
+        cbs = min(a.CC, a.NCB * CB - (ch + 1) * a.CC) / CB;
+        nsteps = steps_of(cbs);
+        start_w(0, nsteps, cbs, gcb0 + (int)((unsigned)a.CC / CB));
+        lds_barrier();                                       // the chunk has been multiplied
+        stage();
+        lds_barrier();
     }
 
     // ---------------------------------------------------------------- the outputs: a lane holds the positions 4 kg .. 4 kg + 3 of a
     // block for channel n16 of the row block
+    const int PQ = a.P * a.Q;
     const int nvalid = (a.NS == 1 ? min(a.TP, a.P - p0) : a.P) * a.Q;      // positions of a sample that exist
-    auto multiplier = [&](int m) { return kIntActs<DT> && a.requant ? a.requant[min((mblk0 + m) * 16 + n16, a.D - 1)] : 0.0f; };
+    auto multiplier = [&](int m) __attribute__((always_inline)) {
+        float rq = rqs[0];
+        if constexpr (MW > 1) rq = m == 1 ? rqs[1] : rq;
+        if constexpr (MW > 2) rq = m == 2 ? rqs[2] : (m == 3 ? rqs[3] : rq);
+        return rq;
+    };
+    const bool relu = a.bits & 4, codes = a.bits & 1 << 16;
     auto put = [&](int m, int i, const Acc& v, float rq) __attribute__((always_inline)) {
         const int d = (mblk0 + m) * 16 + n16;
         const int f = (wn * NW + i) * 16 + 4 * kg;
         if (d >= a.D) return;
         if (a.NS == 1) {
             const int count = min(nvalid - f, 4);
-            if (count > 0) tile_put4<DT>(y, ((int64_t)b0 * a.D + d) * PQ + p0 * a.Q + f, v, a.epi_relu, a.requant, rq, count);
+            if (count > 0) tile_put4<DT>(y, ((int64_t)b0 * a.D + d) * PQ + p0 * a.Q + f, v, relu, codes, rq, count);
         } else {
             // whole planes of several samples: a group of four that reaches into the next sample is stored one by one
             const int sm = tdiv(f, a.inv_TPQ), rem = f - sm * a.TPQ;
             if (rem + 4 <= a.TPQ) {
-                if (f < a.npos && b0 + sm < a.N) tile_put4<DT>(y, ((int64_t)(b0 + sm) * a.D + d) * PQ + rem, v, a.epi_relu, a.requant, rq, 4);
+                if (f < a.npos && b0 + sm < a.N) tile_put4<DT>(y, ((int64_t)(b0 + sm) * a.D + d) * PQ + rem, v, relu, codes, rq, 4);
                 return;
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int smj = tdiv(f + j, a.inv_TPQ), remj = f + j - smj * a.TPQ;
                 if (f + j < a.npos && b0 + smj < a.N)
-                    tile_put4<DT>(y, ((int64_t)(b0 + smj) * a.D + d) * PQ + remj, Acc{v[j], v[j], v[j], v[j]}, a.epi_relu, a.requant, rq, 1);
+                    tile_put4<DT>(y, ((int64_t)(b0 + smj) * a.D + d) * PQ + remj, Acc{v[j], v[j], v[j], v[j]}, relu, codes, rq, 1);
             }
         }
     };
-    const int waves1 = 1 << (a.lwm + a.lwn);                 // waves of one group
+    const int waves1 = 1 << (lwm + lwn);                 // waves of one group
     const int w1 = wave & (waves1 - 1);
     if (KG == 2) {
         // the second group hands its sums to the first, a lane's own 16 bytes per block
@@ -517,7 +617,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
                 acc[t / NW][t % NW] = s;
             }
         }
-        if (!a.epi_pool) {
+        if (!(a.bits & 8)) {
 #pragma unroll
             for (int t = 0; t < BPW; ++t) {
                 const int b = kgrp + t * KG;
@@ -525,7 +625,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
             }
             return;
         }
-    } else if (!a.epi_pool) {
+    } else if (!(a.bits & 8)) {
         if (kgrp > 0) return;
 #pragma unroll
         for (int m = 0; m < MW; ++m) {
@@ -557,6 +657,13 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
 #pragma unroll
             for (int i = 0; i < NW; ++i) give(m, i, acc[m][i]);
     }
+    if constexpr (kIntActs<DT>) {
+        // the multipliers behind the rows (a row is 4 words longer than its sums): by the first wave that holds the row's channels
+        if (kgrp == 0 && wn == 0 && kg == 0) {
+#pragma unroll
+            for (int m = 0; m < MW; ++m) ex[((wm * MW + m) * 16 + n16) * a.epi_pitch + a.epi_pitch - 4] = __float_as_int(rqs[m]);
+        }
+    }
     lds_barrier();
     // One element = V neighbouring outputs of a row (4 where the rows allow it).  A thread keeps to one element of the
     // tile (decoded once) and walks over the output channels; the threads lie as (channel group,
@@ -584,17 +691,18 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
             for (int dl = dg; dl < dend; dl += dgroups) {
                 const int d = db * a.DB + dl;
                 const A* sp = src + dl * a.epi_pitch;
-                const float rq = kIntActs<DT> && a.requant ? a.requant[d] : 0.0f;
+                float rq = 0.0f;
+                if constexpr (kIntActs<DT>) rq = __int_as_float(ex[dl * a.epi_pitch + a.epi_pitch - 4]);
                 if constexpr (V == 4) {
                     const Acc u0 = *reinterpret_cast<const Acc*>(sp), u1 = *reinterpret_cast<const Acc*>(sp + 4);
                     const Acc w0 = *reinterpret_cast<const Acc*>(sp + a.Q), w1_ = *reinterpret_cast<const Acc*>(sp + a.Q + 4);
                     auto most = [](A p, A q, A r, A s) { return tile_max(tile_max(p, q), tile_max(r, s)); };
                     const Acc v = {most(u0[0], u0[1], w0[0], w0[1]), most(u0[2], u0[3], w0[2], w0[3]),
                                    most(u1[0], u1[1], w1_[0], w1_[1]), most(u1[2], u1[3], w1_[2], w1_[3])};
-                    tile_put4<DT>(y, off0 + d * dstride, v, a.epi_relu, a.requant, rq, 4);
+                    tile_put4<DT>(y, off0 + d * dstride, v, relu, codes, rq, 4);
                 } else {
                     const A v = tile_max(tile_max(sp[0], sp[1]), tile_max(sp[a.Q], sp[a.Q + 1]));
-                    tile_put4<DT>(y, off0 + d * dstride, Acc{v, v, v, v}, a.epi_relu, a.requant, rq, 1);
+                    tile_put4<DT>(y, off0 + d * dstride, Acc{v, v, v, v}, relu, codes, rq, 1);
                 }
             }
         }
@@ -604,12 +712,12 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     else pool(std::integral_constant<int, 1>{});
 }
 
-template <sc_dtype_t DT, int MW, int NW>
-static sc_status_t launch_tile_one(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream)
+template <sc_dtype_t DT, int MW, int NW, int LEPV>
+static sc_status_t launch_tile_one(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
     using X = typename Types<DT>::X;
     using Y = typename Types<DT>::Y;
-    auto kernel = &mfma_tile_kernel<DT, MW, NW>;
+    auto kernel = &mfma_tile_kernel<DT, MW, NW, LEPV>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -622,23 +730,23 @@ static sc_status_t launch_tile_one(const Plan& p, const MfmaArgs& a, const void*
     return hipGetLastError() == hipSuccess ? SC_OK : SC_ERR_HIP;
 }
 
-template <sc_dtype_t DT>
-static sc_status_t launch_tile_typed(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream)
+template <sc_dtype_t DT, int LEPV>
+static sc_status_t launch_tile_typed(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
     switch (p.mg.MW * 10 + p.mg.NW) {
-        case 11: return launch_tile_one<DT, 1, 1>(p, a, x, y, grid, stream);
-        case 12: return launch_tile_one<DT, 1, 2>(p, a, x, y, grid, stream);
-        case 14: return launch_tile_one<DT, 1, 4>(p, a, x, y, grid, stream);
-        case 17: return launch_tile_one<DT, 1, 7>(p, a, x, y, grid, stream);
-        case 18: return launch_tile_one<DT, 1, 8>(p, a, x, y, grid, stream);
-        case 21: return launch_tile_one<DT, 2, 1>(p, a, x, y, grid, stream);
-        case 22: return launch_tile_one<DT, 2, 2>(p, a, x, y, grid, stream);
-        case 24: return launch_tile_one<DT, 2, 4>(p, a, x, y, grid, stream);
-        case 27: return launch_tile_one<DT, 2, 7>(p, a, x, y, grid, stream);
-        case 28: return launch_tile_one<DT, 2, 8>(p, a, x, y, grid, stream);
-        case 41: return launch_tile_one<DT, 4, 1>(p, a, x, y, grid, stream);
-        case 42: return launch_tile_one<DT, 4, 2>(p, a, x, y, grid, stream);
-        case 44: return launch_tile_one<DT, 4, 4>(p, a, x, y, grid, stream);
+        case 11: return launch_tile_one<DT, 1, 1, LEPV>(p, a, x, y, grid, stream);
+        case 12: return launch_tile_one<DT, 1, 2, LEPV>(p, a, x, y, grid, stream);
+        case 14: return launch_tile_one<DT, 1, 4, LEPV>(p, a, x, y, grid, stream);
+        case 17: return launch_tile_one<DT, 1, 7, LEPV>(p, a, x, y, grid, stream);
+        case 18: return launch_tile_one<DT, 1, 8, LEPV>(p, a, x, y, grid, stream);
+        case 21: return launch_tile_one<DT, 2, 1, LEPV>(p, a, x, y, grid, stream);
+        case 22: return launch_tile_one<DT, 2, 2, LEPV>(p, a, x, y, grid, stream);
+        case 24: return launch_tile_one<DT, 2, 4, LEPV>(p, a, x, y, grid, stream);
+        case 27: return launch_tile_one<DT, 2, 7, LEPV>(p, a, x, y, grid, stream);
+        case 28: return launch_tile_one<DT, 2, 8, LEPV>(p, a, x, y, grid, stream);
+        case 41: return launch_tile_one<DT, 4, 1, LEPV>(p, a, x, y, grid, stream);
+        case 42: return launch_tile_one<DT, 4, 2, LEPV>(p, a, x, y, grid, stream);
+        case 44: return launch_tile_one<DT, 4, 4, LEPV>(p, a, x, y, grid, stream);
     }
     return SC_ERR_UNSUPPORTED;
 }

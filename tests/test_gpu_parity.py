@@ -2003,3 +2003,36 @@ def test_contraction_split_on_whole_layers(name, C, D, HW, N, sparsity, dtype):
         ran.append(t.buffers)
     assert 8 in ran and 4 in ran
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+@pytest.mark.parametrize("name,C,D,H,W,R,S,stride,ph,pw,N,shapes", [
+    ("more positions than threads", 40, 20, 9, 70, 3, 3, 1, 1, 1, 2, [dict(tile_p=6, tile_d=32), dict(tile_p=2, tile_d=16, wg_threads=512)]),
+    ("several samples, the last group short", 70, 20, 3, 3, 3, 3, 1, 2, 2, 5, [dict(tile_p=5, sub_batch=3), dict(tile_p=5, sub_batch=2, wg_threads=512)]),
+    ("columns only", 150, 37, 1, 30, 1, 5, 1, 0, 2, 3, [dict(tile_p=1), dict(tile_p=1, sub_batch=2, chunk_c=64)]),
+    ("rows only", 33, 16, 7, 9, 3, 1, 1, 1, 0, 2, [dict(tile_p=3), dict(tile_p=7, sub_batch=2)]),
+    ("strided", 70, 20, 11, 13, 3, 3, 2, 1, 1, 3, [dict(tile_p=2, chunk_c=64), dict(tile_p=6, wg_threads=512)]),
+    ("one column of input", 64, 16, 5, 1, 3, 3, 1, 1, 1, 2, [dict(tile_p=2), dict(tile_p=5)]),
+])
+def test_dense_padding_is_cleared_and_nothing_else(name, C, D, H, W, R, S, stride, ph, pw, N, shapes, dtype):
+    """The padding of a staged tile is cleared position by position, next to the staging: right whatever the LDS holds when the
+    workgroup starts.  A launch on NaN (on codes of 127) runs ahead, so that a position left out shows."""
+    import torch
+    l = wl.Layer("pad", C, D, H, W, R, S, stride, stride if S > 1 else 1, ph, pw, N=N, sparsity=0.6, dtype=dtype, seed=940)
+    data = wl.prepare(l)
+    ref = G.oracle_out(l, data)
+    dirty = wl.Layer("dirty", 64, 64, 32, 32, 3, 3, 1, 1, 1, 1, N=32, sparsity=0.6, dtype=dtype, seed=941)
+    ddata = wl.prepare(dirty)
+    dplan = G.make_plan(dirty, ddata)
+    dplan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, tile_p=8, tile_d=32, wg_threads=256)
+    dx = torch.full((32, 64, 32, 32), float("nan") if dtype == "f16" else 127, device="cuda", dtype=torch.float16 if dtype == "f16" else torch.int8)
+    dy = torch.empty((32, 64, 32, 32), device="cuda", dtype=B.torch_out_dtype(dplan.dtype))
+    plan = G.make_plan(l, data)
+    for shape in shapes:
+        plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, **shape)
+        print("case pad", name, dtype, plan.get_tuning().as_dict(), flush=True)
+        for k in range(2):
+            B.forward_torch(dplan, dx, dy)
+            G.check(l, G.run_gpu(plan, data["x"]), ref, f"pad {name} {shape} {k}")
+    plan.destroy()
+    dplan.destroy()
