@@ -51,7 +51,7 @@ struct MfmaArgs {
 // What a launch of the one-shot kernel on the transposed tile is made of.  A kernel reads its arguments through the scalar cache, 64 bytes a miss and about 450 clocks each
 // time that it waits; read where they are first used they cost it six such waits before its first load and eight more before
 // its first multiplication, 3 of the 9 us of an int8 VGG-16 layer.  They are therefore few, derived on the host as far as they
-// can be, and all read at once when the kernel starts (tile_args).
+// can be, and all read at once when the kernel starts (args_at_once).
 struct TileArgs {
     // workgroup order (see tile_block): workgroups / 8 and what is left, inner extent; samples and rows of tiles
     int gq, gr, inner;
@@ -76,6 +76,27 @@ struct TileArgs {
     int bits;
     const float* requant;        // multipliers (without requantisation: any D floats)
 };
+
+// The arguments of a kernel in scalar registers, requested together (see TileArgs).  Opaque to the compiler, which would read
+// them again from memory at each use.
+template <typename Args>
+__device__ __forceinline__ Args args_at_once(const Args& args)
+{
+    static_assert(sizeof(Args) == 3 * sizeof(int16w_));
+    const int16w_* from = reinterpret_cast<const int16w_*>(&args);
+    int16w_ v0 = from[0], v1 = from[1], v2 = from[2];
+    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2));
+    int words[48];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        words[i] = v0[i];
+        words[16 + i] = v1[i];
+        words[32 + i] = v2[i];
+    }
+    Args a;
+    __builtin_memcpy(&a, words, sizeof(a));
+    return a;
+}
 
 // (by the columns per staging load)
 sc_status_t launch_tile_f16_1(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);

@@ -252,26 +252,6 @@ __device__ __forceinline__ void tile_put4(typename Types<DT>::Y* __restrict__ y,
     }
 }
 
-// The arguments in scalar registers, requested together (see TileArgs).  Opaque to the compiler, which would read them again from
-// memory at each use.
-__device__ __forceinline__ TileArgs tile_args(const TileArgs& args)
-{
-    static_assert(sizeof(TileArgs) == 3 * sizeof(int16w_));
-    const int16w_* from = reinterpret_cast<const int16w_*>(&args);
-    int16w_ v0 = from[0], v1 = from[1], v2 = from[2];
-    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2));
-    int words[48];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        words[i] = v0[i];
-        words[16 + i] = v1[i];
-        words[32 + i] = v2[i];
-    }
-    TileArgs a;
-    __builtin_memcpy(&a, words, sizeof(a));
-    return a;
-}
-
 // Workgroup -> (tile of positions bt, block of output channels db of ndb).  Workgroups are dealt round-robin to
 // the 8 XCDs: they are renumbered so that each XCD gets a contiguous run.  Within it either the blocks of one tile
 // are neighbours (they find the tile in the L2 that their siblings loaded), or, where the weights outweigh the
@@ -300,7 +280,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     constexpr int PF = MW >= 2 ? 4 : 8;                      // steps of weights in flight
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
-    const TileArgs a = tile_args(args);
+    const TileArgs a = args_at_once(args);
     constexpr int lepv = LEPV;                               // log2 of the columns per staging load
     const int lwm = a.bits >> 6 & 3, lwn = a.bits >> 8 & 3, lkg = a.bits >> 10 & 3;
     const int NT = (a.bits >> 12 & 15) * 64;

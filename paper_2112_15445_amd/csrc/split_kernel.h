@@ -50,24 +50,6 @@ sc_status_t launch_split_pipe_1(const Plan& p, const SplitArgs& a, const SplitTa
 sc_status_t launch_split_pipe_2(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_split_pipe_4(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 
-__device__ __forceinline__ SplitArgs split_args(const SplitArgs& args)
-{
-    static_assert(sizeof(SplitArgs) == 3 * sizeof(int16w_));
-    const int16w_* from = reinterpret_cast<const int16w_*>(&args);
-    int16w_ v0 = from[0], v1 = from[1], v2 = from[2];
-    asm volatile("" : "+s"(v0), "+s"(v1), "+s"(v2));
-    int words[48];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        words[i] = v0[i];
-        words[16 + i] = v1[i];
-        words[32 + i] = v2[i];
-    }
-    SplitArgs a;
-    __builtin_memcpy(&a, words, sizeof(a));
-    return a;
-}
-
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
 typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
@@ -370,7 +352,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int NT = 256 * KG;
-    const SplitArgs a = split_args(args);
+    const SplitArgs a = args_at_once(args);
     // steps of weights in flight: a step multiplies for 6 MW NW matrix instructions (16 clocks and
     // more each), L2 answers after several hundred clocks.  PF * NW is even (parity of the ring below).
     constexpr int PF = MW * NW >= 7 ? 2 : (MW * NW >= 2 ? 4 : 6);
@@ -575,7 +557,7 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     const int lane = tid & 63;
     const int wave12 = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    const SplitArgs a = split_args(args);
+    const SplitArgs a = args_at_once(args);
     const SplitBlock block = split_block(a);
     const int bt = block.bt, db = block.db;
     const int bg = __builtin_amdgcn_readfirstlane(sdiv(bt, a.inv_tiles_p));
