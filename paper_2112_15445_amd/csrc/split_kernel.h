@@ -12,6 +12,9 @@ namespace sc {
 // first load, in seven trips to memory one after the other).  With that, staging instantiated by the columns of a load and a block's
 // place worked out once for all chunks: 3x3 128-128 at 28 x 28, batch 32 39.9 -> 37.3 us, 3x3 stride 2 512-512 at 14 x 14 51.1 -> 48.9, 1x1
 // 2048-512 at 7 x 7 30.9 -> 28.7, 1-D 300-64 along 64, batch 128 11.3 -> 10.8, 3x3 100-90 at 27 x 31, batch 7 17.3 -> 16.5.
+// (Loads of four columns wherever a run has four, after that: 28.7 -> 27.7, 16.5 -> 15.5 on the last and the last but two, rows of 7, 49 and 31.
+// Two rounds loaded a chunk ahead instead of one: level. The first chunk of the pipelined form staged by all twelve waves: 1-D 10.8 -> 11.5, its
+// registers spill.)
 struct SplitArgs {
     // workgroup order (see split_block): workgroups / 8 and what is left, extents of the two inner indices
     int gq, gr, inner, inner2;
@@ -113,7 +116,7 @@ __device__ __forceinline__ SplitBlock split_block(const SplitArgs& a)
 }
 
 // ------------------------------------------------------------------------------------------------
-// Staging of one chunk: blocks of 8 channels x EPV columns, the widest loads the runs allow, split
+// Staging of one chunk: blocks of 8 channels x EPV columns, loaded with any alignment that an element has, split
 // and transposed in registers, one 16-byte word per position, channel group and image.  `rows` runs
 // of `run` elements per sample and channel (where the staged rows carry no padding columns they are
 // one run).  Blocks are dealt to the threads in rounds; a round is 32 registers of loads per thread.
@@ -182,15 +185,16 @@ __device__ __forceinline__ void split_pad(unsigned char* lds, int tid, int NT, c
 }
 
 // Where a block is read from (bytes from st.xs, in channel 0 of the chunk, and its channel group) and written to (bytes into the first
-// image; -1: no such block, then block 0 is read); columns of it that are staged.
-struct SplitSlot { unsigned off; int cg, dst, left; };
+// image; -1: no such block, then block 0 is read).  A run that is no multiple of EPV ends in a block that starts EPV before its
+// end: the columns that two blocks share are written twice with the same values, and loads have any alignment of 4 bytes.
+struct SplitSlot { unsigned off; int cg, dst; };
 template <int EPV> constexpr int kSplitVB = 4 / EPV;         // blocks per thread and round
 
-template <int EPV>
-__device__ __forceinline__ void split_slots(SplitSlot (&slot)[kSplitVB<EPV>], const SplitStage& st, const SplitArgs& a, int v0, int NT)
+template <int EPV, int VB>
+__device__ __forceinline__ void split_slots(SplitSlot (&slot)[VB], const SplitStage& st, const SplitArgs& a, int v0, int NT)
 {
 #pragma unroll
-    for (int u = 0; u < kSplitVB<EPV>; ++u) {
+    for (int u = 0; u < VB; ++u) {
         const int v = v0 + u * NT;
         const bool live = v < st.nblocks;
         const int vv = live ? v : 0;
@@ -198,50 +202,65 @@ __device__ __forceinline__ void split_slots(SplitSlot (&slot)[kSplitVB<EPV>], co
         int r = vv - mul24(cg, st.per_cg), sm = 0, ii = 0;
         if (st.rowsG != st.per_cg) { sm = sdiv(r, st.inv_rowsG); r -= mul24(sm, st.rowsG); }
         if (st.rowsG != st.G) { ii = sdiv(r, st.inv_G); r -= mul24(ii, st.G); }
-        // (32-bit offsets from a wave-uniform base: one address register per load)
-        slot[u].off = (unsigned)sm * st.sample4 + (unsigned)mul24(ii, (int)st.row4) + (unsigned)r * (EPV * 4);
+        const int col = min(r * EPV, st.run - EPV);
+        slot[u].off = (unsigned)sm * st.sample4 + (unsigned)mul24(ii, (int)st.row4) + (unsigned)col * 4u;
         slot[u].cg = cg;
-        slot[u].dst = live ? mul24(mul24(sm, a.npos1) + st.dst0 + mul24(ii, a.Ws) + r * EPV, a.pitch) + cg * 16 : -1;
-        slot[u].left = st.run - r * EPV;
+        slot[u].dst = live ? mul24(mul24(sm, a.npos1) + st.dst0 + mul24(ii, a.Ws) + col, a.pitch) + cg * 16 : -1;
     }
 }
 
-template <int EPV>
-__device__ __forceinline__ void split_load(float (&pre)[32], const SplitStage& st, const SplitSlot (&slot)[kSplitVB<EPV>])
+template <int EPV, int VB>
+__device__ __forceinline__ void split_load(float (&pre)[32], const SplitStage& st, const SplitSlot (&slot)[VB])
 {
-    struct alignas(EPV * 4) Vec { float e[EPV]; };
+    typedef float Vec __attribute__((ext_vector_type(EPV), aligned(4)));
+    // (whole addresses in the lanes, as tile_src)
+    using Src = const __attribute__((address_space(1))) char*;
+    auto load = [&](int at, Src src) __attribute__((always_inline)) {
+        const Vec t = *reinterpret_cast<const __attribute__((address_space(1))) Vec*>(src);
 #pragma unroll
-    for (int u = 0; u < kSplitVB<EPV>; ++u) {
+        for (int e = 0; e < EPV; ++e) pre[at * EPV + e] = t[e];
+    };
+#pragma unroll
+    for (int u = 0; u < VB; ++u) {
         unsigned off = slot[u].off;
         int cg = slot[u].cg;
         // (opaque: a block's addresses are worked out again for every chunk; kept in registers they took 100 of them and the
         // accumulators spilled)
         asm volatile("" : "+v"(off), "+v"(cg));
-        unsigned o = off + (unsigned)mul24(cg, 8) * st.plane4;
+        const Src base = reinterpret_cast<Src>(reinterpret_cast<uint64_t>(st.xs) + off);
+        if (st.whole) {
+            Src src = base + (uint64_t)((unsigned)mul24(cg, 8) * st.plane4);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            // (channels past the layer's last: the block's place in channel 0, zeroed when it is stored)
-            const unsigned at = st.whole ? o : (cg * 8 + j < st.cleft ? o : off);
-            const Vec t = *reinterpret_cast<const Vec*>(st.xs + at);
+            for (int j = 0; j < 8; ++j) {
+                load(u * 8 + j, src);
+                src += st.plane4;
+                asm("" : "+v"(src));
+                __builtin_amdgcn_sched_barrier(0);           // (one address at a time: registers)
+            }
+        } else {
+            unsigned o = (unsigned)mul24(cg, 8) * st.plane4;
 #pragma unroll
-            for (int e = 0; e < EPV; ++e) pre[(u * 8 + j) * EPV + e] = t.e[e];
-            o += st.plane4;
+            for (int j = 0; j < 8; ++j) {
+                // (channels past the layer's last: the block's place in channel 0, zeroed when it is stored)
+                load(u * 8 + j, base + (uint64_t)(cg * 8 + j < st.cleft ? o : 0u));
+                o += st.plane4;
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 }
 
-template <int EPV>
-__device__ __forceinline__ void split_put(const float (&pre)[32], const SplitStage& st, unsigned char* lds, const SplitSlot (&slot)[kSplitVB<EPV>], const SplitArgs& a)
+template <int EPV, int VB>
+__device__ __forceinline__ void split_put(const float (&pre)[32], const SplitStage& st, unsigned char* lds, const SplitSlot (&slot)[VB], const SplitArgs& a)
 {
 #pragma unroll
-    for (int u = 0; u < kSplitVB<EPV>; ++u) {
+    for (int u = 0; u < VB; ++u) {
         if (slot[u].dst < 0) continue;
         int cg = slot[u].cg, to = slot[u].dst;
         asm volatile("" : "+v"(cg), "+v"(to));
         unsigned char* dst = lds + to;
 #pragma unroll
         for (int e = 0; e < EPV; ++e) {
-            if (EPV > 1 && e >= slot[u].left) continue;
             uint4w w0, w1, w2;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -375,14 +394,14 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 
     // the loads of the first chunk (nblocks = 0: a tile that lies in the padding altogether)
     SplitStage st = split_stage<EPV>(a, x, b0, row0, ch_lo * a.CC);
-    constexpr int VB = kSplitVB<EPV>, per_round = NT * VB;
+    // (the largest wave tile has no registers for the blocks' places, nor for four blocks at once: 1331 spills)
+    constexpr bool kept = MW * NW < 14;
+    constexpr int VB = kept ? kSplitVB<EPV> : 1, per_round = NT * VB;
     float pre[32];
     SplitSlot slots[VB];
     split_slots<EPV>(slots, st, a, tid, NT);
     if (st.nblocks) split_load<EPV>(pre, st, slots);
     __builtin_amdgcn_sched_barrier(0);
-    // (the largest wave tile has no registers for them)
-    constexpr bool kept = MW * NW < 14;
     auto again = [&]() __attribute__((always_inline)) {
         if constexpr (!kept) {
             int v0 = tid;
