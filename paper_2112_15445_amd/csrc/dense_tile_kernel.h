@@ -23,7 +23,8 @@
 //     ahead of the loop over the chunks, so that the compiler knows how many loads are in flight and waits for the input only, not for the weights behind it.
 // Measured per pass, before and after the last of these: f16 3x3 64-64 at 56 x 56, batch 32 14.9, 14.5 us; f16 3x3 256-256 at 14 x 14,
 // batch 32 13.6, 13.0; 4b/16b 3x3 512-512 at 4 x 4, batch 64 11.9, 10.9; the 13 int8 layers of VGG-16, batch 64 121, 111 (a layer launched alone again and
-// again 9.3, 7.5 in the mean: in the stack about 1.5 us of each launch are the first pass through its code).
+// again 9.3, 7.5 in the mean: in the stack about 1.5 us of each launch are the first pass through its code).  More weights in flight (8 and 12 steps) are
+// slower: they compete with the input when a workgroup starts (112 us for the int8 layers).
 #pragma once
 
 #include "dense_mfma_kernel.h"
@@ -34,7 +35,7 @@ namespace sc {
 // Staging.  One block = CV channels x EPV columns of one run (an input row; or, where the staged rows carry no
 // padding columns, all of them).  A run that is no multiple of EPV ends in a block that starts EPV before its end: the
 // columns that two blocks share are written twice with the same values.  The loads therefore have any
-// alignment that an element has.  A round is one load of 32 registers per thread; two rounds are in flight.
+// alignment that an element has.  A round is one load of 32 registers per thread.
 // ------------------------------------------------------------------------------------------------
 struct TileStage {
     const char* xs;              // first staged element of sample 0, channel 0 of the chunk
@@ -323,32 +324,23 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         st.cleft = a.C;
         st.whole = st.cleft >= a.CC;
     }
-    // Rounds of a chunk that are loaded a chunk ahead.  One for the smallest wave tiles: 32 registers fewer leave room
-    // for three or four waves per SIMD (109 - 139 registers; 168 are three), which is what layers with many
-    // short workgroups need to overlap them (4b/16b 3x3 80-383 at 6 x 6, batch 128, 15.8 us with two rounds and two waves, 12.4 with one
-    // and three; 4-bit 3x3 48-32 at 17 x 17, batch 128, 15.7 and 14.6).  Other layers are level (0.99 in the mean over 104).
-    constexpr int PR = (MW * NW >= 16 && MW == 4) || MW * NW <= 4 ? 1 : 2;
+    // One round of a chunk is loaded a chunk ahead.  (Two, the form before, cost 32 registers and half of the code -- 80 KB for the
+    // largest wave tiles, 46 now, of the 64 KB of the instruction cache of two CUs: f16 3x3 64-64 at 56 x 56, batch 32 15.4 -> 15.0 us, the
+    // 13 int8 layers of VGG-16, batch 64 110.9 -> 108.3, other layers level.  109 - 139 registers for the wave tiles of up to four blocks leave
+    // room for three or four waves per SIMD, which layers with many short workgroups need to overlap them: 4b/16b 3x3 80-383 at 6 x 6,
+    // batch 128, 15.8 us with two waves, 12.4 with three.)
     constexpr int EPV = 1 << LEPV, VB = kTileVB<X, EPV>;
-    unsigned pre[PR][32];
-    TileSlot slots[PR][VB];
+    unsigned pre[32];
+    TileSlot slots[VB];
     const int per_round = NT * VB;
     auto locate = [&](TileSlot (&t)[VB], int v0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < VB; ++u) t[u] = tile_slot<X, EPV>(st, a.pitch, v0 + u * NT);
     };
-    auto load_pre = [&](int r) __attribute__((always_inline)) { tile_load<X, EPV>(pre[r], st, slots[r]); };
-    auto store_pre = [&](int r) __attribute__((always_inline)) { tile_store<X, EPV>(pre[r], st, lds, a.pitch, slots[r]); };
-    const bool two = PR == 2 && st.nblocks > per_round;
     // (nblocks = 0: a tile that lies in the padding altogether)
     if (st.nblocks) {
-        locate(slots[0], tid);
-        load_pre(0);
-    }
-    if constexpr (PR == 2) {
-        if (two) {
-            locate(slots[1], tid + per_round);
-            load_pre(1);
-        }
+        locate(slots, tid);
+        tile_load<X, EPV>(pre, st, slots);
     }
     __builtin_amdgcn_sched_barrier(0);
 
@@ -440,25 +432,12 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
 
     // the rest of a chunk, once its first rounds have been loaded
     auto stage = [&]() __attribute__((always_inline)) {
-        if (st.nblocks) store_pre(0);
-        if constexpr (PR == 2) {
-            if (two) store_pre(1);
-        }
-        for (int v0 = tid + PR * per_round; v0 - tid < st.nblocks; v0 += PR * per_round) {
-            TileSlot t[PR][VB];
-            const bool more = PR == 2 && v0 - tid + per_round < st.nblocks;
-            locate(t[0], v0);
-            tile_load<X, EPV>(pre[0], st, t[0]);
-            if constexpr (PR == 2) {
-                if (more) {
-                    locate(t[1], v0 + per_round);
-                    tile_load<X, EPV>(pre[1], st, t[1]);
-                }
-            }
-            tile_store<X, EPV>(pre[0], st, lds, a.pitch, t[0]);
-            if constexpr (PR == 2) {
-                if (more) tile_store<X, EPV>(pre[1], st, lds, a.pitch, t[1]);
-            }
+        if (st.nblocks) tile_store<X, EPV>(pre, st, lds, a.pitch, slots);
+        for (int v0 = tid + per_round; v0 - tid < st.nblocks; v0 += per_round) {
+            TileSlot t[VB];
+            locate(t, v0);
+            tile_load<X, EPV>(pre, st, t);
+            tile_store<X, EPV>(pre, st, lds, a.pitch, t);
         }
     };
     // (the first chunk ahead of the loop, so that the compiler knows there which loads are in flight)
@@ -469,10 +448,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
             st.xs += (int64_t)a.CC * st.plane_b;
             st.cleft -= a.CC;
             st.whole = st.cleft >= a.CC;
-            if (st.nblocks) load_pre(0);
-            if constexpr (PR == 2) {
-                if (two) load_pre(1);
-            }
+            if (st.nblocks) tile_load<X, EPV>(pre, st, slots);
         }
         __builtin_amdgcn_sched_barrier(0);
         // ------------------------------------------------------------ multiply
