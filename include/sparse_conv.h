@@ -201,6 +201,8 @@ typedef struct {
                            LDS (a fixed summation order); waves_m waves of a group lie along the output channels, the
                            others along the positions, so that waves_m x buffers must divide the 4 or 8 waves.
                            0 = one group of four waves, two of eight.
+                           SLAB with pipeline = 3 and producers = 4: 4 = the eight multiplying waves are four groups of two that
+                           split the steps (waves_m 1 or 2), 0 = two groups of four.
                            SLAB with pipeline = 1 and chunk_c > 0: LDS chunk buffers.  0 (or 2) = two, the
                            producer waves share the copy of every chunk; 3 .. 5 = producers + 1 buffers
                            (producers is set to match when 0): every producer wave copies whole chunks by

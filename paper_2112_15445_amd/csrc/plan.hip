@@ -340,22 +340,26 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
 {
     const sc_layer_t& L = p.L;
     if (p.dtype != SC_F32 || !p.splittable || p.has_dup || p.n == 0 || has_epilogue(p)) return SC_ERR_UNSUPPORTED;
-    if (t.wsrc || t.ragged < 0 || t.ragged > 1 || t.pack || t.tile_q || t.buffers || t.stage_rows) return SC_ERR_UNSUPPORTED;
+    if (t.wsrc || t.ragged < 0 || t.ragged > 1 || t.pack || t.tile_q || t.stage_rows) return SC_ERR_UNSUPPORTED;
     // (the dense image never holds the fillers: ragged = 1 says so, the result is the same)
     if (t.producers != 0 && t.producers != 4) return SC_ERR_UNSUPPORTED;      // 4: staging waves of their own, two chunk buffers
     const int PW = t.producers;
     if (t.wg_threads != 0 && t.wg_threads != 256 && t.wg_threads != 512) return SC_ERR_UNSUPPORTED;
-    const int KG = t.wg_threads == 256 ? 1 : 2;               // (eight waves by default: two per SIMD)
+    // groups that split the contraction: one or two of four waves (eight by default: two per SIMD); in the pipelined form, whose
+    // multiplying waves are eight, two of four or (buffers = 4) four of two
+    if (t.buffers != 0 && (!PW || t.wg_threads == 256 || t.buffers != 4)) return SC_ERR_UNSUPPORTED;
+    const int KG = t.buffers ? t.buffers : (t.wg_threads == 256 ? 1 : 2);
     if (t.wg_per_cu == 0) t.wg_per_cu = 1;
     if (t.wg_per_cu < 1 || t.wg_per_cu > 8) return SC_ERR_UNSUPPORTED;
     if (t.tile_p < 0 || t.sub_batch < 0 || t.chunk_c < 0 || t.tile_d < 0 || t.waves_m < 0 || t.split_n < 0) return SC_ERR_UNSUPPORTED;
     const int budget = kMaxLdsBytes / t.wg_per_cu;
     const int KS = std::max(1, t.split_n);
     const int DB = t.tile_d ? t.tile_d : (L.D > 32 ? 64 : (L.D > 16 ? 32 : 16));
-    const int WM = t.waves_m ? t.waves_m : (DB >= 64 ? 2 : 1);
+    const int waves = PW ? 8 / KG : 4;                        // of one group
+    const int WM = t.waves_m ? t.waves_m : std::min(waves, DB >= 64 ? 2 : 1);
     int TP = t.tile_p, NS = t.sub_batch;
     const bool fixed_tile = TP != 0 || NS != 0;
-    const int maxpos = (4 / WM) * 64;
+    const int maxpos = std::max(1, waves / WM) * 64;
     if (!fixed_tile) {
         if (p.P * p.Q <= maxpos) { TP = p.P; NS = std::max(1, std::min(16, maxpos / (p.P * p.Q))); }
         else { TP = std::max(1, maxpos / p.Q); NS = 1; }
@@ -377,7 +381,8 @@ static sc_status_t resolve_split(const Plan& p, sc_tuning_t t, sc_tuning_t* out,
     sc_tuning_t r{};
     r.variant = SC_VARIANT_SLAB;
     r.pipeline = 3;
-    r.wg_threads = 256 * KG;
+    r.wg_threads = PW ? 512 : 256 * KG;
+    r.buffers = KG > 2 ? KG : 0;
     r.tile_p = g.TP;
     r.sub_batch = g.NS;
     r.chunk_c = g.CC;
@@ -1340,7 +1345,12 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
                 push(t);
                 if (p.P * p.Q <= 256 && cc) for (int ks : {2, 4}) { t.split_n = ks; push(t); }
                 // pipelined: small chunks, staged one ahead by waves of their own
-                if (thr == 512 && wpc == 1 && (cc != 256 || is_pointwise(p.L))) { t.split_n = 0; t.producers = 4; t.chunk_c = cc ? cc : 32; push(t); }
+                if (thr == 512 && wpc == 1 && (cc != 256 || is_pointwise(p.L))) {
+                    t.split_n = 0; t.producers = 4; t.chunk_c = cc ? cc : 32; push(t);
+                    // four groups of two waves split the contraction; small tiles of one block of channels with them
+                    if (lw[1] <= 2) { t.buffers = 4; push(t); }
+                    if (lw[0] == 32 && lw[1] == 1 && cc <= 64 && tp <= 4) { t.tile_d = 16; push(t); }
+                }
             };
             for (int tp : {1, 2, 4, 7, 8, 14, 16}) if (tp < p.P) pushk(tp, 0);
             for (int ns : {1, 2, 4}) pushk(p.P, ns);

@@ -42,16 +42,19 @@ struct SplitTable {
     int n;
 };
 
-// (form -- one or two groups of waves, pipelined --, columns per staging load)
+// (form -- one or two groups of waves, pipelined with two or four --, columns per staging load)
 sc_status_t launch_split_one_1(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_split_one_2(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_split_one_4(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_split_two_1(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_split_two_2(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_split_two_4(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
-sc_status_t launch_split_pipe_1(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
-sc_status_t launch_split_pipe_2(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
-sc_status_t launch_split_pipe_4(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_split_pipe2_1(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_split_pipe2_2(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_split_pipe2_4(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_split_pipe4_1(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_split_pipe4_2(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_split_pipe4_4(const Plan& p, const SplitArgs& a, const SplitTable& t, const void* x, void* y, int grid, hipStream_t stream);
 
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 
@@ -298,12 +301,12 @@ __device__ __forceinline__ float split_exact(const float* __restrict__ x, const 
     return sum;
 }
 
-// The wave's outputs: the accumulated ones, or, where one of them is too small for the terms or not finite, the
-// sums over the sparse table.  SHARED: other workgroups may have other chunks of the tile.  `position` as in the
-// kernels.
-template <bool SHARED, int MW, int NW, class Position>
-__device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const float* __restrict__ x, float* __restrict__ y, const SplitArgs& a, const SplitTable& tab,
-                                            int b0, int p0, int mblk0, int kg, int c_lo, int c_hi, const Position& position)
+// The wave's outputs, NB blocks of 16 channels x 16 positions: the accumulated ones, or, where one of them is too small for the terms
+// or not finite, the sums over the sparse table.  SHARED: other workgroups may have other chunks of the tile.  `get(t)`: the sums
+// of block t; `block(t, m, i)`: whether there is a block t, its place in the wave tile; `position` as in the kernels.
+template <bool SHARED, int NB, class Get, class Block, class Position>
+__device__ __forceinline__ void split_store(const Get& get, const Block& block, const float* __restrict__ x, float* __restrict__ y, const SplitArgs& a,
+                                            const SplitTable& tab, int b0, int p0, int mblk0, int kg, int c_lo, int c_hi, const Position& position)
 {
     const int PQ = a.P * a.Q;
     float* yb = y + (int64_t)b0 * a.D * PQ;
@@ -311,31 +314,35 @@ __device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const 
     auto order = [](float v) { return (__float_as_uint(v) << 1) + (1u << 24); };
     unsigned least = ~0u;
 #pragma unroll
-    for (int m = 0; m < MW; ++m)
+    for (int t = 0; t < NB; ++t) {
+        int m, i;
+        if (!block(t, m, i)) continue;
+        const float4v v = get(t);
 #pragma unroll
-        for (int i = 0; i < NW; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; j += 2) least = min(least, min(order(acc[m][i][j]), order(acc[m][i][j + 1])));
+        for (int j = 0; j < 4; j += 2) least = min(least, min(order(v[j]), order(v[j + 1])));
+    }
     bool exact = false;
     if (__ballot(least < a.floor)) {                         // (zeros, as a rule)
 #pragma unroll
-        for (int m = 0; m < MW; ++m)
+        for (int t = 0; t < NB; ++t) {
+            int m, i;
+            if (!block(t, m, i)) continue;
+            const float4v v = get(t);
 #pragma unroll
-            for (int i = 0; i < NW; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const unsigned v = order(acc[m][i][j]);
-                    exact |= v < a.floor && v != 1u << 24;
-                }
+            for (int j = 0; j < 4; ++j) {
+                const unsigned o = order(v[j]);
+                exact |= o < a.floor && o != 1u << 24;
+            }
+        }
     }
     if (__ballot(exact)) {                                   // (wave-uniform)
 #pragma unroll 1
-        for (int i = 0; i < NW; ++i) {
-            int sm, tp, tq;
-            if (!position(i, sm, tp, tq)) continue;
+        for (int t = 0; t < NB; ++t) {
+            int m, i, sm, tp, tq;
+            if (!block(t, m, i) || !position(i, sm, tp, tq)) continue;
 #pragma unroll 1
-            for (int mj = 0; mj < 4 * MW; ++mj) {
-                const int d = (mblk0 + (mj >> 2)) * 16 + 4 * kg + (mj & 3);
+            for (int j = 0; j < 4; ++j) {
+                const int d = (mblk0 + m) * 16 + 4 * kg + j;
                 if (d >= a.D) break;
                 const float v = split_exact(x, a, tab, b0 + sm, d, p0 + tp, tq, c_lo, c_hi);
                 float* yp = yb + ((int64_t)sm * a.D + d) * PQ + (p0 + tp) * a.Q + tq;
@@ -346,19 +353,18 @@ __device__ __forceinline__ void split_store(const float4v (&acc)[MW][NW], const 
         return;
     }
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-        int sm, tp, tq;
-        if (!position(i, sm, tp, tq)) continue;
-        const unsigned o = (unsigned)((sm * a.D + mblk0 * 16 + 4 * kg) * PQ) + (unsigned)(mul24(p0 + tp, a.Q) + tq);
+    for (int t = 0; t < NB; ++t) {
+        int m, i, sm, tp, tq;
+        if (!block(t, m, i) || !position(i, sm, tp, tq)) continue;
+        const float4v v = get(t);
+        const int d = (mblk0 + m) * 16 + 4 * kg;
+        const unsigned o = (unsigned)((sm * a.D + d) * PQ) + (unsigned)(mul24(p0 + tp, a.Q) + tq);
 #pragma unroll
-        for (int m = 0; m < MW; ++m) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if ((mblk0 + m) * 16 + 4 * kg + j >= a.D) continue;
-                float* yp = yb + (o + (unsigned)((16 * m + j) * PQ));
-                if (SHARED && (a.bits & 8)) add_out(yp, acc[m][i][j]);
-                else store_out(yp, acc[m][i][j]);
-            }
+        for (int j = 0; j < 4; ++j) {
+            if (d + j >= a.D) continue;
+            float* yp = yb + (o + (unsigned)(j * PQ));
+            if (SHARED && (a.bits & 8)) add_out(yp, v[j]);
+            else store_out(yp, v[j]);
         }
     }
 }
@@ -374,7 +380,7 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     const SplitArgs a = args_at_once(args);
     // steps of weights in flight: a step multiplies for 6 MW NW matrix instructions (16 clocks and
     // more each), L2 answers after several hundred clocks.  PF * NW is even (parity of the ring below).
-    constexpr int PF = MW * NW >= 7 ? 2 : (MW * NW >= 2 ? 4 : 6);
+    constexpr int PF = MW * NW >= 7 ? 2 : 4;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -434,6 +440,8 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     const int wrow = a.RS * a.NCB * 3072;                    // bytes per 16-row block
     const unsigned char* wbase = wfrag + (int64_t)mblk0 * wrow + lane * 16;
 
+    const float inv_S = __builtin_amdgcn_rcpf((float)a.S);
+
     // the padding does not change from chunk to chunk: written once
     split_pad(lds, tid, NT, st, a);
 
@@ -443,35 +451,27 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         const int gcb0 = c0 >> 5;
         const int ksteps_all = a.RS * cbs;
         const int ksteps = KG > 1 ? (ksteps_all - kgrp + KG - 1) / KG : ksteps_all;
-        const int last = ksteps - 1;
         uint4w aq[PF][MW][3], bq[2][3];
-        StepCursor wc{0, 0, 0, 0}, xc_{0, 0, 0, 0};
-        if (KG > 1 && kgrp) { wc.advance(cbs, a.S, ksteps > 0); xc_.advance(cbs, a.S, ksteps > 0); }
-        int wk = 0, xk = 0;
-        auto fetch_w = [&](uint4w (&av)[MW][3]) {
-            const unsigned char* wu = wbase + (int64_t)(wc.tap * a.NCB + gcb0 + wc.cb) * 3072;
+        const float inv_cbs = __builtin_amdgcn_rcpf((float)cbs);
+        int xtab, wtab;
+        auto table = [&](int s0) __attribute__((always_inline)) {
+            const int s = min(kgrp + KG * (s0 + lane), ksteps_all - 1);
+            const int tap = sdiv(s, inv_cbs), cb = s - tap * cbs, r = sdiv(tap, inv_S);
+            xtab = (r * a.Ws + tap - r * a.S) * a.pitch + cb * 64;
+            wtab = tap * a.NCB + gcb0 + cb;
+        };
+        auto fetch_w = [&](uint4w (&av)[MW][3], int k) __attribute__((always_inline)) {
+            const unsigned char* wu = wbase + (int64_t)__builtin_amdgcn_readlane(wtab, min(k, 63)) * 3072;
 #pragma unroll
             for (int m = 0; m < MW; ++m)
 #pragma unroll
                 for (int t = 0; t < 3; ++t) av[m][t] = *reinterpret_cast<const uint4w*>(wu + m * wrow + t * 1024);
-            wc.template advance<KG>(cbs, a.S, wk < last);
-            wk += wk < last ? 1 : 0;
-        };
-        // the operands of position block i of the step the cursor stands on; after the last block of a
-        // step the cursor moves on
-        auto fetch_x = [&](uint4w (&bv)[3], int i) {
-            const int off = bbase[i] + (xc_.r * a.Ws + xc_.s) * a.pitch + xc_.cb * 64;
-#pragma unroll
-            for (int t = 0; t < 3; ++t) bv[t] = *reinterpret_cast<const uint4w*>(lds + off + t * a.bufsz);
-            if (i == NW - 1) {
-                xc_.template advance<KG>(cbs, a.S, xk < last);
-                xk += xk < last ? 1 : 0;
-            }
         };
         // (by a wave without steps too: behind loads that only some waves issue the compiler waits for the weights before it stages
         // the input)
+        table(0);
 #pragma unroll
-        for (int u = 0; u < PF; ++u) fetch_w(aq[u]);
+        for (int u = 0; u < PF; ++u) fetch_w(aq[u], u);
         if (ch > ch_lo) split_barrier();     // the previous chunk has been multiplied
         again();
         if (st.nblocks) split_put<EPV>(pre, st, lds, slots, a);
@@ -487,31 +487,44 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
             again();
             if (st.nblocks) split_load<EPV>(pre, st, slots);
         }
-        if (KG == 1 || ksteps > 0) fetch_x(bq[0], 0);
-        __builtin_amdgcn_sched_barrier(0);
-        const int main_steps = ksteps / PF * PF;
-        for (int s0 = 0; s0 < main_steps; s0 += PF) {
+        for (int s0 = 0; s0 < ksteps; s0 += 64) {
+            const int n = min(64, ksteps - s0);
+            if (s0 > 0) {
+                table(s0);
 #pragma unroll
-            for (int u = 0; u < PF; ++u) {
-#pragma unroll
-                for (int i = 0; i < NW; ++i) {
-                    // the operands of the next position block (or of the next step's first) come from LDS
-                    // while this one's 6 MW matrix instructions run
-                    fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                fetch_w(aq[u]);
+                for (int u = 0; u < PF; ++u) fetch_w(aq[u], u);
             }
-        }
+            auto fetch_x = [&](uint4w (&bv)[3], int i, int k) __attribute__((always_inline)) {
+                const int off = bbase[i] + __builtin_amdgcn_readlane(xtab, min(k, 63));
 #pragma unroll
-        for (int u = 0; u < PF - 1; ++u) {
-            if (main_steps + u < ksteps) {
+                for (int t = 0; t < 3; ++t) bv[t] = *reinterpret_cast<const uint4w*>(lds + off + t * a.bufsz);
+            };
+            fetch_x(bq[0], 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            const int main_steps = n / PF * PF;
+            for (int k = 0; k < main_steps; k += PF) {
 #pragma unroll
-                for (int i = 0; i < NW; ++i) {
-                    fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
-                    split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
+                for (int u = 0; u < PF; ++u) {
+#pragma unroll
+                    for (int i = 0; i < NW; ++i) {
+                        // the operands of the next position block (or of the next step's first) come from LDS
+                        // while this one's 6 MW matrix instructions run
+                        fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0, i + 1 < NW ? k + u : k + u + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                        split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    fetch_w(aq[u], k + u + PF);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < PF - 1; ++u) {
+                if (main_steps + u < n) {
+#pragma unroll
+                    for (int i = 0; i < NW; ++i) {
+                        fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0, i + 1 < NW ? main_steps + u : main_steps + u + 1);
+                        split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
+                    }
                 }
             }
         }
@@ -537,7 +550,8 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
             for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
     }
-    split_store<true, MW, NW>(acc, x, y, a, tab, b0, p0, mblk0, kg, ch_lo * a.CC, ch_hi * a.CC, position);
+    split_store<true, MW * NW>([&](int t) { return acc[t % MW][t / MW]; }, [](int t, int& m, int& i) { m = t % MW; i = t / MW; return true; },
+                               x, y, a, tab, b0, p0, mblk0, kg, ch_lo * a.CC, ch_hi * a.CC, position);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -548,24 +562,14 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 // 2048-512 layer on 7 x 7 planes.  Protocol of the DENSE variant's pipelined kernel: barrier k says "chunk
 // k is staged" and "chunk k - 1 has been multiplied"; it waits for LDS traffic only, so that weight loads
 // stay in flight across it.  Twelve waves leave 168 registers a wave: wave tiles of at most 8 blocks.
+// The steps of a wave are tabulated 64 at a time, one per lane, in both forms: worked out one after the other by the scalar unit they cost
+// 10 - 15 % (us per pass of the same shape: 3x3 stride 2 512-512 at 14 x 14, batch 32 49.7 -> 43.4, 3x3 128-128 at 28 x 28 38.0 -> 35.2,
+// 1-D 300-64 along 64, batch 128 10.8 -> 9.5, 3x3 100-90 at 27 x 31, batch 7 15.5 -> 14.2, 1x1 2048-512 at 7 x 7 28.0 -> 27.4).
+// Two or four groups of the multiplying waves split the contraction: four where a tile is small, so that its waves do not all read the
+// same weights or the same tile operands (3x3 64-64 at 32 x 32, one image: 5.4 us with two groups, 4.8 with four; eight groups were
+// level there and slower elsewhere).
 // ------------------------------------------------------------------------------------------------
-// One wave-uniform position in the sequence of steps (chunk, filter tap, channel block of the chunk).
-struct SplitCursor {
-    int ch, r, s, tap, cb, cbs;
-    __device__ __forceinline__ void advance(const SplitArgs& a)
-    {
-        if (++cb < cbs) return;
-        cb = 0;
-        ++tap;
-        if (++s == a.S) { s = 0; ++r; }
-        if (tap < a.RS) return;
-        tap = r = s = 0;
-        ++ch;
-        cbs = ch == a.nchunks - 1 ? a.cbs_last : a.CC >> 5;
-    }
-};
-
-template <int MW, int NW, int EPV, bool FULL>
+template <int MW, int NW, int KG, int EPV, bool FULL>
 __global__ void __launch_bounds__(768)
 split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsigned char* __restrict__ wfrag, const SplitArgs args, const SplitTable tab)
 {
@@ -619,32 +623,41 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
         return;
     }
 
-    const int kgrp = wave12 >> 2, wave = wave12 & 3;
+    constexpr int W1 = 8 / KG;                               // waves of one group
+    const int kgrp = wave12 / W1, wave = wave12 % W1;
     const int lwm = a.bits >> 4 & 3, wm = wave & ((1 << lwm) - 1), wn = wave >> lwm;
     const int n16 = lane & 15, kg = lane >> 4;
     const int mblk0 = db * (a.DB >> 4) + wm * MW;
     const int wrow = a.RS * a.NCB * 3072;
     const unsigned char* wbase = wfrag + (int64_t)mblk0 * wrow + lane * 16;
 
-    // the two groups of four waves take the even and the odd steps of the whole contraction
-    const int total = a.RS * a.NCB;
-    const int nsteps = (total - kgrp + 1) >> 1, last = nsteps - 1;
-    SplitCursor wc{0, 0, 0, 0, 0, a.nchunks == 1 ? a.cbs_last : a.CC >> 5}, xc_ = wc;
-    if (kgrp && nsteps > 0) { wc.advance(a); xc_.advance(a); }
-    int wk = 0, xk = 0, nbar = 0;
+    // The groups take steps kgrp, kgrp + KG, ... of the whole contraction (chunk, filter tap, channel block of the chunk).  64 of a
+    // wave's steps are tabulated at a time, one per lane: LDS offset of the tile operands, offset of the weights, chunk.
+    const int total = a.RS * a.NCB, nsteps = (total - kgrp + KG - 1) / KG;
+    const int cbf = a.CC >> 5, spc = a.RS * cbf;
+    const float inv_spc = __builtin_amdgcn_rcpf((float)spc), inv_cbf = __builtin_amdgcn_rcpf((float)cbf);
+    const float inv_last = __builtin_amdgcn_rcpf((float)a.cbs_last), inv_S = __builtin_amdgcn_rcpf((float)a.S);
+    int xtab, wtab, ctab, nbar = 0;
+    auto table = [&](int s0) __attribute__((always_inline)) {
+        const int s = min(kgrp + KG * (s0 + lane), total - 1);
+        ctab = sdiv(s, inv_spc);
+        const bool lastc = ctab == a.nchunks - 1;
+        const int rem = s - ctab * spc, tap = sdiv(rem, lastc ? inv_last : inv_cbf), cb = rem - tap * (lastc ? a.cbs_last : cbf);
+        const int r = sdiv(tap, inv_S);
+        xtab = (ctab & 1) * buf + (r * a.Ws + tap - r * a.S) * a.pitch + cb * 64;
+        wtab = tap * a.NCB + ctab * cbf + cb;
+    };
     uint4w aq[PF][MW][3], bq[2][3];
-    auto fetch_w = [&](uint4w (&av)[MW][3]) {
-        const unsigned char* wu = wbase + (int64_t)(wc.tap * a.NCB + wc.ch * (a.CC >> 5) + wc.cb) * 3072;
+    auto fetch_w = [&](uint4w (&av)[MW][3], int k) __attribute__((always_inline)) {
+        const unsigned char* wu = wbase + (int64_t)__builtin_amdgcn_readlane(wtab, min(k, 63)) * 3072;
 #pragma unroll
         for (int m = 0; m < MW; ++m)
 #pragma unroll
             for (int t = 0; t < 3; ++t) av[m][t] = *reinterpret_cast<const uint4w*>(wu + m * wrow + t * 1024);
-        if (wk < last) { wc.advance(a); wc.advance(a); ++wk; }
     };
-    if (nsteps > 0) {
+    table(0);
 #pragma unroll
-        for (int u = 0; u < PF; ++u) fetch_w(aq[u]);
-    }
+    for (int u = 0; u < PF; ++u) fetch_w(aq[u], u);
     // the padding of both buffers is written once, behind the first weight requests
     __builtin_amdgcn_sched_barrier(0);
     split_pad(lds, tid, NTC, st, a);
@@ -669,34 +682,43 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
 #pragma unroll
         for (int m = 0; m < MW; ++m) acc[m][i] = accs[m][i] = float4v{0, 0, 0, 0};
     }
-    auto fetch_x = [&](uint4w (&bv)[3], int i) {
-        if (i == 0) while (nbar <= xc_.ch) { split_barrier(); ++nbar; }      // the chunk of this step is staged
-        const int off = bbase[i] + (xc_.ch & 1) * buf + (xc_.r * a.Ws + xc_.s) * a.pitch + xc_.cb * 64;
+    for (int s0 = 0; s0 < nsteps; s0 += 64) {
+        const int n = min(64, nsteps - s0);
+        if (s0 > 0) {
+            table(s0);
 #pragma unroll
-        for (int t = 0; t < 3; ++t) bv[t] = *reinterpret_cast<const uint4w*>(lds + off + t * a.bufsz);
-        if (i == NW - 1 && xk < last) { xc_.advance(a); xc_.advance(a); ++xk; }
-    };
-    if (nsteps > 0) {
-        fetch_x(bq[0], 0);
+            for (int u = 0; u < PF; ++u) fetch_w(aq[u], u);
+        }
+        auto fetch_x = [&](uint4w (&bv)[3], int i, int k) __attribute__((always_inline)) {
+            k = min(k, n - 1);
+            if (i == 0) {
+                const int ch = __builtin_amdgcn_readlane(ctab, k);
+                while (nbar <= ch) { split_barrier(); ++nbar; }      // the chunk of this step is staged
+            }
+            const int off = bbase[i] + __builtin_amdgcn_readlane(xtab, k);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) bv[t] = *reinterpret_cast<const uint4w*>(lds + off + t * a.bufsz);
+        };
+        fetch_x(bq[0], 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        const int main_steps = nsteps / PF * PF;
-        for (int s0 = 0; s0 < main_steps; s0 += PF) {
+        const int main_steps = n / PF * PF;
+        for (int k = 0; k < main_steps; k += PF) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
 #pragma unroll
                 for (int i = 0; i < NW; ++i) {
-                    fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0);
+                    fetch_x(bq[(u * NW + i + 1) & 1], i + 1 < NW ? i + 1 : 0, i + 1 < NW ? k + u : k + u + 1);
                     __builtin_amdgcn_sched_barrier(0);
                     split_multiply<FULL, MW, NW>(acc, accs, aq[u], bq[(u * NW + i) & 1], i);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                fetch_w(aq[u]);
+                fetch_w(aq[u], k + u + PF);
             }
         }
-        if (main_steps < nsteps) {
+        if (main_steps < n) {
 #pragma unroll
             for (int i = 0; i < NW; ++i) {
-                if (i + 1 < NW) fetch_x(bq[(i + 1) & 1], i + 1);
+                if (i + 1 < NW) fetch_x(bq[(i + 1) & 1], i + 1, main_steps);
                 split_multiply<FULL, MW, NW>(acc, accs, aq[0], bq[i & 1], i);
             }
         }
@@ -706,30 +728,41 @@ split_pipe_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     for (int m = 0; m < MW; ++m)
 #pragma unroll
         for (int i = 0; i < NW; ++i) acc[m][i] += accs[m][i];
-    // the second group hands its sums to the first (the staging waves have ended)
+    // The groups meet in LDS (the staging waves have ended): block b is added up and stored by group b mod KG, the others give it
+    // theirs, a lane's own 16 bytes per block.
     __syncthreads();
-    float4v* ex = reinterpret_cast<float4v*>(lds) + wave * (MW * NW * 64) + lane;
-    if (kgrp == 1) {
+    constexpr int NB = MW * NW, BPW = (NB + KG - 1) / KG;
+    float4v* ex = reinterpret_cast<float4v*>(lds) + wave * (NB * (KG - 1) * 64) + lane;
 #pragma unroll
-        for (int m = 0; m < MW; ++m)
+    for (int b = 0; b < NB; ++b)
+        if (kgrp != b % KG) ex[(b * (KG - 1) + ((kgrp - b % KG - 1) & (KG - 1))) * 64] = acc[b % MW][b / MW];
+    __syncthreads();
+    float4v sum[BPW];
+    auto owned = [&](int t, int& m, int& i) {
+        const int b = kgrp + t * KG;
+        m = b % MW;
+        i = b / MW;
+        return b < NB;
+    };
 #pragma unroll
-            for (int i = 0; i < NW; ++i) ex[(m * NW + i) * 64] = acc[m][i];
+    for (int t = 0; t < BPW; ++t) {
+#pragma unroll
+        for (int g = 0; g < KG; ++g)
+            if (g == 0 || (t * KG + g < NB && kgrp == g)) sum[t] = acc[(t * KG + g) % MW][(t * KG + g) / MW];
+        if (kgrp + t * KG < NB) {
+#pragma unroll
+            for (int q = 0; q < KG - 1; ++q) sum[t] += ex[((kgrp + t * KG) * (KG - 1) + q) * 64];
+        }
     }
-    __syncthreads();
-    if (kgrp == 1) return;
-#pragma unroll
-    for (int m = 0; m < MW; ++m)
-#pragma unroll
-        for (int i = 0; i < NW; ++i) acc[m][i] += ex[(m * NW + i) * 64];
-    split_store<false, MW, NW>(acc, x, y, a, tab, b0, p0, mblk0, kg, 0, a.C, position);
+    split_store<false, BPW>([&](int t) { return sum[t]; }, owned, x, y, a, tab, b0, p0, mblk0, kg, 0, a.C, position);
 }
 
 template <int MW, int NW, int KG, int EPV, bool FULL>
 static sc_status_t launch_split_full(const Plan& p, const SplitArgs& a, const SplitTable& tab, const void* x, void* y, int grid, hipStream_t stream)
 {
-    // KG = 3: the pipelined form (eight multiplying waves and four that stage)
+    // KG > 2: the pipelined form (eight multiplying waves and four that stage), KG - 10 groups
     auto kernel = [] {
-        if constexpr (KG == 3) return &split_pipe_kernel<MW, NW, EPV, FULL>;
+        if constexpr (KG > 2) return &split_pipe_kernel<MW, NW, KG - 10, EPV, FULL>;
         else return &split_conv_kernel<MW, NW, KG, EPV, FULL>;
     }();
     static std::once_flag once;
@@ -739,7 +772,7 @@ static sc_status_t launch_split_full(const Plan& p, const SplitArgs& a, const Sp
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLdsBytes);
     });
     if (attr_err != hipSuccess) return SC_ERR_HIP;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256 * KG), p.mg.lds_bytes, stream, static_cast<const float*>(x),
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(KG > 2 ? 768 : 256 * KG), p.mg.lds_bytes, stream, static_cast<const float*>(x),
                        static_cast<float*>(y), p.d_wfrag, a, tab);
     return hipGetLastError() == hipSuccess ? SC_OK : SC_ERR_HIP;
 }
@@ -763,7 +796,7 @@ static sc_status_t launch_split_typed(const Plan& p, const SplitArgs& a, const S
         case 21: return launch_split_one<KG, EPV, 2, 1>(p, a, t, x, y, grid, stream);
         case 22: return launch_split_one<KG, EPV, 2, 2>(p, a, t, x, y, grid, stream);
         case 24: return launch_split_one<KG, EPV, 2, 4>(p, a, t, x, y, grid, stream);
-        case 27: if constexpr (KG != 3) return launch_split_one<KG, EPV, 2, 7>(p, a, t, x, y, grid, stream); break;
+        case 27: if constexpr (KG <= 2) return launch_split_one<KG, EPV, 2, 7>(p, a, t, x, y, grid, stream); break;
     }
     return SC_ERR_UNSUPPORTED;
 }

@@ -99,7 +99,9 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     MfmaGeom g{};
     if (TP < 1 || NS < 1 || NS > 16 || CC < 32 || CC % 32) return false;
     if (DB != 16 && DB != 32 && DB != 64 && DB != 128) return false;
-    if ((WM != 1 && WM != 2 && WM != 4) || DB % (16 * WM) || (KG != 1 && KG != 2)) return false;
+    if ((WM != 1 && WM != 2 && WM != 4) || DB % (16 * WM)) return false;
+    // groups that split the contraction: one or two of four waves, in the pipelined form two or four of eight waves in all
+    if (PW ? (KG != 2 && KG != 4) || WM > 8 / KG : KG != 1 && KG != 2) return false;
     g.TP = std::min(TP, p.P);
     g.NS = g.TP < p.P ? 1 : NS;                   // several samples only with whole planes
     g.tiles_p = (p.P + g.TP - 1) / g.TP;
@@ -123,7 +125,7 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     g.WM = WM;
     g.MW = DB / (16 * WM);
     g.KG = KG;
-    const int nb = (g.npos + 15) / 16, wn = 4 / WM, nw = (nb + wn - 1) / wn;
+    const int nb = (g.npos + 15) / 16, wn = (PW ? 8 / KG : 4) / WM, nw = (nb + wn - 1) / wn;
     if (nw > 8) return false;
     g.NW = nw <= 2 ? nw : (nw <= 4 ? 4 : (nw <= 7 ? 7 : 8));
     // accumulators (two sets) and operands in flight within 256 registers
@@ -134,10 +136,11 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     g.bufsz = g.npos_s * g.pitch;
     if ((int64_t)(g.CC / 8) * g.npos_s >= (1 << 19)) return false;     // sdiv() range of the staging
     // pipelined: two chunk buffers, eight multiplying waves, a wave tile of at most 8 blocks in 168 registers
-    if (PW && (PW != 4 || KG != 2 || KS != 1 || g.MW * g.NW > 8)) return false;
+    if (PW && (PW != 4 || KS != 1 || g.MW * g.NW > 8)) return false;
     g.PW = PW;
     int64_t lds = 3ll * g.bufsz * (PW && g.nchunks > 1 ? 2 : 1);
-    if (KG == 2) lds = std::max<int64_t>(lds, (int64_t)g.MW * g.NW * 4096);
+    // (the groups hand on their sums: a wave those of the blocks that it does not store)
+    if (KG >= 2) lds = std::max<int64_t>(lds, (int64_t)g.MW * g.NW * (8 / KG) * (KG - 1) * 1024);
     if (lds > lds_budget || lds > kMaxLdsBytes) return false;
     g.lds_bytes = (int)lds;
     *out = g;
@@ -220,14 +223,15 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
     a.bits = (wmajor ? 1 : 0) | (flat ? 2 : 0) | (p.L.pad_h || p.L.pad_w ? 4 : 0) | (g.DL > 1 ? 8 : 0) | __builtin_ctz(g.WM) << 4;
     const SplitTable tab{static_cast<const float*>(p.d_theta), p.d_col, p.d_len, p.n};
     using Launch = sc_status_t (*)(const Plan&, const SplitArgs&, const SplitTable&, const void*, void*, int, hipStream_t);
-    static const Launch kernels[3][3] = {{launch_split_one_1, launch_split_one_2, launch_split_one_4},
+    static const Launch kernels[4][3] = {{launch_split_one_1, launch_split_one_2, launch_split_one_4},
                                          {launch_split_two_1, launch_split_two_2, launch_split_two_4},
-                                         {launch_split_pipe_1, launch_split_pipe_2, launch_split_pipe_4}};
+                                         {launch_split_pipe2_1, launch_split_pipe2_2, launch_split_pipe2_4},
+                                         {launch_split_pipe4_1, launch_split_pipe4_2, launch_split_pipe4_4}};
     if (g.DL > 1) {
         const sc_status_t st = launch_clear(y, (int64_t)N * p.L.D * p.P * p.Q, stream);
         if (st != SC_OK) return st;
     }
-    return kernels[g.PW ? 2 : g.KG - 1][lepv](p, a, tab, x, y, (int)grid, stream);
+    return kernels[g.PW ? __builtin_ctz(g.KG) + 1 : g.KG - 1][lepv](p, a, tab, x, y, (int)grid, stream);
 }
 
 }  // namespace sc

@@ -2036,3 +2036,47 @@ def test_dense_padding_is_cleared_and_nothing_else(name, C, D, H, W, R, S, strid
             G.check(l, G.run_gpu(plan, data["x"]), ref, f"pad {name} {shape} {k}")
     plan.destroy()
     dplan.destroy()
+
+
+@pytest.mark.parametrize("name,C,D,H,W,R,S,stride,ph,pw,N,sparsity", [
+    ("a step for some groups only", 32, 20, 6, 9, 1, 1, 1, 0, 0, 3, 0.5),
+    ("steps no multiple of the groups, a last chunk of one block", 100, 37, 9, 8, 3, 3, 1, 1, 1, 2, 0.6),
+    ("more steps than a table holds", 300, 40, 5, 6, 3, 3, 1, 1, 1, 2, 0.8),
+    ("more steps than two tables hold", 1100, 24, 4, 7, 3, 3, 2, 1, 1, 2, 0.9),
+    ("one dimension", 70, 33, 1, 40, 1, 5, 1, 0, 2, 3, 0.5),
+    ("rows of two weights", 64, 18, 7, 7, 3, 3, 1, 1, 1, 2, 0.997),
+])
+def test_fp32_split_form_steps_from_tables(name, C, D, H, W, R, S, stride, ph, pw, N, sparsity):
+    """The steps of a wave come from tables of 64: one-shot and pipelined, two and four groups of waves (tuning.buffers = 4), every
+    wave tile that fits, chunks of one to all channel blocks; no further from 64 bits than 2e-6 of the largest output (the sums
+    are of at most 1000 products of 24-bit factors, rounded once for each 32 channels of a tap)."""
+    l = wl.Layer("tables", C, D, H, W, R, S, stride, stride if S > 1 else 1, ph, pw, N=N, sparsity=sparsity, dtype="f32", seed=950)
+    data = wl.prepare(l)
+    ref = G.oracle_out(l, data)
+    plan = G.make_plan(l, data)
+    P = plan.info().P
+    ran = 0
+    for td, wm in ((16, 1), (32, 1), (32, 2), (64, 2), (64, 4)):
+        for kw in (dict(buffers=4, producers=4), dict(producers=4), dict(wg_threads=256), dict(wg_threads=512)):
+            for cc, tp in ((32, 1), (64, P), (0, 2)):
+                try:
+                    _split(plan, tile_d=td, waves_m=wm, chunk_c=cc, tile_p=tp, **kw)
+                except B.SparseConvError as e:
+                    assert e.status == 4
+                    continue
+                t = plan.get_tuning()
+                assert t.buffers == kw.get("buffers", 0) and t.producers == kw.get("producers", 0)
+                print("case tables", name, t.as_dict(), flush=True)
+                G.check(l, G.run_gpu(plan, data["x"]), ref, f"tables {name} {td} {wm} {kw} {cc} {tp}", tol=2e-6)
+                shape, lds = t.as_dict(), plan.info().lds_bytes
+                plan.set_tuning(t)                            # the report installs the same shape again
+                assert plan.get_tuning().as_dict() == shape and plan.info().lds_bytes == lds
+                ran += 1
+    assert ran >= 20
+    for bad in (dict(buffers=4), dict(buffers=8, producers=4), dict(buffers=2, producers=4), dict(buffers=4, producers=4, waves_m=4, tile_d=64),
+                dict(buffers=4, producers=4, wg_threads=256)):
+        before = plan.get_tuning().as_dict()
+        with pytest.raises(B.SparseConvError) as e:
+            _split(plan, **bad)
+        assert e.value.status == 4 and plan.get_tuning().as_dict() == before
+    plan.destroy()
