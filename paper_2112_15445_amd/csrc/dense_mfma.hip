@@ -174,6 +174,8 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
     // pooling windows must not straddle tiles
     if (has_epilogue(p) && p.epi.pool && g.TP < p.P && (g.TP & 1)) return false;
     const bool pooled = has_epilogue(p) && p.epi.pool;
+    // (the one-shot kernel reads a row block of the weights at 32-bit offsets)
+    if (one_shot && (int64_t)L.R * L.S * g.NCB >= (1ll << 22)) return false;
     if (one_shot) {
         // the groups hand on their accumulators (two: the second one's; more: all of them), pooling lays them out by
         // output channel, rows a multiple of 16 bytes

@@ -19,6 +19,9 @@
 //     same weights for several tiles; their sums meet in LDS;
 //   * the operands are exchanged (positions are the rows of the matrix instruction, channels its columns), so
 //     that a lane holds four neighbouring positions of one channel and stores them as one word.
+//   * a step costs a wave little but its matrix instructions: its LDS offset and its place in the weights come from lanes of two registers, and
+//     the weights are read at 32-bit offsets from scalar bases (12 scalar instructions less a step: the int8 layers below 109.3 -> 106.1 us
+//     of the same shapes, 4b/16b 512-512 11.1 -> 10.9, f16 64-64 15.1 -> 14.8);
 //   * a launch reads its arguments at once (TileArgs), staging is instantiated by the columns of a load, and the first chunk is staged
 //     ahead of the loop over the chunks, so that the compiler knows how many loads are in flight and waits for the input only, not for the weights behind it.
 // Measured per pass, before and after the last of these: f16 3x3 64-64 at 56 x 56, batch 32 14.9, 14.5 us; f16 3x3 256-256 at 14 x 14,
@@ -363,9 +366,10 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     const unsigned char* wrows = reinterpret_cast<const unsigned char*>(wfrag) + mblk0 * wrow;
 
     // Steps of a chunk: filter tap, then channel block of the chunk; this wave takes kgrp, kgrp + KG, ...
-    // Up to 64 of them are tabulated one per lane (LDS offset of the tile operands, offset of the weights) and
-    // read back with v_readlane; steps past the last repeat it (operands are requested without a test).
+    // Up to 56 of them are tabulated one per lane (LDS offset of the tile operands, bytes into a row block of the weights) and
+    // read back with v_readlane; the lanes past the last repeat it: operands are requested up to 8 steps ahead, without a test.
     int xtab, wtab;
+    constexpr int kTable = 56;                               // (a multiple of PF, and 8 lanes more)
     auto table = [&](int s0, int n, int cbs, int gcb0) {
         const int s = min(kgrp + KG * (s0 + min(lane, max(n, 1) - 1)), a.RS * cbs - 1);
         const int tap = tdiv(s, cbs == (int)((unsigned)a.CC / CB) ? a.inv_ccb : a.inv_cbs_last);
@@ -373,18 +377,19 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         const int r = tdiv(tap, a.inv_S);
         const int sx = tap - r * a.S;
         xtab = (r * a.Ws + sx) * a.pitch + cb * 64;
-        wtab = tap * a.NCB + gcb0 + cb;
+        wtab = (tap * a.NCB + gcb0 + cb) << 10;
     };
     uint4w aq[PF][MW], bq[4];
     auto fetch_w = [&](uint4w (&av)[MW], int s) __attribute__((always_inline)) {
-        const unsigned char* ws = wrows + ((int64_t)__builtin_amdgcn_readlane(wtab, min(s, 63)) << 10);
+        // (32-bit offsets from a scalar base for each row block: mfma_geometry keeps them below 2^32)
+        const unsigned off = (unsigned)__builtin_amdgcn_readlane(wtab, s) + (unsigned)lane * 16u;
 #pragma unroll
-        for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(ws + m * wrow + (unsigned)lane * 16u);
+        for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(wrows + m * wrow + off);
     };
     // steps of this wave in a chunk of cbs channel blocks
     auto steps_of = [&](int cbs) { const int all = a.RS * cbs; return all > kgrp ? (all - kgrp + KG - 1) >> lkg : 0; };
     auto start_w = [&](int s0, int n, int cbs, int gcb0) __attribute__((always_inline)) {
-        table(s0, min(64, n - s0), cbs, gcb0);
+        table(s0, min(kTable, n - s0), cbs, gcb0);
 #pragma unroll
         for (int u = 0; u < PF; ++u) fetch_w(aq[u], u);
     };
@@ -453,8 +458,8 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         __builtin_amdgcn_sched_barrier(0);
         // ------------------------------------------------------------ multiply
         const int gcb0 = ch * (int)((unsigned)a.CC / CB);
-        for (int s0 = 0; s0 < nsteps; s0 += 64) {
-            const int n = min(64, nsteps - s0);
+        for (int s0 = 0; s0 < nsteps; s0 += kTable) {
+            const int n = min(kTable, nsteps - s0);
             if (s0 > 0) start_w(s0, nsteps, cbs, gcb0);
             // operands of the tile: block b of the sequence (step, position block) goes to slot b mod 4, requested three
             // blocks ahead of its use
@@ -465,7 +470,7 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
                 constexpr int AH = (NW + 2) / NW;            // steps that the requests reach ahead
                 int toff[AH + 1];
 #pragma unroll
-                for (int q = 0; q <= AH; ++q) toff[q] = __builtin_amdgcn_readlane(xtab, min(k + q, 63));
+                for (int q = 0; q <= AH; ++q) toff[q] = __builtin_amdgcn_readlane(xtab, k + q);
 #pragma unroll
                 for (int i = 0; i < NW; ++i) {
                     bq[(u * NW + i + 3) & 3] = *reinterpret_cast<const uint4w*>(lds + bbase[(i + 3) % NW] + toff[(i + 3) / NW]);
