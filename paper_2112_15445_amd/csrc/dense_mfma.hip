@@ -33,6 +33,7 @@
 #include <algorithm>
 
 #include "dense_mfma_kernel.h"
+#include "sc_staging.h"
 
 namespace sc {
 
@@ -182,18 +183,14 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
         if (KG > 1) lds = std::max<int64_t>(lds, (int64_t)(KG == 2 ? waves / 2 : waves) * g.MW * g.NW * 1024);
         g.epi_pitch = WN * g.NW * 16 + 4;
         if (pooled) lds = std::max<int64_t>(lds, (int64_t)g.DB * g.epi_pitch * 4);
-        // the runs that are staged: input rows, or all rows of a tile where they carry no padding columns
+        // the runs that are staged: input rows, or all rows of a tile where they carry no padding columns.  (An
+        // instruction count of a block: its loads and address; for each column the permutations and the LDS write.)
         g.flat = g.Ws == L.W && L.pad_w == 0 ? 1 : 0;
-        g.minrun = std::max(0, std::min(L.W, g.Ws - L.pad_w));
-        if (g.flat) {
-            int least = 0;
-            for (int t = 0; t < g.tiles_p; ++t) {
-                const int row0 = t * g.TP * L.stride_h - L.pad_h;
-                const int rows = std::min(g.Hs, L.H - row0) - std::max(0, -row0);
-                if (rows > 0) least = least ? std::min(least, rows) : rows;
-            }
-            g.minrun = (int)std::min<int64_t>((int64_t)least * L.W, 1 << 20);
-        }
+        const int64_t row = std::max(0, std::min(L.W, g.Ws - L.pad_w));
+        const int64_t least = g.flat ? least_staged_rows(L.H, g.Hs, (int64_t)g.TP * L.stride_h, L.pad_h, g.tiles_p) : 1;
+        const int CV = 16 / p.ex;
+        g.lepv = load_columns(3, CV + 24, p.ex == 2 ? 8 : 12, (int64_t)(g.CC / CV) * g.NS, waves * 64, g.flat ? 1 : g.Hs,
+                              g.flat ? g.Hs * row : row, least * row);
     } else if (pooled || KG == 2) {
         // the accumulators are exchanged through LDS (between the two step groups, or for pooling)
         g.epi_pitch = (4 / g.WM) * g.NW * 16 + 1;
@@ -211,26 +208,6 @@ int mfma_grid_size(const Plan& p, const MfmaGeom& g, int N)
 {
     (void)p;
     return ((N + g.NS - 1) / g.NS) * g.tiles_p * ((g.ndb + g.DL - 1) / g.DL);
-}
-
-// One-shot kernel on the transposed tile: log2 of the columns per staging load, 8, 4, 2 or 1 of them: the least estimated time of a
-// chunk, rounds of NT blocks times a block's instructions (its loads and address, then for each column the permutations and
-// the LDS write).
-static int tile_load_columns(const Plan& p)
-{
-    const MfmaGeom& g = p.mg;
-    const int cv = 16 / p.ex, nt = g.waves * 64;
-    const int64_t run = g.flat ? (int64_t)g.Hs * p.L.W : std::min(p.L.W, g.Ws - p.L.pad_w), rows = g.flat ? 1 : g.Hs;
-    int64_t best = 0;
-    int lepv = 0;
-    for (int l = 3; l >= 0; --l) {
-        const int e = 1 << l;
-        if (e > 1 && e > g.minrun) continue;
-        const int64_t blocks = (int64_t)(g.CC / cv) * g.NS * rows * ((run + e - 1) / e);
-        const int64_t cost = ((blocks + nt - 1) / nt) * (cv + 24 + e * (p.ex == 2 ? 8 : 12));
-        if (l == 3 || best == 0 || cost < best) { best = cost; lepv = l; }
-    }
-    return lepv;
 }
 
 // Arguments of the one-shot kernel on the transposed tile, for one launch of `grid` workgroups.
@@ -297,7 +274,7 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
         using Launch = sc_status_t (*)(const Plan&, const TileArgs&, const void*, void*, int, hipStream_t);
         static const Launch halves[4] = {launch_tile_f16_1, launch_tile_f16_2, launch_tile_f16_4, launch_tile_f16_8};
         static const Launch bytes[4] = {launch_tile_i8_1, launch_tile_i8_2, launch_tile_i8_4, launch_tile_i8_8};
-        return (p.ex == 1 ? bytes : halves)[tile_load_columns(p)](p, tile_launch_args(p, N, (int)grid), x, y, (int)grid, stream);
+        return (p.ex == 1 ? bytes : halves)[g.lepv](p, tile_launch_args(p, N, (int)grid), x, y, (int)grid, stream);
     }
     MfmaArgs a{};
     a.C = p.L.C; a.D = p.L.D; a.N = N; a.H = p.L.H; a.W = p.L.W; a.P = p.P; a.Q = p.Q;

@@ -70,8 +70,8 @@ struct MfmaGeom {
     int WM, MW, NW;        // waves along the output channels; 16-row / 16-column blocks per wave
     int KG;                // groups of waves that split the steps of the contraction (1 or 2; the one-shot form also 4 or 8)
     int waves, WN;         // multiplying waves of the workgroup; those along the positions, waves / (WM KG)
-    int minrun;            // one-shot form: the shortest run of input elements that a tile stages at once (0: none)
-    int flat;              // the staged rows of a sample are one contiguous run per channel
+    int flat;              // one-shot tile and split form: the staged rows of a sample are one contiguous run per channel
+    int lepv;              // ... log2 of the columns per staging load
     int PW;                // pipelined form: waves that stage the chunks (0 = the one-shot form)
     int bufsz;             // bytes of one chunk buffer
     int nat;               // 1 = pointwise layer staged in its natural layout ([channel][position])

@@ -38,6 +38,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "sc_staging.h"
 #include "split_kernel.h"
 
 namespace sc {
@@ -143,39 +144,15 @@ bool split_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int K
     if (KG >= 2) lds = std::max<int64_t>(lds, (int64_t)g.MW * g.NW * (8 / KG) * (KG - 1) * 1024);
     if (lds > lds_budget || lds > kMaxLdsBytes) return false;
     g.lds_bytes = (int)lds;
+    // Columns per staging load, 4, 2 or 1 (an instruction count of a block: its loads and address; for each column 44 to split it and
+    // three LDS writes).  Loads as wide as row length and pointer allow, the rule before, read rows of 7 and 31 values one at a time: see
+    // split_kernel.h.
+    g.flat = g.Ws == L.W && L.pad_w == 0 ? 1 : 0;
+    const int64_t row = std::max(0, std::min(L.W, g.Ws - L.pad_w));
+    const int64_t least = g.flat ? least_staged_rows(L.H, g.Hs, (int64_t)g.TP * L.stride_h, L.pad_h, g.tiles_p) : 1;
+    g.lepv = load_columns(2, 40, 64, (int64_t)(g.CC / 8) * g.NS, PW ? 256 : 256 * KG, g.flat ? 1 : g.Hs, g.flat ? g.Hs * row : row, least * row);
     *out = g;
     return true;
-}
-
-// Log2 of the columns per staging load, 4, 2 or 1 of them (any alignment, at most the shortest run that a tile stages): the
-// least estimated time of a chunk, rounds of blocks times a block's instructions (its loads and address, then for each column 44 to
-// split it and three LDS writes).  Loads as wide as row length and pointer allow, the rule before, read rows of 7 and 31 values one at a time: see split_kernel.h.
-static int split_load_columns(const Plan& p)
-{
-    const MfmaGeom& g = p.mg;
-    const sc_layer_t& L = p.L;
-    const bool flat = g.Ws == L.W && L.pad_w == 0;
-    int64_t minrun = std::max(0, std::min(L.W, g.Ws - L.pad_w)), run = minrun;
-    if (flat) {
-        minrun = 0;
-        for (int t = 0; t < g.tiles_p; ++t) {
-            const int row0 = t * g.TP * L.stride_h - L.pad_h;
-            const int64_t rows = std::min(g.Hs, L.H - row0) - std::max(0, -row0);
-            if (rows > 0) minrun = minrun ? std::min(minrun, rows * L.W) : rows * L.W;
-        }
-        run = (int64_t)g.Hs * L.W;
-    }
-    const int64_t nt = g.PW ? 256 : 256 * g.KG, rows = flat ? 1 : g.Hs;
-    int64_t best = 0;
-    int lepv = 0;
-    for (int l = 2; l >= 0; --l) {
-        const int e = 1 << l;
-        if (e > 1 && e > minrun) continue;
-        const int64_t blocks = (int64_t)(g.CC / 8) * g.NS * rows * ((run + e - 1) / e);
-        const int64_t cost = ((blocks + nt - 1) / nt) * (40 + e * 64);
-        if (best == 0 || cost < best) { best = cost; lepv = l; }
-    }
-    return lepv;
 }
 
 int split_grid_size(const MfmaGeom& g, int N) { return ((N + g.NS - 1) / g.NS) * g.tiles_p * g.ndb * g.DL; }
@@ -218,9 +195,7 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
     const bool wmajor = w / std::min(8.0, combos) + xin / g.DL * std::min(1.0, combos / 8.0) < w + xin / 8.0;
     a.inner = wmajor ? ntiles : g.ndb; a.inner2 = wmajor ? g.ndb : g.DL;
     a.inv_inner = 1.0f / (float)a.inner; a.inv_inner2 = 1.0f / (float)a.inner2;
-    const bool flat = g.Ws == p.L.W && p.L.pad_w == 0;
-    const int lepv = split_load_columns(p);
-    a.bits = (wmajor ? 1 : 0) | (flat ? 2 : 0) | (p.L.pad_h || p.L.pad_w ? 4 : 0) | (g.DL > 1 ? 8 : 0) | __builtin_ctz(g.WM) << 4;
+    a.bits = (wmajor ? 1 : 0) | (g.flat ? 2 : 0) | (p.L.pad_h || p.L.pad_w ? 4 : 0) | (g.DL > 1 ? 8 : 0) | __builtin_ctz(g.WM) << 4;
     const SplitTable tab{static_cast<const float*>(p.d_theta), p.d_col, p.d_len, p.n};
     using Launch = sc_status_t (*)(const Plan&, const SplitArgs&, const SplitTable&, const void*, void*, int, hipStream_t);
     static const Launch kernels[4][3] = {{launch_split_one_1, launch_split_one_2, launch_split_one_4},
@@ -231,7 +206,7 @@ sc_status_t launch_split(const Plan& p, const void* x, void* y, int N, hipStream
         const sc_status_t st = launch_clear(y, (int64_t)N * p.L.D * p.P * p.Q, stream);
         if (st != SC_OK) return st;
     }
-    return kernels[g.PW ? __builtin_ctz(g.KG) + 1 : g.KG - 1][lepv](p, a, tab, x, y, (int)grid, stream);
+    return kernels[g.PW ? __builtin_ctz(g.KG) + 1 : g.KG - 1][g.lepv](p, a, tab, x, y, (int)grid, stream);
 }
 
 }  // namespace sc

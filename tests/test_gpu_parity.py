@@ -2080,3 +2080,32 @@ def test_fp32_split_form_steps_from_tables(name, C, D, H, W, R, S, stride, ph, p
             _split(plan, **bad)
         assert e.value.status == 4 and plan.get_tuning().as_dict() == before
     plan.destroy()
+
+
+def test_a_forward_call_takes_no_time_per_tile_on_the_host():
+    """A tall layer without padding columns in tiles of one row: 200000 tiles, and a call that only launches them.  (Their count
+    must not be walked over in front of every launch, which took 140 us here.)"""
+    import time
+    import torch
+    l = wl.Layer("tall", 32, 16, 200000, 1, 1, 1, 1, 1, 0, 0, N=1, sparsity=0.5, dtype="f32", seed=960)
+    data = wl.prepare(l)
+    plan = G.make_plan(l, data)
+    x = G.to_device(data["x"])
+    y = torch.empty((1, l.D, l.P, l.Q), device="cuda")
+    stream = torch.cuda.current_stream().cuda_stream
+    seconds = {}
+    for tp in (64, 1):
+        _split(plan, tile_p=tp, tile_d=16, waves_m=1)
+        print("case tall", plan.get_tuning().as_dict(), flush=True)
+        times = []
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            plan.forward(x.data_ptr(), y.data_ptr(), 1, 0, 0, stream)
+            times.append(time.perf_counter() - t0)
+        torch.cuda.synchronize()
+        seconds[tp] = min(times)
+        G.check(l, G.to_host(y), G.oracle_out(l, data), f"tall {tp}")
+    print("   seconds of a call", seconds, flush=True)
+    assert seconds[1] <= 3 * seconds[64] + 30e-6, seconds
+    plan.destroy()
