@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsparseconv.so")
-SOURCES = ["slab.hip", "split_pipe2_1.hip", "split_pipe2_2.hip", "split_pipe2_4.hip", "split_pipe4_1.hip", "split_pipe4_2.hip", "split_pipe4_4.hip", "split_two_1.hip", "split_two_2.hip", "split_two_4.hip", "split_one_1.hip", "split_one_2.hip", "split_one_4.hip", "split_mfma.hip", "dense_tile_f16_8.hip", "dense_tile_f16_4.hip", "dense_tile_f16_2.hip", "dense_tile_f16_1.hip", "dense_tile_i8_8.hip", "dense_tile_i8_4.hip", "dense_tile_i8_2.hip", "dense_tile_i8_1.hip", "dense_mfma_pipe_f16.hip", "dense_mfma_pipe_i8.hip", "dense_mfma_nat_f16.hip", "dense_mfma_nat_i8.hip", "dense_mfma_pipe_nat_f16.hip", "dense_mfma_pipe_nat_i8.hip", "dense_mfma_dl_f16.hip", "dense_mfma_dl_i8.hip", "plan.hip", "gather.hip", "dense_mfma.hip", "dense_library.hip"]
+SOURCES = ["slab.hip", "split_pipe2_1.hip", "split_pipe2_2.hip", "split_pipe2_4.hip", "split_pipe4_1.hip", "split_pipe4_2.hip", "split_pipe4_4.hip", "split_two_1.hip", "split_two_2.hip", "split_two_4.hip", "split_one_1.hip", "split_one_2.hip", "split_one_4.hip", "split_mfma.hip", "dense_tile_f16_8.hip", "dense_tile_f16_4.hip", "dense_tile_f16_2.hip", "dense_tile_f16_1.hip", "dense_tile_i8_8.hip", "dense_tile_i8_4.hip", "dense_tile_i8_2.hip", "dense_tile_i8_1.hip", "dense_tile_wide_f16.hip", "dense_tile_wide_i8.hip", "dense_mfma_pipe_f16.hip", "dense_mfma_pipe_i8.hip", "dense_mfma_nat_f16.hip", "dense_mfma_nat_i8.hip", "dense_mfma_pipe_nat_f16.hip", "dense_mfma_pipe_nat_i8.hip", "dense_mfma_dl_f16.hip", "dense_mfma_dl_i8.hip", "plan.hip", "gather.hip", "dense_mfma.hip", "dense_library.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC]

@@ -175,8 +175,6 @@ bool mfma_geometry(const Plan& p, int TP, int NS, int CC, int DB, int WM, int ld
     // pooling windows must not straddle tiles
     if (has_epilogue(p) && p.epi.pool && g.TP < p.P && (g.TP & 1)) return false;
     const bool pooled = has_epilogue(p) && p.epi.pool;
-    // (the one-shot kernel reads a row block of the weights at 32-bit offsets)
-    if (one_shot && (int64_t)L.R * L.S * g.NCB >= (1ll << 22)) return false;
     if (one_shot) {
         // the groups hand on their accumulators (two: the second one's; more: all of them), pooling lays them out by
         // output channel, rows a multiple of 16 bytes
@@ -274,7 +272,10 @@ sc_status_t launch_mfma(const Plan& p, const void* x, void* y, int N, hipStream_
         using Launch = sc_status_t (*)(const Plan&, const TileArgs&, const void*, void*, int, hipStream_t);
         static const Launch halves[4] = {launch_tile_f16_1, launch_tile_f16_2, launch_tile_f16_4, launch_tile_f16_8};
         static const Launch bytes[4] = {launch_tile_i8_1, launch_tile_i8_2, launch_tile_i8_4, launch_tile_i8_8};
-        return (p.ex == 1 ? bytes : halves)[g.lepv](p, tile_launch_args(p, N, (int)grid), x, y, (int)grid, stream);
+        // (steps at 32-bit offsets inside a 16-row block of the weights, 1 KB a step, unless it is 4 GB or more)
+        const bool wide = (int64_t)p.L.R * p.L.S * g.NCB >= (1ll << 22);
+        const Launch launch = wide ? (p.ex == 1 ? launch_tile_i8_wide : launch_tile_f16_wide) : (p.ex == 1 ? bytes : halves)[g.lepv];
+        return launch(p, tile_launch_args(p, N, (int)grid), x, y, (int)grid, stream);
     }
     MfmaArgs a{};
     a.C = p.L.C; a.D = p.L.D; a.N = N; a.H = p.L.H; a.W = p.L.W; a.P = p.P; a.Q = p.Q;

@@ -107,6 +107,9 @@ sc_status_t launch_tile_i8_1(const Plan& p, const TileArgs& a, const void* x, vo
 sc_status_t launch_tile_i8_2(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_tile_i8_4(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_tile_i8_8(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+// (16-row blocks of weights of 4 GB and more)
+sc_status_t launch_tile_f16_wide(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
+sc_status_t launch_tile_i8_wide(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_mfma_pipe_f16(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_mfma_pipe_i8(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);
 sc_status_t launch_mfma_nat_f16(const Plan& p, const MfmaArgs& a, const void* x, void* y, int grid, hipStream_t stream);

@@ -272,7 +272,9 @@ __device__ __forceinline__ TileBlock tile_block(const TileArgs& a)
     return {a.bits & 1 ? lo : hi, a.bits & 1 ? hi : lo};
 }
 
-template <sc_dtype_t DT, int MW, int NW, int LEPV>
+// WIDE: a 16-row block of the weights is 4 GB or more (filter taps x channel blocks of 2^22 and more: 134 million input channels x taps in 16 bits),
+// and its steps are addressed in 64 bits.  Instantiated for one column a load only.
+template <sc_dtype_t DT, int MW, int NW, int LEPV, bool WIDE>
 __global__ void __launch_bounds__(512, 2)
 mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>::Y* __restrict__ y,
                  const uint4w* __restrict__ wfrag, const TileArgs args)
@@ -368,7 +370,8 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     // Steps of a chunk: filter tap, then channel block of the chunk; this wave takes kgrp, kgrp + KG, ...
     // Up to 56 of them are tabulated one per lane (LDS offset of the tile operands, bytes into a row block of the weights) and
     // read back with v_readlane; the lanes past the last repeat it: operands are requested up to 8 steps ahead, without a test.
-    int xtab, wtab;
+    int xtab;
+    unsigned wtab;
     constexpr int kTable = 56;                               // (a multiple of PF, and 8 lanes more)
     auto table = [&](int s0, int n, int cbs, int gcb0) {
         const int s = min(kgrp + KG * (s0 + min(lane, max(n, 1) - 1)), a.RS * cbs - 1);
@@ -377,14 +380,20 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         const int r = tdiv(tap, a.inv_S);
         const int sx = tap - r * a.S;
         xtab = (r * a.Ws + sx) * a.pitch + cb * 64;
-        wtab = (tap * a.NCB + gcb0 + cb) << 10;
+        wtab = (unsigned)(tap * a.NCB + gcb0 + cb) << (WIDE ? 0 : 10);
     };
     uint4w aq[PF][MW], bq[4];
     auto fetch_w = [&](uint4w (&av)[MW], int s) __attribute__((always_inline)) {
-        // (32-bit offsets from a scalar base for each row block: mfma_geometry keeps them below 2^32)
-        const unsigned off = (unsigned)__builtin_amdgcn_readlane(wtab, s) + (unsigned)lane * 16u;
+        if constexpr (WIDE) {
+            const unsigned char* ws = wrows + ((uint64_t)(unsigned)__builtin_amdgcn_readlane((int)wtab, s) << 10);
 #pragma unroll
-        for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(wrows + m * wrow + off);
+            for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(ws + m * wrow + (unsigned)lane * 16u);
+        } else {
+            // (32-bit offsets from a scalar base for each row block)
+            const unsigned off = (unsigned)__builtin_amdgcn_readlane((int)wtab, s) + (unsigned)lane * 16u;
+#pragma unroll
+            for (int m = 0; m < MW; ++m) av[m] = *reinterpret_cast<const uint4w*>(wrows + m * wrow + off);
+        }
     };
     // steps of this wave in a chunk of cbs channel blocks
     auto steps_of = [&](int cbs) { const int all = a.RS * cbs; return all > kgrp ? (all - kgrp + KG - 1) >> lkg : 0; };
@@ -673,12 +682,12 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
     else pool(std::integral_constant<int, 1>{});
 }
 
-template <sc_dtype_t DT, int MW, int NW, int LEPV>
+template <sc_dtype_t DT, int MW, int NW, int LEPV, bool WIDE>
 static sc_status_t launch_tile_one(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
     using X = typename Types<DT>::X;
     using Y = typename Types<DT>::Y;
-    auto kernel = &mfma_tile_kernel<DT, MW, NW, LEPV>;
+    auto kernel = &mfma_tile_kernel<DT, MW, NW, LEPV, WIDE>;
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [&] {
@@ -691,23 +700,23 @@ static sc_status_t launch_tile_one(const Plan& p, const TileArgs& a, const void*
     return hipGetLastError() == hipSuccess ? SC_OK : SC_ERR_HIP;
 }
 
-template <sc_dtype_t DT, int LEPV>
+template <sc_dtype_t DT, int LEPV, bool WIDE = false>
 static sc_status_t launch_tile_typed(const Plan& p, const TileArgs& a, const void* x, void* y, int grid, hipStream_t stream)
 {
     switch (p.mg.MW * 10 + p.mg.NW) {
-        case 11: return launch_tile_one<DT, 1, 1, LEPV>(p, a, x, y, grid, stream);
-        case 12: return launch_tile_one<DT, 1, 2, LEPV>(p, a, x, y, grid, stream);
-        case 14: return launch_tile_one<DT, 1, 4, LEPV>(p, a, x, y, grid, stream);
-        case 17: return launch_tile_one<DT, 1, 7, LEPV>(p, a, x, y, grid, stream);
-        case 18: return launch_tile_one<DT, 1, 8, LEPV>(p, a, x, y, grid, stream);
-        case 21: return launch_tile_one<DT, 2, 1, LEPV>(p, a, x, y, grid, stream);
-        case 22: return launch_tile_one<DT, 2, 2, LEPV>(p, a, x, y, grid, stream);
-        case 24: return launch_tile_one<DT, 2, 4, LEPV>(p, a, x, y, grid, stream);
-        case 27: return launch_tile_one<DT, 2, 7, LEPV>(p, a, x, y, grid, stream);
-        case 28: return launch_tile_one<DT, 2, 8, LEPV>(p, a, x, y, grid, stream);
-        case 41: return launch_tile_one<DT, 4, 1, LEPV>(p, a, x, y, grid, stream);
-        case 42: return launch_tile_one<DT, 4, 2, LEPV>(p, a, x, y, grid, stream);
-        case 44: return launch_tile_one<DT, 4, 4, LEPV>(p, a, x, y, grid, stream);
+        case 11: return launch_tile_one<DT, 1, 1, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 12: return launch_tile_one<DT, 1, 2, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 14: return launch_tile_one<DT, 1, 4, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 17: return launch_tile_one<DT, 1, 7, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 18: return launch_tile_one<DT, 1, 8, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 21: return launch_tile_one<DT, 2, 1, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 22: return launch_tile_one<DT, 2, 2, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 24: return launch_tile_one<DT, 2, 4, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 27: return launch_tile_one<DT, 2, 7, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 28: return launch_tile_one<DT, 2, 8, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 41: return launch_tile_one<DT, 4, 1, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 42: return launch_tile_one<DT, 4, 2, LEPV, WIDE>(p, a, x, y, grid, stream);
+        case 44: return launch_tile_one<DT, 4, 4, LEPV, WIDE>(p, a, x, y, grid, stream);
     }
     return SC_ERR_UNSUPPORTED;
 }

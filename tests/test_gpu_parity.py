@@ -2109,3 +2109,50 @@ def test_a_forward_call_takes_no_time_per_tile_on_the_host():
     print("   seconds of a call", seconds, flush=True)
     assert seconds[1] <= 3 * seconds[64] + 30e-6, seconds
     plan.destroy()
+
+
+@pytest.mark.parametrize("dtype,C", [("f16", 16_000_000), ("i8", 32_000_000)])
+def test_dense_tile_on_weights_of_more_than_4_gb_a_row_block(dtype, C):
+    """The one-shot matrix-core kernel where 16 output channels have more than 4 GB of dense weights (9 taps x 500000 channel blocks of
+    1 KB, 36.9 GB in all): a few weights anywhere, and in the last channels, whose last tap lies past 4 GB.  Every output against
+    the sum of its products; fp16 to its rounding (2^-11) and that of 60 fp32 sums."""
+    import torch
+    D, H, W, N = 40, 2, 2, 2
+    rng = np.random.default_rng(970)
+    K = 9 * C
+    rowptr = np.zeros(D + 1, np.int32)
+    cols = []
+    for d in range(D):
+        c = np.concatenate([rng.integers(0, K, 40), K - 1 - rng.integers(0, 9 * 500, 20)])
+        cols.append(np.unique(c))
+        rowptr[d + 1] = rowptr[d] + cols[-1].size
+    colidx = np.concatenate(cols).astype(np.int32)
+    if dtype == "f16":
+        values, scales = rng.normal(0, 0.05, colidx.size).astype(np.float16), None
+        x = rng.integers(-100, 100, (N, C, H, W), dtype=np.int8).astype(np.float16)
+    else:
+        values, scales = rng.integers(-127, 128, colidx.size).astype(np.int8), np.full(D, 0.01, np.float32)
+        x = rng.integers(-127, 128, (N, C, H, W), dtype=np.int8)
+    ref = np.zeros((N, D, H, W))
+    mag = np.zeros((N, D, H, W))
+    for d in range(D):
+        for j in range(rowptr[d], rowptr[d + 1]):
+            c, tap = divmod(int(colidx[j]), 9)
+            xp = np.pad(x[:, c].astype(np.float64), ((0, 0), (1, 1), (1, 1)))[:, tap // 3:tap // 3 + H, tap % 3:tap % 3 + W]
+            ref[:, d] += float(values[j]) * xp
+            mag[:, d] += abs(float(values[j])) * np.abs(xp)
+    plan = B.Plan.create_csr(B.make_layer(C, D, H, W, 3, 3, (1, 1), (1, 1)), B.DTYPES[dtype], rowptr, colidx, values, scales)
+    xd = G.to_device(x)
+    y = torch.empty((N, D, H, W), device="cuda", dtype=B.torch_out_dtype(plan.dtype))
+    for shape in (dict(tile_d=16, waves_m=1, wg_threads=512, buffers=8, chunk_c=2048), dict(tile_d=64, waves_m=2, sub_batch=2, chunk_c=1024)):
+        plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, tile_p=H, **shape)
+        print("case wide", dtype, plan.get_tuning().as_dict(), flush=True)
+        y.view(torch.uint8).fill_(0x7f)
+        plan.forward(xd.data_ptr(), y.data_ptr(), N, 0, 0, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        got = G.to_host(y).astype(np.float64)
+        if dtype == "i8":
+            assert np.array_equal(got, ref)
+        else:
+            assert np.all(np.abs(got - ref) <= 2.0 ** -11 * np.abs(ref) + 60 * 2.0 ** -24 * mag)
+    plan.destroy()
