@@ -108,3 +108,29 @@ def full_batch_parity(l: wl.Layer, data, plan: B.Plan, x_dev=None, ws=None, grou
     except AssertionError as e:
         return {"ok": False, "samples": idx, "error": str(e)[:300]}
     return {"ok": True, "samples": idx, "rel_err": rel_err(got, ref)}
+
+
+def load_columns(widest, block, column, groups, threads, rows, run, minrun):
+    """Columns per staging load of the matrix-core kernels: the cheapest width that the shortest run holds, the wider of two that
+    are level (csrc/sc_staging.h; compared with it in test_staging_host.py)."""
+    cost = {}
+    for e in (1 << l for l in range(widest, -1, -1)):
+        if e == 1 or e <= minrun:
+            cost[e] = -(-groups * rows * -(-run // e) // threads) * (block + e * column)
+    return max(e for e in cost if cost[e] == min(cost.values()))
+
+
+def split_staging(l: wl.Layer, t):
+    """How a launch shape of the fp32 split form stages: (columns per load, whether a run ends in a block that overlaps the
+    one before, whether a chunk has more rounds of blocks than the one -- pipelined: two -- loaded a chunk ahead)."""
+    TP, NS, piped = t.tile_p, t.sub_batch, t.producers > 0
+    threads = 256 if piped or t.wg_threads == 256 else 512
+    Hs, Ws = (TP - 1) * l.stride_h + l.R, (l.Q - 1) * l.stride_w + l.S
+    starts = range(-l.pad_h, (l.P - 1) * l.stride_h - l.pad_h + 1, TP * l.stride_h)
+    staged = [r for r in (min(Hs, l.H - s) - max(0, -s) for s in starts) if r > 0]
+    row = max(0, min(l.W, Ws - l.pad_w))
+    flat = Ws == l.W and l.pad_w == 0
+    runs = [r * row for r in staged] if flat else [row]
+    cols = load_columns(2, 40, 64, t.chunk_c // 8 * NS, threads, 1 if flat else Hs, Hs * row if flat else row, min(runs))
+    blocks = t.chunk_c // 8 * min(NS, l.N) * (1 if flat else max(staged)) * -(-max(runs) // cols)
+    return cols, any(r % cols for r in runs), blocks > threads * (4 // cols) * (2 if piped else 1)

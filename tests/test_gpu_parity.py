@@ -1431,7 +1431,10 @@ def test_fp32_split_form_on_the_matrix_cores(name, C, D, H, W, R, S, sh, sw, ph,
                    # pipelined: staging waves of their own (with eight multiplying waves only)
                    {"producers": 4}, {"producers": 4, "tile_d": 32, "waves_m": 1, "tile_p": 1, "chunk_c": 32},
                    {"producers": 4, "tile_d": 64, "waves_m": 4, "tile_p": 3, "chunk_c": 64}, {"producers": 4, "tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32},
-                   {"producers": 4, "tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 96, "ragged": 1}):
+                   {"producers": 4, "tile_d": 128, "waves_m": 4, "tile_p": 2, "chunk_c": 96, "ragged": 1},
+                   # ... in four groups: wave tiles of one block and of a number that four does not divide among them
+                   {"producers": 4, "buffers": 4}, {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1, "chunk_c": 32},
+                   {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1000, "chunk_c": 32}, {"producers": 4, "buffers": 4, "tile_d": 64, "waves_m": 2, "tile_p": 2, "chunk_c": 64}):
             try:
                 _split(plan, wg_threads=threads, **kw)
             except B.SparseConvError as e:
@@ -1480,7 +1483,9 @@ def test_fp32_split_form_element_by_element_on_short_rows(n):
 
     plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_GATHER, split_n=1)
     gather = error()
-    for kw in ({}, {"wg_threads": 256, "tile_d": 64, "waves_m": 2}, {"producers": 4}):
+    # (the last one: wave tiles of seven blocks, 192 positions)
+    for kw in ({}, {"wg_threads": 256, "tile_d": 64, "waves_m": 2}, {"producers": 4}, {"producers": 4, "buffers": 4},
+               {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1}, {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 8}):
         _split(plan, **kw)
         print("case split short rows", n, plan.get_tuning().as_dict(), flush=True)
         e = error()
@@ -1520,7 +1525,9 @@ def test_fp32_split_form_sums_outputs_that_the_terms_do_not_serve_entry_by_entry
 
     v = data["values"].astype(np.float64)
     for kw in ({}, {"wg_threads": 256, "tile_d": 64, "waves_m": 4, "tile_p": 3}, {"tile_d": 32, "waves_m": 1, "tile_p": 2, "chunk_c": 32, "split_n": 2},
-               {"producers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2, "chunk_c": 32}, {"tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32}):
+               {"producers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2, "chunk_c": 32}, {"tile_d": 64, "waves_m": 2, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32},
+               {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1, "chunk_c": 32}, {"producers": 4, "buffers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2, "chunk_c": 32},
+               {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1000, "sub_batch": 3 if H == 7 else 1, "chunk_c": 32}):
         _split(plan, **kw)
         for what, x in (("everywhere", everywhere), ("single", single), ("shared", shared)):
             print("case split tiny", C, D, xe, we, kw, what, flush=True)
@@ -1550,7 +1557,9 @@ def test_fp32_split_form_on_inputs_whose_first_term_is_infinite(bad):
         plan = B.Plan.create_csr(G.layer_desc(l), B.DTYPES["f32"], data["rowptr"], data["colidx"], values, None, None)
         plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_GATHER, split_n=1)
         want = G.run_gpu(plan, inp)
-        for kw in ({}, {"producers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2}, {"wg_threads": 256, "chunk_c": 32, "tile_p": 3}):
+        for kw in ({}, {"producers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2}, {"wg_threads": 256, "chunk_c": 32, "tile_p": 3},
+                   {"producers": 4, "buffers": 4, "tile_d": 32, "waves_m": 2, "tile_p": 2}, {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1, "chunk_c": 32},
+                   {"producers": 4, "buffers": 4, "tile_d": 16, "waves_m": 1, "tile_p": 1000, "sub_batch": 2, "chunk_c": 32}):
             _split(plan, **kw)
             print("case split huge", bad, kw, flush=True)
             got = G.run_gpu(plan, inp)
@@ -1564,9 +1573,9 @@ def test_fp32_split_form_on_inputs_whose_first_term_is_infinite(bad):
 @pytest.mark.parametrize("W,shift", [(28, 0), (28, 1), (28, 2), (14, 0), (14, 1), (6, 2), (7, 0), (7, 3)])
 @pytest.mark.parametrize("R", [1, 3])
 def test_fp32_split_form_staging_loads_of_every_width(W, shift, R):
-    """Rows and pointers that allow 16-, 8- and 4-byte loads (rows of a multiple of 4, of 2 and odd ones, x at 4, 8 and
-    12 bytes past 16), one-shot and pipelined, tiles of rows and of whole planes, output channels that fill one block of
-    16 or less of it."""
+    """Rows of a multiple of 4, of 2 and odd ones, x at 4, 8 and 12 bytes past 16, one-shot and pipelined, tiles of rows and of whole
+    planes, output channels that fill one block of 16 or less of it.  (The width of a load follows neither row length nor pointer
+    but an estimate of the time; every width with and without a run's last block overlapping the one before: the next test.)"""
     import torch
     l = wl.Layer("widths", 45, 13, 8, W, R, R, 1, 1, R // 2, R // 2, N=3, sparsity=0.6, dtype="f32", seed=W)
     data = wl.prepare(l)
@@ -1588,6 +1597,55 @@ def test_fp32_split_form_staging_loads_of_every_width(W, shift, R):
         torch.cuda.synchronize()
         G.check(l, G.to_host(y), ref, f"widths {W} {shift} {kw}", tol=2e-6)
     plan.destroy()
+
+
+@pytest.mark.parametrize("form", ["one", "two", "pipe2", "pipe4"])
+def test_fp32_split_form_staging_of_every_width_and_tail(form):
+    """Every instantiation by the columns of a staging load in every form -- one-shot with one and two groups of waves, pipelined with
+    two and four --, with runs that are whole loads and runs that end in a load overlapping the one before, with chunks of no
+    more rounds than are loaded ahead and of more, x at each multiple of 4 bytes; and the one-shot wave tile of 2 x 7 blocks, which stages
+    one block at a time, in each width.  What a shape stages is worked out by split_staging; none of it may be left out."""
+    import torch
+    kw = {"one": dict(wg_threads=256), "two": dict(wg_threads=512), "pipe2": dict(producers=4), "pipe4": dict(producers=4, buffers=4)}[form]
+    everything = {(c, tail, more) for c in (1, 2, 4) for tail in (False, True) for more in (False, True) if c > 1 or not tail}
+    seen, large = {}, set()
+    for k, (C, H, W, R, sw, N) in enumerate([(130, 8, 31, 1, 1, 3), (100, 8, 31, 1, 1, 2), (45, 6, 28, 1, 1, 3), (100, 6, 28, 1, 1, 2), (45, 9, 14, 1, 1, 4), (130, 14, 14, 1, 1, 1),
+                                             (128, 200, 2, 1, 2, 2), (45, 7, 7, 3, 1, 5), (70, 9, 31, 3, 1, 2), (64, 13, 28, 1, 1, 2)]):
+        l = wl.Layer("stage", C, 29, H, W, R, R, 1, sw, R // 2, R // 2, N=N, sparsity=0.6, dtype="f32", seed=980 + k)
+        data = wl.prepare(l)
+        ref = None
+        plan = G.make_plan(l, data)
+        buf = torch.full((data["x"].size + 8,), float("nan"), device="cuda")
+        for td, tp, ns, cc in ((td, tp, ns, cc) for td in (16, 32) for tp in (1, 2, 3, 5, 9, 13, 1000) for ns in (1, 2, 3, 4) for cc in (32, 64, 96, 128, 256)):
+            if tp >= l.P and tp != 1000 or tp != 1000 and ns > 1 or ns > N:
+                continue
+            try:
+                _split(plan, tile_d=td, waves_m=1, tile_p=tp, sub_batch=ns, chunk_c=cc, **kw)
+            except B.SparseConvError as e:
+                assert e.status == 4
+                continue
+            t = plan.get_tuning()
+            key = G.split_staging(l, t)
+            blocks = -(-t.sub_batch * t.tile_p * l.Q // 16)           # of 16 positions; four waves along them in the one-shot form
+            by_one = td == 32 and 16 < blocks <= 28 and not kw.get("producers")
+            if seen.get((key, k), 0) >= 2 and (not by_one or key[0] in large):
+                continue
+            if ref is None:
+                ref = G.oracle_out(l, data)
+            shift = sum(seen.values()) % 4
+            seen[key, k] = seen.get((key, k), 0) + 1
+            if by_one:
+                large.add(key[0])
+            x = buf[shift:shift + data["x"].size]
+            x.copy_(torch.from_numpy(np.ascontiguousarray(data["x"])).cuda().flatten())
+            y = torch.full(ref.shape, float("nan"), device="cuda")
+            print("case stage", form, key, shift, (C, H, W, R), t.as_dict(), flush=True)
+            plan.forward(x.data_ptr(), y.data_ptr(), l.N, 0, 0, torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            G.check(l, G.to_host(y), ref, f"stage {form} {key} {t.as_dict()}", tol=2e-6)
+        plan.destroy()
+    assert {key for key, _ in seen} == everything, everything - {key for key, _ in seen}
+    assert kw.get("producers") or large == {1, 2, 4}, large
 
 
 def test_autotune_gives_the_dense_weights_back_when_a_gather_kernel_wins():

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+import gpu_util as G
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -53,19 +55,13 @@ def test_shortest_tile_is_the_first_or_the_last(staging):
 
 
 def test_columns_of_a_load_fit_the_shortest_run(staging):
-    """The rule of both forms, written out: the cheapest width that the shortest run holds, the wider of two that are level."""
+    """The rule of both forms against the one written out in Python."""
     rng = random.Random(2)
     for _ in range(4000):
         widest, block, column = rng.choice([(2, 40, 64), (3, 32, 8), (3, 40, 12)])
         groups, threads = rng.randint(1, 300), rng.choice([256, 512])
         rows, run = rng.randint(1, 40), rng.randint(0, 200)
         minrun = rng.randint(0, run)
-        cost = {}
-        for l in range(widest, -1, -1):
-            e = 1 << l
-            if e == 1 or e <= minrun:
-                cost[l] = -(-groups * rows * -(-run // e) // threads) * (block + e * column)
         got = staging.columns(widest, block, column, groups, threads, rows, run, minrun)
-        least = min(cost.values())
-        assert got == max(l for l in cost if cost[l] == least), (groups, threads, rows, run, minrun)
+        assert 1 << got == G.load_columns(widest, block, column, groups, threads, rows, run, minrun), (groups, threads, rows, run, minrun)
         assert got == 0 or 1 << got <= minrun
