@@ -134,3 +134,19 @@ def split_staging(l: wl.Layer, t):
     cols = load_columns(2, 40, 64, t.chunk_c // 8 * NS, threads, 1 if flat else Hs, Hs * row if flat else row, min(runs))
     blocks = t.chunk_c // 8 * min(NS, l.N) * (1 if flat else max(staged)) * -(-max(runs) // cols)
     return cols, any(r % cols for r in runs), blocks > threads * (4 // cols) * (2 if piped else 1)
+
+
+def tile_staging(l: wl.Layer, t):
+    """The instantiation of the one-shot matrix-core kernel that a launch shape runs and how it stages: (blocks of 16 output channels and of 16
+    positions of a wave, columns per load), whether a run ends in a block that overlaps the one before."""
+    TP, NS, waves = t.tile_p, t.sub_batch, t.wg_threads // 64
+    CV = 16 if l.dtype in ("i8", "cb4") else 8
+    nw = -(-(-(-NS * TP * l.Q // 16)) // (waves // (t.waves_m * (t.buffers or waves // 4))))
+    Hs, Ws = (TP - 1) * l.stride_h + l.R, (l.Q - 1) * l.stride_w + l.S
+    starts = range(-l.pad_h, (l.P - 1) * l.stride_h - l.pad_h + 1, TP * l.stride_h)
+    staged = [r for r in (min(Hs, l.H - s) - max(0, -s) for s in starts) if r > 0]
+    row = max(0, min(l.W, Ws - l.pad_w))
+    flat = Ws == l.W and l.pad_w == 0
+    runs = [r * row for r in staged] if flat else [row]
+    cols = load_columns(3, CV + 24, 8 if CV == 8 else 12, t.chunk_c // CV * NS, t.wg_threads, 1 if flat else Hs, Hs * row if flat else row, min(runs))
+    return (t.tile_d // 16 // t.waves_m, min(n for n in (1, 2, 4, 7, 8) if n >= nw), cols), any(r % cols for r in runs)

@@ -1957,6 +1957,37 @@ def test_dense_staging_deals_blocks_by_fours(W, dtype):
         plan.destroy()
 
 
+@pytest.mark.parametrize("dtype", ["f16", "i8"])
+def test_dense_one_shot_kernel_in_every_instantiation(dtype):
+    """Every wave tile with every width of a staging load, runs that are whole loads and runs that end in a load overlapping the one
+    before, a last chunk that is not whole.  What a shape runs is worked out by tile_staging; none of it may be left out."""
+    block = 64 if dtype == "i8" else 32
+    seen = set()
+    for k, (C, H, W, R) in enumerate([(2060, 1, 16, 1), (2060, 3, 5, 1), (1030, 2, 16, 1), (1030, 5, 6, 1), (1030, 4, 16, 1), (1030, 7, 9, 1), (1030, 7, 16, 1),
+                                      (1030, 7, 15, 1), (1030, 8, 16, 1), (1030, 9, 13, 1), (200, 8, 15, 3), (70, 6, 9, 3)]):
+        l = wl.Layer("inst", C, 70, H, W, R, R, 1, 1, R // 2, R // 2, N=2, sparsity=0.9, dtype=dtype, seed=990 + k)
+        data = wl.prepare(l)
+        ref = G.oracle_out(l, data)
+        plan = G.make_plan(l, data)
+        for td, threads, kg, cc in ((td, threads, kg, cc) for td in (16, 32, 64) for threads in (256, 512) for kg in (4, 8) for cc in (32, 64, 128, 256, 512, 1024, 2048)):
+            if cc % block:
+                continue
+            try:
+                plan.set_tuning(B.sc_tuning_t(), variant=B.SC_VARIANT_DENSE, tile_d=td, waves_m=1, wg_threads=threads, buffers=kg, wg_per_cu=1, chunk_c=cc, tile_p=1000, sub_batch=1)
+            except B.SparseConvError as e:
+                assert e.status == 4
+                continue
+            key = G.tile_staging(l, plan.get_tuning())
+            if key in seen:
+                continue
+            seen.add(key)
+            print("case inst", dtype, key, plan.get_tuning().as_dict(), flush=True)
+            G.check(l, G.run_gpu(plan, data["x"]), ref, f"inst {dtype} {key}")
+        plan.destroy()
+    assert seen == {((m, n, c), tail) for m in (1, 2, 4) for n in (1, 2, 4, 7, 8) for c in (1, 2, 4, 8) for tail in (False, True)
+                    if (m < 4 or n <= 4) and (c > 1 or not tail)}
+
+
 @pytest.mark.parametrize("pool", [0, 2])
 @pytest.mark.parametrize("dtype", ["f16", "i8"])
 @pytest.mark.parametrize("D,tile_d,threads,split_n", [(37, 64, 256, 2), (16, 16, 256, 16), (37, 64, 512, 2), (130, 128, 256, 16)])
