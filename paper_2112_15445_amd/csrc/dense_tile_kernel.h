@@ -330,10 +330,11 @@ mfma_tile_kernel(const typename Types<DT>::X* __restrict__ x, typename Types<DT>
         st.whole = st.cleft >= a.CC;
     }
     // One round of a chunk is loaded a chunk ahead.  (Two, the form before, cost 32 registers and half of the code -- 80 KB for the
-    // largest wave tiles, 46 now, of the 64 KB of the instruction cache of two CUs: f16 3x3 64-64 at 56 x 56, batch 32 15.4 -> 15.0 us, the
-    // 13 int8 layers of VGG-16, batch 64 110.9 -> 108.3, other layers level.  109 - 139 registers for the wave tiles of up to four blocks leave
-    // room for three or four waves per SIMD, which layers with many short workgroups need to overlap them: 4b/16b 3x3 80-383 at 6 x 6,
-    // batch 128, 15.8 us with two waves, 12.4 with three.)
+    // largest wave tiles, where 14 and 16 blocks now take 38 - 49 in 16 and 56 - 65 in 8 bits, of the 64 KB of the instruction cache of two
+    // CUs: f16 3x3 64-64 at 56 x 56, batch 32 15.4 -> 15.0 us, the 13 int8 layers of VGG-16, batch 64 110.9 -> 108.3, other layers level.
+    // 108 - 139 registers for the wave tiles of up to four blocks, but 4 x 1 blocks with 153 - 174, leave room for three or four waves per
+    // SIMD, which layers with many short workgroups need to overlap them: 4b/16b 3x3 80-383 at 6 x 6, batch 128, 15.8 us with two waves,
+    // 12.4 with three.  1 x 7, 1 x 8 and 2 x 4 blocks with 138 - 157 leave it for three.)
     constexpr int EPV = 1 << LEPV, VB = kTileVB<X, EPV>;
     unsigned pre[32];
     TileSlot slots[VB];

@@ -571,8 +571,10 @@ static bool default_dense_tuning(const Plan& p, int gather_variant, sc_tuning_t*
         if ((int64_t)g.NS * L.C * L.H * L.W >= (1ll << 29) || (int64_t)g.DB * g.npos >= (1 << 19) || g.npos_s >= (1 << 16) ||
             (int64_t)g.tiles_p * g.ndb >= (1 << 19))
             continue;
-        // clocks of a batch of N.  (Workgroups that share a CU: by LDS, and on the one-shot kernel by its registers, three waves
-        // per SIMD with the smallest wave tiles, else two.)
+        // clocks of a batch of N.  (Workgroups that share a CU: by LDS, and on the one-shot kernel by registers, three waves
+        // per SIMD with the smallest wave tiles, else two.  That, and the clocks of start and chunk below, are of the form of the kernel that the
+        // choice was measured with; the present one starts sooner and has room for three waves with 1 x 7, 1 x 8 and 2 x 4 blocks too.
+        // Other figures take other tiles, which nobody has measured against these.)
         auto estimate = [&](double N) {
             const double wgs = std::ceil(N / g.NS) * g.tiles_p * g.ndb, per_cu = std::ceil(wgs / kNumCU);
             const int room = kMaxLdsBytes / std::max(g.lds_bytes, 1);
@@ -1347,7 +1349,10 @@ static void build_candidates(const Plan& p, std::vector<sc_tuning_t>* out)
                 // pipelined: small chunks, staged one ahead by waves of their own
                 if (thr == 512 && wpc == 1 && (cc != 256 || is_pointwise(p.L))) {
                     t.split_n = 0; t.producers = 4; t.chunk_c = cc ? cc : 32; push(t);
-                    // four groups of two waves split the contraction; small tiles of one block of channels with them
+                    // Four groups of two waves split the contraction; with them also blocks of 16 channels, which make more
+                    // workgroups of a single image (us with the best shape of 32 channels and more, and of 16: 3x3 128-128 at 28 x 28 7.7, 6.7; 100-90
+                    // at 27 x 31 8.0, 7.1; 1-D 300-64, batch 128 10.1, 11.3).  Offered from one layout, with small tiles and chunks, to keep the
+                    // search as long as it was; larger chunks would take 512-512 at 7 x 7, one image, from 12.4 to 11.6.
                     if (lw[1] <= 2) { t.buffers = 4; push(t); }
                     if (lw[0] == 32 && lw[1] == 1 && cc <= 64 && tp <= 4) { t.tile_d = 16; push(t); }
                 }

@@ -12,7 +12,8 @@ namespace sc {
 // first load, in seven trips to memory one after the other).  With that, staging instantiated by the columns of a load and a block's
 // place worked out once for all chunks: 3x3 128-128 at 28 x 28, batch 32 39.9 -> 37.3 us, 3x3 stride 2 512-512 at 14 x 14 51.1 -> 48.9, 1x1
 // 2048-512 at 7 x 7 30.9 -> 28.7, 1-D 300-64 along 64, batch 128 11.3 -> 10.8, 3x3 100-90 at 27 x 31, batch 7 17.3 -> 16.5.
-// (Loads of four columns wherever a run has four, after that: 28.7 -> 27.7, 16.5 -> 15.5 on the last and the last but two, rows of 7, 49 and 31.
+// (Loads of any alignment and of up to four columns, as load_columns in sc_staging.h estimates to be fastest, instead of as wide as row length and pointer
+// allow, after that: 28.7 -> 27.7 and 16.5 -> 15.5 on the last but two and the last, runs of 49 and rows of 31.
 // Two rounds loaded a chunk ahead instead of one: level. The first chunk of the pipelined form staged by all twelve waves: 1-D 10.8 -> 11.5, its
 // registers spill.)
 struct SplitArgs {
@@ -380,6 +381,8 @@ split_conv_kernel(const float* __restrict__ x, float* __restrict__ y, const unsi
     const SplitArgs a = args_at_once(args);
     // steps of weights in flight: a step multiplies for 6 MW NW matrix instructions (16 clocks and
     // more each), L2 answers after several hundred clocks.  PF * NW is even (parity of the ring below).
+    // (Six steps for the tile of one block, before the steps came from tables, are no part of a table's 64; with four, and the tables, 21 such
+    // shapes on seven layers take 0.62 - 0.98 of the time.)
     constexpr int PF = MW * NW >= 7 ? 2 : 4;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
