@@ -4,6 +4,8 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import time
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -21,7 +23,7 @@ def build(verbose: bool = False, jobs: int = 8, incremental: bool = False) -> st
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    procs = []
+    todo = []
     objs = []
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
@@ -31,30 +33,34 @@ def build(verbose: bool = False, jobs: int = 8, incremental: bool = False) -> st
             deps.append(os.path.join(ROOT, "include", "sparse_conv.h"))
             if all(os.path.getmtime(d) <= os.path.getmtime(obj) for d in deps):
                 continue
-        cmd = [hipcc, "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
-        if len(procs) >= jobs:
-            _drain(procs)
-    _drain(procs)
+        todo.append((src, [hipcc, "-c", os.path.join(CSRC, src), "-o", obj] + FLAGS))
+    # (a compiler starts as soon as another one ends: the units differ by a factor of twenty)
+    pool = ThreadPoolExecutor(jobs)
+    try:
+        for done in [pool.submit(_compile, src, cmd, verbose) for src, cmd in todo]:
+            done.result()
+    finally:
+        pool.shutdown(cancel_futures=True)
     tmp = LIB + f".tmp{os.getpid()}"
     subprocess.check_call([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs + ["-ldl"])
     os.replace(tmp, LIB)
     return LIB
 
 
-def _drain(procs):
-    while procs:
-        src, p = procs.pop(0)
-        out, _ = p.communicate()
-        text = out.decode(errors="replace")
-        # the host pass does not know the device-only target feature; that warning is harmless
-        text = "\n".join(l for l in text.splitlines() if "packed-fp32-ops" not in l and l.strip())
-        if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n{text}")
-        if text.strip():
-            print(text, file=sys.stderr)
+def _compile(src, cmd, verbose):
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    t0 = time.monotonic()
+    p = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    if verbose:
+        print(f"{src}: {time.monotonic() - t0:.0f} s", flush=True)
+    text = p.stdout.decode(errors="replace")
+    # the host pass does not know the device-only target feature; that warning is harmless
+    text = "\n".join(l for l in text.splitlines() if "packed-fp32-ops" not in l and l.strip())
+    if p.returncode != 0:
+        raise RuntimeError(f"hipcc failed on {src}:\n{text}")
+    if text.strip():
+        print(text, file=sys.stderr)
 
 
 if __name__ == "__main__":
